@@ -12,8 +12,9 @@
 // K = 27 Cin, operands loaded straight from global memory into MFMA fragments
 // (a 16-voxel x 4-channel slab per lane group is one 8-byte load).  Input
 // gradient: the same kernel with taps flipped and channels swapped, the ReLU
-// mask of the forward input fused into the epilogue.  Weight gradient: split-K
-// over voxel chunks with a fixed-order reduction.  Master weights, gradients and
+// mask of the forward input fused into the epilogue.  Weight gradient: a GEMM over
+// voxels with every tap in registers, split over voxel tiles with a fixed-order
+// reduction.  Master weights, gradients and
 // Adam moments are FP32.
 #include <hip/hip_runtime.h>
 
@@ -184,44 +185,112 @@ __global__ __launch_bounds__(256) void k_conv2(const bf16_t* __restrict__ X, int
   }
 }
 
-// partial[chunk][tap][o][i] = sum over the chunk's voxels v of dY[v, o] X[v + tap, i]
-template <int TAPS>
-__global__ __launch_bounds__(256) void k_wgrad(const bf16_t* __restrict__ X, int xcs, int xco, int Cin,
-                                               const bf16_t* __restrict__ dY, int ycs, int yco, int Cout,
-                                               float* __restrict__ partial, Vol vol, int chunk) {
+// partial[blk][tap][o][i] = sum over the block's voxels v of dY[v, o] X[v + tap, i]
+//
+// An implicit GEMM with K = voxels: M = 16 output channels, N = 16 input channels, one
+// accumulator per tap, so a wave keeps all 27 taps of one (o, i) tile pair in registers
+// (108 values per lane) and every dY fragment serves 27 MFMAs.  A workgroup takes one
+// 16-channel chunk of X and NO output tiles; it stages a 2 x 4 x TX voxel tile of dY and
+// the tile's X halo (4 x 6 x (TX + 2) voxels) in LDS, channels last, and walks tiles with a
+// grid stride.  A K-step is 32 voxels; both operands need voxels along the lane's registers
+// while memory holds channels there, so fragments come from the transposing LDS read
+// (ds_read_b64_tr_b16: the 16 lanes of a group address four rows of 16 channels, lane c gets
+// channel c of the four rows).  A tap is then a row offset, with no unaligned access.  With
+// NO < 4 the waves split the K-steps and add their accumulators through LDS at the end.
+// Voxels outside the volume are staged as zeros in both tiles.
+// Bound: LDS reads (56 of 8 bytes a lane per 27 MFMAs), at a fraction of the matrix rate;
+// the element-by-element loads of the earlier kernel (two bytes a lane, nothing reused
+// between taps) took 422 us a layer at 32 x 32 x 128 on average; a training step on two
+// samples of 32 x 32 x 128 went from 14.3 to 3.5 ms.
+template <int TAPS, int NO, int TX>
+struct WgradTile {
+  static constexpr int waves = NO == 3 ? 3 : 4;
+  static constexpr int ks = waves / NO;                  // waves sharing an output tile
+  static constexpr int hx = TX + 2, hvox = 4 * 6 * hx, vox = 2 * 4 * TX;
+  static constexpr int stage = (hvox + NO * vox) * 16 * 2;
+  static constexpr int red = ks > 1 ? NO * TAPS * 256 * 4 : 0;
+  static constexpr int bytes = stage > red ? stage : red;
+};
+
+typedef __attribute__((address_space(3))) s4v* lds_s4v;
+__device__ __forceinline__ bf8v read_rows8(bf16_t* p) {   // rows 0-3 and 4-7 of 16 channels
+  const s4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4v)p);
+  const s4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4v)(p + 64));
+  return __builtin_bit_cast(bf8v, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+template <int TAPS, int NO, int TX>
+__global__ __launch_bounds__((64 * WgradTile<TAPS, NO, TX>::waves)) void k_wgrad(
+    const bf16_t* __restrict__ X, int xcs, int xco, int Cin, const bf16_t* __restrict__ dY, int ycs, int yco, int Cout,
+    float* __restrict__ partial, Vol vol, int o0) {
+  using Tl = WgradTile<TAPS, NO, TX>;
+  __shared__ __attribute__((aligned(16))) unsigned char smem[Tl::bytes];
+  bf16_t* xt = reinterpret_cast<bf16_t*>(smem);           // [halo voxel][16]
+  bf16_t* yt = xt + Tl::hvox * 16;                        // [output tile][voxel][16]
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int m = lane & 15, kq = lane >> 4;
-  const int tap = blockIdx.y;
-  const long V = vol.V();
-  const long v0 = (long)blockIdx.x * chunk;
-  const int dz = TAPS == 1 ? 0 : tap / 9 - 1, dy = TAPS == 1 ? 0 : (tap / 3) % 3 - 1,
-            dx = TAPS == 1 ? 0 : tap % 3 - 1;
-  const int to_n = Cout / 16, ti_n = Cin / 16;
-  for (int tile = wave; tile < to_n * ti_n; tile += 4) {
-    const int to = tile / ti_n, ti = tile % ti_n;
-    f4v acc = f4v{0.f, 0.f, 0.f, 0.f};
-    for (long vb = v0; vb < v0 + chunk && vb < V; vb += 16) {
-      s4v a, b;
+  const int ot = wave % NO, part = wave / NO;
+  const int rowoff = (m >> 2) * 16 + (m & 3) * 4;         // this lane's share of a transposing read
+  const int ntx = (vol.W + TX - 1) / TX, nty = (vol.H + 3) / 4, ntz = (vol.D + 1) / 2;
+  const int ntiles = ntx * nty * ntz;
+  const int ci = blockIdx.y * 16;
+  f4v acc[TAPS];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const long v = vb + 4 * kq + i;
-        short av = 0, bv = 0;
-        if (v < V && v < v0 + chunk) {
-          av = (short)dY[v * ycs + yco + to * 16 + m];
-          const int x = (int)(v % vol.W), y = (int)((v / vol.W) % vol.H), z = (int)(v / ((long)vol.W * vol.H));
-          const int zz = z + dz, yy = y + dy, xx = x + dx;
-          if (zz >= 0 && zz < vol.D && yy >= 0 && yy < vol.H && xx >= 0 && xx < vol.W)
-            bv = (short)X[(((long)zz * vol.H + yy) * vol.W + xx) * xcs + xco + ti * 16 + m];
-        }
-        a[i] = av;
-        b[i] = bv;
-      }
-      acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc, 0, 0, 0);
+  for (int t = 0; t < TAPS; ++t) acc[t] = f4v{0.f, 0.f, 0.f, 0.f};
+  for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+    const int x0 = (tile % ntx) * TX, y0 = ((tile / ntx) % nty) * 4, z0 = (tile / (ntx * nty)) * 2;
+    __syncthreads();
+    for (int e = threadIdx.x; e < 2 * Tl::hvox; e += 64 * Tl::waves) {
+      const int hv = e >> 1, hf = e & 1;
+      const int xx = x0 + hv % Tl::hx - 1, yy = y0 + (hv / Tl::hx) % 6 - 1, zz = z0 + hv / (Tl::hx * 6) - 1;
+      u4v val = u4v{0u, 0u, 0u, 0u};
+      if (xx >= 0 && xx < vol.W && yy >= 0 && yy < vol.H && zz >= 0 && zz < vol.D)
+        val = *reinterpret_cast<const u4v*>(X + (((long)zz * vol.H + yy) * vol.W + xx) * xcs + xco + ci + hf * 8);
+      *reinterpret_cast<u4v*>(xt + hv * 16 + hf * 8) = val;
     }
+    for (int e = threadIdx.x; e < 2 * NO * Tl::vox; e += 64 * Tl::waves) {
+      const int hf = e & 1, o = (e >> 1) % NO, v = (e >> 1) / NO;
+      const int xx = x0 + v % TX, yy = y0 + (v / TX) % 4, zz = z0 + v / (TX * 4);
+      u4v val = u4v{0u, 0u, 0u, 0u};
+      if (xx < vol.W && yy < vol.H && zz < vol.D)
+        val = *reinterpret_cast<const u4v*>(dY + (((long)zz * vol.H + yy) * vol.W + xx) * ycs + yco + (o0 + o) * 16 +
+                                            hf * 8);
+      *reinterpret_cast<u4v*>(yt + (o * Tl::vox + v) * 16 + hf * 8) = val;
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int k = part; k < Tl::vox / 32; k += Tl::ks) {
+      const int v = 32 * k + 8 * kq;                       // this lane group's eight voxels
+      const int row = v / TX, x = v % TX;
+      const bf8v a = read_rows8(yt + (ot * Tl::vox + v) * 16 + rowoff);
+      bf16_t* xb = xt + (((row >> 2) * 6 + (row & 3)) * Tl::hx + x) * 16 + rowoff;
+#pragma unroll
+      for (int t = 0; t < TAPS; ++t) {
+        const int off = TAPS == 1 ? (6 + 1) * Tl::hx + 1 : ((t / 9) * 6 + (t / 3) % 3) * Tl::hx + t % 3;
+        acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, read_rows8(xb + off * 16), acc[t], 0, 0, 0);
+      }
+    }
+  }
+  if constexpr (Tl::ks > 1) {
+    float* red = reinterpret_cast<float*>(smem) + ot * TAPS * 256;
+#pragma unroll 1
+    for (int p = 1; p < Tl::ks; ++p) {
+      __syncthreads();
+      if (part == p)
+#pragma unroll
+        for (int t = 0; t < TAPS; ++t) *reinterpret_cast<f4v*>(red + (t * 64 + lane) * 4) = acc[t];
+      __syncthreads();
+      if (part == 0)
+#pragma unroll
+        for (int t = 0; t < TAPS; ++t) acc[t] += *reinterpret_cast<const f4v*>(red + (t * 64 + lane) * 4);
+    }
+    if (part != 0) return;
+  }
+#pragma unroll
+  for (int t = 0; t < TAPS; ++t)
 #pragma unroll
     for (int r = 0; r < 4; ++r)
-      partial[(((long)blockIdx.x * TAPS + tap) * Cout + to * 16 + 4 * kq + r) * Cin + ti * 16 + m] = acc[r];
-  }
+      partial[(((long)blockIdx.x * TAPS + t) * Cout + (o0 + ot) * 16 + 4 * kq + r) * Cin + ci + m] = acc[t][r];
 }
 
 // g (+)= sum over chunks of partial (fixed order)
@@ -512,20 +581,47 @@ hipError_t conv_launch(int taps, const bf16_t* X, int xcs, int xco, int Cin, con
   return hipGetLastError();
 }
 
+// Voxel tiles are spread over enough workgroups to give every CU four (counting the
+// chunks of 16 input channels), as far as the partials fit; output tiles go in groups of
+// four, a smaller last group in a second launch.  Rows of 16 voxels where the volume is
+// no wider (the deep levels), else 32.
+template <int TAPS, int TX>
+static void wgrad_launch_no(int no, dim3 grid, int o0, hipStream_t s, const bf16_t* X, int xcs, int xco, int Cin,
+                            const bf16_t* dY, int ycs, int yco, int Cout, float* partial, Vol vol) {
+#define VIE_WGRAD(NOV)                                                                                             \
+  if (no == NOV)                                                                                                   \
+    hipLaunchKernelGGL((k_wgrad<TAPS, NOV, TX>), grid, dim3(64 * WgradTile<TAPS, NOV, TX>::waves), 0, s, X, xcs,   \
+                       xco, Cin, dY, ycs, yco, Cout, partial, vol, o0);
+  VIE_WGRAD(1)
+  VIE_WGRAD(2)
+  VIE_WGRAD(3)
+  VIE_WGRAD(4)
+#undef VIE_WGRAD
+}
+
 hipError_t wgrad_launch(int taps, const bf16_t* X, int xcs, int xco, int Cin, const bf16_t* dY, int ycs, int yco,
                         int Cout, float* partial, long partial_cap, float* g, int accumulate, Vol vol, hipStream_t s) {
-  const long V = vol.V();
   const long per = (long)taps * Cout * Cin;
-  int chunk = 2048;
-  while ((V + chunk - 1) / chunk * per > partial_cap) chunk *= 2;
-  const int nchunk = (int)((V + chunk - 1) / chunk);
-  if (taps == 27)
-    hipLaunchKernelGGL((k_wgrad<27>), dim3(nchunk, 27), dim3(256), 0, s, X, xcs, xco, Cin, dY, ycs, yco, Cout,
-                       partial, vol, chunk);
-  else
-    hipLaunchKernelGGL((k_wgrad<1>), dim3(nchunk, 1), dim3(256), 0, s, X, xcs, xco, Cin, dY, ycs, yco, Cout,
-                       partial, vol, chunk);
-  hipLaunchKernelGGL(k_wreduce, dim3(gblocks(per)), dim3(256), 0, s, partial, nchunk, per, g, accumulate);
+  const bool narrow = vol.W <= 16;
+  const int tx = narrow ? 16 : 32;
+  const long tiles = (long)((vol.D + 1) / 2) * ((vol.H + 3) / 4) * ((vol.W + tx - 1) / tx);
+  const int ichunks = Cin / 16, otiles = Cout / 16;
+  long nblk = std::max(1, 1024 / (ichunks * ((otiles + 3) / 4)));
+  nblk = std::max(1L, std::min(std::min(nblk, tiles), partial_cap / per));
+  if (nblk * per > partial_cap) return hipErrorInvalidValue;
+  for (int o0 = 0; o0 < otiles; o0 += 4) {
+    const int no = std::min(4, otiles - o0);
+    const dim3 grid((unsigned)nblk, (unsigned)ichunks);
+    if (taps == 27 && narrow)
+      wgrad_launch_no<27, 16>(no, grid, o0, s, X, xcs, xco, Cin, dY, ycs, yco, Cout, partial, vol);
+    else if (taps == 27)
+      wgrad_launch_no<27, 32>(no, grid, o0, s, X, xcs, xco, Cin, dY, ycs, yco, Cout, partial, vol);
+    else if (narrow)
+      wgrad_launch_no<1, 16>(no, grid, o0, s, X, xcs, xco, Cin, dY, ycs, yco, Cout, partial, vol);
+    else
+      wgrad_launch_no<1, 32>(no, grid, o0, s, X, xcs, xco, Cin, dY, ycs, yco, Cout, partial, vol);
+  }
+  hipLaunchKernelGGL(k_wreduce, dim3(gblocks(per)), dim3(256), 0, s, partial, (int)nblk, per, g, accumulate);
   return hipGetLastError();
 }
 

@@ -50,6 +50,27 @@ def test_conv_forward_and_gradients_match_oracle(case):
     assert err < 1e-5, ("wgrad", err)
 
 
+# edges of the weight-gradient kernel: one voxel, rows of 16 and 32 voxels filled and
+# exceeded, odd heights and depths of the 2 x 4 tile, one to five output tiles (a second
+# launch), several tiles per workgroup
+@pytest.mark.parametrize("dims,taps,cin,cout", [((1, 1, 1), 27, 16, 64), ((3, 5, 16), 27, 32, 80),
+                                                ((2, 4, 17), 27, 16, 48), ((5, 9, 40), 27, 16, 16),
+                                                ((2, 4, 32), 27, 48, 32), ((3, 6, 33), 1, 32, 48),
+                                                ((24, 32, 64), 27, 112, 16)])
+def test_weight_gradient_at_tile_edges(dims, taps, cin, cout):
+    vie = _dev()
+    rng = np.random.default_rng(sum(dims) + cin + cout)
+    X = rng.standard_normal(dims + (cin,)).astype(np.float32)
+    dY = rng.standard_normal(dims + (cout,)).astype(np.float32)
+    V = int(np.prod(dims))
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    got = vie.conv_test(2, dims, taps, cin, cout, t(X.reshape(V, cin)), t(dY.reshape(V, cout))).cpu().numpy()
+    want = nn.conv3d_wgrad(X, dY, ntaps=taps)
+    # FP32 sums of V products of unit variance: rounding of order 2^-24 sqrt(V) of an entry of size sqrt(V)
+    err = np.max(np.abs(got - want)) / max(np.max(np.abs(want)), np.sqrt(V))
+    assert err < 1e-5, err
+
+
 def _chi(wg):
     return torch.from_numpy(mv.contrast(wg.eps(), wg.eps_b)).cuda()
 
