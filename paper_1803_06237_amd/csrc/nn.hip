@@ -293,13 +293,38 @@ __global__ __launch_bounds__((64 * WgradTile<TAPS, NO, TX>::waves)) void k_wgrad
       partial[(((long)blockIdx.x * TAPS + t) * Cout + (o0 + ot) * 16 + 4 * kq + r) * Cin + ci + m] = acc[t][r];
 }
 
-// g (+)= sum over chunks of partial (fixed order)
-__global__ void k_wreduce(const float* __restrict__ partial, int nchunk, long per, float* __restrict__ g,
-                          int accumulate) {
-  for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < per; i += (long)gridDim.x * blockDim.x) {
+// g (+)= sum over chunks of partial, in a fixed order.  A block sums 64 entries with 16
+// threads each (every 16th chunk, four loads in flight), then adds the 16 through LDS: with
+// one thread per entry the up to 1000 partials of a layer were one chain of loads (43 us a
+// layer on average at 32 x 32 x 128).
+constexpr int kWrSplit = 16;
+__global__ __launch_bounds__(64 * kWrSplit) void k_wreduce(const float* __restrict__ partial, int nchunk, long per,
+                                                           float* __restrict__ g, int accumulate) {
+  __shared__ float red[kWrSplit][64];
+  const int lane = threadIdx.x & 63, part = threadIdx.x >> 6;
+  for (long i0 = (long)blockIdx.x * 64; i0 < per; i0 += (long)gridDim.x * 64) {
+    const long i = i0 + lane;
     float s = 0.f;
-    for (int c = 0; c < nchunk; ++c) s += partial[(long)c * per + i];
-    g[i] = accumulate ? g[i] + s : s;
+    if (i < per) {
+      int c = part;
+      for (; c + 3 * kWrSplit < nchunk; c += 4 * kWrSplit) {
+        float v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = partial[(long)(c + k * kWrSplit) * per + i];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) s += v[k];
+      }
+      for (; c < nchunk; c += kWrSplit) s += partial[(long)c * per + i];
+    }
+    red[part][lane] = s;
+    __syncthreads();
+    if (part == 0 && i < per) {
+      float t = 0.f;
+#pragma unroll
+      for (int k = 0; k < kWrSplit; ++k) t += red[k][lane];
+      g[i] = accumulate ? g[i] + t : t;
+    }
+    __syncthreads();
   }
 }
 
@@ -621,7 +646,8 @@ hipError_t wgrad_launch(int taps, const bf16_t* X, int xcs, int xco, int Cin, co
     else
       wgrad_launch_no<1, 32>(no, grid, o0, s, X, xcs, xco, Cin, dY, ycs, yco, Cout, partial, vol);
   }
-  hipLaunchKernelGGL(k_wreduce, dim3(gblocks(per)), dim3(256), 0, s, partial, (int)nblk, per, g, accumulate);
+  hipLaunchKernelGGL(k_wreduce, dim3((unsigned)std::min<long>(4096, (per + 63) / 64)), dim3(64 * kWrSplit), 0, s,
+                     partial, (int)nblk, per, g, accumulate);
   return hipGetLastError();
 }
 
