@@ -34,6 +34,7 @@ typedef unsigned short bf16_t;
 typedef short s4v __attribute__((ext_vector_type(4)));
 typedef __bf16 bf8v __attribute__((ext_vector_type(8)));
 typedef unsigned int u4v __attribute__((ext_vector_type(4)));
+typedef unsigned int u2v __attribute__((ext_vector_type(2)));
 typedef float f4v __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ bf16_t f2bf(float f) {   // round to nearest, ties to even
@@ -83,7 +84,7 @@ template <int TAPS, int NT, int TZ, int MT>
 __global__ __launch_bounds__(256) void k_conv2(const bf16_t* __restrict__ X, int xcs, int xco, int Cin,
                                                const bf16_t* __restrict__ Wt, int Cout, bf16_t* __restrict__ Y,
                                                int ycs, int yco, float* __restrict__ Yf, Vol vol, int relu,
-                                               const bf16_t* __restrict__ mask, int mcs, int mco, int g0) {
+                                               const bf16_t* __restrict__ mask, int mcs, int mco, int n0) {
   using Tl = ConvTile<TZ, MT>;
   constexpr int kHx = Tl::hx, kHy = Tl::hy, kHvox = Tl::hvox;
   constexpr int MI = TZ * MT;                  // M-tiles per wave
@@ -99,45 +100,82 @@ __global__ __launch_bounds__(256) void k_conv2(const bf16_t* __restrict__ X, int
   const int ty = b % nty;
   const int tz = b / nty;
   const int x0 = tx * Tl::tx, y0 = ty * Tl::ty, z0 = tz * Tl::tz;
-  const int nt0 = (g0 + blockIdx.y) * 4;       // first N-tile of this workgroup's group
+  const int nt0 = n0 + blockIdx.y * NT;        // first N-tile of this workgroup's group
   const int m = lane & 15, kq = lane >> 4;     // fragment row / K-quarter
   const int half = kq & 1, second = kq >> 1;   // channel half, which tap of the pair
   // wave rows: TZ = 2: (wave / 2, 2 (wave % 2) + {0, 1}); TZ = 1: (0, wave)
   const int wz = TZ == 2 ? wave >> 1 : 0, wy = TZ == 2 ? 2 * (wave & 1) : wave;
   // this lane's halo row for tap offset 0 (the halo corner) of its first M-tile
   const int lds_lane = (half * kHvox + (wz * kHy + wy) * kHx + m) * 8;
+  // piece e of the chunk's halo tile: channels 8 (e & 1) .. + 7 of halo voxel e / 2
+  auto halo_voxel = [&](int e) {               // -1 outside the volume
+    const int hv = e >> 1;
+    const int xx = x0 + hv % kHx - 1, yy = y0 + (hv / kHx) % kHy - 1, zz = z0 + hv / (kHx * kHy) - 1;
+    const bool in = xx >= 0 && xx < vol.W && yy >= 0 && yy < vol.H && zz >= 0 && zz < vol.D;
+    return in ? (zz * vol.H + yy) * vol.W + xx : -1;
+  };
+  auto halo_load = [&](int e, int v, int ch) {
+    return v >= 0 ? *reinterpret_cast<const u4v*>(X + (long)v * xcs + xco + ch * 16 + (e & 1) * 8)
+                  : u4v{0u, 0u, 0u, 0u};
+  };
+  auto halo_store = [&](int e, u4v v) {
+    *reinterpret_cast<u4v*>(tile + ((e & 1) * kHvox + (e >> 1)) * 8) = v;
+  };
+  // B fragment e = (pair, N-tile, lane) of the chunk: W[tap][co][ci .. ci + 7]
+  auto frag_load = [&](int e, int ch) {
+    const int l = e & 63, t = (e >> 6) % NT, tp = (e >> 6) / NT;
+    const int lm = l & 15, lq = l >> 4;
+    const int tap = TAPS == 1 ? 0 : 2 * tp + (lq >> 1);
+    u4v val = u4v{0u, 0u, 0u, 0u};
+    if (TAPS == 1 ? (lq >> 1) == 0 : tap < 27)
+      val = *reinterpret_cast<const u4v*>(Wt + ((long)tap * Cout + (nt0 + t) * 16 + lm) * Cin + ch * 16 + (lq & 1) * 8);
+    return val;
+  };
+  // The next chunk's halo pieces and B fragments wait in registers while this chunk's MFMAs
+  // run: a chunk then costs its compute, not its memory latency.  Not for the large tile with
+  // one N-tile: its layers have one chunk (48 -> 16: three) and four workgroups per CU to
+  // overlap, which the registers would not leave room for (25 us a layer at 32 x 32 x 256).
+  constexpr bool kAhead = TZ == 1 || NT > 1;
+  constexpr int kHalo = 2 * kHvox, kFrag = NPAIR * NT * 64;
+  constexpr int NH = kAhead ? (kHalo + 255) / 256 : 1, NW = kAhead ? (kFrag + 255) / 256 : 1;
+  u4v hreg[NH], wreg[NW];
+  int hvox[NH];
+  auto load_chunk = [&](int ch) {
+#pragma unroll
+    for (int q = 0; q < NH; ++q) hreg[q] = halo_load(threadIdx.x, hvox[q], ch);
+#pragma unroll
+    for (int q = 0; q < NW; ++q)
+      if ((int)threadIdx.x + 256 * q < kFrag) wreg[q] = frag_load(threadIdx.x + 256 * q, ch);
+  };
   f4v acc[MI][NT];
 #pragma unroll
   for (int i = 0; i < MI; ++i)
 #pragma unroll
     for (int t = 0; t < NT; ++t) acc[i][t] = f4v{0.f, 0.f, 0.f, 0.f};
   const int nchunk = Cin / 16;
+  if constexpr (kAhead) {
+#pragma unroll
+    for (int q = 0; q < NH; ++q) {
+      const int e = threadIdx.x + 256 * q;
+      hvox[q] = e < kHalo ? halo_voxel(e) : -1;
+    }
+    load_chunk(0);
+  }
   for (int ch = 0; ch < nchunk; ++ch) {
     __syncthreads();
-    // halo tile: one 16-byte (8-channel) piece per step
-    for (int e = threadIdx.x; e < 2 * kHvox; e += 256) {
-      const int hv = e >> 1, hf = e & 1;
-      const int hx = hv % kHx, hy = (hv / kHx) % kHy, hz = hv / (kHx * kHy);
-      const int xx = x0 + hx - 1, yy = y0 + hy - 1, zz = z0 + hz - 1;
-      u4v val = u4v{0u, 0u, 0u, 0u};
-      if (xx >= 0 && xx < vol.W && yy >= 0 && yy < vol.H && zz >= 0 && zz < vol.D) {
-        const long v = ((long)zz * vol.H + yy) * vol.W + xx;
-        val = *reinterpret_cast<const u4v*>(X + v * xcs + xco + ch * 16 + hf * 8);
-      }
-      *reinterpret_cast<u4v*>(tile + ((long)hf * kHvox + hv) * 8) = val;
-    }
-    // B fragments of the chunk: entry (pair, N-tile, lane) = W[tap][co][ci .. ci + 7]
-    for (int e = threadIdx.x; e < NPAIR * NT * 64; e += 256) {
-      const int l = e & 63, t = (e >> 6) % NT, tp = (e >> 6) / NT;
-      const int lm = l & 15, lq = l >> 4;
-      const int tap = TAPS == 1 ? 0 : 2 * tp + (lq >> 1);
-      u4v val = u4v{0u, 0u, 0u, 0u};
-      if (TAPS == 1 ? (lq >> 1) == 0 : tap < 27)
-        val = *reinterpret_cast<const u4v*>(Wt + ((long)tap * Cout + (nt0 + t) * 16 + lm) * Cin + ch * 16 +
-                                            (lq & 1) * 8);
-      wfrag[e] = val;
+    if constexpr (kAhead) {
+#pragma unroll
+      for (int q = 0; q < NH; ++q)
+        if ((int)threadIdx.x + 256 * q < kHalo) halo_store(threadIdx.x + 256 * q, hreg[q]);
+#pragma unroll
+      for (int q = 0; q < NW; ++q)
+        if ((int)threadIdx.x + 256 * q < kFrag) wfrag[threadIdx.x + 256 * q] = wreg[q];
+    } else {
+      for (int e = threadIdx.x; e < kHalo; e += 256) halo_store(e, halo_load(e, halo_voxel(e), ch));
+      for (int e = threadIdx.x; e < kFrag; e += 256) wfrag[e] = frag_load(e, ch);
     }
     __syncthreads();
+    if (kAhead && ch + 1 < nchunk) load_chunk(ch + 1);
 #pragma unroll
     for (int tp = 0; tp < NPAIR; ++tp) {
       constexpr int kStep = kHx * kHy;
@@ -155,32 +193,42 @@ __global__ __launch_bounds__(256) void k_conv2(const bf16_t* __restrict__ X, int
         // M-tile i: row (i / MT) of the wave, voxels 16 (i % MT) .. + 15
         const int ao = lds_lane + (off + (i / MT) * kHx + 16 * (i % MT)) * 8;
         const bf8v a = __builtin_bit_cast(bf8v, *reinterpret_cast<const u4v*>(tile + ao));
+        // weights as the first operand: a lane then holds four consecutive output
+        // channels of one voxel, stored as one 8-byte (FP32: 16-byte) value
 #pragma unroll
-        for (int t = 0; t < NT; ++t) acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bfr[t], acc[i][t], 0, 0, 0);
+        for (int t = 0; t < NT; ++t)
+          acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[t], a, acc[i][t], 0, 0, 0);
       }
     }
   }
-  // D[row = 4 kq + r][col = m]: voxel 16 (i % MT) + 4 kq + r of wave row i / MT
+  // D[row = 4 kq + r][col = m]: channel 4 kq + r, voxel 16 (i % MT) + m of wave row i / MT
   const int zz = z0 + wz;
   if (zz >= vol.D) return;
 #pragma unroll
   for (int i = 0; i < MI; ++i) {
-    const int yy = y0 + wy + i / MT;
-    if (yy >= vol.H) continue;
+    const int yy = y0 + wy + i / MT, xx = x0 + 16 * (i % MT) + m;
+    if (yy >= vol.H || xx >= vol.W) continue;
+    const long vo = ((long)zz * vol.H + yy) * vol.W + xx;
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-      const int n = (nt0 + t) * 16 + m;
+      const int n = (nt0 + t) * 16 + 4 * kq;
+      f4v val = acc[i][t];
+      if (relu)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int xx = x0 + 16 * (i % MT) + 4 * kq + r;
-        if (xx >= vol.W) continue;
-        const long vo = ((long)zz * vol.H + yy) * vol.W + xx;
-        float val = acc[i][t][r];
-        if (relu) val = fmaxf(val, 0.f);
-        if (mask) val = bf2f(mask[vo * mcs + mco + n]) > 0.f ? val : 0.f;
-        if (Y) Y[vo * ycs + yco + n] = f2bf(val);
-        if (Yf) Yf[vo * Cout + n] = val;
+        for (int r = 0; r < 4; ++r) val[r] = fmaxf(val[r], 0.f);
+      if (mask) {
+        const u2v mk = *reinterpret_cast<const u2v*>(mask + vo * mcs + mco + n);
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          val[r] = __uint_as_float(r & 1 ? mk[r / 2] & 0xFFFF0000u : mk[r / 2] << 16) > 0.f ? val[r] : 0.f;
       }
+      if (Y) {
+        u2v o;
+#pragma unroll
+        for (int r = 0; r < 2; ++r) o[r] = (unsigned)f2bf(val[2 * r]) | ((unsigned)f2bf(val[2 * r + 1]) << 16);
+        *reinterpret_cast<u2v*>(Y + vo * ycs + yco + n) = o;
+      }
+      if (Yf) *reinterpret_cast<f4v*>(Yf + vo * Cout + n) = val;
     }
   }
 }
@@ -538,42 +586,42 @@ static inline AdamK adam_constants(int t, float lr) {
 static inline int gblocks(long n) { return (int)std::min<long>(4096, (n + 255) / 256); }
 
 // k_conv2 may use more than 64 KiB of dynamic LDS (83.5 KiB with four N-tiles)
-template <int TAPS, int TZ, int MT>
-static hipError_t allow_conv_lds_shape() {
+template <int TAPS>
+static hipError_t allow_conv_lds_taps() {
   const auto a = hipFuncAttributeMaxDynamicSharedMemorySize;
   hipError_t e;
-  if ((e = hipFuncSetAttribute((const void*)k_conv2<TAPS, 1, TZ, MT>, a, (int)conv2_lds<TZ, MT>(TAPS, 1)))) return e;
-  if ((e = hipFuncSetAttribute((const void*)k_conv2<TAPS, 2, TZ, MT>, a, (int)conv2_lds<TZ, MT>(TAPS, 2)))) return e;
-  if ((e = hipFuncSetAttribute((const void*)k_conv2<TAPS, 3, TZ, MT>, a, (int)conv2_lds<TZ, MT>(TAPS, 3)))) return e;
-  return hipFuncSetAttribute((const void*)k_conv2<TAPS, 4, TZ, MT>, a, (int)conv2_lds<TZ, MT>(TAPS, 4));
+  if ((e = hipFuncSetAttribute((const void*)k_conv2<TAPS, 1, 2, 2>, a, (int)conv2_lds<2, 2>(TAPS, 1)))) return e;
+  if ((e = hipFuncSetAttribute((const void*)k_conv2<TAPS, 2, 2, 2>, a, (int)conv2_lds<2, 2>(TAPS, 2)))) return e;
+  if ((e = hipFuncSetAttribute((const void*)k_conv2<TAPS, 3, 2, 2>, a, (int)conv2_lds<2, 2>(TAPS, 3)))) return e;
+  if ((e = hipFuncSetAttribute((const void*)k_conv2<TAPS, 4, 2, 2>, a, (int)conv2_lds<2, 2>(TAPS, 4)))) return e;
+  return hipFuncSetAttribute((const void*)k_conv2<TAPS, 1, 1, 1>, a, (int)conv2_lds<1, 1>(TAPS, 1));
 }
 static hipError_t allow_conv_lds() {
-  hipError_t e;
-  if ((e = allow_conv_lds_shape<27, 2, 2>())) return e;
-  if ((e = allow_conv_lds_shape<1, 2, 2>())) return e;
-  if ((e = allow_conv_lds_shape<27, 1, 1>())) return e;
-  return allow_conv_lds_shape<1, 1, 1>();
+  const hipError_t e = allow_conv_lds_taps<27>();
+  return e ? e : allow_conv_lds_taps<1>();
 }
 
-template <int TAPS, int TZ, int MT>
-static void conv2_launch_nt(int nt, dim3 grid, int g0, hipStream_t s, const bf16_t* X, int xcs, int xco, int Cin,
-                            const bf16_t* W, int Cout, bf16_t* Y, int ycs, int yco, float* Yf, Vol vol, int relu,
-                            const bf16_t* mask, int mcs, int mco) {
-  const size_t lds = conv2_lds<TZ, MT>(TAPS, nt);
-#define VIE_CONV2(NTV)                                                                                           \
-  if (nt == NTV)                                                                                                 \
-    hipLaunchKernelGGL((k_conv2<TAPS, NTV, TZ, MT>), grid, dim3(256), lds, s, X, xcs, xco, Cin, W, Cout, Y, ycs,  \
-                       yco, Yf, vol, relu, mask, mcs, mco, g0);
-  VIE_CONV2(1)
-  VIE_CONV2(2)
-  VIE_CONV2(3)
-  VIE_CONV2(4)
+template <int TAPS>
+static void conv2_launch_nt(bool big, int nt, dim3 grid, int n0, hipStream_t s, const bf16_t* X, int xcs, int xco,
+                            int Cin, const bf16_t* W, int Cout, bf16_t* Y, int ycs, int yco, float* Yf, Vol vol,
+                            int relu, const bf16_t* mask, int mcs, int mco) {
+#define VIE_CONV2(NTV, TZ, MT)                                                                                   \
+  if (nt == NTV && big == (TZ == 2))                                                                             \
+    hipLaunchKernelGGL((k_conv2<TAPS, NTV, TZ, MT>), grid, dim3(256), (conv2_lds<TZ, MT>(TAPS, NTV)), s, X, xcs,  \
+                       xco, Cin, W, Cout, Y, ycs, yco, Yf, vol, relu, mask, mcs, mco, n0);
+  VIE_CONV2(1, 2, 2)
+  VIE_CONV2(2, 2, 2)
+  VIE_CONV2(3, 2, 2)
+  VIE_CONV2(4, 2, 2)
+  VIE_CONV2(1, 1, 1)
 #undef VIE_CONV2
 }
 
-// Output-channel groups of four N-tiles in one launch, a smaller last group in a
-// second.  The 2 x 4 x 32 voxel tile where it gives at least 512 workgroups, else the
-// 1 x 4 x 16 tile (the small levels of the network).
+// The 2 x 4 x 32 voxel tile where it gives at least 512 workgroups, with output-channel
+// groups of four N-tiles in one launch and a smaller last group in a second; else the
+// 1 x 4 x 16 tile (the small levels of the network) with one N-tile per workgroup: at
+// level 2 of 32 x 32 x 256 three N-tiles leave 64 workgroups for 256 CUs, one gives 192
+// with a third of the weights to stage each.
 hipError_t conv_launch(int taps, const bf16_t* X, int xcs, int xco, int Cin, const bf16_t* W, int Cout, bf16_t* Y,
                        int ycs, int yco, float* Yf, Vol vol, int relu, const bf16_t* mask, int mcs, int mco,
                        hipStream_t s) {
@@ -582,27 +630,18 @@ hipError_t conv_launch(int taps, const bf16_t* X, int xcs, int xco, int Cin, con
   const long big = (long)((vol.D + 1) / 2) * ((vol.H + kCty - 1) / kCty) * ((vol.W + 31) / 32);
   const long small = (long)vol.D * ((vol.H + kCty - 1) / kCty) * ((vol.W + 15) / 16);
   const bool use_big = big >= 512;
-  const int ntiles = Cout / 16, full = ntiles / 4, rest = ntiles % 4;
-  auto go = [&](int nt, int groups, int g0) {
+  const int ntiles = Cout / 16, per = use_big ? 4 : 1, full = ntiles / per, rest = ntiles % per;
+  auto go = [&](int nt, int groups, int n0) {
     const dim3 grid((unsigned)(use_big ? big : small), (unsigned)groups);
-    if (use_big) {
-      if (taps == 27)
-        conv2_launch_nt<27, 2, 2>(nt, grid, g0, s, X, xcs, xco, Cin, W, Cout, Y, ycs, yco, Yf, vol, relu, mask, mcs,
-                                  mco);
-      else
-        conv2_launch_nt<1, 2, 2>(nt, grid, g0, s, X, xcs, xco, Cin, W, Cout, Y, ycs, yco, Yf, vol, relu, mask, mcs,
-                                 mco);
-    } else {
-      if (taps == 27)
-        conv2_launch_nt<27, 1, 1>(nt, grid, g0, s, X, xcs, xco, Cin, W, Cout, Y, ycs, yco, Yf, vol, relu, mask, mcs,
-                                  mco);
-      else
-        conv2_launch_nt<1, 1, 1>(nt, grid, g0, s, X, xcs, xco, Cin, W, Cout, Y, ycs, yco, Yf, vol, relu, mask, mcs,
-                                 mco);
-    }
+    if (taps == 27)
+      conv2_launch_nt<27>(use_big, nt, grid, n0, s, X, xcs, xco, Cin, W, Cout, Y, ycs, yco, Yf, vol, relu, mask, mcs,
+                          mco);
+    else
+      conv2_launch_nt<1>(use_big, nt, grid, n0, s, X, xcs, xco, Cin, W, Cout, Y, ycs, yco, Yf, vol, relu, mask, mcs,
+                         mco);
   };
-  if (full) go(4, full, 0);
-  if (rest) go(rest, 1, full);
+  if (full) go(per, full, 0);
+  if (rest) go(rest, 1, full * per);
   return hipGetLastError();
 }
 
