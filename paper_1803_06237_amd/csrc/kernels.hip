@@ -102,7 +102,8 @@ __global__ __launch_bounds__(1024) void k_zinv(const cx<T>* __restrict__ U, cons
 }
 
 // ------------------------------------------------------------------ pass 2
-// Cross-sections other than 64 x 64: one workgroup per kz plane.  x transforms
+// Cross-sections the register kernels do not take (a side of 1, 2 or 4 points), and the 64 x 32
+// pass the tuner compares with them: one workgroup per kz plane.  x transforms
 // of the 3 n2 valid rows, then for each chunk of cc x-frequencies the y
 // transforms, the 3 x 3 Green product and the inverse y transforms, finally the
 // inverse x transforms and the crop; U is read and overwritten in place.  The
@@ -196,6 +197,8 @@ hipError_t launch_pass(int which, const Geom& g, const Tune& t, const void* x, v
     return launch_xy64<T>(g, t.xyv, U, goct, tw[0], s);
   } else if (which == 1 && g.M1 == 64 && g.M2 == 32 && (t.xyv == 1 || t.xyv == 2)) {
     return launch_xy6432<T>(g, t.xyv, U, goct, tw[0], tw[1], s);
+  } else if (which == 1 && xyr_fits(g)) {
+    return launch_xyr<T>(g, U, goct, tw[0], tw[1], s);
   } else if (which == 1) {
     hipLaunchKernelGGL((k_xyp<T>), dim3(g.M3), dim3(t.xythreads), xy_lds_bytes<T>(g, t.cc), s, (C*)U,
                        (const C*)goct, g, t.cc, (const C*)tw[0], (const C*)tw[1]);

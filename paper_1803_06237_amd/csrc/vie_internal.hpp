@@ -65,6 +65,15 @@ hipError_t launch_spectrum(const Geom& g, const double2* table_dev, double2* ful
 hipError_t launch_curl_spectrum(const Geom& g, const double2* ktable_dev, double2* full_tmp, double2* koct64,
                                 float2* koct32, const double2* const tw64[3], hipStream_t s);
 
+// Register-transform xy pass (xyr.hip): cross-sections of 8 to 64 points a side other than
+// 64 x 64 and 64 x 32, which have kernels of their own.  Its batched form takes 64 x 32 too,
+// in items of xyr_planes_per_group planes.
+bool xyr_fits(const Geom& g);
+bool xyr_fits_batch(const Geom& g);
+int xyr_planes_per_group(const Geom& g);
+template <typename T>
+hipError_t launch_xyr(const Geom& g, void* U, const void* goct, const void* tw1, const void* tw2, hipStream_t s);
+
 // LDS bytes of the generic xy pass with column chunks of cc x-frequencies
 template <typename T>
 size_t xy_lds_bytes(const Geom& g, int cc);
@@ -107,6 +116,7 @@ struct PassDesc {
   const void* chi;
   const void* twz;      // z twiddles, length M3
   const void* twx;      // x twiddles, length M1
+  const void* twy;      // y twiddles, length M2
   int P;                // pencils per workgroup in the z passes
   const int* active;    // device flag; 0 skips the system (nullptr: always on)
 };

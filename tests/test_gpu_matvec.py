@@ -291,6 +291,38 @@ def test_every_64x32_xy_variant_matches_the_oracle(n):
             assert err < (1e-12 if precision == 0 else 5e-6)
 
 
+# register cross-section pass: every circulant cross-section of 8 to 64 points a side it takes
+# (rows and columns of 1, 2, 4 and 8 lanes), sizes that fill and just exceed a power of two,
+# and fewer planes than a workgroup has room for (z circulants of 1, 4, 8); 16-row shapes
+# with 512 planes, from where the pass is used for them
+@pytest.mark.parametrize("n", [(4, 3, 1), (3, 4, 2), (5, 4, 3), (9, 3, 2), (17, 4, 3), (32, 3, 1), (4, 7, 3),
+                               (8, 8, 2), (16, 5, 5), (31, 8, 2), (3, 9, 4), (6, 16, 3), (10, 13, 3), (4, 17, 2),
+                               (7, 32, 2), (16, 25, 3), (4, 5, 257), (5, 8, 300), (3, 9, 260)], ids=lambda g: "x".join(map(str, g)))
+def test_register_cross_sections_match_the_oracle(n):
+    vie = _dev()
+    rng = np.random.default_rng(1000 + sum(n))
+    kap = mv.kappa_of(H, K0, EPSB)
+    spec = mv.spectrum(green.green_table(n, kap))
+    eps = EPSB + 10 * rng.random(n) + 1j * rng.random(n)
+    chi = mv.contrast(eps, EPSB)
+    plan = vie.Plan(n, H, K0, EPSB, fp32=True)
+    plan.set_contrast(_t(eps))
+    x = _cvec(rng, (3,) + n)
+    want = mv.matvec_fft(spec, chi, x)
+    for got, bar in ((plan.matvec(_t(x)), 1e-12), (plan.matvec_c64(_t(x, torch.complex64)), 5e-6)):
+        err = np.linalg.norm(got.cpu().numpy() - want) / np.linalg.norm(want)
+        assert err < bar, (got.dtype, err)
+
+
+def test_register_cross_section_with_many_planes_sampled_outputs():
+    """9 x 9 x 400 (32 x 32 x 1024): more workgroups than CUs, the form without preloaded spectra."""
+    vie = _dev()
+    wg = inputs.Waveguide(n=(9, 9, 400), h=0.05, core_x=(2, 7), core_y=(2, 7), core_z=(0, 400), n_abs=40, d=2,
+                          sigma_max=2.0)
+    assert _sparse_sample_check(vie, wg, nnz=16, nout=48, precision=64, seed=5) < 1e-12
+    assert _sparse_sample_check(vie, wg, nnz=16, nout=48, precision=32, seed=6) < 5e-6
+
+
 TUNED_GRIDS = {
     "30x12x1377_M3_4096": lambda: inputs.strip_paper(9.45, 2),
     "32x32x512_M3_1024": lambda: inputs.strip_long(d=2),
