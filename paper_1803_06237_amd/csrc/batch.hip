@@ -98,7 +98,8 @@ struct KDesc {
 
 // Support compression of one system: Krylov vectors hold the 3 s n3 values of the
 // support columns, comp[(a s + p) n3 + i3] = full[a][col[p]][i3], and the product
-// runs on the full-length buffers fx (zero off the support) and fy.
+// runs on the full-length buffers fx (zero off the support) and fy.  fx is null where the
+// support is every column: the product then runs on the vectors themselves.
 struct SDesc {
   const int* col;   // s increasing column indices i1 n2 + i2
   int s;
@@ -444,6 +445,7 @@ __global__ __launch_bounds__(kT) void k_b_scatter(const KDesc* __restrict__ d, c
     const KDesc& D = d[s];
     if ((act_sel ? *D.act0 : *D.act) == 0) continue;
     const SDesc& S = sd[s];
+    if (!S.fx) continue;
     const cx<T>* src = vsel<T>(D, which, j);
     cx<T>* fx = (cx<T>*)S.fx;
     const long e0 = (long)(item - prefix[s]) * kC + threadIdx.x;
@@ -466,6 +468,7 @@ __global__ __launch_bounds__(kT) void k_b_gather(const KDesc* __restrict__ d, co
     const KDesc& D = d[s];
     if ((act_sel ? *D.act0 : *D.act) == 0) continue;
     const SDesc& S = sd[s];
+    if (!S.fx) continue;
     cx<T>* dst = vsel<T>(D, which, j);
     const cx<T>* b = (const cx<T>*)D.b;
     const cx<T>* fy = (const cx<T>*)S.fy;
@@ -490,13 +493,7 @@ using namespace vie;
 
 namespace {
 
-struct SysPlan {            // what the batch needs from a plan
-  Geom g;
-  Tune t64, t32;
-  void *U64, *U32, *goct64, *goct32, *chi64, *chi32;
-  const void* tw64[3];
-  const void* tw32[3];
-};
+struct SysPlan : SolveView {};   // the operator of one system; U64, U32 are the batch's own
 
 template <typename T>
 struct BatchLevel {         // one Krylov level (outer FP64 or inner FP32) for the whole batch
@@ -522,8 +519,8 @@ struct BatchLevel {         // one Krylov level (outer FP64 or inner FP32) for t
   }
 };
 
-// matvec descriptors for one level: step (V_j or Z_j -> V_{j+1}) and residual (x -> r),
-// both on the full-length buffers of the support descriptors
+// matvec descriptors for one level: step (V_j or Z_j -> V_{j+1}) and residual (x -> r), on
+// the full-length buffers of the support descriptors or, for direct systems, on the vectors
 struct PassSet {
   std::vector<SDesc> h_sd;        // per system, filled before build_passes
   SDesc* d_sd = nullptr;
@@ -533,6 +530,7 @@ struct PassSet {
   // z-pass groups: systems sharing a four-step shape, launched together
   struct Group {
     int A, B, P;
+    bool direct;
     std::vector<int> sys;
     int* d_zpre = nullptr;
     int ztotal = 0;
@@ -541,11 +539,17 @@ struct PassSet {
   };
   std::vector<Group> zgroups;
   std::vector<int> zsingle;      // systems on the generic z kernels
-  std::vector<int> xy_sys;       // systems on the batched xy64 kernel
-  int* d_xypre = nullptr;
-  int xytotal = 0;
-  PassDesc* d_xy = nullptr;       // step flags
-  PassDesc* d_xy_res = nullptr;   // cycle flags (residual products)
+  // cross-section groups: systems of one circulant cross-section with a batched kernel
+  struct XyGroup {
+    int M1, M2;
+    std::vector<int> sys;
+    int* d_pre = nullptr;
+    int total = 0;
+    PassDesc* d_step = nullptr;   // step flags
+    PassDesc* d_res = nullptr;    // cycle flags (residual products)
+  };
+  std::vector<XyGroup> xygroups;
+  bool any_scatter = false;       // some system is not direct
   std::vector<int> xysingle;
 };
 
@@ -647,37 +651,67 @@ hipError_t build_passes(vie_batch_s* B, PassSet& PS, const BatchLevel<T>& L, std
     pd.chi = dbl ? P.chi64 : P.chi32;
     pd.twz = dbl ? P.tw64[2] : P.tw32[2];
     pd.twx = dbl ? P.tw64[0] : P.tw32[0];
-    // the products read fx and write fy; the batched scatter and gather around
-    // them move the compressed Krylov vectors
+    pd.twy = dbl ? P.tw64[1] : P.tw32[1];
     pd.active = D.act;
-    pd.xb = PS.h_sd[s].fx;
-    pd.xs = 0;
-    pd.yb = PS.h_sd[s].fy;
-    pd.ys = 0;
-    pd.b = nullptr;
+    if (P.direct) {
+      pd.xb = L.flex ? D.Z : D.V;
+      pd.yb = D.V;
+      pd.xs = pd.ys = D.n;
+    } else {
+      // the products read fx and write fy; the batched scatter and gather around
+      // them move the compressed Krylov vectors
+      pd.xb = PS.h_sd[s].fx;
+      pd.yb = PS.h_sd[s].fy;
+      PS.any_scatter = true;
+    }
     PS.h_step[s] = pd;
     pd.active = D.act0;
+    if (P.direct) {
+      pd.xb = D.x;
+      pd.yb = D.r;
+      pd.b = D.b;
+      pd.xs = pd.ys = 0;
+    }
     PS.h_res[s] = pd;
   }
   if ((e = alloc((void**)&PS.d_sd, sizeof(SDesc) * n))) return e;
   if ((e = hipMemcpy(PS.d_sd, PS.h_sd.data(), sizeof(SDesc) * n, hipMemcpyHostToDevice))) return e;
-  // z groups
+  // z groups.  A plan's own operator keeps its tuned choice between the four-step and the
+  // generic passes; on a box the batch has pencils enough for the four-step ones, short of
+  // the FP64 shapes with 64 values per thread.  Pencils per workgroup: those that leave the
+  // fewest idle in the last block of a row, then the most.
   for (int s = 0; s < n; ++s) {
     int A, Bv, Pp;
-    const Tune& t = dbl ? B->sp[s].t64 : B->sp[s].t32;
-    if (t.z4 && z4_shape<T>(B->sp[s].g.M3, &A, &Bv, &Pp)) {
-      auto it = std::find_if(PS.zgroups.begin(), PS.zgroups.end(),
-                             [&](const PassSet::Group& G) { return G.A == A && G.B == Bv && G.P == Pp; });
+    const SysPlan& P = B->sp[s];
+    const Tune& t = dbl ? P.t64 : P.t32;
+    if ((P.box ? !(dbl && P.g.M3 >= 2048) : t.z4 != 0) && z4_shape<T>(P.g.M3, &A, &Bv, &Pp)) {
+      int opts[8];
+      const int no = z4_pencil_options<T>(P.g.M3, opts, 8);
+      auto padded = [&](int q) { return (P.g.n1 + q - 1) / q * q; };
+      for (int i = 0; i < no; ++i)
+        if (padded(opts[i]) < padded(Pp) || (padded(opts[i]) == padded(Pp) && opts[i] > Pp)) Pp = opts[i];
+      auto it = std::find_if(PS.zgroups.begin(), PS.zgroups.end(), [&](const PassSet::Group& G) {
+        return G.A == A && G.B == Bv && G.P == Pp && G.direct == P.direct;
+      });
       if (it == PS.zgroups.end()) {
-        PS.zgroups.push_back(PassSet::Group{A, Bv, Pp, {}, nullptr, 0, nullptr, nullptr});
+        PS.zgroups.push_back(PassSet::Group{A, Bv, Pp, P.direct, {}, nullptr, 0, nullptr, nullptr});
         it = PS.zgroups.end() - 1;
       }
       it->sys.push_back(s);
     } else {
       PS.zsingle.push_back(s);
     }
-    if (B->sp[s].g.M1 == 64 && B->sp[s].g.M2 == 64) PS.xy_sys.push_back(s);
-    else PS.xysingle.push_back(s);
+    if (!((P.g.M1 == 64 && P.g.M2 == 64) || xyr_fits_batch(P.g))) {
+      PS.xysingle.push_back(s);
+      continue;
+    }
+    auto it = std::find_if(PS.xygroups.begin(), PS.xygroups.end(),
+                           [&](const PassSet::XyGroup& G) { return G.M1 == P.g.M1 && G.M2 == P.g.M2; });
+    if (it == PS.xygroups.end()) {
+      PS.xygroups.push_back(PassSet::XyGroup{P.g.M1, P.g.M2, {}, nullptr, 0, nullptr, nullptr});
+      it = PS.xygroups.end() - 1;
+    }
+    it->sys.push_back(s);
   }
   for (auto& G : PS.zgroups) {
     std::vector<int> pre(G.sys.size() + 1, 0);
@@ -698,72 +732,79 @@ hipError_t build_passes(vie_batch_s* B, PassSet& PS, const BatchLevel<T>& L, std
     if ((e = alloc((void**)&G.d_res, sizeof(PassDesc) * rs.size()))) return e;
     if ((e = hipMemcpy(G.d_res, rs.data(), sizeof(PassDesc) * rs.size(), hipMemcpyHostToDevice))) return e;
   }
-  if (!PS.xy_sys.empty()) {
-    std::vector<int> pre(PS.xy_sys.size() + 1, 0);
+  for (auto& G : PS.xygroups) {
+    std::vector<int> pre(G.sys.size() + 1, 0);
     std::vector<PassDesc> st, rs;
-    for (size_t i = 0; i < PS.xy_sys.size(); ++i) {
-      const Geom& g = B->sp[PS.xy_sys[i]].g;
-      pre[i + 1] = pre[i] + (g.M3 == 1 ? 1 : g.M3 / 2);
-      st.push_back(PS.h_step[PS.xy_sys[i]]);
-      rs.push_back(PS.h_res[PS.xy_sys[i]]);
+    for (size_t i = 0; i < G.sys.size(); ++i) {
+      const Geom& g = B->sp[G.sys[i]].g;
+      const int per = xyr_fits_batch(g) ? xyr_planes_per_group(g) : 2;   // else plane pairs
+      pre[i + 1] = pre[i] + (g.M3 + per - 1) / per;
+      st.push_back(PS.h_step[G.sys[i]]);
+      rs.push_back(PS.h_res[G.sys[i]]);
     }
-    PS.xytotal = pre.back();
-    if ((e = alloc((void**)&PS.d_xypre, sizeof(int) * pre.size()))) return e;
-    if ((e = hipMemcpy(PS.d_xypre, pre.data(), sizeof(int) * pre.size(), hipMemcpyHostToDevice))) return e;
-    if ((e = alloc((void**)&PS.d_xy, sizeof(PassDesc) * st.size()))) return e;
-    if ((e = hipMemcpy(PS.d_xy, st.data(), sizeof(PassDesc) * st.size(), hipMemcpyHostToDevice))) return e;
-    if ((e = alloc((void**)&PS.d_xy_res, sizeof(PassDesc) * rs.size()))) return e;
-    if ((e = hipMemcpy(PS.d_xy_res, rs.data(), sizeof(PassDesc) * rs.size(), hipMemcpyHostToDevice))) return e;
+    G.total = pre.back();
+    if ((e = alloc((void**)&G.d_pre, sizeof(int) * pre.size()))) return e;
+    if ((e = hipMemcpy(G.d_pre, pre.data(), sizeof(int) * pre.size(), hipMemcpyHostToDevice))) return e;
+    if ((e = alloc((void**)&G.d_step, sizeof(PassDesc) * st.size()))) return e;
+    if ((e = hipMemcpy(G.d_step, st.data(), sizeof(PassDesc) * st.size(), hipMemcpyHostToDevice))) return e;
+    if ((e = alloc((void**)&G.d_res, sizeof(PassDesc) * rs.size()))) return e;
+    if ((e = hipMemcpy(G.d_res, rs.data(), sizeof(PassDesc) * rs.size(), hipMemcpyHostToDevice))) return e;
   }
   return hipSuccess;
 }
 
 // Batched matvec on compressed vectors: residual = false: V_{j+1} = A (V_j or
 // Z_j), systems gated by their step flags; true: r = b - A x, gated by the cycle
-// flags.  Scatter into fx, the three passes fx -> fy, gather from fy.
+// flags.  Direct systems run the three passes on the vectors; the others scatter into
+// fx, run fx -> fy and gather from fy.
 template <typename T>
 hipError_t batch_matvec(vie_batch_s* B, PassSet& PS, const BatchLevel<T>& L, bool residual, int j) {
   hipStream_t s = B->stream;
   hipError_t e;
-  const int mode = 0;
-  const int jx = 0, jy = 0;
+  const int jx = residual ? 0 : j, jy = residual ? 0 : j + 1;
   const bool dbl = sizeof(T) == 8;
   const int act_sel = residual ? 1 : 0;
   const int gsz = L.ctotal < 4096 ? (L.ctotal > 0 ? L.ctotal : 1) : 4096;
-  hipLaunchKernelGGL((k_b_scatter<T>), dim3(gsz), dim3(kT), 0, s, L.d, PS.d_sd, L.d_cpre, L.nsys, L.ctotal,
-                     residual ? 2 : (L.flex ? 1 : 0), residual ? 0 : j, act_sel);
-  if ((e = hipGetLastError())) return e;
+  if (PS.any_scatter) {
+    hipLaunchKernelGGL((k_b_scatter<T>), dim3(gsz), dim3(kT), 0, s, L.d, PS.d_sd, L.d_cpre, L.nsys, L.ctotal,
+                       residual ? 2 : (L.flex ? 1 : 0), residual ? 0 : j, act_sel);
+    if ((e = hipGetLastError())) return e;
+  }
   for (int which = 0; which < 3; ++which) {
     if (which == 1) {
-      if (PS.xytotal > 0 &&
-          (e = launch_pass_batch<T>(1, 0, residual ? PS.d_xy_res : PS.d_xy, PS.d_xypre, (int)PS.xy_sys.size(), PS.xytotal, 0, 0, 0, 0, 0, s)))
-        return e;
+      for (auto& G : PS.xygroups) {
+        const PassDesc* d = residual ? G.d_res : G.d_step;
+        const int ns = (int)G.sys.size();
+        if ((e = G.M1 == 64 && G.M2 == 64 ? launch_xy64_batch<T>(d, G.d_pre, ns, G.total, s)
+                                          : launch_xyr_batch<T>(G.M1, G.M2, d, G.d_pre, ns, G.total, s)))
+          return e;
+      }
       for (int sidx : PS.xysingle) {
         const SysPlan& P = B->sp[sidx];
-        const void* tw[3] = {dbl ? P.tw64[0] : P.tw32[0], dbl ? P.tw64[1] : P.tw32[1], dbl ? P.tw64[2] : P.tw32[2]};
         if ((e = launch_pass<T>(1, P.g, dbl ? P.t64 : P.t32, nullptr, nullptr, nullptr, 0, dbl ? P.U64 : P.U32,
-                                dbl ? P.goct64 : P.goct32, dbl ? P.chi64 : P.chi32, tw, s)))
+                                dbl ? P.goct64 : P.goct32, dbl ? P.chi64 : P.chi32, dbl ? P.tw64 : P.tw32, s)))
           return e;
       }
       continue;
     }
     for (auto& G : PS.zgroups)
-      if ((e = launch_pass_batch<T>(which, mode, residual ? G.d_res : G.d_step, G.d_zpre, (int)G.sys.size(),
-                                    G.ztotal, G.A, G.B, G.P, jx, jy, s)))
+      if ((e = launch_z4_batch<T>(which, residual && G.direct ? 1 : 0, residual ? G.d_res : G.d_step, G.d_zpre,
+                                  (int)G.sys.size(), G.ztotal, G.A, G.B, G.P, jx, jy, s)))
         return e;
     for (int sidx : PS.zsingle) {
       const SysPlan& P = B->sp[sidx];
       const PassDesc& pd = residual ? PS.h_res[sidx] : PS.h_step[sidx];
       const void* xp = (const cx<T>*)pd.xb + (long)jx * pd.xs;
       void* yp = (cx<T>*)pd.yb + (long)jy * pd.ys;
-      const void* tw[3] = {dbl ? P.tw64[0] : P.tw32[0], dbl ? P.tw64[1] : P.tw32[1], dbl ? P.tw64[2] : P.tw32[2]};
-      if ((e = launch_pass<T>(which, P.g, dbl ? P.t64 : P.t32, xp, yp, pd.b, mode, dbl ? P.U64 : P.U32,
-                              dbl ? P.goct64 : P.goct32, dbl ? P.chi64 : P.chi32, tw, s)))
+      if ((e = launch_pass<T>(which, P.g, dbl ? P.t64 : P.t32, xp, yp, pd.b, residual && P.direct ? 1 : 0,
+                              dbl ? P.U64 : P.U32, dbl ? P.goct64 : P.goct32, dbl ? P.chi64 : P.chi32,
+                              dbl ? P.tw64 : P.tw32, s)))
         return e;
     }
   }
-  hipLaunchKernelGGL((k_b_gather<T>), dim3(gsz), dim3(kT), 0, s, L.d, PS.d_sd, L.d_cpre, L.nsys, L.ctotal,
-                     residual ? 4 : 0, residual ? 0 : j + 1, residual ? 1 : 0, act_sel);
+  if (PS.any_scatter)
+    hipLaunchKernelGGL((k_b_gather<T>), dim3(gsz), dim3(kT), 0, s, L.d, PS.d_sd, L.d_cpre, L.nsys, L.ctotal,
+                       residual ? 4 : 0, residual ? 0 : j + 1, residual ? 1 : 0, act_sel);
   return hipGetLastError();
 }
 
@@ -864,8 +905,9 @@ extern "C" int vie_solve_batch(vie_plan_t const* plans, const vie_c128* const* r
   B.circ.assign(count, nullptr);
   std::vector<long> n(count), nfull(count);
   std::vector<Support> sup(count);
+  std::vector<SysPlan> own(count);   // the plans' own operators (b off the support)
   for (int s = 0; s < count; ++s) {
-    SysPlan& P = B.sp[s];
+    SysPlan& P = own[s];
     hipStream_t st;
     int hc = 0;
     if (!plans[s] || !rhs[s] || !x[s]) return VIE_EINVAL;
@@ -879,6 +921,8 @@ extern "C" int vie_solve_batch(vie_plan_t const* plans, const vie_c128* const* r
     const int* col = nullptr;
     int ns = 0;
     if ((rc = plan_support(plans[s], &col, &ns))) return rc;
+    if ((rc = plan_solve_view(plans[s], &B.sp[s]))) return rc;
+    P.direct = (long)ns == (long)P.g.n1 * P.g.n2;
     sup[s] = Support{col, ns, (long)P.g.n1 * P.g.n2, P.g.n3};
     nfull[s] = 3 * P.g.N;
     n[s] = sup[s].size();   // Krylov vectors hold the support columns only
@@ -929,36 +973,47 @@ extern "C" int vie_solve_batch(vie_plan_t const* plans, const vie_c128* const* r
   BTRY(hipHostMalloc(&hflags, sizeof(int) * count * 4 + sizeof(double) * count * 4, hipHostMallocDefault));
   // Support compression (as in vie_solve): off the support A is the identity, so
   // x = b there; on it the system is A_SS x_S = b_S - (A b_off)_S with b_off = b
-  // off the support.  Per system: full-length product buffers fx (zero off the
-  // support) and fy, the compressed right-hand side bc and solution xc.
+  // off the support.  Per system: the compressed right-hand side bc and solution xc and,
+  // unless its support is every column of its operator's grid, the product's full-length
+  // buffers fx (zero off the support) and fy.
   B.p64.h_sd.resize(count);
   B.p32.h_sd.resize(count);
   long nmax = 1;
   for (int i = 0; i < count; ++i) {
-    const size_t len = n[i] > 0 ? (size_t)n[i] : 1;
+    const SysPlan& P = B.sp[i];
+    const size_t len = n[i] > 0 ? (size_t)n[i] : 1, nv = 3 * (size_t)P.g.N;
     void *fx = nullptr, *fy = nullptr, *bc = nullptr, *xc = nullptr;
-    BTRY(dmalloc(&fx, sizeof(double2) * nfull[i]));
-    extra.push_back(fx);
-    BTRY(dmalloc(&fy, sizeof(double2) * nfull[i]));
-    extra.push_back(fy);
     BTRY(dmalloc(&bc, sizeof(double2) * len));
     extra.push_back(bc);
     BTRY(dmalloc(&xc, sizeof(double2) * len));
     extra.push_back(xc);
-    B.p64.h_sd[i] = SDesc{sup[i].col, sup[i].s, sup[i].n3, sup[i].n12, fx, fy};
+    if (!P.direct) {
+      BTRY(dmalloc(&fx, sizeof(double2) * nv));
+      extra.push_back(fx);
+      BTRY(dmalloc(&fy, sizeof(double2) * nv));
+      extra.push_back(fy);
+      BTRY(hipMemsetAsync(fx, 0, sizeof(double2) * nv, s));
+    }
+    B.p64.h_sd[i] = SDesc{P.col, P.ns, P.g.n3, (long)P.g.n1 * P.g.n2, fx, fy};
     bptr[i] = bc;
     xptr[i] = xc;
     if (B.mixed) {
       void *fx32 = nullptr, *fy32 = nullptr;
-      BTRY(dmalloc(&fx32, sizeof(float2) * nfull[i]));
-      extra.push_back(fx32);
-      BTRY(dmalloc(&fy32, sizeof(float2) * nfull[i]));
-      extra.push_back(fy32);
-      BTRY(hipMemsetAsync(fx32, 0, sizeof(float2) * nfull[i], s));
-      B.p32.h_sd[i] = SDesc{sup[i].col, sup[i].s, sup[i].n3, sup[i].n12, fx32, fy32};
+      if (!P.direct) {
+        BTRY(dmalloc(&fx32, sizeof(float2) * nv));
+        extra.push_back(fx32);
+        BTRY(dmalloc(&fy32, sizeof(float2) * nv));
+        extra.push_back(fy32);
+        BTRY(hipMemsetAsync(fx32, 0, sizeof(float2) * nv, s));
+      }
+      B.p32.h_sd[i] = SDesc{P.col, P.ns, P.g.n3, (long)P.g.n1 * P.g.n2, fx32, fy32};
     }
     nmax = std::max(nmax, nfull[i]);
   }
+  // b off the support, one system after the other (set-up only)
+  double2* boffv = nullptr;
+  BTRY(dmalloc(&boffv, sizeof(double2) * nmax));
+  extra.push_back(boffv);
   // norms: sq[3 i] = ||b_S||^2, sq[3 i + 1] = ||b_off||^2, sq[3 i + 2] = ||b_c||^2
   double2* dsq = nullptr;
   double2* part = nullptr;
@@ -969,14 +1024,14 @@ extern "C" int vie_solve_batch(vie_plan_t const* plans, const vie_c128* const* r
   BTRY(hipMemsetAsync(dsq, 0, sizeof(double2) * 3 * count, s));
   using K = KrylovOps<double>;
   for (int i = 0; i < count; ++i) {
-    double2* fx = (double2*)B.p64.h_sd[i].fx;
-    BTRY(hipMemcpyAsync(fx, rhs[i], sizeof(double2) * nfull[i], hipMemcpyDeviceToDevice, s));
     if (sup[i].s > 0) {
       BTRY(gather<double>(sup[i], (const double2*)rhs[i], (double2*)bptr[i], nullptr, s));
       BTRY(K::nrm2sq((const double2*)bptr[i], n[i], part, dsq + 3 * i, s));
-      BTRY(zero_support<double>(sup[i], fx, s));
     }
-    BTRY(K::nrm2sq(fx, nfull[i], part, dsq + 3 * i + 1, s));
+    if (own[i].direct) continue;   // nothing off the support
+    BTRY(hipMemcpyAsync(boffv, rhs[i], sizeof(double2) * nfull[i], hipMemcpyDeviceToDevice, s));
+    if (sup[i].s > 0) BTRY(zero_support<double>(sup[i], boffv, s));
+    BTRY(K::nrm2sq(boffv, nfull[i], part, dsq + 3 * i + 1, s));
   }
   std::vector<double2> hsq(3 * count);
   BTRY(hipMemcpyAsync(hsq.data(), dsq, sizeof(double2) * 3 * count, hipMemcpyDeviceToHost, s));
@@ -989,13 +1044,24 @@ extern "C" int vie_solve_batch(vie_plan_t const* plans, const vie_c128* const* r
     }
     boff[i] = sup[i].s > 0 && hsq[3 * i + 1].x > 0;
     if (!boff[i]) continue;
-    const SysPlan& P = B.sp[i];
-    const SDesc& S = B.p64.h_sd[i];
-    BTRY(launch_matvec<double>(P.g, P.t64, S.fx, S.fy, nullptr, 0, P.U64, P.goct64, P.chi64, P.tw64, s));
-    BTRY(gather<double>(sup[i], (const double2*)S.fy, (double2*)bptr[i], (const double2*)bptr[i], s));
+    // with the plan's own operator, on buffers of its own (the plan's may be in use)
+    const SysPlan& P = own[i];
+    double2 *y = nullptr, *U = nullptr;
+    BTRY(dmalloc(&y, sizeof(double2) * nfull[i]));
+    extra.push_back(y);
+    BTRY(dmalloc(&U, sizeof(double2) * 3 * (size_t)P.g.n1 * P.g.n2 * P.g.M3));
+    extra.push_back(U);
+    BTRY(hipMemcpyAsync(boffv, rhs[i], sizeof(double2) * nfull[i], hipMemcpyDeviceToDevice, s));
+    BTRY(zero_support<double>(sup[i], boffv, s));
+    BTRY(launch_matvec<double>(P.g, P.t64, boffv, y, nullptr, 0, U, P.goct64, P.chi64, P.tw64, s));
+    BTRY(gather<double>(sup[i], y, (double2*)bptr[i], (const double2*)bptr[i], s));
     BTRY(K::nrm2sq((const double2*)bptr[i], n[i], part, dsq + 3 * i + 2, s));
+    BTRY(hipStreamSynchronize(s));
+    (void)hipFree(extra.back());
+    extra.pop_back();
+    (void)hipFree(extra.back());
+    extra.pop_back();
   }
-  for (int i = 0; i < count; ++i) BTRY(hipMemsetAsync(B.p64.h_sd[i].fx, 0, sizeof(double2) * nfull[i], s));
   BTRY(hipMemcpyAsync(hsq.data(), dsq, sizeof(double2) * 3 * count, hipMemcpyDeviceToHost, s));
   BTRY(hipStreamSynchronize(s));
   // ||r|| / ||b|| = (||r_c|| / ||b_c||) * ratio with ratio = ||b_c|| / ||b||

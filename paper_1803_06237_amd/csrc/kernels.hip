@@ -39,12 +39,6 @@ hipError_t launch_z4(int which, const Geom& g, int P, const void* x, void* y, co
                      const void* chi, const void* twz, hipStream_t st);
 template <typename T>
 hipError_t allow_lds_z4();
-template <typename T>
-hipError_t launch_z4_batch(int which, int mode, const PassDesc* d, const int* prefix, int nsys, int total, int A,
-                           int B, int P, int jx, int jy, hipStream_t st);
-template <typename T>
-hipError_t launch_xy64_batch(const PassDesc* d, const int* prefix, int nsys, int total, hipStream_t s);
-
 constexpr int kMaxV = 16;   // complex values per thread per FFT stage
 
 // ------------------------------------------------------------------ pass 1
@@ -222,17 +216,6 @@ hipError_t launch_matvec(const Geom& g, const Tune& t, const void* x, void* y, c
   return hipSuccess;
 }
 
-template <typename T>
-hipError_t launch_pass_batch(int which, int mode, const PassDesc* d, const int* prefix, int nsys, int total, int A,
-                             int B, int P, int jx, int jy, hipStream_t s) {
-  if (which == 1) return launch_xy64_batch<T>(d, prefix, nsys, total, s);
-  return launch_z4_batch<T>(which, mode, d, prefix, nsys, total, A, B, P, jx, jy, s);
-}
-template hipError_t launch_pass_batch<double>(int, int, const PassDesc*, const int*, int, int, int, int, int, int,
-                                              int, hipStream_t);
-template hipError_t launch_pass_batch<float>(int, int, const PassDesc*, const int*, int, int, int, int, int, int,
-                                             int, hipStream_t);
-
 template hipError_t launch_pass<double>(int, const Geom&, const Tune&, const void*, void*, const void*, int, void*,
                                         const void*, const void*, const void* const[3], hipStream_t);
 template hipError_t launch_pass<float>(int, const Geom&, const Tune&, const void*, void*, const void*, int, void*,
@@ -264,8 +247,9 @@ template hipError_t allow_lds<float>(size_t);
 
 // Circulant embedding of one tensor component: slot k_d < n_d holds offset k_d,
 // slot k_d > M_d - n_d holds offset k_d - M_d (sign from the parity), others 0.
-__global__ void k_embed(const double2* __restrict__ table, double2* __restrict__ F, Geom g, int comp,
-                        int pa, int pb) {
+// table holds t1 x t2 x t3 >= n1 x n2 x n3 offsets per component.
+__global__ void k_embed(const double2* __restrict__ table, int t1, int t2, int t3, double2* __restrict__ F, Geom g,
+                        int comp, int pa, int pb) {
   const long P = (long)g.M1 * g.M2 * g.M3;
   for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < P; i += (long)gridDim.x * blockDim.x) {
     const int k3 = (int)(i % g.M3);
@@ -290,7 +274,7 @@ __global__ void k_embed(const double2* __restrict__ table, double2* __restrict__
     }
     double2 v = {0.0, 0.0};
     if (!zero) {
-      v = table[(((long)comp * g.n1 + o[0]) * g.n2 + o[1]) * g.n3 + o[2]];
+      v = table[(((long)comp * t1 + o[0]) * t2 + o[1]) * t3 + o[2]];
       v.x *= sign;
       v.y *= sign;
     }
@@ -362,14 +346,14 @@ static hipError_t fft_axis(double2* F, const Geom& g, int axis, const double2* t
   return hipGetLastError();
 }
 
-hipError_t launch_spectrum(const Geom& g, const double2* table_dev, double2* full_tmp, double2* goct64,
-                           float2* goct32, const double2* const tw64[3], hipStream_t s) {
+hipError_t launch_spectrum(const Geom& g, const double2* table_dev, const int t[3], double2* full_tmp,
+                           double2* goct64, float2* goct32, const double2* const tw64[3], hipStream_t s) {
   static const int comp_ab[6][2] = {{0, 0}, {0, 1}, {0, 2}, {1, 1}, {1, 2}, {2, 2}};
   const double invP = 1.0 / ((double)g.M1 * g.M2 * g.M3);
   hipError_t e;
   for (int c = 0; c < 6; ++c) {
-    hipLaunchKernelGGL(k_embed, dim3(2048), dim3(256), 0, s, table_dev, full_tmp, g, c, comp_ab[c][0],
-                       comp_ab[c][1]);
+    hipLaunchKernelGGL(k_embed, dim3(2048), dim3(256), 0, s, table_dev, t[0], t[1], t[2], full_tmp, g, c,
+                       comp_ab[c][0], comp_ab[c][1]);
     if ((e = hipGetLastError())) return e;
     for (int axis = 2; axis >= 0; --axis)
       if ((e = fft_axis(full_tmp, g, axis, tw64[axis], s))) return e;
@@ -387,7 +371,8 @@ hipError_t launch_curl_spectrum(const Geom& g, const double2* ktable_dev, double
   const double invP = 1.0 / ((double)g.M1 * g.M2 * g.M3);
   hipError_t e;
   for (int c = 0; c < 3; ++c) {
-    hipLaunchKernelGGL(k_embed, dim3(2048), dim3(256), 0, s, ktable_dev, full_tmp, g, c, odd_axis[c], -1);
+    hipLaunchKernelGGL(k_embed, dim3(2048), dim3(256), 0, s, ktable_dev, g.n1, g.n2, g.n3, full_tmp, g, c,
+                       odd_axis[c], -1);
     if ((e = hipGetLastError())) return e;
     for (int axis = 2; axis >= 0; --axis)
       if ((e = fft_axis(full_tmp, g, axis, tw64[axis], s))) return e;

@@ -134,6 +134,33 @@ struct GmresWs {
   }
 };
 
+// Bump allocation inside one array, 256-byte aligned.
+struct ScratchCarver {
+  unsigned char* base;
+  size_t used = 0;
+  template <typename P>
+  P* take(size_t count) {
+    used = (used + 255) & ~(size_t)255;
+    P* r = reinterpret_cast<P*>(base + used);
+    used += sizeof(P) * (count ? count : 1);
+    return r;
+  }
+};
+
+// The operator on the bounding box of the support; every array lies in one allocation.
+struct BoxOp {
+  int lo1 = 0, lo2 = 0;        // first column of the box in the plan's grid
+  Geom g{};
+  Tune t64{}, t32{};
+  void* arena = nullptr;
+  double2 *goct64 = nullptr, *chi64 = nullptr, *U64 = nullptr;
+  float2 *goct32 = nullptr, *chi32 = nullptr, *U32 = nullptr;
+  double2* tw64[3] = {nullptr, nullptr, nullptr};
+  float2* tw32[3] = {nullptr, nullptr, nullptr};
+  int* col = nullptr;
+  bool fresh = false;          // chi and col match the plan's contrast
+};
+
 }  // namespace
 
 struct vie_plan_s {
@@ -159,6 +186,11 @@ struct vie_plan_s {
   int* colflag = nullptr;      // device, n1 n2 flags
   int* scol = nullptr;         // device, ns column indices i1 n2 + i2, increasing
   int ns = 0;
+  int box[4] = {0, 0, 0, 0};   // bounding box of the support columns: [i1 lo, hi), [i2 lo, hi)
+  BoxOp* sub = nullptr;        // the operator on that box (solve_view)
+  bool sub_none = false;       // the box is not worth an operator of its own
+  std::mutex sub_mu;           // solves of several threads may share the plan's read-only parts
+  double2* table_dev = nullptr;   // Toeplitz table on the device
   double2* fx = nullptr;       // full FP64 operator input, zero off the support
   double2* fy = nullptr;       // full FP64 operator output
   double2* fw = nullptr;       // full FP64 base vector (learned-circulant tier)
@@ -220,6 +252,28 @@ int ilog2(int v) {
   int l = 0;
   while ((1 << l) < v) ++l;
   return l;
+}
+
+// circulant lengths: the power of two >= 2 n - 1
+Geom make_geom(const int n[3]) {
+  Geom g{};
+  int M[3];
+  for (int d = 0; d < 3; ++d)
+    for (M[d] = 1; M[d] < 2 * n[d] - 1;) M[d] <<= 1;
+  g.n1 = n[0];
+  g.n2 = n[1];
+  g.n3 = n[2];
+  g.M1 = M[0];
+  g.M2 = M[1];
+  g.M3 = M[2];
+  g.L1 = ilog2(g.M1);
+  g.L2 = ilog2(g.M2);
+  g.L3 = ilog2(g.M3);
+  g.H1 = g.M1 / 2 + 1;
+  g.H2 = g.M2 / 2 + 1;
+  g.H3 = g.M3 / 2 + 1;
+  g.N = (long)g.n1 * g.n2 * g.n3;
+  return g;
 }
 
 template <typename T>
@@ -481,65 +535,188 @@ struct Op32 {
   }
 };
 
-// The operator on support-compressed vectors: scatter into a full vector that is
-// zero off the support, FFT product, gather the support back.
-struct Op64c {
-  vie_plan_s* p;
-  Support u;
-  double2* fx;   // full-length input (zero off the support) and output
-  double2* fy;
-  hipError_t full(const double2* xc) {
-    hipError_t e = scatter<double>(u, xc, fx, p->stream);
+// ---- the operator on the support's bounding box --------------------------------
+void box_release(vie_plan_s* p) {
+  if (!p->sub) return;
+  (void)hipStreamSynchronize(p->stream);
+  if (p->sub->arena) (void)hipFree(p->sub->arena);
+  delete p->sub;
+  p->sub = nullptr;
+}
+
+// Launch shapes of the box, by rule (its first solve does not wait for timing): the
+// four-step z passes with the most pencils per workgroup that still leave two workgroups per
+// CU in FP64, one per two CUs in FP32, else the generic ones; in FP64 those also from 2048
+// points on, where the four-step shapes hold 64 values per thread.  (20 x 9 x 512, 540
+// pencils: FP64 generic, FP32 four pencils per workgroup, as the tuner finds.)
+template <typename T>
+bool box_tune(const Geom& g, size_t budget, Tune* t) {
+  if (!pick_tune<T>(g, budget, std::min<size_t>(budget, 65536), t)) return false;
+  t->xyv = 2;
+  if (!t->z4) return true;
+  int opts[8];
+  const int n = z4_pencil_options<T>(g.M3, opts, 8);
+  t->zp = 0;
+  for (int i = 0; i < n; ++i) {
+    const int wgs = 3 * g.n2 * ((g.n1 + opts[i] - 1) / opts[i]);
+    if (wgs >= (sizeof(T) == 8 ? 512 : 128) && opts[i] > t->zp) t->zp = opts[i];
+  }
+  if (t->zp == 0 || (sizeof(T) == 8 && g.M3 >= 2048)) t->z4 = t->zp = 0;
+  return true;
+}
+
+hipError_t box_build(vie_plan_s* p) {
+  auto* b = new BoxOp();
+  p->sub = b;
+  const int n[3] = {p->box[1] - p->box[0], p->box[3] - p->box[2], p->g.n3};
+  b->g = make_geom(n);
+  const Geom& g = b->g;
+  const size_t budget = lds_budget(p->device);
+  if (!box_tune<double>(g, budget, &b->t64) || !box_tune<float>(g, budget, &b->t32)) return hipErrorInvalidValue;
+  const bool f32 = p->goct32 != nullptr;
+  const size_t H = (size_t)g.H1 * g.H2 * g.H3, N = (size_t)g.N, u = (size_t)3 * g.n1 * g.n2 * g.M3;
+  const int M[2] = {g.M1, g.M2};
+  // sizes first, then the same walk with the allocation's address
+  for (int walk = 0; walk < 2; ++walk) {
+    ScratchCarver c{static_cast<unsigned char*>(b->arena)};
+    b->goct64 = c.take<double2>(6 * H);
+    b->chi64 = c.take<double2>(N);
+    b->U64 = c.take<double2>(u);
+    if (f32) {
+      b->goct32 = c.take<float2>(6 * H);
+      b->chi32 = c.take<float2>(N);
+      b->U32 = c.take<float2>(u);
+    }
+    for (int d = 0; d < 2; ++d) {
+      b->tw64[d] = c.take<double2>(M[d]);
+      b->tw32[d] = c.take<float2>(M[d]);
+    }
+    b->col = c.take<int>((size_t)g.n1 * g.n2);
+    if (walk == 0)
+      if (hipError_t e = dmalloc(&b->arena, c.used)) return e;
+  }
+  b->tw64[2] = p->tw64[2];   // the box keeps the plan's length along z
+  b->tw32[2] = p->tw32[2];
+  for (int d = 0; d < 2; ++d) {
+    std::vector<double2> h64(M[d]);
+    std::vector<float2> h32(M[d]);
+    for (int k = 0; k < M[d]; ++k) {
+      const long double a = -2.0L * 3.14159265358979323846264338327950288L * k / M[d];
+      h64[k] = double2{(double)std::cos(a), (double)std::sin(a)};
+      h32[k] = float2{(float)std::cos(a), (float)std::sin(a)};
+    }
+    hipError_t e = hipMemcpy(b->tw64[d], h64.data(), sizeof(double2) * M[d], hipMemcpyHostToDevice);
+    if (!e) e = hipMemcpy(b->tw32[d], h32.data(), sizeof(float2) * M[d], hipMemcpyHostToDevice);
     if (e) return e;
-    const void* tw[3] = {p->tw64[0], p->tw64[1], p->tw64[2]};
-    return launch_matvec<double>(p->g, p->t64, fx, fy, nullptr, 0, p->U64, p->goct64, p->chi64, tw, p->stream);
   }
-  hipError_t apply(const double2* xc, double2* yc) {
-    hipError_t e = full(xc);
-    return e ? e : gather<double>(u, fy, yc, nullptr, p->stream);
+  double2* full = nullptr;
+  hipError_t e = dmalloc(&full, sizeof(double2) * (size_t)g.M1 * g.M2 * g.M3);
+  const int t[3] = {p->g.n1, p->g.n2, p->g.n3};
+  const double2* tw[3] = {b->tw64[0], b->tw64[1], b->tw64[2]};
+  if (!e) e = launch_spectrum(g, p->table_dev, t, full, b->goct64, b->goct32, tw, p->stream);
+  if (!e) e = hipStreamSynchronize(p->stream);
+  if (full) (void)hipFree(full);
+  return e;
+}
+
+// The plan's contrast and support columns in the box's numbering.
+hipError_t box_refresh(vie_plan_s* p) {
+  BoxOp* b = p->sub;
+  b->lo1 = p->box[0];
+  b->lo2 = p->box[2];
+  const Geom &f = p->g, &g = b->g;
+  const size_t at = ((size_t)b->lo1 * f.n2 + b->lo2) * f.n3, run = (size_t)g.n2 * g.n3, pitch = (size_t)f.n2 * f.n3;
+  hipError_t e = hipMemcpy2DAsync(b->chi64, run * sizeof(double2), p->chi64 + at, pitch * sizeof(double2),
+                                  run * sizeof(double2), g.n1, hipMemcpyDeviceToDevice, p->stream);
+  if (!e && b->goct32)
+    e = hipMemcpy2DAsync(b->chi32, run * sizeof(float2), p->chi32 + at, pitch * sizeof(float2), run * sizeof(float2),
+                         g.n1, hipMemcpyDeviceToDevice, p->stream);
+  std::vector<int> col(p->ns);
+  if (!e) e = hipMemcpyAsync(col.data(), p->scol, sizeof(int) * p->ns, hipMemcpyDeviceToHost, p->stream);
+  if (!e) e = hipStreamSynchronize(p->stream);
+  for (int& c : col) c = (c / f.n2 - b->lo1) * g.n2 + c % f.n2 - b->lo2;
+  if (!e) e = hipMemcpy(b->col, col.data(), sizeof(int) * p->ns, hipMemcpyHostToDevice);
+  b->fresh = e == hipSuccess;
+  return e;
+}
+
+SolveView plan_view(const vie_plan_s* p) {
+  return SolveView{p->g, p->t64, p->t32, p->goct64, p->goct32, p->chi64, p->chi32, p->U64, p->U32,
+                   {p->tw64[0], p->tw64[1], p->tw64[2]}, {p->tw32[0], p->tw32[1], p->tw32[2]}, p->scol, p->ns,
+                   (long)p->ns == (long)p->g.n1 * p->g.n2, false};
+}
+
+// The view the solvers use.  The box pays where it has a smaller circulant cross-section or
+// at most three quarters of the columns: all passes shrink with it (32 x 32 x 512 guide with
+// a 20 x 9 core, circulant 64 x 32 instead of 64 x 64 and a sixth of the z pencils: FP64
+// product with scatter and gather 137 us, on the box 64 us).  Built on first use unless
+// `build` is false (callers that may not allocate); where the build fails, for want of
+// memory say, the plan's own operator serves.
+SolveView solve_view(vie_plan_s* p, bool build) {
+  std::lock_guard<std::mutex> lk(p->sub_mu);
+  if (p->ns > 0 && !p->sub && !p->sub_none && build) {
+    const int n[3] = {p->box[1] - p->box[0], p->box[3] - p->box[2], p->g.n3};
+    const Geom g = make_geom(n);
+    p->sub_none = !(g.M1 * g.M2 < p->g.M1 * p->g.M2 || 4L * n[0] * n[1] <= 3L * p->g.n1 * p->g.n2);
+    if (!p->sub_none && box_build(p) != hipSuccess) {
+      (void)hipGetLastError();
+      box_release(p);
+      p->sub_none = true;
+    }
   }
-  hipError_t residual(const double2* xc, const double2* bc, double2* rc) {
-    hipError_t e = full(xc);
-    return e ? e : gather<double>(u, fy, rc, bc, p->stream);
+  if (p->sub && !p->sub->fresh && build && box_refresh(p) != hipSuccess) {
+    (void)hipGetLastError();
+    box_release(p);
+    p->sub_none = true;
+  }
+  if (!p->sub || !p->sub->fresh) return plan_view(p);
+  const BoxOp* b = p->sub;
+  return SolveView{b->g, b->t64, b->t32, b->goct64, b->goct32, b->chi64, b->chi32, b->U64, b->U32,
+                   {b->tw64[0], b->tw64[1], b->tw64[2]}, {b->tw32[0], b->tw32[1], b->tw32[2]}, b->col, p->ns,
+                   (long)p->ns == (long)b->g.n1 * b->g.n2, true};
+}
+
+// The operator on support-compressed vectors.  Where the support is every column of the
+// view's grid the product runs on the vectors themselves; else they are scattered into a
+// vector fx of the grid that is zero off the support, and the product gathered back.
+template <typename T>
+struct OpC {
+  vie_plan_s* p;
+  const SolveView& v;
+  cx<T>* fx;   // vectors of the view's grid: input (zero off the support) and output
+  cx<T>* fy;
+  hipError_t product(const cx<T>* x, cx<T>* y, const cx<T>* b, int mode) {
+    constexpr bool dbl = sizeof(T) == 8;
+    return launch_matvec<T>(v.g, dbl ? v.t64 : v.t32, x, y, b, mode, dbl ? v.U64 : v.U32, dbl ? v.goct64 : v.goct32,
+                            dbl ? v.chi64 : v.chi32, dbl ? v.tw64 : v.tw32, p->stream);
+  }
+  Support support() const { return Support{v.col, v.ns, (long)v.g.n1 * v.g.n2, v.g.n3}; }
+  hipError_t apply(const cx<T>* xc, cx<T>* yc) {
+    if (v.direct) return product(xc, yc, nullptr, 0);
+    hipError_t e = scatter<T>(support(), xc, fx, p->stream);
+    if (!e) e = product(fx, fy, nullptr, 0);
+    return e ? e : gather<T>(support(), fy, yc, nullptr, p->stream);
+  }
+  hipError_t residual(const cx<T>* xc, const cx<T>* bc, cx<T>* rc) {
+    if (v.direct) return product(xc, rc, bc, 1);
+    hipError_t e = scatter<T>(support(), xc, fx, p->stream);
+    if (!e) e = product(fx, fy, nullptr, 0);
+    return e ? e : gather<T>(support(), fy, rc, bc, p->stream);
   }
 };
-struct Op32c {
-  vie_plan_s* p;
-  Support u;
-  hipError_t full(const float2* xc) {
-    hipError_t e = scatter<float>(u, xc, p->fx32, p->stream);
-    if (e) return e;
-    const void* tw[3] = {p->tw32[0], p->tw32[1], p->tw32[2]};
-    return launch_matvec<float>(p->g, p->t32, p->fx32, p->fy32, nullptr, 0, p->U32, p->goct32, p->chi32, tw,
-                                p->stream);
-  }
-  hipError_t apply(const float2* xc, float2* yc) {
-    hipError_t e = full(xc);
-    return e ? e : gather<float>(u, p->fy32, yc, nullptr, p->stream);
-  }
-  hipError_t residual(const float2* xc, const float2* bc, float2* rc) {
-    hipError_t e = full(xc);
-    return e ? e : gather<float>(u, p->fy32, rc, bc, p->stream);
-  }
-};
+using Op64c = OpC<double>;
+using Op32c = OpC<float>;
 
 // The FP32 product on FP64 support-compressed vectors: the inner solve of the mixed
-// tier with FP64 Arnoldi (precision 5).  x is rounded to FP32, the FP32 product runs
-// on the full grid, the gathered result is widened back to FP64.
+// tier with FP64 Arnoldi (precision 5).  x is rounded to FP32 and the product's
+// result widened back to FP64.
 struct Op32in64c {
-  vie_plan_s* p;
-  Support u;
+  Op32c A;
   long n;
   hipError_t apply(const double2* xc, double2* yc) {
-    hipError_t e = convert<double, float>(xc, p->v32a, n, p->stream);
-    if (e) return e;
-    if ((e = scatter<float>(u, p->v32a, p->fx32, p->stream))) return e;
-    const void* tw[3] = {p->tw32[0], p->tw32[1], p->tw32[2]};
-    if ((e = launch_matvec<float>(p->g, p->t32, p->fx32, p->fy32, nullptr, 0, p->U32, p->goct32, p->chi32, tw,
-                                  p->stream)))
-      return e;
-    if ((e = gather<float>(u, p->fy32, p->v32b, nullptr, p->stream))) return e;
-    return convert<float, double>(p->v32b, yc, n, p->stream);
+    hipError_t e = convert<double, float>(xc, A.p->v32a, n, A.p->stream);
+    if (!e) e = A.apply(A.p->v32a, A.p->v32b);
+    return e ? e : convert<float, double>(A.p->v32b, yc, n, A.p->stream);
   }
   // the inner solve starts from zero and never confirms a true residual
   hipError_t residual(const double2*, const double2*, double2*) { return hipErrorNotSupported; }
@@ -751,6 +928,12 @@ int vie::plan_export(vie_plan_t p, Geom* g, Tune* t64, Tune* t32, void** U64, vo
 
 vie::Circ* vie::plan_circ(vie_plan_t p) { return p ? p->circ : nullptr; }
 
+int vie::plan_solve_view(vie_plan_t p, SolveView* v) {
+  if (!p || !p->has_contrast) return VIE_ESTATE;
+  *v = solve_view(p, true);
+  return VIE_OK;
+}
+
 int vie::plan_support(vie_plan_t p, const int** col, int* ns) {
   if (!p || !p->has_contrast) return VIE_ESTATE;
   *col = p->scol;
@@ -807,18 +990,6 @@ void scratch_init(int device) {
   g_scratch_done[device] = true;
 }
 
-// Bump allocation inside the scratch array, 256-byte aligned.
-struct ScratchCarver {
-  unsigned char* base;
-  size_t used = 0;
-  template <typename P>
-  P* take(size_t count) {
-    used = (used + 255) & ~(size_t)255;
-    P* r = reinterpret_cast<P*>(base + used);
-    used += sizeof(P) * (count ? count : 1);
-    return r;
-  }
-};
 }  // namespace
 
 extern "C" {
@@ -853,25 +1024,8 @@ int vie_plan(vie_plan_t* out, const int grid[3], double h, double k0, double eps
   p->flags = flags;
   p->stream = reinterpret_cast<hipStream_t>(hip_stream);
   Geom& g = p->g;
-  g.n1 = grid[0];
-  g.n2 = grid[1];
-  g.n3 = grid[2];
-  int Ms[3];
-  for (int d = 0; d < 3; ++d) {
-    int M = 1;
-    while (M < 2 * grid[d] - 1) M <<= 1;
-    Ms[d] = M;
-  }
-  g.M1 = Ms[0];
-  g.M2 = Ms[1];
-  g.M3 = Ms[2];
-  g.L1 = ilog2(g.M1);
-  g.L2 = ilog2(g.M2);
-  g.L3 = ilog2(g.M3);
-  g.H1 = g.M1 / 2 + 1;
-  g.H2 = g.M2 / 2 + 1;
-  g.H3 = g.M3 / 2 + 1;
-  g.N = (long)g.n1 * g.n2 * g.n3;
+  g = make_geom(grid);
+  const int Ms[3] = {g.M1, g.M2, g.M3};
   auto bail = [&](int code) {
     vie_destroy(p);
     return code;
@@ -895,10 +1049,8 @@ int vie_plan(vie_plan_t* out, const int grid[3], double h, double k0, double eps
   const bool f32 = (flags & VIE_WITH_FP32) != 0;
   const long H = (long)g.H1 * g.H2 * g.H3;
   const long P = (long)g.M1 * g.M2 * g.M3;
-  double2* table_dev = nullptr;
   double2* full = nullptr;
   auto cleanup_tmp = [&]() {
-    if (table_dev) (void)hipFree(table_dev);
     if (full) (void)hipFree(full);
   };
 #define PLANTRY(expr)                                   \
@@ -923,16 +1075,16 @@ int vie_plan(vie_plan_t* out, const int grid[3], double h, double k0, double eps
   PLANTRY(dmalloc(&p->flag, sizeof(int)));
   PLANTRY(dmalloc(&p->colflag, sizeof(int) * (size_t)g.n1 * g.n2));
   PLANTRY(dmalloc(&p->scol, sizeof(int) * (size_t)g.n1 * g.n2));
-  PLANTRY(dmalloc(&table_dev, sizeof(double2) * 6 * g.N));
+  PLANTRY(dmalloc(&p->table_dev, sizeof(double2) * 6 * g.N));
   PLANTRY(dmalloc(&full, sizeof(double2) * P));
-  PLANTRY(hipMemcpyAsync(table_dev, table->data(), sizeof(double2) * 6 * g.N, hipMemcpyHostToDevice, p->stream));
+  PLANTRY(hipMemcpyAsync(p->table_dev, table->data(), sizeof(double2) * 6 * g.N, hipMemcpyHostToDevice, p->stream));
   {
     const double2* tw[3] = {p->tw64[0], p->tw64[1], p->tw64[2]};
-    PLANTRY(launch_spectrum(g, table_dev, full, p->goct64, p->goct32, tw, p->stream));
+    PLANTRY(launch_spectrum(g, p->table_dev, grid, full, p->goct64, p->goct32, tw, p->stream));
   }
   PLANTRY(hipStreamSynchronize(p->stream));
   cleanup_tmp();
-  table_dev = full = nullptr;
+  full = nullptr;
   if (!(flags & VIE_NO_AUTOTUNE)) {
     // launch-shape tuning on the plan's own buffers; the contrast is zeroed first
     // (set_contrast overwrites it)
@@ -972,9 +1124,27 @@ int vie_set_contrast(vie_plan_t p, const vie_c128* eps) {
   HIPTRY(p, column_flags(p->chi64, n12, p->g.n3, p->colflag, p->stream));
   HIPTRY(p, hipMemcpyAsync(flags.data(), p->colflag, sizeof(int) * n12, hipMemcpyDeviceToHost, p->stream));
   HIPTRY(p, hipStreamSynchronize(p->stream));
+  int box[4] = {p->g.n1, 0, p->g.n2, 0};
   for (long c = 0; c < n12; ++c)
-    if (flags[c]) cols.push_back((int)c);
+    if (flags[c]) {
+      cols.push_back((int)c);
+      const int i1 = (int)(c / p->g.n2), i2 = (int)(c % p->g.n2);
+      box[0] = std::min(box[0], i1);
+      box[1] = std::max(box[1], i1 + 1);
+      box[2] = std::min(box[2], i2);
+      box[3] = std::max(box[3], i2 + 1);
+    }
   p->ns = (int)cols.size();
+  {
+    std::lock_guard<std::mutex> lk(p->sub_mu);
+    if (p->sub) {
+      // another box of the same size keeps the spectrum, which depends on its size only
+      if (box[1] - box[0] == p->sub->g.n1 && box[3] - box[2] == p->sub->g.n2) p->sub->fresh = false;
+      else box_release(p);
+    }
+    p->sub_none = false;
+    std::copy(box, box + 4, p->box);
+  }
   if (p->ns) HIPTRY(p, hipMemcpy(p->scol, cols.data(), sizeof(int) * cols.size(), hipMemcpyHostToDevice));
   p->has_contrast = true;
   return VIE_OK;
@@ -1068,7 +1238,7 @@ int solve_options(vie_plan_s* p, const vie_c128* b, vie_c128* x, double tol, con
 }
 
 int solve_impl(vie_plan_s* p, const vie_c128* b, vie_c128* x, double tol, const vie_solve_opts& o,
-               vie_solve_info* info, const SolveBufs& B, std::chrono::steady_clock::time_point t0) {
+               vie_solve_info* info, const SolveBufs& B, bool may_allocate, std::chrono::steady_clock::time_point t0) {
   hipStream_t s = p->stream;
   const long nfull = 3 * p->g.N;
   const double2* bd = reinterpret_cast<const double2*>(b);
@@ -1105,8 +1275,13 @@ int solve_impl(vie_plan_s* p, const vie_c128* b, vie_c128* x, double tol, const 
   const Support u{p->scol, p->ns, (long)p->g.n1 * p->g.n2, p->g.n3};
   const long n = u.size();
   using K = KrylovOps<double>;
-  HIPTRY(p, K::zero(B.fx, nfull, s));
-  if (p->fx32) HIPTRY(p, KrylovOps<float>::zero(p->fx32, nfull, s));
+  // the learned tiers' network works on the plan's grid and shares fx with the operator
+  const bool learned = o.precision == 2 || o.precision == 4;
+  const SolveView view = learned ? plan_view(p) : solve_view(p, may_allocate);
+  if (learned || !view.direct) {
+    HIPTRY(p, K::zero(B.fx, nfull, s));
+    if (p->fx32) HIPTRY(p, KrylovOps<float>::zero(p->fx32, nfull, s));
+  }
   double tmp_h[1];
   auto read_norm2 = [&](const double2* v, long len, double* out) -> hipError_t {
     hipError_t e = K::nrm2sq(v, len, B.partial_full, B.sumsq_full, s);
@@ -1144,7 +1319,7 @@ int solve_impl(vie_plan_s* p, const vie_c128* b, vie_c128* x, double tol, const 
   const double ratio = std::sqrt(bcsq) / bnorm;   // ||b_c|| / ||b||
   const double tolc = tol / ratio;
   if (o.use_x0) HIPTRY(p, gather<double>(u, xd, B.xc, nullptr, s));
-  Op64c A{p, u, B.fx, B.fy};
+  Op64c A{p, view, B.fx, B.fy};
   // mixed tiers: an outer FGMRES that stalled hands its iterate to FP64 GMRES for
   // the rest of the iteration budget (same stall rule)
   auto mixed_fallback = [&](int code) -> int {
@@ -1158,7 +1333,7 @@ int solve_impl(vie_plan_s* p, const vie_c128* b, vie_c128* x, double tol, const 
     status = gmres_core<double, Op64c, NoPrecond>(p, *B.ws, A, nullptr, n, B.bc, B.xc, tolc, o.restart, o.maxit,
                                                   o.use_x0 != 0, true, st);
   } else if (o.precision == 1) {
-    Op32c A32{p, u};
+    Op32c A32{p, view, p->fx32, p->fy32};
     // right preconditioner: z = inner FP32 GMRES solve of A z = v
     auto inner = [&](const void* v, void* z, Stats& outer) -> hipError_t {
       hipError_t e = convert<double, float>(reinterpret_cast<const double2*>(v), p->v32a, n, s);
@@ -1180,7 +1355,7 @@ int solve_impl(vie_plan_s* p, const vie_c128* b, vie_c128* x, double tol, const 
   } else if (o.precision == 5) {
     // mixed tier with FP64 inner Arnoldi: the inner GMRES keeps its Krylov vectors,
     // Gram-Schmidt and Hessenberg data in FP64 and only its products run in FP32
-    Op32in64c A32{p, u, n};
+    Op32in64c A32{Op32c{p, view, p->fx32, p->fy32}, n};
     auto inner = [&](const void* v, void* z, Stats& outer) -> hipError_t {
       Stats si;
       int rc = gmres_core<double, Op32in64c, NoPrecond>(p, p->ws64i, A32, nullptr, n,
@@ -1334,7 +1509,7 @@ int vie_solve(vie_plan_t p, const vie_c128* b, vie_c128* x, double tol, const vi
   }
   if (o.precision == 4 && !p->fw) HIPTRY(p, dmalloc(&p->fw, sizeof(double2) * nfull));
   const SolveBufs B{p->fx, p->fy, p->fw, p->bc, p->xc, p->partial_full, p->sumsq_full, &p->ws64};
-  return solve_impl(p, b, x, tol, o, info, B, t0);
+  return solve_impl(p, b, x, tol, o, info, B, true, t0);
 }
 
 int vie_solve_noalloc(vie_plan_t p, const vie_c128* b, vie_c128* x, double tol, const vie_solve_opts* opts,
@@ -1390,7 +1565,7 @@ int vie_solve_noalloc(vie_plan_t p, const vie_c128* b, vie_c128* x, double tol, 
                 "vie_solve_noalloc: this grid, support and restart need " + std::to_string(c.used) +
                     " bytes of scratch; the limit is " + std::to_string(kScratchBytes));
   B.ws = &ws;
-  return solve_impl(p, b, x, tol, o, info, B, t0);
+  return solve_impl(p, b, x, tol, o, info, B, false, t0);
 }
 
 int vie_profile_matvec(vie_plan_t p, int precision, const void* x, void* y, int reps, double pass_ms[3],
@@ -1740,6 +1915,7 @@ void vie_destroy(vie_plan_t p) {
     (void)hipStreamSynchronize(p->stream);
     circ_destroy(p->circ);
   }
+  box_release(p);
   p->ws64.release();
   p->ws32.release();
   p->ws64i.release();
@@ -1748,7 +1924,7 @@ void vie_destroy(vie_plan_t p) {
   if (p->npin) (void)hipHostFree(p->npin);
   for (void* q : {(void*)p->goct64, (void*)p->goct32, (void*)p->chi64, (void*)p->chi32, (void*)p->U64,
                   (void*)p->U32, (void*)p->rvec, (void*)p->v32a, (void*)p->v32b, (void*)p->flag, (void*)p->colflag,
-                  (void*)p->scol, (void*)p->fx, (void*)p->fy, (void*)p->fw, (void*)p->fx32, (void*)p->fy32, (void*)p->bc,
+                  (void*)p->scol, (void*)p->table_dev, (void*)p->fx, (void*)p->fy, (void*)p->fw, (void*)p->fx32, (void*)p->fy32, (void*)p->bc,
                   (void*)p->xc, (void*)p->partial_full, (void*)p->sumsq_full, (void*)p->koct64,
                   (void*)p->koct32, (void*)p->chim64, (void*)p->chim32, (void*)p->Um64, (void*)p->Um32,
                   (void*)p->S64, (void*)p->S32, (void*)p->jm32a, (void*)p->jm32b})

@@ -59,8 +59,9 @@ hipError_t launch_pass(int which, const Geom& g, const Tune& t, const void* x, v
                        void* U, const void* goct, const void* chi, const void* const tw[3], hipStream_t s);
 
 // ---- plan-time spectrum -----------------------------------------------------
-hipError_t launch_spectrum(const Geom& g, const double2* table_dev, double2* full_tmp, double2* goct64,
-                           float2* goct32, const double2* const tw64[3], hipStream_t s);
+// table_dev: 6 components of t[0] x t[1] x t[2] offsets, at least the grid's
+hipError_t launch_spectrum(const Geom& g, const double2* table_dev, const int t[3], double2* full_tmp,
+                           double2* goct64, float2* goct32, const double2* const tw64[3], hipStream_t s);
 
 hipError_t launch_curl_spectrum(const Geom& g, const double2* ktable_dev, double2* full_tmp, double2* koct64,
                                 float2* koct32, const double2* const tw64[3], hipStream_t s);
@@ -121,12 +122,17 @@ struct PassDesc {
   const int* active;    // device flag; 0 skips the system (nullptr: always on)
 };
 
-// which: 0 forward z, 1 xy + Green, 2 inverse z (+ contrast; mode 1: residual).
-// items: prefix[s] = first item of system s (z passes: pencil blocks; xy pass:
-// plane pairs), prefix[nsys] = total.  All systems share (A, B) for the z passes.
+// Batched z passes (which: 0 forward, 2 inverse + contrast; mode 1: residual) and
+// cross-section passes.  items: prefix[s] = first item of system s (z passes: pencil blocks;
+// 64 x 64: plane pairs; the others: groups of xyr_planes_per_group planes), prefix[nsys] =
+// total.  All systems of a launch share (A, B) or the circulant cross-section.
 template <typename T>
-hipError_t launch_pass_batch(int which, int mode, const PassDesc* d, const int* prefix, int nsys, int total, int A,
-                             int B, int P, int jx, int jy, hipStream_t s);
+hipError_t launch_z4_batch(int which, int mode, const PassDesc* d, const int* prefix, int nsys, int total, int A,
+                           int B, int P, int jx, int jy, hipStream_t st);
+template <typename T>
+hipError_t launch_xy64_batch(const PassDesc* d, const int* prefix, int nsys, int total, hipStream_t s);
+template <typename T>
+hipError_t launch_xyr_batch(int M1, int M2, const PassDesc* d, const int* prefix, int nsys, int total, hipStream_t s);
 template <typename T>
 bool z4_shape(int M3, int* A, int* B, int* P);
 
@@ -178,6 +184,23 @@ int plan_export(vie_plan_t p, Geom* g, Tune* t64, Tune* t32, void** U64, void** 
                 int* has_contrast);
 // The plan's block-circulant preconditioner, or null when none is built.
 Circ* plan_circ(vie_plan_t p);
+// The operator as the solvers use it on support-compressed vectors: the plan's own, or the
+// plan's operator on the bounding box of the support (built on first use, kept with the plan).
+// A_SS depends on differences of support voxels only, so the smaller embedding gives the same
+// product.  col: the ns support columns i1 n2 + i2 of g's grid; direct: they are all of its
+// columns, so a compressed vector is a vector of g's grid; box: g is the box's grid.
+struct SolveView {
+  Geom g;
+  Tune t64, t32;
+  void *goct64, *goct32, *chi64, *chi32, *U64, *U32;
+  const void* tw64[3];
+  const void* tw32[3];
+  const int* col;
+  int ns;
+  bool direct;
+  bool box;
+};
+int plan_solve_view(vie_plan_t p, SolveView* v);
 // The plan's support columns (device, *ns increasing indices i1 n2 + i2 where the
 // contrast is non-zero on some slice), valid while the contrast is unchanged.
 int plan_support(vie_plan_t p, const int** col, int* ns);
