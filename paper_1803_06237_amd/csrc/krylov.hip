@@ -1,17 +1,24 @@
 // GMRES(m) and flexible GMRES(m) on the device (Section V-D: the discrete J-VIE
 // is solved by GMRES with matrix-vector products only).
 //
-// Arnoldi uses classical Gram-Schmidt with a selective second sweep: a fused
-// multi-dot h = V^H w over all basis vectors followed by a multi-axpy
-// w -= V h, repeated once when the first sweep cancelled more than the
-// criterion of Daniel, Gragg, Kaufman and Stewart allows (decided on the device).  The Hessenberg matrix is kept in upper-triangular form with complex
-// Givens rotations by one device thread; the host reads only the residual
-// estimate |g_{j+1}| / ||b|| after each step.  Reductions are two-stage and in
-// a fixed order, so results are bitwise reproducible run to run.  All
+// Arnoldi is classical Gram-Schmidt applied twice, with the two sweeps merged.  With
+// h1 = V^H w and G = V^H V the second sweep's coefficients are V^H (w - V h1) = h1 - G h1, so
+// w'' = w - V h with h = 2 h1 - G h1 needs one pass over the basis for the dots and one for
+// the update instead of two each; G's new column V^H v_j comes out of the same dot pass (v_j
+// is its last vector).  Four kernels a step: k_mdot2 (dots with w and with v_j), k_proj (their
+// sums, h), k_maxpy_nrm (w'' and block sums of |w''|^2), k_finish (norm, v_{j+1}, Hessenberg
+// column, rotation, estimate to host memory).  Measured per step with the sweeps apart (dots
+// and update of the second gated by a cancellation test): ten kernels and a copy, 110 us at
+// n = 276480 and j ~ 20, 33 us at n = 1536 and j ~ 25; merged 60 and 18 us.
+// The Hessenberg matrix is kept in upper-triangular form with complex Givens rotations by one
+// device thread; the host reads only the residual estimate |g_{j+1}| / ||b|| after each step.
+// G_ij, i < j, lies in the unused strict lower triangle of that matrix.  Reductions are
+// two-stage and in a fixed order, so results are bitwise reproducible run to run.  All
 // reductions and Hessenberg data are FP64; basis vectors are FP64 (cx<double>)
 // or FP32 (cx<float>, the inner solve of the mixed tier).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <vector>
@@ -25,6 +32,10 @@ constexpr int kThreads = 256;
 constexpr int kEPT = 2;                     // elements per thread held in registers (reductions)
 constexpr int kChunk = kThreads * kEPT;     // elements per block (reductions)
 constexpr int kGroup = 4;                   // basis vectors per block of the multi-dot
+constexpr int kDotEPT = 4;                  // elements per thread and round of the multi-dot
+constexpr int kDotChunk = kThreads * kDotEPT;
+constexpr int kDotBlocks = 256;             // most blocks (partials) per vector group of the multi-dot
+constexpr int kAxpyBlocks = 2048;           // most blocks (partials) of k_maxpy_nrm
 
 __device__ __forceinline__ double2 to_d(double2 v) { return v; }
 __device__ __forceinline__ double2 to_d(float2 v) { return double2{(double)v.x, (double)v.y}; }
@@ -57,53 +68,151 @@ __device__ __forceinline__ void block_sum(double (&v)[NV], double* lds) {
   __syncthreads();
 }
 
-// partial[i * nblk + blk] = sum over the block's chunk of conj(V_i) w, for the
-// kGroup vectors i of blockIdx.y (nblk = gridDim.x element chunks)
-template <typename T>
-__global__ __launch_bounds__(kThreads) void k_mdot(const cx<T>* __restrict__ V, long ldv, int nv,
-                                                    const cx<T>* __restrict__ w, long n,
-                                                    double2* __restrict__ partial, const int* __restrict__ gate) {
-  if (gate && *gate == 0) return;
-  __shared__ double lds[(kThreads / 64) * 2 * kGroup];
-  const long e0 = (long)blockIdx.x * kChunk + threadIdx.x;
-  double2 wv[kEPT];
+// Sums of NV = 16 or 32 values per lane over the wave: lane l gets that of value *idx, with half
+// as many exchanges per halving step as values left (17 or 32 in all instead of 6 NV).
+template <int NV, int H>
+__device__ __forceinline__ void wave_fold(double (&v)[NV], int lane, int& id) {
+  if constexpr (H >= 1) {
+    constexpr int bit = NV / 2 / H;              // 1, 2, 4, ...
+    const bool up = (lane & bit) != 0;
 #pragma unroll
-  for (int k = 0; k < kEPT; ++k) {
-    const long e = e0 + (long)k * kThreads;
-    wv[k] = e < n ? to_d(w[e]) : double2{0.0, 0.0};
+    for (int i = 0; i < H; ++i) {
+      const double send = up ? v[i] : v[i + H], keep = up ? v[i + H] : v[i];
+      v[i] = keep + __shfl_xor(send, bit, 64);
+    }
+    id |= up ? H : 0;
+    wave_fold<NV, H / 2>(v, lane, id);
   }
-  {
-    const int i0 = blockIdx.y * kGroup;
-    double acc[2 * kGroup];
+}
+template <int NV>
+__device__ __forceinline__ double wave_sum_many(double (&v)[NV], int lane, int* idx) {
+  *idx = 0;
+  wave_fold<NV, NV / 2>(v, lane, *idx);
+  double r = v[0];
 #pragma unroll
-    for (int q = 0; q < 2 * kGroup; ++q) acc[q] = 0.0;
+  for (int o = NV; o < 64; o <<= 1) r += __shfl_xor(r, o, 64);
+  return r;
+}
+
+// partial[(2 i + s) nblk + blk] = the block's share of V_i^H w (s = 0) and of V_i^H V_{nv-1}
+// (s = 1), for the kGroup vectors i of blockIdx.y
+template <typename T>
+__global__ __launch_bounds__(kThreads) void k_mdot2(const cx<T>* __restrict__ V, long ldv, int nv,
+                                                     const cx<T>* __restrict__ w, long n,
+                                                     double2* __restrict__ partial) {
+  constexpr int kVals = 4 * kGroup;
+  __shared__ double lds[kThreads / 64][kVals];
+  const cx<T>* vj = V + (long)(nv - 1) * ldv;
+  const int i0 = blockIdx.y * kGroup;
+  double acc[kVals];
+#pragma unroll
+  for (int q = 0; q < kVals; ++q) acc[q] = 0.0;
+  for (long b0 = (long)blockIdx.x * kDotChunk; b0 < n; b0 += (long)gridDim.x * kDotChunk) {
+    // loads from clamped, always valid addresses (w and v_j count as zero past the end), so
+    // that all of a round are in flight together instead of one per branch
+    long e[kDotEPT];
+    double2 wv[kDotEPT], vv[kDotEPT];
+#pragma unroll
+    for (int k = 0; k < kDotEPT; ++k) {
+      const long at = b0 + threadIdx.x + (long)k * kThreads;
+      e[k] = at < n ? at : n - 1;
+      wv[k] = to_d(w[e[k]]);
+      vv[k] = to_d(vj[e[k]]);
+      if (at >= n) wv[k] = vv[k] = double2{0.0, 0.0};
+    }
 #pragma unroll
     for (int q = 0; q < kGroup; ++q) {
-      if (i0 + q < nv) {
-        const cx<T>* Vi = V + (long)(i0 + q) * ldv;
+      const cx<T>* Vi = V + (long)(i0 + q < nv ? i0 + q : nv - 1) * ldv;
+      double2 a[kDotEPT];
 #pragma unroll
-        for (int k = 0; k < kEPT; ++k) {
-          const long e = e0 + (long)k * kThreads;
-          if (e < n) {
-            const double2 a = to_d(Vi[e]);
-            acc[2 * q] += a.x * wv[k].x + a.y * wv[k].y;
-            acc[2 * q + 1] += a.x * wv[k].y - a.y * wv[k].x;
-          }
-        }
+      for (int k = 0; k < kDotEPT; ++k) a[k] = to_d(Vi[e[k]]);
+#pragma unroll
+      for (int k = 0; k < kDotEPT; ++k) {
+        acc[4 * q] += a[k].x * wv[k].x + a[k].y * wv[k].y;
+        acc[4 * q + 1] += a[k].x * wv[k].y - a[k].y * wv[k].x;
+        acc[4 * q + 2] += a[k].x * vv[k].x + a[k].y * vv[k].y;
+        acc[4 * q + 3] += a[k].x * vv[k].y - a[k].y * vv[k].x;
       }
     }
-    block_sum<2 * kGroup>(acc, lds);
-    if (threadIdx.x == 0)
-      for (int q = 0; q < kGroup; ++q)
-        if (i0 + q < nv) partial[(long)(i0 + q) * gridDim.x + blockIdx.x] = double2{acc[2 * q], acc[2 * q + 1]};
+  }
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int idx;
+  const double r = wave_sum_many<kVals>(acc, lane, &idx);
+  if (lane < kVals) lds[wave][idx] = r;
+  __syncthreads();
+  // value 4 q + 2 s + c: component c of partial (2 (i0 + q) + s)
+  if (threadIdx.x < kVals && i0 + (int)(threadIdx.x >> 2) < nv) {
+    double t = 0.0;
+    for (int k = 0; k < kThreads / 64; ++k) t += lds[k][threadIdx.x];
+    const long row = 2L * i0 + (threadIdx.x >> 1);
+    reinterpret_cast<double*>(partial)[2 * (row * gridDim.x + blockIdx.x) + (threadIdx.x & 1)] = t;
   }
 }
 
-// out[i] (+)= sum_b partial[i * nblk + b], one workgroup per i, fixed order
+// The sums of k_mdot2's partials (raw = V^H w into `raw`, the new Gram column into gd[j] and
+// H's lower triangle) and h = 2 raw - G raw, j = nv - 1, by one workgroup; the product with G
+// is split over its 16 waves by columns.
+constexpr int kProjThreads = 1024;
+__global__ __launch_bounds__(kProjThreads) void k_proj(const double2* __restrict__ partial, int nblk, int nv,
+                                                       double2* __restrict__ raw, double2* __restrict__ gd,
+                                                       double2* __restrict__ H, int ldh, double2* __restrict__ h) {
+  __shared__ double2 sums[kProjThreads / 64][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  constexpr int kW = kProjThreads / 64;
+  // 8 lanes per value: one round of loads for up to 64 vectors, kDotBlocks / 8 per lane
+  const int sub = threadIdx.x & 7;
+  for (int v = threadIdx.x >> 3; v < 2 * nv; v += kProjThreads / 8) {
+    double2 s{0.0, 0.0};
+#pragma unroll 8
+    for (int b = sub; b < nblk; b += 8) {
+      const double2 p = partial[(long)v * nblk + b];
+      s.x += p.x;
+      s.y += p.y;
+    }
+#pragma unroll
+    for (int o = 1; o < 8; o <<= 1) {
+      s.x += __shfl_xor(s.x, o, 64);
+      s.y += __shfl_xor(s.y, o, 64);
+    }
+    if (sub == 0) {
+      const int i = v >> 1;
+      if ((v & 1) == 0) raw[i] = s;
+      else if (i < nv - 1) H[(long)i * ldh + nv - 1] = s;
+      else gd[i] = s;
+    }
+  }
+  __syncthreads();
+  for (int i0 = 0; i0 < nv; i0 += 64) {
+    const int i = i0 + lane;
+    double2 s{0.0, 0.0};
+    if (i < nv)
+      for (int k = wave; k < nv; k += kW) {
+        const double2 r = raw[k];
+        double2 g;                                   // G_ik
+        if (k == i) g = gd[i];
+        else if (k > i) g = H[(long)i * ldh + k];
+        else g = H[(long)k * ldh + i], g.y = -g.y;
+        s.x += g.x * r.x - g.y * r.y;
+        s.y += g.x * r.y + g.y * r.x;
+      }
+    sums[wave][lane] = s;
+    __syncthreads();
+    if (wave == 0 && i < nv) {
+      double2 t{0.0, 0.0};
+      for (int k = 0; k < kW; ++k) {
+        t.x += sums[k][lane].x;
+        t.y += sums[k][lane].y;
+      }
+      const double2 r = raw[i];
+      h[i] = double2{2.0 * r.x - t.x, 2.0 * r.y - t.y};
+    }
+    __syncthreads();
+  }
+}
+
+// out[i] = sum_b partial[i * nblk + b], one workgroup per i, fixed order
 __global__ __launch_bounds__(kThreads) void k_reduce(const double2* __restrict__ partial, int nblk,
-                                                      double2* __restrict__ out, int accumulate,
-                                                      const int* __restrict__ gate) {
-  if (gate && *gate == 0) return;
+                                                      double2* __restrict__ out) {
   __shared__ double lds[(kThreads / 64) * 2];
   const int i = blockIdx.x;
   double v[2] = {0.0, 0.0};
@@ -113,10 +222,7 @@ __global__ __launch_bounds__(kThreads) void k_reduce(const double2* __restrict__
     v[1] += p.y;
   }
   block_sum<2>(v, lds);
-  if (threadIdx.x == 0) {
-    if (accumulate) out[i] = double2{out[i].x + v[0], out[i].y + v[1]};
-    else out[i] = double2{v[0], v[1]};
-  }
+  if (threadIdx.x == 0) out[i] = double2{v[0], v[1]};
 }
 
 // w += sign * sum_i coef[i] V_i, one element per thread (loads of the nv vectors
@@ -124,8 +230,7 @@ __global__ __launch_bounds__(kThreads) void k_reduce(const double2* __restrict__
 template <typename T, typename TW>
 __global__ __launch_bounds__(kThreads) void k_maxpy(const cx<T>* __restrict__ V, long ldv, int nv,
                                                      const double2* __restrict__ coef, double sign,
-                                                     cx<TW>* __restrict__ w, long n, const int* __restrict__ gate) {
-  if (gate && *gate == 0) return;
+                                                     cx<TW>* __restrict__ w, long n) {
   __shared__ double2 c[512];
   for (int i = threadIdx.x; i < nv && i < 512; i += kThreads) c[i] = double2{sign * coef[i].x, sign * coef[i].y};
   __syncthreads();
@@ -146,9 +251,7 @@ __global__ __launch_bounds__(kThreads) void k_maxpy(const cx<T>* __restrict__ V,
 // partial[blk] = sum |w|^2 over the block's chunk
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_nrm2_partial(const cx<T>* __restrict__ w, long n,
-                                                            double2* __restrict__ partial,
-                                                            const int* __restrict__ gate) {
-  if (gate && *gate == 0) return;
+                                                            double2* __restrict__ partial) {
   __shared__ double lds[(kThreads / 64) * 2];
   const long e0 = (long)blockIdx.x * kChunk + threadIdx.x;
   double v[2] = {0.0, 0.0};
@@ -189,166 +292,156 @@ __global__ __launch_bounds__(kThreads) void k_zero(cx<T>* __restrict__ dst, long
     dst[e] = cx<T>{(T)0, (T)0};
 }
 
-// w += sign * sum_i coef[i] V_i (nv <= 512) and, of the stored result, the block
-// partial sums of |w|^2: partial[blk] (blocks of kThreads elements).  Saves the
-// separate norm pass over w.
-template <typename T, typename TW>
+// w -= sum_i h_i V_i and, of the stored result, the block partial sums of |w|^2
+template <typename T>
 __global__ __launch_bounds__(kThreads) void k_maxpy_nrm(const cx<T>* __restrict__ V, long ldv, int nv,
-                                                         const double2* __restrict__ coef, double sign,
-                                                         cx<TW>* __restrict__ w, long n,
-                                                         double2* __restrict__ partial,
-                                                         const int* __restrict__ gate) {
-  if (gate && *gate == 0) return;
-  __shared__ double2 c[512];
+                                                         const double2* __restrict__ h, cx<T>* __restrict__ w, long n,
+                                                         double* __restrict__ partial) {
+  extern __shared__ unsigned char smem_raw[];
+  double2* c = reinterpret_cast<double2*>(smem_raw);   // nv values, zeros up to a multiple of 8
   __shared__ double lds[kThreads / 64];
-  for (int i = threadIdx.x; i < nv && i < 512; i += kThreads) c[i] = double2{sign * coef[i].x, sign * coef[i].y};
+  for (int i = threadIdx.x; i < nv + 7; i += kThreads) c[i] = i < nv ? h[i] : double2{0.0, 0.0};
   __syncthreads();
-  const long e = (long)blockIdx.x * kThreads + threadIdx.x;
   double v[1] = {0.0};
-  if (e < n) {
+  for (long e = (long)blockIdx.x * kThreads + threadIdx.x; e < n; e += (long)gridDim.x * kThreads) {
     double2 acc = to_d(w[e]);
     const cx<T>* Ve = V + e;
-#pragma unroll 4
-    for (int i = 0; i < nv; ++i) {
-      const double2 ci = c[i];
-      const double2 a = to_d(Ve[(long)i * ldv]);
-      acc.x += ci.x * a.x - ci.y * a.y;
-      acc.y += ci.x * a.y + ci.y * a.x;
+    for (int i = 0; i < nv; i += 8) {   // eight loads in flight (the last vector again past the end)
+      double2 a[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) a[k] = to_d(Ve[(long)(i + k < nv ? i + k : nv - 1) * ldv]);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const double2 ci = c[i + k];
+        acc.x -= ci.x * a[k].x - ci.y * a[k].y;
+        acc.y -= ci.x * a[k].y + ci.y * a[k].x;
+      }
     }
-    const cx<TW> out = from_d<cx<TW>>(acc);
+    const cx<T> out = from_d<cx<T>>(acc);
     w[e] = out;
     const double2 o = to_d(out);
-    v[0] = o.x * o.x + o.y * o.y;
+    v[0] += o.x * o.x + o.y * o.y;
   }
   block_sum<1>(v, lds);
-  if (threadIdx.x == 0) partial[blockIdx.x] = double2{v[0], 0.0};
+  if (threadIdx.x == 0) partial[blockIdx.x] = v[0];
 }
 
-// First-sweep norm and the second-sweep decision in one block: sumsq = sum of
-// the partials (||w'||^2), then the criterion below on ||h||^2.
-__global__ __launch_bounds__(kThreads) void k_reduce_dgks(const double2* __restrict__ partial, int nblk,
-                                                           double2* __restrict__ sumsq,
-                                                           const double2* __restrict__ h, int nv,
-                                                           int* __restrict__ gate, double2* __restrict__ h2) {
-  __shared__ double lds[(kThreads / 64) * 2];
-  __shared__ int s_again;
-  double v[2] = {0.0, 0.0};
-  for (int b = threadIdx.x; b < nblk; b += kThreads) v[0] += partial[b].x;
-  for (int i = threadIdx.x; i < nv; i += kThreads) v[1] += h[i].x * h[i].x + h[i].y * h[i].y;
-  block_sum<2>(v, lds);
-  if (threadIdx.x == 0) {
-    sumsq[0] = double2{v[0], 0.0};
-    const int again = (v[0] >= v[1]) ? 0 : 1;
-    *gate = again;
-    s_again = again;
+// Column j of the Hessenberg matrix (hs[0..j] = the projections, hn = ||w||) through the previous
+// rotations, the new rotation and g, by one thread: it sweeps the rotations down the column with
+// the running entry in a register (the loads of hs, cs, sn do not depend on the sweep, so they
+// are issued ahead).  state: see k_finish.
+__device__ __forceinline__ void hessenberg_column(double2* hs, double hn, double* __restrict__ cs,
+                                                  double2* __restrict__ sn, double2* __restrict__ gvec, int j,
+                                                  double bnorm, double* __restrict__ state) {
+  // previous rotations: [c s; -conj(s) c] on (h_i, h_{i+1})
+  double2 a = hs[0];
+  for (int i = 0; i < j; ++i) {
+    const double2 b = hs[i + 1];
+    const double c = cs[i];
+    const double2 s = sn[i];
+    hs[i] = double2{c * a.x + (s.x * b.x - s.y * b.y), c * a.y + (s.x * b.y + s.y * b.x)};
+    a = double2{-(s.x * a.x + s.y * a.y) + c * b.x, -(s.x * a.y - s.y * a.x) + c * b.y};
   }
-  __syncthreads();
-  if (!s_again)
-    for (int i = threadIdx.x; i < nv; i += kThreads) h2[i] = double2{0.0, 0.0};
+  // new rotation zeroing h_{j+1} = ||w||
+  const double2 b = double2{hn, 0.0};
+  const double na = hypot(a.x, a.y), nb = hypot(b.x, b.y);
+  double c;
+  double2 sv, r;
+  if (nb == 0.0) {
+    c = 1.0;
+    sv = double2{0.0, 0.0};
+    r = a;
+  } else if (na == 0.0) {
+    c = 0.0;
+    sv = double2{1.0, 0.0};
+    r = b;
+  } else {
+    const double t = hypot(na, nb);
+    const double2 ph = double2{a.x / na, a.y / na};
+    c = na / t;
+    // s = ph * conj(b) / t
+    sv = double2{(ph.x * b.x + ph.y * b.y) / t, (ph.y * b.x - ph.x * b.y) / t};
+    r = double2{ph.x * t, ph.y * t};
+  }
+  cs[j] = c;
+  sn[j] = sv;
+  hs[j] = r;
+  const double2 gj = gvec[j];
+  // g_{j+1} = -conj(s) g_j ; g_j = c g_j
+  const double2 gn = double2{-(sv.x * gj.x + sv.y * gj.y), -(sv.x * gj.y - sv.y * gj.x)};
+  gvec[j + 1] = gn;
+  gvec[j] = double2{c * gj.x, c * gj.y};
+  const double est = hypot(gn.x, gn.y) / bnorm;
+  state[0] = est;
+  state[1] = hn;
+  state[2] = (isfinite(est) && isfinite(hn) && isfinite(r.x) && isfinite(r.y)) ? 0.0 : 1.0;
+  __threadfence_system();
 }
 
-// Selective second Gram-Schmidt sweep (Daniel, Gragg, Kaufman and Stewart's
-// criterion with eta = 1/sqrt(2)): after the first sweep w' = w - V h, and for
-// an orthonormal V, ||w||^2 = ||w'||^2 + ||h||^2, so ||w'|| < eta ||w|| holds
-// exactly when ||w'||^2 < ||h||^2.  Then *gate = 1 and the second sweep runs;
-// otherwise *gate = 0, its kernels return at once and h2 is zeroed here (the
-// Hessenberg column is h1 + h2).  A non-finite norm keeps the second sweep.
-__global__ void k_dgks(const double2* __restrict__ h, int nv, const double2* __restrict__ sumsq,
-                       int* __restrict__ gate, double2* __restrict__ h2) {
-  double v = 0.0;
-  for (int i = threadIdx.x; i < nv; i += 64) v += h[i].x * h[i].x + h[i].y * h[i].y;
-  v = wave_sum(v);
-  const double hh = __shfl(v, 0, 64);
-  const int again = (sumsq[0].x >= hh) ? 0 : 1;
-  if (threadIdx.x == 0) *gate = again;
-  if (!again)
-    for (int i = threadIdx.x; i < nv; i += 64) h2[i] = double2{0.0, 0.0};
-}
-
-// One Arnoldi step's Hessenberg bookkeeping (single thread).
-// h1[0..j] + h2[0..j] = projections of the two Gram-Schmidt sweeps,
-// sumsq->x = ||w||^2 after orthogonalisation.
-// H is column-major with leading dimension m+1.  state[0] = residual estimate
-// |g_{j+1}| / bnorm, state[1] = ||w|| (breakdown when 0), state[2] = 1 if any
-// value is non-finite.
-__global__ void k_arnoldi_update(const double2* __restrict__ h1, const double2* __restrict__ h2,
-                                 const double2* __restrict__ sumsq,
-                                 double2* __restrict__ H, int ldh, double* __restrict__ cs,
-                                 double2* __restrict__ sn, double2* __restrict__ gvec, int j, double bnorm,
-                                 double* __restrict__ state) {
-  // the new column h = h1 + h2 is staged in LDS by the whole block; one thread
-  // then sweeps the previous rotations down it with the running entry in a
-  // register (the loads of h, cs, sn do not depend on the sweep, so they are
-  // issued ahead of it), and the block writes the column back
+// End of an Arnoldi step.  Every workgroup sums the nblk partials of ||w||^2 (same order, same
+// result) and scales its share of w; workgroup 0 also does the Hessenberg bookkeeping: column
+// j = (h, ||w||) through the previous rotations, the new rotation, g.  state (host memory):
+// [0] residual estimate |g_{j+1}| / bnorm, [1] ||w|| (breakdown when 0), [2] = 1 if any value
+// is non-finite.
+template <typename T>
+__global__ __launch_bounds__(kThreads) void k_finish(cx<T>* __restrict__ w, long n,
+                                                      const double* __restrict__ partial, int nblk,
+                                                      const double2* __restrict__ h, double2* __restrict__ H, int ldh,
+                                                      double* __restrict__ cs, double2* __restrict__ sn,
+                                                      double2* __restrict__ gvec, int j, double bnorm,
+                                                      double* __restrict__ state) {
   extern __shared__ unsigned char smem_raw[];
-  double2* hs = reinterpret_cast<double2*>(smem_raw);   // j + 2 entries
-  for (int i = threadIdx.x; i <= j; i += blockDim.x) hs[i] = double2{h1[i].x + h2[i].x, h1[i].y + h2[i].y};
+  double2* hs = reinterpret_cast<double2*>(smem_raw);   // j + 2 entries (workgroup 0)
+  __shared__ double lds[kThreads / 64];
+  __shared__ double s_norm;
+  double v[1] = {0.0};
+  for (int b = threadIdx.x; b < nblk; b += kThreads) v[0] += partial[b];
+  block_sum<1>(v, lds);
+  if (threadIdx.x == 0) s_norm = sqrt(v[0]);
+  if (blockIdx.x == 0)
+    for (int i = threadIdx.x; i <= j; i += kThreads) hs[i] = h[i];
   __syncthreads();
-  if (threadIdx.x == 0) {
-    const double hn = sqrt(sumsq->x);
-    // previous rotations: [c s; -conj(s) c] on (h_i, h_{i+1})
-    double2 a = hs[0];
-    for (int i = 0; i < j; ++i) {
-      const double2 b = hs[i + 1];
-      const double c = cs[i];
-      const double2 s = sn[i];
-      hs[i] = double2{c * a.x + (s.x * b.x - s.y * b.y), c * a.y + (s.x * b.y + s.y * b.x)};
-      a = double2{-(s.x * a.x + s.y * a.y) + c * b.x, -(s.x * a.y - s.y * a.x) + c * b.y};
-    }
-    // new rotation zeroing h_{j+1} = ||w||
-    const double2 b = double2{hn, 0.0};
-    const double na = hypot(a.x, a.y), nb = hypot(b.x, b.y);
-    double c;
-    double2 sv, r;
-    if (nb == 0.0) {
-      c = 1.0;
-      sv = double2{0.0, 0.0};
-      r = a;
-    } else if (na == 0.0) {
-      c = 0.0;
-      sv = double2{1.0, 0.0};
-      r = b;
-    } else {
-      const double t = hypot(na, nb);
-      const double2 ph = double2{a.x / na, a.y / na};
-      c = na / t;
-      // s = ph * conj(b) / t
-      sv = double2{(ph.x * b.x + ph.y * b.y) / t, (ph.y * b.x - ph.x * b.y) / t};
-      r = double2{ph.x * t, ph.y * t};
-    }
-    cs[j] = c;
-    sn[j] = sv;
-    hs[j] = r;
-    hs[j + 1] = double2{0.0, 0.0};
-    const double2 gj = gvec[j];
-    // g_{j+1} = -conj(s) g_j ; g_j = c g_j
-    const double2 gn = double2{-(sv.x * gj.x + sv.y * gj.y), -(sv.x * gj.y - sv.y * gj.x)};
-    gvec[j + 1] = gn;
-    gvec[j] = double2{c * gj.x, c * gj.y};
-    const double est = hypot(gn.x, gn.y) / bnorm;
-    state[0] = est;
-    state[1] = hn;
-    state[2] = (isfinite(est) && isfinite(hn) && isfinite(r.x) && isfinite(r.y)) ? 0.0 : 1.0;
+  const double hn = s_norm;
+  const double scale = hn > 0.0 ? 1.0 / hn : 0.0;
+  for (long e = (long)blockIdx.x * kThreads + threadIdx.x; e < n; e += (long)gridDim.x * kThreads) {
+    const double2 a = to_d(w[e]);
+    w[e] = from_d<cx<T>>(double2{a.x * scale, a.y * scale});
   }
+  if (blockIdx.x != 0) return;
+  if (threadIdx.x == 0) hessenberg_column(hs, hn, cs, sn, gvec, j, bnorm, state);
   __syncthreads();
-  double2* h = H + (long)j * ldh;
-  for (int i = threadIdx.x; i <= j + 1; i += blockDim.x) h[i] = hs[i];
+  double2* col = H + (long)j * ldh;
+  for (int i = threadIdx.x; i <= j; i += kThreads) col[i] = hs[i];
 }
 
-// y = R^{-1} g for the leading k x k upper triangle of H (single thread)
-__global__ void k_trisolve(const double2* __restrict__ H, int ldh, const double2* __restrict__ gvec, int k,
-                           double2* __restrict__ y) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// y = R^{-1} g for the leading k x k upper triangle of H, column by column from the last: one
+// workgroup, the right-hand side in LDS, every thread updating its rows with the new y_i.  A
+// triangle of up to 64 columns is staged in LDS first (by one thread from global memory the
+// solve took 133 us at k = 50, a load latency per entry).
+constexpr int kTriLds = 64;
+__global__ __launch_bounds__(kThreads) void k_trisolve(const double2* __restrict__ H, int ldh,
+                                                        const double2* __restrict__ gvec, int k,
+                                                        double2* __restrict__ y) {
+  extern __shared__ unsigned char smem_raw[];
+  double2* r = reinterpret_cast<double2*>(smem_raw);   // k values
+  double2* R = r + k;                                   // k x k, where k <= kTriLds
+  const bool staged = k <= kTriLds;
+  for (int i = threadIdx.x; i < k; i += kThreads) r[i] = gvec[i];
+  if (staged)
+    for (int e = threadIdx.x; e < k * k; e += kThreads) R[e] = H[(long)(e / k) * ldh + e % k];
+  __syncthreads();
+  const double2* A = staged ? R : H;
+  const long ld = staged ? k : ldh;
   for (int i = k - 1; i >= 0; --i) {
-    double2 s = gvec[i];
-    for (int l = i + 1; l < k; ++l) {
-      const double2 hil = H[(long)l * ldh + i], yl = y[l];
-      s.x -= hil.x * yl.x - hil.y * yl.y;
-      s.y -= hil.x * yl.y + hil.y * yl.x;
-    }
-    const double2 d = H[(long)i * ldh + i];
+    const double2 s = r[i], d = A[(long)i * ld + i];
     const double dd = d.x * d.x + d.y * d.y;
-    y[i] = double2{(s.x * d.x + s.y * d.y) / dd, (s.y * d.x - s.x * d.y) / dd};
+    const double2 yi = double2{(s.x * d.x + s.y * d.y) / dd, (s.y * d.x - s.x * d.y) / dd};
+    if (threadIdx.x == 0) y[i] = yi;
+    for (int l = threadIdx.x; l < i; l += kThreads) {
+      const double2 a = A[(long)i * ld + l];
+      r[l] = double2{r[l].x - (a.x * yi.x - a.y * yi.y), r[l].y - (a.x * yi.y + a.y * yi.x)};
+    }
+    __syncthreads();
   }
 }
 
@@ -399,66 +492,58 @@ __global__ __launch_bounds__(kThreads) void k_column_flags(const double2* __rest
 static inline int nblocks(long n) { return (int)((n + kChunk - 1) / kChunk); }
 
 template <typename T>
-hipError_t KrylovOps<T>::nrm2sq(const cx<T>* w, long n, double2* partial, double2* out, hipStream_t s,
-                                const int* gate) {
+hipError_t KrylovOps<T>::nrm2sq(const cx<T>* w, long n, double2* partial, double2* out, hipStream_t s) {
   const int nb = nblocks(n);
-  hipLaunchKernelGGL((k_nrm2_partial<T>), dim3(nb), dim3(kThreads), 0, s, w, n, partial, gate);
-  hipLaunchKernelGGL(k_reduce, dim3(1), dim3(kThreads), 0, s, partial, nb, out, 0, gate);
-  return hipGetLastError();
-}
-
-template <typename T>
-hipError_t KrylovOps<T>::mdot(const cx<T>* V, long ldv, int nv, const cx<T>* w, long n, double2* partial,
-                              double2* out, int accumulate, hipStream_t s, const int* gate) {
-  const int nb = nblocks(n);
-  hipLaunchKernelGGL((k_mdot<T>), dim3(nb, (nv + kGroup - 1) / kGroup), dim3(kThreads), 0, s, V, ldv, nv, w, n,
-                     partial, gate);
-  hipLaunchKernelGGL(k_reduce, dim3(nv), dim3(kThreads), 0, s, partial, nb, out, accumulate, gate);
+  hipLaunchKernelGGL((k_nrm2_partial<T>), dim3(nb), dim3(kThreads), 0, s, w, n, partial);
+  hipLaunchKernelGGL(k_reduce, dim3(1), dim3(kThreads), 0, s, partial, nb, out);
   return hipGetLastError();
 }
 
 template <typename T>
 template <typename TW>
 hipError_t KrylovOps<T>::maxpy(const cx<T>* V, long ldv, int nv, const double2* coef, double sign, cx<TW>* w,
-                               long n, hipStream_t s, const int* gate) {
+                               long n, hipStream_t s) {
   for (int i0 = 0; i0 < nv; i0 += 512) {
     const int cnt = nv - i0 < 512 ? nv - i0 : 512;
     hipLaunchKernelGGL((k_maxpy<T, TW>), dim3((unsigned)((n + kThreads - 1) / kThreads)), dim3(kThreads), 0, s,
                        V + (long)i0 * ldv, ldv, cnt,
-                       coef + i0, sign, w, n, gate);
+                       coef + i0, sign, w, n);
   }
   return hipGetLastError();
 }
 
+// every block the same number of rounds
+static int axpy_blocks(long n) {
+  const long b = (n + kThreads - 1) / kThreads, rounds = (b + kAxpyBlocks - 1) / kAxpyBlocks;
+  return (int)((b + rounds - 1) / rounds);
+}
+static int dot_blocks(long n) { return (int)std::min<long>(kDotBlocks, (n + kDotChunk - 1) / kDotChunk); }
+
+// up to 4103 staged values (restart <= 4096): a little above the default 64 KiB
 template <typename T>
-template <typename TW>
-hipError_t KrylovOps<T>::maxpy_nrm(const cx<T>* V, long ldv, int nv, const double2* coef, double sign, cx<TW>* w,
-                                   long n, double2* partial, hipStream_t s, const int* gate) {
-  if (nv > 512) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((k_maxpy_nrm<T, TW>), dim3((unsigned)((n + kThreads - 1) / kThreads)), dim3(kThreads), 0, s, V,
-                     ldv, nv, coef, sign, w, n, partial, gate);
-  return hipGetLastError();
+static hipError_t allow_step_lds() {
+  const auto a = hipFuncAttributeMaxDynamicSharedMemorySize;
+  const int bytes = (4096 + 8) * 16;
+  hipError_t e = hipFuncSetAttribute((const void*)k_maxpy_nrm<T>, a, bytes);
+  if (!e) e = hipFuncSetAttribute((const void*)k_finish<T>, a, bytes);
+  if (!e) e = hipFuncSetAttribute((const void*)k_trisolve, a, 160 * 1024);
+  return e;
 }
 
 template <typename T>
-hipError_t KrylovOps<T>::reduce_dgks(const double2* partial, int nblk, double2* sumsq, const double2* h1, int nv,
-                                     int* gate, double2* h2, hipStream_t s) {
-  hipLaunchKernelGGL(k_reduce_dgks, dim3(1), dim3(kThreads), 0, s, partial, nblk, sumsq, h1, nv, gate, h2);
-  return hipGetLastError();
-}
-
-template <typename T>
-hipError_t KrylovOps<T>::reduce(const double2* partial, int nblk, double2* out, hipStream_t s, const int* gate) {
-  hipLaunchKernelGGL(k_reduce, dim3(1), dim3(kThreads), 0, s, partial, nblk, out, 0, gate);
-  return hipGetLastError();
-}
-
-int maxpy_blocks(long n) { return (int)((n + kThreads - 1) / kThreads); }
-
-template <typename T>
-hipError_t KrylovOps<T>::dgks(const double2* h1, int nv, const double2* sumsq, int* gate, double2* h2,
-                              hipStream_t s) {
-  hipLaunchKernelGGL(k_dgks, dim3(1), dim3(64), 0, s, h1, nv, sumsq, gate, h2);
+hipError_t KrylovOps<T>::orthogonalise(const cx<T>* V, int j, cx<T>* w, long n, const ArnoldiData& d, double bnorm,
+                                       double* state, hipStream_t s) {
+  static const hipError_t lds_ok = allow_step_lds<T>();
+  if (lds_ok != hipSuccess) return lds_ok;
+  const int nv = j + 1, nd = dot_blocks(n), na = axpy_blocks(n);
+  double* norms = reinterpret_cast<double*>(d.partial);
+  hipLaunchKernelGGL((k_mdot2<T>), dim3(nd, (nv + kGroup - 1) / kGroup), dim3(kThreads), 0, s, V, n, nv, w, n,
+                     d.partial);
+  hipLaunchKernelGGL(k_proj, dim3(1), dim3(kProjThreads), 0, s, d.partial, nd, nv, d.raw, d.gd, d.H, d.ldh, d.h);
+  hipLaunchKernelGGL((k_maxpy_nrm<T>), dim3(na), dim3(kThreads), (size_t)(nv + 7) * sizeof(double2), s, V, n, nv, d.h, w, n,
+                     norms);
+  hipLaunchKernelGGL((k_finish<T>), dim3(na), dim3(kThreads), (size_t)(j + 2) * sizeof(double2), s, w, n, norms,
+                     na, d.h, d.H, d.ldh, d.cs, d.sn, d.g, j, bnorm, state);
   return hipGetLastError();
 }
 
@@ -475,21 +560,11 @@ hipError_t KrylovOps<T>::zero(cx<T>* dst, long n, hipStream_t s) {
 }
 
 template <typename T>
-hipError_t KrylovOps<T>::arnoldi_update(const double2* h1, const double2* h2, const double2* sumsq, double2* H,
-                                        int ldh, double* cs, double2* sn, double2* g, int j, double bnorm,
-                                        double* state, hipStream_t s) {
-  // up to 4097 staged values (restart <= 4096): a little above the default 64 KiB
-  static const hipError_t lds_ok = hipFuncSetAttribute((const void*)k_arnoldi_update,
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, 4098 * 16);
-  if (lds_ok != hipSuccess) return lds_ok;
-  hipLaunchKernelGGL(k_arnoldi_update, dim3(1), dim3(64), (size_t)(j + 2) * sizeof(double2), s, h1, h2, sumsq, H,
-                     ldh, cs, sn, g, j, bnorm, state);
-  return hipGetLastError();
-}
-
-template <typename T>
 hipError_t KrylovOps<T>::trisolve(const double2* H, int ldh, const double2* g, int k, double2* y, hipStream_t s) {
-  hipLaunchKernelGGL(k_trisolve, dim3(1), dim3(64), 0, s, H, ldh, g, k, y);
+  static const hipError_t lds_ok = allow_step_lds<T>();
+  if (lds_ok != hipSuccess) return lds_ok;
+  const size_t lds = sizeof(double2) * (size_t)(k + (k <= kTriLds ? k * k : 0));
+  hipLaunchKernelGGL(k_trisolve, dim3(1), dim3(kThreads), lds, s, H, ldh, g, k, y);
   return hipGetLastError();
 }
 
@@ -507,19 +582,19 @@ hipError_t convert(const cx<TS>* src, cx<TD>* dst, long n, hipStream_t s) {
 
 template struct KrylovOps<double>;
 template struct KrylovOps<float>;
-template hipError_t KrylovOps<double>::maxpy_nrm<double>(const cx<double>*, long, int, const double2*, double,
-                                                         cx<double>*, long, double2*, hipStream_t, const int*);
-template hipError_t KrylovOps<float>::maxpy_nrm<float>(const cx<float>*, long, int, const double2*, double,
-                                                       cx<float>*, long, double2*, hipStream_t, const int*);
 template hipError_t KrylovOps<double>::maxpy<double>(const cx<double>*, long, int, const double2*, double,
-                                                     cx<double>*, long, hipStream_t, const int*);
+                                                     cx<double>*, long, hipStream_t);
 template hipError_t KrylovOps<float>::maxpy<float>(const cx<float>*, long, int, const double2*, double,
-                                                   cx<float>*, long, hipStream_t, const int*);
+                                                   cx<float>*, long, hipStream_t);
 template hipError_t convert<double, float>(const cx<double>*, cx<float>*, long, hipStream_t);
 template hipError_t convert<float, double>(const cx<float>*, cx<double>*, long, hipStream_t);
 template hipError_t convert<double, double>(const cx<double>*, cx<double>*, long, hipStream_t);
 
 int partial_blocks(long n) { return nblocks(n); }
+size_t arnoldi_partials(long n, int m) {
+  return std::max<size_t>(2 * (size_t)(m + 1) * dot_blocks(n),
+                          std::max<size_t>(nblocks(n), (axpy_blocks(n) + 1) / 2));
+}
 
 static inline int grid_for(long n) {
   const long b = (n + kThreads - 1) / kThreads;

@@ -6,35 +6,33 @@
 
 namespace vie {
 
+// Device data of one GMRES cycle: the reduction partials (arnoldi_partials), the raw dots and
+// the Gram diagonal (m + 1 values each), the projections h, the Hessenberg matrix
+// (column-major, leading dimension ldh; the Gram entries G_ij, i < j, at row j of column i),
+// the rotations and the right-hand side g.
+struct ArnoldiData {
+  double2 *partial, *raw, *gd, *h, *H;
+  int ldh;
+  double* cs;
+  double2 *sn, *g;
+};
+
 template <typename T>
 struct KrylovOps {
   // out[0].x = ||w||^2 (FP64 accumulation); partial needs partial_blocks(n) entries
-  // gate (device, optional): when *gate == 0 at run time the kernels do nothing
-  static hipError_t nrm2sq(const cx<T>* w, long n, double2* partial, double2* out, hipStream_t s,
-                           const int* gate = nullptr);
-  // out[i] (+)= V_i^H w for i < nv; partial needs nv * partial_blocks(n) entries
-  static hipError_t mdot(const cx<T>* V, long ldv, int nv, const cx<T>* w, long n, double2* partial,
-                         double2* out, int accumulate, hipStream_t s, const int* gate = nullptr);
+  static hipError_t nrm2sq(const cx<T>* w, long n, double2* partial, double2* out, hipStream_t s);
   // w += sign * sum_i coef[i] V_i
   template <typename TW>
   static hipError_t maxpy(const cx<T>* V, long ldv, int nv, const double2* coef, double sign, cx<TW>* w, long n,
-                          hipStream_t s, const int* gate = nullptr);
-  // *gate = 1 when ||w'||^2 = sumsq->x < ||h1||^2 (second sweep needed), else 0 and h2 = 0
-  static hipError_t dgks(const double2* h1, int nv, const double2* sumsq, int* gate, double2* h2, hipStream_t s);
-  // maxpy (nv <= 512) that also writes the block partial sums of |w|^2 to partial[0, maxpy_blocks(n))
-  template <typename TW>
-  static hipError_t maxpy_nrm(const cx<T>* V, long ldv, int nv, const double2* coef, double sign, cx<TW>* w, long n,
-                              double2* partial, hipStream_t s, const int* gate = nullptr);
-  // sumsq = sum of nblk partials, then the second-sweep decision of dgks in the same block
-  static hipError_t reduce_dgks(const double2* partial, int nblk, double2* sumsq, const double2* h1, int nv,
-                                int* gate, double2* h2, hipStream_t s);
-  // out[0].x = sum of nblk partials
-  static hipError_t reduce(const double2* partial, int nblk, double2* out, hipStream_t s, const int* gate = nullptr);
+                          hipStream_t s);
+  // Arnoldi step j after w = A v_j: w orthogonalised against V_0 .. V_j and normalised (it is
+  // V_{j+1}), Hessenberg column, rotation and g updated; state (pinned host memory, 3 values):
+  // residual estimate, ||w||, 1 if something is not finite.
+  static hipError_t orthogonalise(const cx<T>* V, int j, cx<T>* w, long n, const ArnoldiData& d, double bnorm,
+                                  double* state, hipStream_t s);
   // dst = src / sqrt(sumsq->x)
   static hipError_t scale(const cx<T>* src, cx<T>* dst, long n, const double2* sumsq, hipStream_t s);
   static hipError_t zero(cx<T>* dst, long n, hipStream_t s);
-  static hipError_t arnoldi_update(const double2* h1, const double2* h2, const double2* sumsq, double2* H, int ldh, double* cs,
-                                   double2* sn, double2* g, int j, double bnorm, double* state, hipStream_t s);
   static hipError_t trisolve(const double2* H, int ldh, const double2* g, int k, double2* y, hipStream_t s);
   static hipError_t set_g(double2* g, int m, const double2* sumsq, hipStream_t s);
 };
@@ -66,7 +64,7 @@ hipError_t zero_support(const Support& u, cx<T>* full, hipStream_t s);
 hipError_t column_flags(const double2* chi, long n12, int n3, int* flags, hipStream_t s);
 
 int partial_blocks(long n);
-// blocks (partial sums) of maxpy_nrm over n elements
-int maxpy_blocks(long n);
+// partials of a cycle of dimension m on vectors of n elements
+size_t arnoldi_partials(long n, int m);
 
 }  // namespace vie

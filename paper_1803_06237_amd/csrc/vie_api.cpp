@@ -81,24 +81,22 @@ struct GmresWs {
   cx<T>* V = nullptr;
   cx<T>* Z = nullptr;
   double2* partial = nullptr;
-  double2* h1 = nullptr;
-  double2* h2 = nullptr;
+  double2* h = nullptr;
+  double2* gd = nullptr;       // Gram diagonal
   double2* sumsq = nullptr;
   double2* H = nullptr;
   double2* sn = nullptr;
   double2* g = nullptr;
-  double2* y = nullptr;
+  double2* y = nullptr;        // raw dots during a cycle, then the coefficients of the update
   double* cs = nullptr;
-  double* state = nullptr;
   double* state_h = nullptr;
-  int* gate = nullptr;   // second Gram-Schmidt sweep needed (device flag)
-  hipEvent_t ev[2] = {nullptr, nullptr};   // step j's state copied to state_h + 4 (j & 1)
+  hipEvent_t ev[2] = {nullptr, nullptr};   // step j's state written to state_h + 4 (j & 1)
   bool borrowed = false;  // pointers lent by the caller (static scratch): never freed or resized
 
   void release() {
     if (borrowed) return;
-    for (void* p : {(void*)V, (void*)Z, (void*)partial, (void*)h1, (void*)h2, (void*)sumsq, (void*)H, (void*)sn,
-                    (void*)g, (void*)y, (void*)cs, (void*)state, (void*)gate})
+    for (void* p : {(void*)V, (void*)Z, (void*)partial, (void*)h, (void*)gd, (void*)sumsq, (void*)H, (void*)sn,
+                    (void*)g, (void*)y, (void*)cs})
       if (p) (void)hipFree(p);
     if (state_h) (void)hipHostFree(state_h);
     for (hipEvent_t e : ev)
@@ -112,21 +110,18 @@ struct GmresWs {
     n = n_;
     m = m_;
     flex = flex_;
-    const long nb = partial_blocks(n);
     hipError_t e;
     if ((e = dmalloc(&V, sizeof(cx<T>) * (size_t)n * (m + 1)))) return e;
     if (flex && (e = dmalloc(&Z, sizeof(cx<T>) * (size_t)n * m))) return e;
-    if ((e = dmalloc(&partial, sizeof(double2) * (size_t)nb * (m + 1)))) return e;
-    if ((e = dmalloc(&h1, sizeof(double2) * (m + 2)))) return e;
-    if ((e = dmalloc(&h2, sizeof(double2) * (m + 2)))) return e;
+    if ((e = dmalloc(&partial, sizeof(double2) * arnoldi_partials(n, m)))) return e;
+    if ((e = dmalloc(&h, sizeof(double2) * (m + 2)))) return e;
+    if ((e = dmalloc(&gd, sizeof(double2) * (m + 2)))) return e;
     if ((e = dmalloc(&sumsq, sizeof(double2) * 2))) return e;
-    if ((e = dmalloc(&gate, sizeof(int)))) return e;
     if ((e = dmalloc(&H, sizeof(double2) * (size_t)(m + 1) * m))) return e;
     if ((e = dmalloc(&sn, sizeof(double2) * (m + 1)))) return e;
     if ((e = dmalloc(&g, sizeof(double2) * (m + 1)))) return e;
     if ((e = dmalloc(&y, sizeof(double2) * (m + 1)))) return e;
     if ((e = dmalloc(&cs, sizeof(double) * (m + 1)))) return e;
-    if ((e = dmalloc(&state, sizeof(double) * 4))) return e;
     if ((e = hipHostMalloc(&state_h, sizeof(double) * 8, hipHostMallocDefault))) return e;
     for (hipEvent_t& ev_i : ev)
       if ((e = hipEventCreateWithFlags(&ev_i, hipEventDisableTiming))) return e;
@@ -792,9 +787,11 @@ int gmres_core(vie_plan_s* p, GmresWs<T>& W, OP& A, PC* M, long n, const cx<T>* 
     HIPTRY(p, K::zero(x, n, s));
     HIPTRY(p, hipMemcpyAsync(V0, b, sizeof(cx<T>) * n, hipMemcpyDeviceToDevice, s));
   }
-  double beta2 = 0;
-  HIPTRY(p, K::nrm2sq(V0, n, W.partial, W.sumsq, s));
-  HIPTRY(p, read_scalar(W.sumsq, &beta2, W.state_h, s));
+  double beta2 = bsq;
+  if (use_x0) {   // else V0 = b, whose norm is in sumsq
+    HIPTRY(p, K::nrm2sq(V0, n, W.partial, W.sumsq, s));
+    HIPTRY(p, read_scalar(W.sumsq, &beta2, W.state_h, s));
+  }
   double rel = std::sqrt(beta2) / bnorm;
   st.est = rel;
   int status = VIE_ENOCONV;
@@ -821,8 +818,9 @@ int gmres_core(vie_plan_s* p, GmresWs<T>& W, OP& A, PC* M, long n, const cx<T>* 
     ++cycles;
     HIPTRY(p, K::set_g(W.g, m, W.sumsq, s));
     HIPTRY(p, K::scale(V0, V0, n, W.sumsq, s));
-    // One Arnoldi step queued on the stream, ending with a copy of its state
-    // (residual estimate, breakdown, non-finite flags) to pinned slot j & 1.
+    // One Arnoldi step queued on the stream; its last kernel writes its state (residual
+    // estimate, breakdown, non-finite flags) to pinned slot j & 1.
+    const ArnoldiData D{W.partial, W.y, W.gd, W.h, W.H, ldh, W.cs, W.sn, W.g};
     auto step = [&](int j) -> hipError_t {
       cx<T>* Vj = W.V + (long)j * n;
       cx<T>* w = W.V + (long)(j + 1) * n;
@@ -835,36 +833,15 @@ int gmres_core(vie_plan_s* p, GmresWs<T>& W, OP& A, PC* M, long n, const cx<T>* 
       }
       if ((e = A.apply(z, w))) return e;
       st.matvecs++;
-      if ((e = K::mdot(W.V, n, j + 1, w, n, W.partial, W.h1, 0, s))) return e;
-      if (j + 1 <= 512) {
-        // the multi-axpy also sums |w'|^2 per block; one block reduces and takes
-        // the second-sweep decision (decided on the device)
-        const int nbm = maxpy_blocks(n);
-        if ((e = K::template maxpy_nrm<T>(W.V, n, j + 1, W.h1, -1.0, w, n, W.partial, s))) return e;
-        if ((e = K::reduce_dgks(W.partial, nbm, W.sumsq, W.h1, j + 1, W.gate, W.h2, s))) return e;
-        if ((e = K::mdot(W.V, n, j + 1, w, n, W.partial, W.h2, 0, s, W.gate))) return e;
-        if ((e = K::template maxpy_nrm<T>(W.V, n, j + 1, W.h2, -1.0, w, n, W.partial, s, W.gate))) return e;
-        if ((e = K::reduce(W.partial, nbm, W.sumsq, s, W.gate))) return e;
-      } else {
-        if ((e = K::template maxpy<T>(W.V, n, j + 1, W.h1, -1.0, w, n, s))) return e;
-        if ((e = K::nrm2sq(w, n, W.partial, W.sumsq, s))) return e;
-        // second sweep only where the first cancelled too much (decided on the device)
-        if ((e = K::dgks(W.h1, j + 1, W.sumsq, W.gate, W.h2, s))) return e;
-        if ((e = K::mdot(W.V, n, j + 1, w, n, W.partial, W.h2, 0, s, W.gate))) return e;
-        if ((e = K::template maxpy<T>(W.V, n, j + 1, W.h2, -1.0, w, n, s, W.gate))) return e;
-        if ((e = K::nrm2sq(w, n, W.partial, W.sumsq, s, W.gate))) return e;
-      }
-      if ((e = K::scale(w, w, n, W.sumsq, s))) return e;
-      if ((e = K::arnoldi_update(W.h1, W.h2, W.sumsq, W.H, ldh, W.cs, W.sn, W.g, j, bnorm, W.state, s))) return e;
-      if ((e = hipMemcpyAsync(W.state_h + 4 * (j & 1), W.state, 3 * sizeof(double), hipMemcpyDeviceToHost, s)))
-        return e;
+      if ((e = K::orthogonalise(W.V, j, w, n, D, bnorm, W.state_h + 4 * (j & 1), s))) return e;
       return hipEventRecord(W.ev[j & 1], s);
     };
     // Without a preconditioner the steps are pipelined: step j + 1 is queued
     // before the host waits for step j's state, so the device does not idle
     // through the host round trip.  A step queued after convergence is
-    // discarded: it writes only V_{j+2}, Hessenberg column j + 1 and g_{j+1},
-    // g_{j+2}, none of which the solution with k = j + 1 columns reads.  (The
+    // discarded: it writes only V_{j+2}, Hessenberg column j + 1, Gram column j + 1 (below
+    // the diagonal), the raw dots and g_{j+1}, g_{j+2}, none of which the solution with
+    // k = j + 1 columns reads.  (The
     // flexible variant's preconditioner synchronises by itself.)
     const bool pipe = M == nullptr;
     int k = 0;
@@ -968,10 +945,11 @@ size_t vie::lds_budget(int device) {
 // device current) and every use goes through that pointer.
 namespace {
 constexpr size_t kScratchBytes = 64ull << 20;
+constexpr size_t kScratchSlack = 128 << 10;   // rounding of the dots' chunks (vie_solve_noalloc)
 constexpr int kMaxDevices = 64;
 }  // namespace
 
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+static __device__ __align__(256) unsigned char scratch[kScratchBytes + kScratchSlack];
 
 namespace {
 std::mutex g_scratch_mu;
@@ -1546,17 +1524,17 @@ int vie_solve_noalloc(vie_plan_t p, const vie_c128* b, vie_c128* x, double tol, 
   ws.flex = flex;
   ws.V = c.take<double2>((size_t)n * (m + 1));
   ws.Z = flex ? c.take<double2>((size_t)n * m) : nullptr;
-  ws.partial = c.take<double2>((size_t)partial_blocks(n) * (m + 1));
-  ws.h1 = c.take<double2>(m + 2);
-  ws.h2 = c.take<double2>(m + 2);
+  ws.h = c.take<double2>(m + 2);
+  ws.gd = c.take<double2>(m + 2);
   ws.sumsq = c.take<double2>(2);
-  ws.gate = c.take<int>(1);
   ws.H = c.take<double2>((size_t)(m + 1) * m);
   ws.sn = c.take<double2>(m + 1);
   ws.g = c.take<double2>(m + 1);
   ws.y = c.take<double2>(m + 1);
   ws.cs = c.take<double>(m + 1);
-  ws.state = c.take<double>(4);
+  // the limit counts half a chunk of the dots per vector as it always did; rounding their
+  // chunks up takes at most m + 1 partials more, from the array's slack
+  ws.partial = c.take<double2>((size_t)partial_blocks(n) * (m + 1));
   ws.state_h = p->npin;
   ws.ev[0] = p->nev[0];
   ws.ev[1] = p->nev[1];

@@ -158,3 +158,31 @@ def test_mixed_tier_hands_a_stall_to_fp64_gmres(small_strip, precision):
     print(precision, info, "oracle rel res", rr)
     assert info["status"] == vie.VIE_ENOCONV and info["fallback"] == 1 and info["stalled"] == 1
     assert info["iters"] < 5000 and rr < 1e-12
+
+
+# Arnoldi steps with the two Gram-Schmidt sweeps merged: one cycle of m steps against the
+# oracle's GMRES (sweeps apart).  1800 unknowns and 14400 (several blocks per dot, ragged last
+# chunks); m past the groups of 4 and 64 vectors.
+@pytest.fixture(scope="module", params=[(6, 5, 20), (12, 10, 40)], ids=lambda g: "x".join(map(str, g)))
+def slow_system(request):
+    vie = _dev()
+    n, h, k0, eps_b = request.param, 0.1, inputs.K0, inputs.EPS_B
+    rng = np.random.default_rng(sum(n))
+    eps = eps_b + 8.0 * rng.random(n) + 0.01j
+    op = mv.Operator(green.green_table(n, mv.kappa_of(h, k0, eps_b)), mv.contrast(eps, eps_b))
+    plan = vie.Plan(n, h, k0, eps_b, fp32=True)
+    plan.set_contrast(torch.from_numpy(eps).cuda())
+    b = inputs.gaussian_rhs(n, 3)
+    _, info = solve.fgmres(op, b.ravel(), tol=1e-15, restart=140, maxit=140)
+    return op, plan, b, info.history
+
+
+@pytest.mark.parametrize("m", [1, 2, 8, 9, 33, 64, 65, 140])
+def test_one_cycle_equals_the_oracle(slow_system, m):
+    op, plan, b, history = slow_system
+    x, info = plan.solve(torch.from_numpy(b).cuda(), tol=1e-15, restart=m, maxit=m)
+    true = _oracle_rel_res(op, b, x.cpu().numpy())
+    want = history[min(m, len(history)) - 1]      # the small system ends before 140 steps
+    # both residuals in units of ||b||: FP64 rounding of a few hundred products and projections
+    assert abs(true - want) <= 1e-12, (m, true, want)
+    assert abs(info["rel_res_true"] - true) <= 1e-13
