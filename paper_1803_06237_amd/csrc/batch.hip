@@ -30,7 +30,7 @@ namespace vie {
 namespace {
 
 constexpr int kT = 256;
-constexpr int kE = 8;
+constexpr int kE = 4;
 constexpr int kC = kT * kE;   // elements per chunk
 
 __device__ __forceinline__ double2 d2(double2 v) { return v; }
@@ -79,16 +79,18 @@ struct KDesc {
   void* r;          // residual buffer (cycle start vector)
   long n;
   int nchunk;
-  double2* partial; // (m + 1) * nchunk
-  double2* h1;
-  double2* h2;
+  double2* partial; // 2 (m + 1) * nchunk
+  double2* h;       // projections of the step
+  double2* raw;     // V^H w
+  double2* gd;      // Gram diagonal
   double2* sumsq;   // [0] ||w||^2 of the current vector, [1] ||b||^2
-  double2* H;       // (m + 1) * m, column-major
+  double2* H;       // (m + 1) * m, column-major; Gram entry G_ij, i < j, at row j of column i
   double* cs;
   double2* sn;
   double2* g;
   double2* y;
   int* act;         // active in the current step
+  int* go;          // act as the step's projections found it (act may clear while it ends)
   const int* act0;  // active for the cycle
   int* kdone;       // Arnoldi steps of the current cycle
   int* iters;       // accumulated steps
@@ -121,110 +123,181 @@ __device__ __forceinline__ cx<T>* vsel(const KDesc& D, int which, int j) {
   }
 }
 
-// partial[i * nchunk + chunk] = V_i^H w over the chunk, i <= j, w = V_{j+1}
+// Arnoldi steps as in the single solver (krylov.hip): the two Gram-Schmidt sweeps merged by
+// the Gram matrix G = V^H V, h = 2 V^H w - G V^H w, one dot pass and one update pass over the
+// basis per step.  (With the sweeps apart, in workgroups that walked all vectors of a chunk:
+// 117 us of dots and updates per FP32 step of eight systems of 968k unknowns together; now 28.)
+
+// partial[(2 i + s) nchunk + chunk] = V_i^H w (s = 0) and V_i^H V_j (s = 1) over the chunk, for
+// the four vectors i of blockIdx.y; w = V_{j+1}
 template <typename T>
 __global__ __launch_bounds__(kT) void k_b_mdot(const KDesc* __restrict__ d, const int* __restrict__ prefix, int nsys,
-                                               int total, int j) {
-  __shared__ double lds[(kT / 64) * 8];
-  for (int item = blockIdx.x; item < total; item += gridDim.x) {
-    const int s = find_item(prefix, nsys, item);
-    const KDesc& D = d[s];
-    if (*D.act == 0) continue;
-    const int chunk = item - prefix[s];
-    const long e0 = (long)chunk * kC + threadIdx.x;
-    const cx<T>* w = (const cx<T>*)D.V + (long)(j + 1) * D.n;
-    double2 wv[kE];
+                                               int j) {
+  __shared__ double lds[kT / 64][16];
+  const int item = blockIdx.x;
+  const int s = find_item(prefix, nsys, item);
+  const KDesc& D = d[s];
+  if (*D.act == 0) return;
+  const int chunk = item - prefix[s], i0 = blockIdx.y * 4;
+  const long n = D.n;
+  const cx<T>* V = (const cx<T>*)D.V;
+  const cx<T>* vj = V + (long)j * n;
+  const cx<T>* w = vj + n;
+  // loads from clamped, always valid addresses: all in flight together
+  long e[kE];
+  double2 wv[kE], vv[kE];
+#pragma unroll
+  for (int k = 0; k < kE; ++k) {
+    const long at = (long)chunk * kC + threadIdx.x + (long)k * kT;
+    e[k] = at < n ? at : n - 1;
+    wv[k] = d2(w[e[k]]);
+    vv[k] = d2(vj[e[k]]);
+    if (at >= n) wv[k] = vv[k] = double2{0.0, 0.0};
+  }
+  double acc[16];
+#pragma unroll
+  for (int q = 0; q < 16; ++q) acc[q] = 0.0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const cx<T>* Vi = V + (long)(i0 + q <= j ? i0 + q : j) * n;
+    double2 a[kE];
+#pragma unroll
+    for (int k = 0; k < kE; ++k) a[k] = d2(Vi[e[k]]);
 #pragma unroll
     for (int k = 0; k < kE; ++k) {
-      const long e = e0 + (long)k * kT;
-      wv[k] = e < D.n ? d2(w[e]) : double2{0.0, 0.0};
+      acc[4 * q] += a[k].x * wv[k].x + a[k].y * wv[k].y;
+      acc[4 * q + 1] += a[k].x * wv[k].y - a[k].y * wv[k].x;
+      acc[4 * q + 2] += a[k].x * vv[k].x + a[k].y * vv[k].y;
+      acc[4 * q + 3] += a[k].x * vv[k].y - a[k].y * vv[k].x;
     }
-    for (int i0 = 0; i0 <= j; i0 += 4) {
-      double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  }
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int idx;
+  const double r = wave_sum_many<16>(acc, lane, &idx);
+  if (lane < 16) lds[wave][idx] = r;
+  __syncthreads();
+  if (threadIdx.x < 16 && i0 + (int)(threadIdx.x >> 2) <= j) {
+    double t = 0.0;
+    for (int k = 0; k < kT / 64; ++k) t += lds[k][threadIdx.x];
+    const long row = 2L * i0 + (threadIdx.x >> 1);
+    reinterpret_cast<double*>(D.partial)[2 * (row * D.nchunk + chunk) + (threadIdx.x & 1)] = t;
+  }
+}
+
+// Sums of the dots, the new Gram column and h, one workgroup per system (as k_proj)
+constexpr int kProjT = 1024;
+__global__ __launch_bounds__(kProjT) void k_b_proj(const KDesc* __restrict__ d, int j, int m) {
+  __shared__ double2 sums[kProjT / 64][64];
+  const KDesc& D = d[blockIdx.x];
+  const int on = *D.act;
+  if (threadIdx.x == 0) *D.go = on;
+  if (on == 0) return;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nv = j + 1, ldh = m + 1, sub = threadIdx.x & 7;
+  constexpr int kW = kProjT / 64;
+  for (int v = threadIdx.x >> 3; v < 2 * nv; v += kProjT / 8) {
+    double2 s{0.0, 0.0};
+#pragma unroll 8
+    for (int b = sub; b < D.nchunk; b += 8) {
+      const double2 p = D.partial[(long)v * D.nchunk + b];
+      s.x += p.x;
+      s.y += p.y;
+    }
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        if (i0 + q <= j) {
-          const cx<T>* Vi = (const cx<T>*)D.V + (long)(i0 + q) * D.n;
-#pragma unroll
-          for (int k = 0; k < kE; ++k) {
-            const long e = e0 + (long)k * kT;
-            if (e < D.n) {
-              const double2 a = d2(Vi[e]);
-              acc[2 * q] += a.x * wv[k].x + a.y * wv[k].y;
-              acc[2 * q + 1] += a.x * wv[k].y - a.y * wv[k].x;
-            }
-          }
-        }
+    for (int o = 1; o < 8; o <<= 1) {
+      s.x += __shfl_xor(s.x, o, 64);
+      s.y += __shfl_xor(s.y, o, 64);
+    }
+    if (sub == 0) {
+      const int i = v >> 1;
+      if ((v & 1) == 0) D.raw[i] = s;
+      else if (i < j) D.H[(long)i * ldh + j] = s;
+      else D.gd[i] = s;
+    }
+  }
+  __syncthreads();
+  for (int i0 = 0; i0 < nv; i0 += 64) {
+    const int i = i0 + lane;
+    double2 s{0.0, 0.0};
+    if (i < nv)
+      for (int k = wave; k < nv; k += kW) {
+        const double2 r = D.raw[k];
+        double2 g;                                   // G_ik
+        if (k == i) g = D.gd[i];
+        else if (k > i) g = D.H[(long)i * ldh + k];
+        else g = D.H[(long)k * ldh + i], g.y = -g.y;
+        s.x += g.x * r.x - g.y * r.y;
+        s.y += g.x * r.y + g.y * r.x;
       }
-      bsum<8>(acc, lds);
-      if (threadIdx.x == 0)
-        for (int q = 0; q < 4; ++q)
-          if (i0 + q <= j) D.partial[(long)(i0 + q) * D.nchunk + chunk] = double2{acc[2 * q], acc[2 * q + 1]};
+    sums[wave][lane] = s;
+    __syncthreads();
+    if (wave == 0 && i < nv) {
+      double2 t{0.0, 0.0};
+      for (int k = 0; k < kW; ++k) {
+        t.x += sums[k][lane].x;
+        t.y += sums[k][lane].y;
+      }
+      const double2 r = D.raw[i];
+      D.h[i] = double2{2.0 * r.x - t.x, 2.0 * r.y - t.y};
     }
+    __syncthreads();
   }
 }
 
-// h[i] = sum over chunks of partial[i], i < count; items (s, i)
-__global__ __launch_bounds__(kT) void k_b_reduce(const KDesc* __restrict__ d, int nsys, int count, int which) {
-  __shared__ double lds[(kT / 64) * 2];
-  for (int item = blockIdx.x; item < nsys * count; item += gridDim.x) {
-    const int s = item / count, i = item % count;
-    const KDesc& D = d[s];
-    if (*D.act == 0) continue;
-    double v[2] = {0.0, 0.0};
-    for (int c = threadIdx.x; c < D.nchunk; c += kT) {
-      const double2 p = D.partial[(long)i * D.nchunk + c];
-      v[0] += p.x;
-      v[1] += p.y;
-    }
-    bsum<2>(v, lds);
-    if (threadIdx.x == 0) {
-      double2* out = which == 0 ? D.h1 : (which == 1 ? D.h2 : D.sumsq);
-      out[i] = double2{v[0], v[1]};
-    }
-  }
-}
-
-// w = V_{j+1} -= sum_{i <= j} h_i V_i   (which = 0: h1, 1: h2)
+// w = V_{j+1} -= sum_{i <= j} h_i V_i and partial[chunk].x = ||w||^2 over the chunk
 template <typename T>
 __global__ __launch_bounds__(kT) void k_b_orth(const KDesc* __restrict__ d, const int* __restrict__ prefix, int nsys,
-                                               int total, int j, int which) {
+                                               int j) {
   __shared__ double2 c[512];
-  for (int item = blockIdx.x; item < total; item += gridDim.x) {
-    const int s = find_item(prefix, nsys, item);
-    const KDesc& D = d[s];
-    if (*D.act == 0) continue;
-    const double2* h = which == 0 ? D.h1 : D.h2;
-    __syncthreads();
-    for (int i = threadIdx.x; i <= j; i += kT) c[i] = h[i];
-    __syncthreads();
-    const long e0 = (long)(item - prefix[s]) * kC + threadIdx.x;
-    cx<T>* w = (cx<T>*)D.V + (long)(j + 1) * D.n;
-    double2 acc[kE];
+  __shared__ double lds[kT / 64];
+  const int item = blockIdx.x;
+  const int s = find_item(prefix, nsys, item);
+  const KDesc& D = d[s];
+  if (*D.go == 0) return;
+  for (int i = threadIdx.x; i <= j + 1; i += kT) c[i] = i <= j ? D.h[i] : double2{0.0, 0.0};
+  __syncthreads();
+  const long n = D.n;
+  const int chunk = item - prefix[s];
+  const cx<T>* V = (const cx<T>*)D.V;
+  cx<T>* w = (cx<T>*)D.V + (long)(j + 1) * n;
+  long e[kE];
+  double2 acc[kE];
+#pragma unroll
+  for (int k = 0; k < kE; ++k) {
+    const long at = (long)chunk * kC + threadIdx.x + (long)k * kT;
+    e[k] = at < n ? at : n - 1;
+    acc[k] = d2(w[e[k]]);
+  }
+  for (int i = 0; i <= j; i += 2) {   // eight loads in flight (the last vector again past the end)
+    const cx<T>* Vi = V + (long)i * n;
+    const cx<T>* Vk = V + (long)(i < j ? i + 1 : i) * n;
+    double2 a[kE], b[kE];
 #pragma unroll
     for (int k = 0; k < kE; ++k) {
-      const long e = e0 + (long)k * kT;
-      acc[k] = e < D.n ? d2(w[e]) : double2{0.0, 0.0};
+      a[k] = d2(Vi[e[k]]);
+      b[k] = d2(Vk[e[k]]);
     }
-    for (int i = 0; i <= j; ++i) {
-      const double2 ci = c[i];
-      const cx<T>* Vi = (const cx<T>*)D.V + (long)i * D.n;
-#pragma unroll
-      for (int k = 0; k < kE; ++k) {
-        const long e = e0 + (long)k * kT;
-        if (e < D.n) {
-          const double2 a = d2(Vi[e]);
-          acc[k].x -= ci.x * a.x - ci.y * a.y;
-          acc[k].y -= ci.x * a.y + ci.y * a.x;
-        }
-      }
-    }
+    const double2 ca = c[i], cb = c[i + 1];
 #pragma unroll
     for (int k = 0; k < kE; ++k) {
-      const long e = e0 + (long)k * kT;
-      if (e < D.n) w[e] = fromd<cx<T>>(acc[k]);
+      acc[k].x -= ca.x * a[k].x - ca.y * a[k].y;
+      acc[k].y -= ca.x * a[k].y + ca.y * a[k].x;
+      acc[k].x -= cb.x * b[k].x - cb.y * b[k].y;
+      acc[k].y -= cb.x * b[k].y + cb.y * b[k].x;
     }
   }
+  double v[1] = {0.0};
+#pragma unroll
+  for (int k = 0; k < kE; ++k) {
+    const long at = (long)chunk * kC + threadIdx.x + (long)k * kT;
+    if (at < n) {
+      const cx<T> out = fromd<cx<T>>(acc[k]);
+      w[at] = out;
+      const double2 o = d2(out);
+      v[0] += o.x * o.x + o.y * o.y;
+    }
+  }
+  bsum<1>(v, lds);
+  if (threadIdx.x == 0) D.partial[chunk] = double2{v[0], 0.0};
 }
 
 // partial[chunk] = ||v||^2 over the chunk, v selected by (which, j); act_sel: 0 -> act, 1 -> act0
@@ -302,23 +375,48 @@ __global__ void k_b_init(const KDesc* __restrict__ d, int nsys, int m) {
   }
 }
 
-// Hessenberg column j, Givens rotations, residual estimate and step mask.
-__global__ void k_b_givens(const KDesc* __restrict__ d, int nsys, int j, int m) {
-  for (int s = blockIdx.x * blockDim.x + threadIdx.x; s < nsys; s += gridDim.x * blockDim.x) {
-    const KDesc& D = d[s];
-    if (*D.act == 0) continue;
-    double2* h = D.H + (long)j * (m + 1);
-    for (int i = 0; i <= j; ++i) h[i] = double2{D.h1[i].x + D.h2[i].x, D.h1[i].y + D.h2[i].y};
-    const double hn = sqrt(D.sumsq[0].x);
-    h[j + 1] = double2{hn, 0.0};
+// End of step j: every workgroup sums its system's partials of ||w||^2 and scales its chunk of
+// V_{j+1}; the system's first one also does the Hessenberg column, the rotations, the residual
+// estimate and the step mask.
+template <typename T>
+__global__ __launch_bounds__(kT) void k_b_finish(const KDesc* __restrict__ d, const int* __restrict__ prefix, int nsys,
+                                                 int j, int m) {
+  __shared__ double lds[kT / 64];
+  __shared__ double2 h[512];
+  __shared__ double s_norm;
+  const int item = blockIdx.x;
+  const int s = find_item(prefix, nsys, item);
+  const KDesc& D = d[s];
+  if (*D.go == 0) return;
+  const int chunk = item - prefix[s];
+  double v[1] = {0.0};
+  for (int c = threadIdx.x; c < D.nchunk; c += kT) v[0] += D.partial[c].x;
+  bsum<1>(v, lds);
+  if (threadIdx.x == 0) s_norm = sqrt(v[0]);
+  if (chunk == 0)
+    for (int i = threadIdx.x; i <= j; i += kT) h[i] = D.h[i];
+  __syncthreads();
+  const double hn = s_norm, f = hn > 0.0 ? 1.0 / hn : 0.0;
+  cx<T>* w = (cx<T>*)D.V + (long)(j + 1) * D.n;
+#pragma unroll
+  for (int k = 0; k < kE; ++k) {
+    const long e = (long)chunk * kC + threadIdx.x + (long)k * kT;
+    if (e < D.n) {
+      const double2 a = d2(w[e]);
+      w[e] = fromd<cx<T>>(double2{a.x * f, a.y * f});
+    }
+  }
+  if (chunk != 0) return;
+  if (threadIdx.x == 0) {
+    double2 a = h[0];
     for (int i = 0; i < j; ++i) {
-      const double2 a = h[i], bb = h[i + 1];
+      const double2 bb = h[i + 1];
       const double c = D.cs[i];
       const double2 sn = D.sn[i];
       h[i] = double2{c * a.x + (sn.x * bb.x - sn.y * bb.y), c * a.y + (sn.x * bb.y + sn.y * bb.x)};
-      h[i + 1] = double2{-(sn.x * a.x + sn.y * a.y) + c * bb.x, -(sn.x * a.y - sn.y * a.x) + c * bb.y};
+      a = double2{-(sn.x * a.x + sn.y * a.y) + c * bb.x, -(sn.x * a.y - sn.y * a.x) + c * bb.y};
     }
-    const double2 a = h[j], bb = h[j + 1];
+    const double2 bb = double2{hn, 0.0};
     const double na = hypot(a.x, a.y), nb = hypot(bb.x, bb.y);
     double c;
     double2 sn, r;
@@ -340,7 +438,6 @@ __global__ void k_b_givens(const KDesc* __restrict__ d, int nsys, int j, int m) 
     D.cs[j] = c;
     D.sn[j] = sn;
     h[j] = r;
-    h[j + 1] = double2{0.0, 0.0};
     const double2 gj = D.g[j];
     D.g[j + 1] = double2{-(sn.x * gj.x + sn.y * gj.y), -(sn.x * gj.y - sn.y * gj.x)};
     D.g[j] = double2{c * gj.x, c * gj.y};
@@ -351,26 +448,32 @@ __global__ void k_b_givens(const KDesc* __restrict__ d, int nsys, int j, int m) 
     *D.iters += 1;
     if (!(est > D.tol) || hn == 0.0 || !isfinite(est)) *D.act = 0;
   }
+  __syncthreads();
+  double2* col = D.H + (long)j * (m + 1);
+  for (int i = threadIdx.x; i <= j; i += kT) col[i] = h[i];
 }
 
-// y = R^{-1} g over the kdone leading columns
-__global__ void k_b_trisolve(const KDesc* __restrict__ d, int nsys, int m) {
-  for (int s = blockIdx.x * blockDim.x + threadIdx.x; s < nsys; s += gridDim.x * blockDim.x) {
-    const KDesc& D = d[s];
-    if (*D.act0 == 0) continue;
-    const int k = *D.kdone;
-    for (int i = k - 1; i >= 0; --i) {
-      double2 acc = D.g[i];
-      for (int l = i + 1; l < k; ++l) {
-        const double2 hil = D.H[(long)l * (m + 1) + i], yl = D.y[l];
-        acc.x -= hil.x * yl.x - hil.y * yl.y;
-        acc.y -= hil.x * yl.y + hil.y * yl.x;
-      }
-      const double2 dd = D.H[(long)i * (m + 1) + i];
-      const double q = dd.x * dd.x + dd.y * dd.y;
-      D.y[i] = q > 0 ? double2{(acc.x * dd.x + acc.y * dd.y) / q, (acc.y * dd.x - acc.x * dd.y) / q}
-                     : double2{0.0, 0.0};
+// y = R^{-1} g over the kdone leading columns, one workgroup per system: the right-hand side in
+// LDS, every thread updating its rows with the new y_i
+__global__ __launch_bounds__(kT) void k_b_trisolve(const KDesc* __restrict__ d, int m) {
+  __shared__ double2 r[512];
+  const KDesc& D = d[blockIdx.x];
+  if (*D.act0 == 0) return;
+  const int k = *D.kdone;
+  for (int i = threadIdx.x; i < k; i += kT) r[i] = D.g[i];
+  __syncthreads();
+  for (int i = k - 1; i >= 0; --i) {
+    const double2* A = D.H + (long)i * (m + 1);
+    const double2 acc = r[i], dd = A[i];
+    const double q = dd.x * dd.x + dd.y * dd.y;
+    const double2 yi = q > 0 ? double2{(acc.x * dd.x + acc.y * dd.y) / q, (acc.y * dd.x - acc.x * dd.y) / q}
+                             : double2{0.0, 0.0};
+    if (threadIdx.x == 0) D.y[i] = yi;
+    for (int l = threadIdx.x; l < i; l += kT) {
+      const double2 a = A[l];
+      r[l] = double2{r[l].x - (a.x * yi.x - a.y * yi.y), r[l].y - (a.x * yi.y + a.y * yi.x)};
     }
+    __syncthreads();
   }
 }
 
@@ -583,9 +686,9 @@ hipError_t build_level(BatchLevel<T>& L, const std::vector<long>& n, int m, bool
   L.h.resize(L.nsys);
   L.cpre.assign(L.nsys + 1, 0);
   hipError_t e;
-  int* flags = nullptr;   // per system: act, kdone, iters
-  if ((e = L.alloc((void**)&flags, sizeof(int) * 3 * L.nsys))) return e;
-  if ((e = hipMemset(flags, 0, sizeof(int) * 3 * L.nsys))) return e;
+  int* flags = nullptr;   // per system: act, kdone, iters, go
+  if ((e = L.alloc((void**)&flags, sizeof(int) * 4 * L.nsys))) return e;
+  if ((e = hipMemset(flags, 0, sizeof(int) * 4 * L.nsys))) return e;
   double* est = nullptr;
   if ((e = L.alloc((void**)&est, sizeof(double) * L.nsys))) return e;
   for (int s = 0; s < L.nsys; ++s) {
@@ -603,13 +706,14 @@ hipError_t build_level(BatchLevel<T>& L, const std::vector<long>& n, int m, bool
     D.x = x[s];
     D.b = b[s];
     if ((e = L.alloc(&D.r, sizeof(cx<T>) * len))) return e;
-    if ((e = L.alloc((void**)&D.partial, sizeof(double2) * (size_t)(m + 1) * nch))) return e;
+    if ((e = L.alloc((void**)&D.partial, sizeof(double2) * 2 * (size_t)(m + 1) * nch))) return e;
     double2* small = nullptr;
-    const size_t per = (size_t)(m + 2) * 2 + 2 + (size_t)(m + 1) * m + 3 * (size_t)(m + 1);
+    const size_t per = (size_t)(m + 2) * 3 + 2 + (size_t)(m + 1) * m + 3 * (size_t)(m + 1);
     if ((e = L.alloc((void**)&small, sizeof(double2) * per))) return e;
-    D.h1 = small;
-    D.h2 = D.h1 + (m + 2);
-    D.sumsq = D.h2 + (m + 2);
+    D.h = small;
+    D.raw = D.h + (m + 2);
+    D.gd = D.raw + (m + 2);
+    D.sumsq = D.gd + (m + 2);
     D.H = D.sumsq + 2;
     D.sn = D.H + (size_t)(m + 1) * m;
     D.g = D.sn + (m + 1);
@@ -618,6 +722,7 @@ hipError_t build_level(BatchLevel<T>& L, const std::vector<long>& n, int m, bool
     D.act = flags + s;
     D.kdone = flags + L.nsys + s;
     D.iters = flags + 2 * L.nsys + s;
+    D.go = flags + 3 * L.nsys + s;
     D.act0 = act_cycle_src ? act_cycle_src + s : act_cycle + s;
     D.est = est + s;
     D.tol = tol;
@@ -866,17 +971,16 @@ hipError_t enqueue_cycle(vie_batch_s* B, BatchLevel<T>& L, PassSet& PS, int) {
       }
     }
     if ((e = batch_matvec<T>(B, PS, L, false, j))) return e;
-    const int g = grid_for(L.ctotal);
-    for (int pass = 0; pass < 2; ++pass) {
-      hipLaunchKernelGGL((k_b_mdot<T>), dim3(g), dim3(kT), 0, s, L.d, L.d_cpre, L.nsys, L.ctotal, j);
-      hipLaunchKernelGGL(k_b_reduce, dim3(grid_for(L.nsys * (j + 1))), dim3(kT), 0, s, L.d, L.nsys, j + 1, pass);
-      hipLaunchKernelGGL((k_b_orth<T>), dim3(g), dim3(kT), 0, s, L.d, L.d_cpre, L.nsys, L.ctotal, j, pass);
+    if (L.ctotal > 0) {
+      const dim3 chunks((unsigned)L.ctotal);
+      hipLaunchKernelGGL((k_b_mdot<T>), dim3((unsigned)L.ctotal, (unsigned)(j + 4) / 4), dim3(kT), 0, s, L.d, L.d_cpre,
+                         L.nsys, j);
+      hipLaunchKernelGGL(k_b_proj, dim3((unsigned)L.nsys), dim3(kProjT), 0, s, L.d, j, L.m);
+      hipLaunchKernelGGL((k_b_orth<T>), chunks, dim3(kT), 0, s, L.d, L.d_cpre, L.nsys, j);
+      hipLaunchKernelGGL((k_b_finish<T>), chunks, dim3(kT), 0, s, L.d, L.d_cpre, L.nsys, j, L.m);
     }
-    if ((e = batch_norm<T>(s, L, 0, j + 1, 0, 0))) return e;
-    hipLaunchKernelGGL((k_b_scale<T>), dim3(g), dim3(kT), 0, s, L.d, L.d_cpre, L.nsys, L.ctotal, 0, j + 1, j + 1, 0);
-    hipLaunchKernelGGL(k_b_givens, dim3((L.nsys + 63) / 64), dim3(64), 0, s, L.d, L.nsys, j, L.m);
   }
-  hipLaunchKernelGGL(k_b_trisolve, dim3((L.nsys + 63) / 64), dim3(64), 0, s, L.d, L.nsys, L.m);
+  hipLaunchKernelGGL(k_b_trisolve, dim3((unsigned)L.nsys), dim3(kT), 0, s, L.d, L.m);
   hipLaunchKernelGGL((k_b_update<T>), dim3(grid_for(L.ctotal)), dim3(kT), 0, s, L.d, L.d_cpre, L.nsys, L.ctotal);
   return hipGetLastError();
 }

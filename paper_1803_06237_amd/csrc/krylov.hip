@@ -68,32 +68,6 @@ __device__ __forceinline__ void block_sum(double (&v)[NV], double* lds) {
   __syncthreads();
 }
 
-// Sums of NV = 16 or 32 values per lane over the wave: lane l gets that of value *idx, with half
-// as many exchanges per halving step as values left (17 or 32 in all instead of 6 NV).
-template <int NV, int H>
-__device__ __forceinline__ void wave_fold(double (&v)[NV], int lane, int& id) {
-  if constexpr (H >= 1) {
-    constexpr int bit = NV / 2 / H;              // 1, 2, 4, ...
-    const bool up = (lane & bit) != 0;
-#pragma unroll
-    for (int i = 0; i < H; ++i) {
-      const double send = up ? v[i] : v[i + H], keep = up ? v[i + H] : v[i];
-      v[i] = keep + __shfl_xor(send, bit, 64);
-    }
-    id |= up ? H : 0;
-    wave_fold<NV, H / 2>(v, lane, id);
-  }
-}
-template <int NV>
-__device__ __forceinline__ double wave_sum_many(double (&v)[NV], int lane, int* idx) {
-  *idx = 0;
-  wave_fold<NV, NV / 2>(v, lane, *idx);
-  double r = v[0];
-#pragma unroll
-  for (int o = NV; o < 64; o <<= 1) r += __shfl_xor(r, o, 64);
-  return r;
-}
-
 // partial[(2 i + s) nblk + blk] = the block's share of V_i^H w (s = 0) and of V_i^H V_{nv-1}
 // (s = 1), for the kGroup vectors i of blockIdx.y
 template <typename T>

@@ -6,6 +6,32 @@
 
 namespace vie {
 
+// Sums of NV (a power of two up to 64) values per lane over the wave: lane l gets that of value *idx, with half
+// as many exchanges per halving step as values left (17 in all for 16 values instead of 96).
+template <int NV, int H>
+__device__ __forceinline__ void wave_fold(double (&v)[NV], int lane, int& id) {
+  if constexpr (H >= 1) {
+    constexpr int bit = NV / 2 / H;              // 1, 2, 4, ...
+    const bool up = (lane & bit) != 0;
+#pragma unroll
+    for (int i = 0; i < H; ++i) {
+      const double send = up ? v[i] : v[i + H], keep = up ? v[i + H] : v[i];
+      v[i] = keep + __shfl_xor(send, bit, 64);
+    }
+    id |= up ? H : 0;
+    wave_fold<NV, H / 2>(v, lane, id);
+  }
+}
+template <int NV>
+__device__ __forceinline__ double wave_sum_many(double (&v)[NV], int lane, int* idx) {
+  *idx = 0;
+  wave_fold<NV, NV / 2>(v, lane, *idx);
+  double r = v[0];
+#pragma unroll
+  for (int o = NV; o < 64; o <<= 1) r += __shfl_xor(r, o, 64);
+  return r;
+}
+
 // Device data of one GMRES cycle: the reduction partials (arnoldi_partials), the raw dots and
 // the Gram diagonal (m + 1 values each), the projections h, the Hessenberg matrix
 // (column-major, leading dimension ldh; the Gram entries G_ij, i < j, at row j of column i),
