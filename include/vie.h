@@ -432,16 +432,12 @@ int vie_nn_adam_test(long n, float* w, float* m, float* v, const float* g, int t
  *   negating m_d multiplies K^{ab} by -1 exactly when d is neither a nor b.
  * vie_jm_enable -- builds the spectrum of K and the JM buffers and sets mu_r = 1
  *   everywhere.  Idempotent.  VIE_EINVAL when M1 M2 > 4096.  Synchronises.
- *   The cross-section pass runs fused (spectra in LDS) when the six
- *   row-transformed components of a plane fit with one column chunk:
- *   (6 n2 M1 + 6 M2 cc) complex values in 160 KiB for some cc >= 1 (every FP32
- *   grid; in FP64 e.g. the 30 x 12 strip), else with the x-frequencies in two
- *   halves of M1/2 (even and odd kx in turn; in FP64 the 32 x 32
- *   cross-section); otherwise through full spectra in HBM (6 M1 M2 M3 complex
- *   values per precision, allocated only then).
+ *   The cross-section pass runs fused, in one kernel over the kz planes (every
+ *   grid fits; 64 x 64 circulant sections in FP64 with the x-frequencies in two
+ *   halves, even and odd kx in turn).
  * vie_jm_set_route / vie_jm_get_route -- per precision (0 FP64, 1 FP32): fused 1
- *   = the fused pass (VIE_EINVAL where it does not fit), 0 = through HBM
- *   (allocates the spectra on first use).  Same results to rounding.
+ *   = the fused pass, 0 = through full spectra in HBM (6 M1 M2 M3 complex
+ *   values, allocated on first use).  Same results to rounding.
  * vie_jm_set_permeability -- mu_r: device, N relative permeabilities (copied).
  *   VIE_EINVAL for a zero or non-finite entry.  Synchronises.
  * vie_jm_rhs -- b = h^{3/2} (M_eps e_inc, M_mu etah_inc): e_inc and etah_inc

@@ -213,7 +213,7 @@ struct vie_plan_s {
   float2* S32 = nullptr;
   float2* jm32a = nullptr;
   float2* jm32b = nullptr;
-  bool jm_fused64 = false;   // cross-section pass with the spectra in LDS (else through S64 / S32)
+  bool jm_fused64 = false;   // cross-section pass in one kernel (else through S64 / S32)
   bool jm_fused32 = false;
   std::shared_ptr<const std::vector<std::complex<double>>> table;   // host Toeplitz table
   GmresWs<double> ws64;
@@ -1717,13 +1717,9 @@ int vie_jm_enable(vie_plan_t p) {
   JMTRY(hipMemsetAsync(p->chim64, 0, sizeof(double2) * g.N, p->stream));
   JMTRY(hipMemsetAsync(p->chim32, 0, sizeof(float2) * g.N, p->stream));
   JMTRY(dmalloc(&p->Um64, sizeof(double2) * nU));
-  p->jm_fused64 = jm_fused_shape<double>(g, nullptr, nullptr);
-  p->jm_fused32 = f32 && jm_fused_shape<float>(g, nullptr, nullptr);
-  if (!p->jm_fused64) JMTRY(dmalloc(&p->S64, sizeof(double2) * jm_spectrum_values(g)));
-  if (f32) {
-    JMTRY(dmalloc(&p->Um32, sizeof(float2) * nU));
-    if (!p->jm_fused32) JMTRY(dmalloc(&p->S32, sizeof(float2) * jm_spectrum_values(g)));
-  }
+  if (f32) JMTRY(dmalloc(&p->Um32, sizeof(float2) * nU));
+  p->jm_fused64 = true;
+  p->jm_fused32 = f32;
   JMTRY(dmalloc(&kdev, sizeof(double2) * 3 * g.N));
   JMTRY(dmalloc(&full, sizeof(double2) * P));
   JMTRY(hipMemcpyAsync(kdev, kt->data(), sizeof(double2) * 3 * g.N, hipMemcpyHostToDevice, p->stream));
@@ -1742,9 +1738,6 @@ int vie_jm_set_route(vie_plan_t p, int precision, int fused) {
   if (!p->jm) return fail(p, VIE_ESTATE, "vie_jm_enable first");
   if (precision != 0 && precision != 1) return fail(p, VIE_EINVAL, "precision must be 0 (FP64) or 1 (FP32)");
   if (precision == 1 && !p->goct32) return fail(p, VIE_ESTATE, "plan made without VIE_WITH_FP32");
-  const bool fits = precision == 0 ? jm_fused_shape<double>(p->g, nullptr, nullptr)
-                                   : jm_fused_shape<float>(p->g, nullptr, nullptr);
-  if (fused && !fits) return fail(p, VIE_EINVAL, "the fused cross-section pass does not fit this grid");
   if (!fused) {
     void** S = precision == 0 ? (void**)&p->S64 : (void**)&p->S32;
     const size_t cs = precision == 0 ? sizeof(double2) : sizeof(float2);

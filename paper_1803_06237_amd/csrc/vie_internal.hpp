@@ -82,12 +82,9 @@ size_t xy_lds_bytes(const Geom& g, int cc);
 // ---- JM-VIE product (jm.hip) --------------------------------------------------
 // y = (I - M T~) x on 6N vectors (electric then magnetic, each [3][n1][n2][n3]);
 // mode 1: y = b - (I - M T~) x.  Ue, Um: z-pass intermediates of each half.
-// fused: one cross-section kernel with the spectra in LDS (requires
-// jm_fused_shape); otherwise the spectra go through S, jm_spectrum_values(g)
-// values.  M1 M2 <= 4096.
+// fused: one cross-section kernel (register transforms, jmr.hip, or LDS stages);
+// otherwise the spectra go through S, jm_spectrum_values(g) values.  M1, M2 <= 64.
 size_t jm_spectrum_values(const Geom& g);
-template <typename T>
-bool jm_fused_shape(const Geom& g, int* cc, int* threads, int* split = nullptr);
 template <typename T>
 hipError_t allow_lds_jm();
 template <typename T>

@@ -120,6 +120,34 @@ def test_other_cross_section_route_matches_oracle(case, precision):
         plan.set_jm_route(precision, default)
 
 
+# every pair of circulant sides of 8 to 64 points, with one, two and more planes per workgroup
+# and incomplete last workgroups (z circulants of 1, 4 and 16)
+@pytest.mark.parametrize("n1", [3, 7, 16, 27])
+@pytest.mark.parametrize("n2", [4, 5, 13, 31])
+@pytest.mark.parametrize("n3", [1, 2, 7])
+def test_register_cross_sections_match_oracle(n1, n2, n3):
+    vie = _dev()
+    n = (n1, n2, n3)
+    rng = np.random.default_rng(61 + 100 * n1 + n2)
+    kap = mv.kappa_of(H, K0, EPSB)
+    eps, mu = _materials(rng, n)
+    spec = mv.spectrum(green.green_table(n, kap))
+    kspec = jm.curl_spectrum(jm.curl_table(n, kap))
+    plan = vie.Plan(n, H, K0, EPSB, fp32=True)
+    plan.set_contrast(_t(eps))
+    plan.jm_enable()
+    plan.set_permeability(_t(mu))
+    x = _cvec(rng, (6,) + n)
+    want = jm.jm_matvec(spec, kspec, mv.contrast(eps, EPSB), jm.magnetic_contrast(mu), kap, x)
+    for precision, dtype, tol in ((0, None, 1e-12), (1, torch.complex64, 5e-6)):
+        plan.set_jm_route(precision, True)
+        product = plan.jm_matvec_c64 if precision else plan.jm_matvec
+        got = product(_t(x, dtype)).cpu().numpy().astype(np.complex128)
+        err = np.linalg.norm(got - want) / np.linalg.norm(want)
+        print(f"grid {n} precision {precision} rel err {err:.3e}", flush=True)
+        assert err < tol
+
+
 JM_BENCH_CASES = {
     "guide32x32x512": lambda: _magnetic(inputs.strip_long(d=2)),
     "strip30x12x1377": lambda: inputs.strip_paper(9.45, 2, 1e-10, magnetic=True),
