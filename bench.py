@@ -57,7 +57,7 @@ def jm_pass_bytes(n, M, cs, fused):
     S3 = 3 * M1 * M2 * M3 * cs
     z = {"z forward (x2)": 2 * (3 * N * cs + U), "z inverse (x2)": 2 * (U + 7 * N * cs)}
     if fused:
-        z["k_jm_xy"] = 4 * U + G + K
+        z["fused cross-section pass"] = 4 * U + G + K
     else:
         z["k_jm_xyfwd (x2)"] = 2 * (U + S3)
         z["k_jm_product"] = 4 * S3 + G + K
@@ -181,13 +181,19 @@ def profiled_traffic(kernel: str):
     return None
 
 
+Z_LENGTHS = (512, 640, 768, 800, 960, 1024, 1152, 1280, 1440, 1600, 1920, 2048, 2304, 2560, 2880, 3072, 3600, 4096)
+
+
 def circulant(n):
+    """The library's circulant lengths: powers of two, along z from 512 on its own list."""
     out = []
     for v in n:
         m = 1
         while m < 2 * v - 1:
             m *= 2
         out.append(m)
+    if out[2] >= 512:
+        out[2] = min(m for m in Z_LENGTHS if m >= 2 * n[2] - 1)
     return tuple(out)
 
 

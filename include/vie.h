@@ -31,7 +31,9 @@
  *
  * Size limits of this version: n1, n2 <= 32 and n3 <= 2048 (circulant lengths
  * up to 64, 64 and 4096); each circulant length is the power of two
- * >= 2 n_d - 1.
+ * >= 2 n_d - 1, along z where that is 512 or more the shortest length
+ * >= 2 n3 - 1 among 512, 640, 768, 800, 960, 1024, 1152, 1280, 1440, 1600, 1920,
+ * 2048, 2304, 2560, 2880, 3072, 3600 and 4096.
  */
 #ifndef VIE_H
 #define VIE_H
@@ -274,8 +276,9 @@ int vie_circulant_apply(vie_plan_t plan, const vie_c128* r, vie_c128* z);
  * candidate shapes of the product's kernels on the plan's own buffers (two
  * untimed and five timed whole products each, HIP events, in three interleaved
  * rounds of which each candidate keeps its best) and keeps the fastest:
- * pencils per workgroup of the four-step z passes, or the generic z passes
- * (circulant lengths 512 to 4096 have four-step shapes), crossed with, for
+ * pencils per workgroup of the three-stage z passes (circulant lengths from 512
+ * on), or the generic z passes (at a length that is no power of two: one pencil
+ * per workgroup), crossed with, for
  * 64 x 64 circulant cross-sections, the xy pass variant (0: full plane in LDS;
  * 1: x-frequency halves, two workgroups per CU; 2: full plane with 512 threads
  * and private exchange areas, one workgroup per CU) and, for 64 x 32 ones (the
@@ -293,8 +296,8 @@ int vie_circulant_apply(vie_plan_t plan, const vie_c128* r, vie_c128* z);
  *   *z_pencils (0 when the z passes use the generic kernels).
  * vie_set_tune: force a choice (xy_variant 0-2, ignored where the cross-section
  *   has a single xy pass); z_pencils -1 = the generic z passes, 0 = the
- *   four-step z passes with their default pencils (generic where the grid has no
- *   four-step shape), any other value must be one of the tuner's candidates
+ *   three-stage z passes with their default pencils (generic below a length of
+ *   512), any other value must be one of the tuner's candidates
  *   (VIE_EINVAL otherwise).  Synchronises the plan's stream first.
  */
 int vie_get_tune(vie_plan_t plan, int precision, int* xy_variant, int* z_pencils);

@@ -630,9 +630,9 @@ struct PassSet {
   PassDesc* d_step = nullptr;
   PassDesc* d_res = nullptr;
   std::vector<PassDesc> h_step, h_res;
-  // z-pass groups: systems sharing a four-step shape, launched together
+  // z-pass groups: systems sharing a length and a pencil count, launched together
   struct Group {
-    int A, B, P;
+    int M3, P;
     bool direct;
     std::vector<int> sys;
     int* d_zpre = nullptr;
@@ -781,25 +781,24 @@ hipError_t build_passes(vie_batch_s* B, PassSet& PS, const BatchLevel<T>& L, std
   }
   if ((e = alloc((void**)&PS.d_sd, sizeof(SDesc) * n))) return e;
   if ((e = hipMemcpy(PS.d_sd, PS.h_sd.data(), sizeof(SDesc) * n, hipMemcpyHostToDevice))) return e;
-  // z groups.  A plan's own operator keeps its tuned choice between the four-step and the
-  // generic passes; on a box the batch has pencils enough for the four-step ones, short of
-  // the FP64 shapes with 64 values per thread.  Pencils per workgroup: those that leave the
+  // z groups.  A plan's own operator keeps its tuned choice between the three-stage and
+  // the generic passes; on a box the batch has pencils enough for the three-stage ones.  Pencils per workgroup: those that leave the
   // fewest idle in the last block of a row, then the most.
   for (int s = 0; s < n; ++s) {
-    int A, Bv, Pp;
     const SysPlan& P = B->sp[s];
     const Tune& t = dbl ? P.t64 : P.t32;
-    if ((P.box ? !(dbl && P.g.M3 >= 2048) : t.z4 != 0) && z4_shape<T>(P.g.M3, &A, &Bv, &Pp)) {
-      int opts[8];
-      const int no = z4_pencil_options<T>(P.g.M3, opts, 8);
+    int opts[8];
+    const int no = z3_pencil_options<T>(P.g.M3, opts, 8);
+    if ((P.box || t.z3) && no) {
+      int Pp = opts[0];
       auto padded = [&](int q) { return (P.g.n1 + q - 1) / q * q; };
       for (int i = 0; i < no; ++i)
         if (padded(opts[i]) < padded(Pp) || (padded(opts[i]) == padded(Pp) && opts[i] > Pp)) Pp = opts[i];
       auto it = std::find_if(PS.zgroups.begin(), PS.zgroups.end(), [&](const PassSet::Group& G) {
-        return G.A == A && G.B == Bv && G.P == Pp && G.direct == P.direct;
+        return G.M3 == P.g.M3 && G.P == Pp && G.direct == P.direct;
       });
       if (it == PS.zgroups.end()) {
-        PS.zgroups.push_back(PassSet::Group{A, Bv, Pp, P.direct, {}, nullptr, 0, nullptr, nullptr});
+        PS.zgroups.push_back(PassSet::Group{P.g.M3, Pp, P.direct, {}, nullptr, 0, nullptr, nullptr});
         it = PS.zgroups.end() - 1;
       }
       it->sys.push_back(s);
@@ -893,8 +892,8 @@ hipError_t batch_matvec(vie_batch_s* B, PassSet& PS, const BatchLevel<T>& L, boo
       continue;
     }
     for (auto& G : PS.zgroups)
-      if ((e = launch_z4_batch<T>(which, residual && G.direct ? 1 : 0, residual ? G.d_res : G.d_step, G.d_zpre,
-                                  (int)G.sys.size(), G.ztotal, G.A, G.B, G.P, jx, jy, s)))
+      if ((e = launch_z3_batch<T>(which, residual && G.direct ? 1 : 0, residual ? G.d_res : G.d_step, G.d_zpre,
+                                  (int)G.sys.size(), G.ztotal, G.M3, G.P, jx, jy, s)))
         return e;
     for (int sidx : PS.zsingle) {
       const SysPlan& P = B->sp[sidx];

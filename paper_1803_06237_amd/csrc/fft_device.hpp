@@ -97,6 +97,26 @@ template <typename T, bool INV> __device__ __forceinline__ void dft8(cx<T>* v) {
   v[7] = csub(e[3], o3);
 }
 
+// 8-point DFT of v[0..3] with v[4..7] = 0 (zero padding), forward
+template <typename T>
+__device__ __forceinline__ void dft8_padded(cx<T>* v) {
+  const T r = (T)0.70710678118654752440;
+  const cx<T> r2 = rot90<false>(v[2]), r3 = rot90<false>(v[3]);
+  const cx<T> e[4] = {cadd(v[0], v[2]), cadd(v[0], r2), csub(v[0], v[2]), csub(v[0], r2)};
+  const cx<T> o[4] = {cadd(v[1], v[3]), cadd(v[1], r3), csub(v[1], v[3]), csub(v[1], r3)};
+  const cx<T> o1{(o[1].x + o[1].y) * r, (o[1].y - o[1].x) * r};
+  const cx<T> o2 = rot90<false>(o[2]);
+  const cx<T> o3{(o[3].y - o[3].x) * r, (-o[3].x - o[3].y) * r};
+  v[0] = cadd(e[0], o[0]);
+  v[4] = csub(e[0], o[0]);
+  v[1] = cadd(e[1], o1);
+  v[5] = csub(e[1], o1);
+  v[2] = cadd(e[2], o2);
+  v[6] = csub(e[2], o2);
+  v[3] = cadd(e[3], o3);
+  v[7] = csub(e[3], o3);
+}
+
 template <typename T, int R, bool INV> __device__ __forceinline__ void dft(cx<T>* v) {
   if constexpr (R == 2) dft2<T, INV>(v);
   else if constexpr (R == 4) dft4<T, INV>(v);

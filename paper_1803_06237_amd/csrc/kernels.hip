@@ -5,8 +5,9 @@
 // product is a circular convolution after embedding in a circulant of size
 // M = (M1, M2, M3) >= 2n - 1 and zero padding x.  Three passes over HBM:
 //
-//   pass 1 (k_zfwd):  per z-pencil of one component: zero-pad n3 -> M3, forward
-//                     FFT, write kz-plane-major  U[kz][c][i2][i1]
+//   pass 1 (k_zfwd, from M3 = 512 on zpass.hip):  per z-pencil of one component:
+//                     zero-pad n3 -> M3, forward FFT, write kz-plane-major
+//                     U[kz][c][i2][i1]
 //   pass 2 (k_xyp):   per kz plane: forward FFT along i1 (pad n1 -> M1) and i2
 //                     (pad n2 -> M2), 3x3 symmetric product with the Green
 //                     spectrum, inverse FFT along i2 and i1, crop to n2 x n1
@@ -35,10 +36,10 @@ hipError_t launch_xy6432(const Geom& g, int V, void* U, const void* goct, const 
 template <typename T>
 hipError_t allow_lds_xy6432();
 template <typename T>
-hipError_t launch_z4(int which, const Geom& g, int P, const void* x, void* y, const void* b, int mode, void* U,
+hipError_t launch_z3(int which, const Geom& g, int P, const void* x, void* y, const void* b, int mode, void* U,
                      const void* chi, const void* twz, hipStream_t st);
 template <typename T>
-hipError_t allow_lds_z4();
+hipError_t allow_lds_z3();
 constexpr int kMaxV = 16;   // complex values per thread per FFT stage
 
 // ------------------------------------------------------------------ pass 1
@@ -181,7 +182,9 @@ template <typename T>
 hipError_t launch_pass(int which, const Geom& g, const Tune& t, const void* x, void* y, const void* b, int mode,
                        void* U, const void* goct, const void* chi, const void* const tw[3], hipStream_t s) {
   using C = cx<T>;
-  if (which != 1 && t.z4) return launch_z4<T>(which, g, t.zp, x, y, b, mode, U, chi, tw[2], s);
+  // a length that is no power of two has no generic form: one pencil per workgroup instead
+  if (which != 1 && (t.z3 || (g.M3 & (g.M3 - 1))))
+    return launch_z3<T>(which, g, t.z3 ? t.zp : 1, x, y, b, mode, U, chi, tw[2], s);
   const int nb1 = (g.n1 + t.tp - 1) / t.tp;
   const dim3 gz(3 * g.n2 * nb1);
   const size_t zl = z_lds_bytes<T>(g, t.tp);
@@ -237,7 +240,7 @@ hipError_t allow_lds(size_t bytes) {
     return e;
   if ((e = allow_lds_xy64<T>())) return e;
   if ((e = allow_lds_xy6432<T>())) return e;
-  if ((e = allow_lds_z4<T>())) return e;
+  if ((e = allow_lds_z3<T>())) return e;
   return hipFuncSetAttribute((const void*)k_xyp<T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 template hipError_t allow_lds<double>(size_t);
@@ -326,6 +329,8 @@ __global__ void k_octant(const double2* __restrict__ F, double2* __restrict__ g6
 
 static hipError_t fft_axis(double2* F, const Geom& g, int axis, const double2* tw, hipStream_t s) {
   const long M1 = g.M1, M2 = g.M2, M3 = g.M3;
+  int r[3];
+  if (axis == 2 && z3_radices(g.M3, r)) return launch_z3_lines(g.M3, M1 * M2, F, tw, s);
   int Llog2, L;
   long es, inner_cnt, inner_stride, outer, nlines;
   if (axis == 2) {

@@ -1,5 +1,5 @@
 // Host check of the pass kernels' workgroup-to-work maps (block_maps.hpp) over
-// every shape the library accepts: n1, n2 <= 32, circulant lengths M3 = 2^k <=
+// every shape the library accepts: n1, n2 <= 32, every circulant length M3 <=
 // 4096, both precisions, every pencil count the launchers and the tuner use.
 // Each map must be a bijection onto the work items of its launch, and every
 // write a kernel derives from its item must land inside the buffer it writes.
@@ -223,26 +223,32 @@ int pow2_at_least(int v) {
   return m;
 }
 
+// the library's circulant length along z
+int circulant_length(int n3) {
+  const int m = pow2_at_least(2 * n3 - 1);
+  return m >= 512 ? vie::z3_length(2 * n3 - 1) : m;
+}
+
 bool run_all(Checker& ck) {
   if (!check_xy6432(ck, [](int c, int y, int kx) { return vie::xy32_hand(c, y, kx); })) return false;
-  for (int M3 = 1; M3 <= 4096; M3 <<= 1)
-    if (!check_planes(ck, M3)) return false;
+  for (int n3 = 1; n3 <= 2048; ++n3)
+    if (!check_planes(ck, circulant_length(n3))) return false;
   for (int n1 = 1; n1 <= 32; ++n1)
     for (int n2 = 1; n2 <= 32; ++n2) {
       // generic z passes: P = tp in {1, 2, 4, 8, 16}
       for (int tp = 1; tp <= 16; tp <<= 1)
         if (!check_pencil_map(ck, n1, n2, tp, [](int b, int nb) { return vie::xcd_group8(b, nb); }, "generic z"))
           return false;
-      // four-step z passes: every pencil count of each precision
-      for (int M3 = 512; M3 <= 4096; M3 <<= 1) {
+      // three-stage z passes: every pencil count of each precision
+      for (int M3 = 512; M3 <= 4096; M3 = M3 == 4096 ? 4097 : vie::z3_length(M3 + 1)) {
         for (int vb : {8, 16}) {
           int opts[8];
-          const int n = vb == 16 ? vie::z4_pencil_options<double>(M3, opts, 8)
-                                 : vie::z4_pencil_options<float>(M3, opts, 8);
+          const int n = vb == 16 ? vie::z3_pencil_options<double>(M3, opts, 8)
+                                 : vie::z3_pencil_options<float>(M3, opts, 8);
           for (int i = 0; i < n; ++i) {
             const int P = opts[i];
             if (!check_pencil_map(ck, n1, n2, P,
-                                  [P, vb](int b, int nb) { return vie::xcd_group(b, nb, P, vb); }, "four-step z"))
+                                  [P, vb](int b, int nb) { return vie::xcd_group(b, nb, P, vb); }, "three-stage z"))
               return false;
           }
         }
@@ -250,8 +256,8 @@ bool run_all(Checker& ck) {
     }
   // write extents for every n3 <= 2048 at its circulant length, a few n1, n2
   for (int n3 = 1; n3 <= 2048; ++n3) {
-    const int M3 = pow2_at_least(2 * n3 - 1);
-    if (M3 > 1 && 2 * n3 > M3) return ck.fail("n3 above half its circulant length (four-step padding)");
+    const int M3 = circulant_length(n3);
+    if (M3 > 1 && 2 * n3 > M3) return ck.fail("n3 above half its circulant length (padding)");
     for (int n1 : {1, 7, 20, 32})
       for (int n2 : {1, 9, 32})
         for (int P : {1, 2, 4, 8, 16})

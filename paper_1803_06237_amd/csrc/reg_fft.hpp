@@ -31,26 +31,6 @@ __device__ __forceinline__ int rcol(int c0, int a, int k, int kx) {
   return rhand<LX, LY>(c0 + (k & 1), (k >> 1) * LY + ((a + k * LY / 8) & (LY - 1)), kx);
 }
 
-// 8-point DFT of v[0..3] with v[4..7] = 0 (the zero padding)
-template <typename T>
-__device__ __forceinline__ void dft8_padded(cx<T>* v) {
-  const T r = (T)0.70710678118654752440;
-  const cx<T> r2 = rot90<false>(v[2]), r3 = rot90<false>(v[3]);
-  const cx<T> e[4] = {cadd(v[0], v[2]), cadd(v[0], r2), csub(v[0], v[2]), csub(v[0], r2)};
-  const cx<T> o[4] = {cadd(v[1], v[3]), cadd(v[1], r3), csub(v[1], v[3]), csub(v[1], r3)};
-  const cx<T> o1{(o[1].x + o[1].y) * r, (o[1].y - o[1].x) * r};
-  const cx<T> o2 = rot90<false>(o[2]);
-  const cx<T> o3{(o[3].y - o[3].x) * r, (-o[3].x - o[3].y) * r};
-  v[0] = cadd(e[0], o[0]);
-  v[4] = csub(e[0], o[0]);
-  v[1] = cadd(e[1], o1);
-  v[5] = csub(e[1], o1);
-  v[2] = cadd(e[2], o2);
-  v[6] = csub(e[2], o2);
-  v[3] = cadd(e[3], o3);
-  v[7] = csub(e[3], o3);
-}
-
 // 8 / L transforms of L points on v[0..L), v[L..2 L), ...
 template <typename T, bool INV, int L>
 __device__ __forceinline__ void dft_tail(cx<T>* v) {

@@ -22,6 +22,7 @@
 #include <vector>
 
 #include "krylov.hpp"
+#include "block_maps.hpp"
 #include "vie_internal.hpp"
 
 namespace vie {
@@ -249,12 +250,15 @@ int ilog2(int v) {
   return l;
 }
 
-// circulant lengths: the power of two >= 2 n - 1
+// circulant lengths: the power of two >= 2 n - 1, along z from 512 on the shortest of the
+// three-stage passes' lengths (every pass's work and the intermediate are proportional to it:
+// FP64 30 x 12 x 1377 takes 206 us at 4096 and 158 us at 2880)
 Geom make_geom(const int n[3]) {
   Geom g{};
   int M[3];
   for (int d = 0; d < 3; ++d)
     for (M[d] = 1; M[d] < 2 * n[d] - 1;) M[d] <<= 1;
+  if (M[2] >= 512) M[2] = z3_length(2 * n[2] - 1);
   g.n1 = n[0];
   g.n2 = n[1];
   g.n3 = n[2];
@@ -298,15 +302,15 @@ bool pick_tune(const Geom& g, size_t budget, size_t zbudget, Tune* t) {
   if (xt < 512) xt = 512;
   if (xt > 1024) return false;
   t->xythreads = xt;
-  const size_t z4 = z4_lds_bytes<T>(g.M3);
-  t->z4 = (z4 > 0 && z4 <= budget) ? 1 : 0;
+  int opts[8];
+  t->z3 = z3_pencil_options<T>(g.M3, opts, 8) > 0 && z3_lds_bytes(g.M3, opts[0]) <= budget ? 1 : 0;
   t->xyv = sizeof(T) == 8 ? 1 : 0;
   t->zp = 0;
   return true;
 }
 
 // ---- plan-time tuning of launch shapes ----------------------------------------
-// Candidates: the four-step z passes' pencils per workgroup (the forward and the
+// Candidates: the three-stage z passes' pencils per workgroup (the forward and the
 // inverse pass share the choice) and the 64 x 64 xy pass variant.  Each candidate
 // runs two untimed and five timed whole products (all three passes) between HIP
 // events; the fastest wins.  Results are kept per (device, grid, precision) for
@@ -333,7 +337,7 @@ hipError_t time_passes(const Geom& g, const Tune& t, int w0, int w1, const void*
   return e;
 }
 
-// Persistent tuner cache: one line "arch n1 n2 n3 value_bytes z4 zp xyv" per tuned
+// Persistent tuner cache: one line "arch n1 n2 n3 value_bytes z3 zp xyv" per tuned
 // shape, in the file named by VIE_TUNE_CACHE (empty: no file), by default
 // $XDG_CACHE_HOME/vie-mi355x/tune.txt or $HOME/.cache/vie-mi355x/tune.txt.  A
 // process reads it before timing candidates and appends what it tunes; the last
@@ -361,12 +365,12 @@ bool tune_cache_lookup(const std::string& arch, const Geom& g, int vb, Tune* t) 
   FILE* f = std::fopen(path.c_str(), "r");
   if (!f) return false;
   char a[128];
-  int n1, n2, n3, b, z4, zp, xyv;
+  int n1, n2, n3, b, z3, zp, xyv;
   bool found = false;
   Tune best = *t;
-  while (std::fscanf(f, "%127s %d %d %d %d %d %d %d", a, &n1, &n2, &n3, &b, &z4, &zp, &xyv) == 8) {
+  while (std::fscanf(f, "%127s %d %d %d %d %d %d %d", a, &n1, &n2, &n3, &b, &z3, &zp, &xyv) == 8) {
     if (arch == a && n1 == g.n1 && n2 == g.n2 && n3 == g.n3 && b == vb) {
-      best.z4 = z4;
+      best.z3 = z3;
       best.zp = zp;
       best.xyv = xyv;
       found = true;
@@ -376,9 +380,9 @@ bool tune_cache_lookup(const std::string& arch, const Geom& g, int vb, Tune* t) 
   // only shapes this build can launch
   if (found) {
     int opts[8];
-    const int n = vb == 16 ? z4_pencil_options<double>(g.M3, opts, 8) : z4_pencil_options<float>(g.M3, opts, 8);
-    bool ok = best.xyv >= 0 && best.xyv <= 2 && (best.z4 == 0 || best.z4 == 1) && (t->z4 || !best.z4);
-    if (best.z4) {
+    const int n = vb == 16 ? z3_pencil_options<double>(g.M3, opts, 8) : z3_pencil_options<float>(g.M3, opts, 8);
+    bool ok = best.xyv >= 0 && best.xyv <= 2 && (best.z3 == 0 || best.z3 == 1) && (t->z3 || !best.z3);
+    if (best.z3) {
       bool hit = false;
       for (int i = 0; i < n; ++i) hit = hit || opts[i] == best.zp;
       ok = ok && hit;
@@ -400,7 +404,7 @@ void tune_cache_store(const std::string& arch, const Geom& g, int vb, const Tune
   }
   char line[256];
   const int len = std::snprintf(line, sizeof line, "%s %d %d %d %d %d %d %d\n", arch.c_str(), g.n1, g.n2, g.n3, vb,
-                                t.z4, t.zp, t.xyv);
+                                t.z3, t.zp, t.xyv);
   const int fd = ::open(path.c_str(), O_WRONLY | O_CREAT | O_APPEND, 0644);
   if (fd < 0) return;
   (void)!::write(fd, line, (size_t)len);
@@ -420,7 +424,7 @@ hipError_t autotune(const Geom& g, int device, Tune* t, void* U, const void* goc
     }
   }
   // the suffix names the candidate set: lines written for an older set are not read
-  const std::string arch = device_arch(device) + "/xy6432";
+  const std::string arch = device_arch(device) + "/z3";
   if (tune_cache_lookup(arch, g, (int)sizeof(cx<T>), t)) {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     g_tune_cache[key] = *t;
@@ -436,8 +440,8 @@ hipError_t autotune(const Geom& g, int device, Tune* t, void* U, const void* goc
   // round: single rounds let launch noise decide between shapes within 1 % of
   // each other, and the choice then changed from one process to the next.
   constexpr int kRounds = 3;
-  // Candidates: the four-step pencil counts and the generic LDS z passes (the
-  // 64-value shapes of long pencils run at low occupancy in FP64), crossed with
+  // Candidates: the three-stage pencil counts and the generic LDS z passes (one pencil
+  // per workgroup where the length is no power of two), crossed with
   // the xy variants of 64 x 64 planes.  They are timed jointly, as whole
   // back-to-back products: the z pass's write pattern decides what the xy pass
   // finds in L2 and the Infinity Cache, so a pass timed alone, or with events
@@ -447,16 +451,16 @@ hipError_t autotune(const Geom& g, int device, Tune* t, void* U, const void* goc
   std::vector<Tune> cand;
   {
     std::vector<Tune> zc;
-    if (t->z4) {
+    if (t->z3) {
       int opts[8];
-      const int n = z4_pencil_options<T>(g.M3, opts, 8);
+      const int n = z3_pencil_options<T>(g.M3, opts, 8);
       for (int i = 0; i < n; ++i) {
         Tune c = *t;
         c.zp = opts[i];
         zc.push_back(c);
       }
       Tune c = *t;
-      c.z4 = 0;
+      c.z3 = 0;
       c.zp = 0;
       zc.push_back(c);
     } else {
@@ -494,16 +498,25 @@ hipError_t autotune(const Geom& g, int device, Tune* t, void* U, const void* goc
   return e;
 }
 
+// W_M^k, k < M; z: followed by the three-stage passes' tables (z_twiddles)
 template <typename T>
-hipError_t make_twiddles(int M, cx<T>** out) {
-  std::vector<cx<T>> h(M);
+hipError_t make_twiddles(int M, cx<T>** out, bool z = false) {
+  std::vector<cx<T>> h(z ? z_twiddles(M) : M);
   for (int k = 0; k < M; ++k) {
     long double a = -2.0L * 3.14159265358979323846264338327950288L * k / M;
     h[k] = cx<T>{(T)std::cos(a), (T)std::sin(a)};
   }
-  hipError_t e = dmalloc(out, sizeof(cx<T>) * M);
+  int r[3];
+  if (z && z3_radices(M, r)) {
+    const int N1 = r[1] * r[2];
+    for (int k = 0; k < r[0]; ++k)
+      for (int t = 0; t < N1; ++t) h[M + k * N1 + t] = h[k * t % M];
+    for (int k = 0; k < r[1]; ++k)
+      for (int u = 0; u < r[2]; ++u) h[2 * M + k * r[2] + u] = h[r[0] * u * k % M];
+  }
+  hipError_t e = dmalloc(out, sizeof(cx<T>) * h.size());
   if (e) return e;
-  return hipMemcpy(*out, h.data(), sizeof(cx<T>) * M, hipMemcpyHostToDevice);
+  return hipMemcpy(*out, h.data(), sizeof(cx<T>) * h.size(), hipMemcpyHostToDevice);
 }
 
 // ---- operator wrappers used by the solvers ---------------------------------
@@ -540,23 +553,18 @@ void box_release(vie_plan_s* p) {
 }
 
 // Launch shapes of the box, by rule (its first solve does not wait for timing): the
-// four-step z passes with the most pencils per workgroup that still leave two workgroups per
-// CU in FP64, one per two CUs in FP32, else the generic ones; in FP64 those also from 2048
-// points on, where the four-step shapes hold 64 values per thread.  (20 x 9 x 512, 540
-// pencils: FP64 generic, FP32 four pencils per workgroup, as the tuner finds.)
+// three-stage z passes with the most pencils per workgroup that still leave one workgroup per
+// CU, else with the fewest.
 template <typename T>
 bool box_tune(const Geom& g, size_t budget, Tune* t) {
   if (!pick_tune<T>(g, budget, std::min<size_t>(budget, 65536), t)) return false;
   t->xyv = 2;
-  if (!t->z4) return true;
+  if (!t->z3) return true;
   int opts[8];
-  const int n = z4_pencil_options<T>(g.M3, opts, 8);
-  t->zp = 0;
-  for (int i = 0; i < n; ++i) {
-    const int wgs = 3 * g.n2 * ((g.n1 + opts[i] - 1) / opts[i]);
-    if (wgs >= (sizeof(T) == 8 ? 512 : 128) && opts[i] > t->zp) t->zp = opts[i];
-  }
-  if (t->zp == 0 || (sizeof(T) == 8 && g.M3 >= 2048)) t->z4 = t->zp = 0;
+  const int n = z3_pencil_options<T>(g.M3, opts, 8);
+  t->zp = *std::min_element(opts, opts + n);
+  for (int i = 0; i < n; ++i)
+    if (pencil_blocks(g.n1, g.n2, opts[i]) >= 256 && opts[i] > t->zp) t->zp = opts[i];
   return true;
 }
 
@@ -1040,8 +1048,8 @@ int vie_plan(vie_plan_t* out, const int grid[3], double h, double k0, double eps
     }                                                   \
   } while (0)
   for (int d = 0; d < 3; ++d) {
-    PLANTRY(make_twiddles<double>(Ms[d], &p->tw64[d]));
-    PLANTRY(make_twiddles<float>(Ms[d], &p->tw32[d]));
+    PLANTRY(make_twiddles<double>(Ms[d], &p->tw64[d], d == 2));
+    PLANTRY(make_twiddles<float>(Ms[d], &p->tw32[d], d == 2));
   }
   PLANTRY(dmalloc(&p->goct64, sizeof(double2) * 6 * H));
   if (f32) PLANTRY(dmalloc(&p->goct32, sizeof(float2) * 6 * H));
@@ -1603,10 +1611,10 @@ int vie_get_tune(vie_plan_t p, int precision, int* xy_variant, int* z_pencils) {
   if (precision != 0 && precision != 1) return fail(p, VIE_EINVAL, "precision must be 0 or 1");
   const Tune& t = precision == 0 ? p->t64 : p->t32;
   int opts[8];
-  const int n = precision == 0 ? z4_pencil_options<double>(p->g.M3, opts, 8)
-                               : z4_pencil_options<float>(p->g.M3, opts, 8);
+  const int n = precision == 0 ? z3_pencil_options<double>(p->g.M3, opts, 8)
+                               : z3_pencil_options<float>(p->g.M3, opts, 8);
   if (xy_variant) *xy_variant = xy_variants(p->g) > 1 ? t.xyv : -1;
-  if (z_pencils) *z_pencils = t.z4 && n ? (t.zp ? t.zp : opts[0]) : 0;
+  if (z_pencils) *z_pencils = t.z3 && n ? (t.zp ? t.zp : opts[0]) : 0;
   return VIE_OK;
 }
 
@@ -1615,8 +1623,8 @@ int vie_set_tune(vie_plan_t p, int precision, int xy_variant, int z_pencils) {
   if (precision != 0 && precision != 1) return fail(p, VIE_EINVAL, "precision must be 0 or 1");
   if (xy_variant < 0 || xy_variant > 2) return fail(p, VIE_EINVAL, "xy_variant must be 0, 1 or 2");
   int opts[8];
-  const int n = precision == 0 ? z4_pencil_options<double>(p->g.M3, opts, 8)
-                               : z4_pencil_options<float>(p->g.M3, opts, 8);
+  const int n = precision == 0 ? z3_pencil_options<double>(p->g.M3, opts, 8)
+                               : z3_pencil_options<float>(p->g.M3, opts, 8);
   Tune& t = precision == 0 ? p->t64 : p->t32;
   if (z_pencils > 0) {
     bool ok = false;
@@ -1627,7 +1635,7 @@ int vie_set_tune(vie_plan_t p, int precision, int xy_variant, int z_pencils) {
   }
   HIPTRY(p, hipStreamSynchronize(p->stream));
   t.xyv = xy_variant;
-  t.z4 = (z_pencils >= 0 && n > 0) ? 1 : 0;
+  t.z3 = (z_pencils >= 0 && n > 0) ? 1 : 0;
   t.zp = z_pencils > 0 ? z_pencils : 0;
   return VIE_OK;
 }

@@ -17,8 +17,8 @@ int curl_table(const int n[3], double kappa, std::complex<double>* out, int nthr
 // Geometry and launch shapes of one operator, passed to the kernel launchers.
 struct Geom {
   int n1, n2, n3;           // voxel grid
-  int M1, M2, M3;           // circulant sizes (powers of two)
-  int L1, L2, L3;           // log2 of M
+  int M1, M2, M3;           // circulant sizes: powers of two, M3 from 512 on a length of the z3 passes
+  int L1, L2, L3;           // log2 of M (where it is a power of two)
   int H1, H2, H3;           // octant extents M/2 + 1
   long N;                   // voxels
 };
@@ -28,23 +28,32 @@ struct Tune {
   int zthreads;  // threads per workgroup in the z passes
   int cc;        // column chunk in the xy pass
   int xythreads; // threads per workgroup in the xy pass
-  int z4;        // 1: z passes use the register four-step kernels
+  int z3;        // 1: z passes use the three-stage register kernels
   int xyv;       // xy pass variant; 64 x 64: 0 full plane, 1 x-frequency halves, 2 wide;
                  // 64 x 32: 0 generic padded LDS pass, 1 and 2 register transforms
                  // (1: column exchange areas of their own, 2: exchange in the hand-off)
-  int zp;        // pencils per workgroup in the four-step z passes (0: the default for M3)
+  int zp;        // pencils per workgroup in the three-stage z passes (0: the default for M3)
 };
 
 // Number of xy pass variants of a cross-section: 3 for 64 x 64 and 64 x 32, else 1.
 inline int xy_variants(const Geom& g) { return g.M1 == 64 && (g.M2 == 64 || g.M2 == 32) ? 3 : 1; }
 
-// Candidate pencil counts of the four-step z passes for M3 (empty when none exist);
-// the first is the default.
+// Three-stage z passes (zpass.hip).  Candidate pencil counts for M3 (empty when M3 is not
+// one of their lengths), the first is the default; their shortest length >= need (0: none);
+// the radices of a length; LDS of P pencils.
 template <typename T>
-int z4_pencil_options(int M3, int* out, int cap);
-
-template <typename T>
-size_t z4_lds_bytes(int M3, int P = 0);   // 0 when no four-step instance exists for M3
+int z3_pencil_options(int M3, int* out, int cap);
+int z3_length(int need);
+bool z3_radices(int M3, int r[3]);
+size_t z3_lds_bytes(int M3, int P);
+// in-place FFT of contiguous lines of M3 values
+hipError_t launch_z3_lines(int M3, long lines, double2* F, const double2* twz, hipStream_t st);
+// Entries of the z twiddle table: W_M3^k, k < M3, and for the three-stage lengths
+// M3 = R1 R2 R3 also W_M3^(t k1) at M3 + R2 R3 k1 + t and W_(R2 R3)^(u k2) at 2 M3 + R3 k2 + u.
+inline size_t z_twiddles(int M3) {
+  int r[3];
+  return z3_radices(M3, r) ? 2 * (size_t)M3 + r[1] * r[2] : M3;
+}
 
 // ---- matvec passes (kernels.hip) ----------------------------------------
 // mode for the inverse z pass: 0 -> y = x - chi u ; 1 -> y = b - (x - chi u)
@@ -112,7 +121,7 @@ struct PassDesc {
   void* U;
   const void* goct;
   const void* chi;
-  const void* twz;      // z twiddles, length M3
+  const void* twz;      // z twiddles, z_twiddles(M3) values
   const void* twx;      // x twiddles, length M1
   const void* twy;      // y twiddles, length M2
   int P;                // pencils per workgroup in the z passes
@@ -122,16 +131,14 @@ struct PassDesc {
 // Batched z passes (which: 0 forward, 2 inverse + contrast; mode 1: residual) and
 // cross-section passes.  items: prefix[s] = first item of system s (z passes: pencil blocks;
 // 64 x 64: plane pairs; the others: groups of xyr_planes_per_group planes), prefix[nsys] =
-// total.  All systems of a launch share (A, B) or the circulant cross-section.
+// total.  All systems of a launch share (M3, P) or the circulant cross-section.
 template <typename T>
-hipError_t launch_z4_batch(int which, int mode, const PassDesc* d, const int* prefix, int nsys, int total, int A,
-                           int B, int P, int jx, int jy, hipStream_t st);
+hipError_t launch_z3_batch(int which, int mode, const PassDesc* d, const int* prefix, int nsys, int total, int M3,
+                           int P, int jx, int jy, hipStream_t st);
 template <typename T>
 hipError_t launch_xy64_batch(const PassDesc* d, const int* prefix, int nsys, int total, hipStream_t s);
 template <typename T>
 hipError_t launch_xyr_batch(int M1, int M2, const PassDesc* d, const int* prefix, int nsys, int total, hipStream_t s);
-template <typename T>
-bool z4_shape(int M3, int* A, int* B, int* P);
 
 // ---- Krylov building blocks (krylov.hip) -----------------------------------
 template <typename T>

@@ -1,343 +1,257 @@
 // Passes 1 and 3 of the matvec (zero-padded z FFT / inverse z FFT with crop and
-// contrast) as four-step transforms held in registers.
+// contrast) as three-stage transforms held in registers, for circulant lengths
+// M3 >= 512.
 //
-// Length M3 = A * B.  Each pencil is handled by A threads.  Thread a holds
-// x[a + A b] (b < B), takes a B-point DFT over b in registers, multiplies by
-// W_M3^(a k1), and one LDS exchange hands the values of frequency k1 of all A
-// threads to the thread that owns task k1 (tasks k1 = a + A t, t < B / A),
-// which finishes with an A-point DFT: X[k1 + B k2], k2 < A.  The inverse is the
-// same with conjugate twiddles.  The zero padding (x[n] = 0 for n >= n3) and
-// the crop (only n < n3 kept) come for free from the index ranges.
+// M3 = R1 R2 R3 with radices of 8 to 16 (z3_radices).  With n = u + R3 s + R2 R3 j
+// and k = k1 + R1 k2 + R1 R2 k3 (u, k3 < R3; s, k2 < R2; j, k1 < R1):
+//   A: per t = u + R3 s: R1 points over j, times W_M3^(t k1);
+//   B: per (u, k1): R2 points over s, times W_(R2 R3)^(u k2);
+//   C: per q = k1 + R1 k2: R3 points over u, giving X[q + R1 R2 k3].
+// The inverse runs C, B, A with conjugate twiddles.  The zero padding (x[n] = 0 for
+// n >= n3) and the crop (only n < n3 kept) are half of A's R1 values.
 //
-// A block handles P pencils of consecutive i1 at fixed (component, i2), so the
-// kz-plane-major intermediate U[kz][c][i2][i1] is written and read in runs of P
-// elements through an LDS staging array [kz][P + 1] (padded against bank
-// conflicts); the z-contiguous vectors x, y, chi are accessed directly.
+// A workgroup handles P pencils of consecutive i1 at fixed (component, i2), one
+// task of each stage per thread.  A's threads run along z, the contiguous axis of
+// x, y and chi; C's run over the pencils first, so that the kz-plane-major
+// intermediate U[kz][c][i2][i1] is read and written in runs of P elements straight
+// from and to registers.  Between the stages the values pass through LDS, in 8-byte
+// elements (FP64: real parts, then imaginary parts; FP32: whole values), with row
+// pitches that spread the 32 lanes of an access over the banks (Z3Map).
 //
-// The exchange moves the real parts, then the imaginary parts, and the staging
-// array holds one half of the kz range at a time.  That halves the LDS of a
-// pencil (8 KiB at M3 = 1024 in FP64), so a CU holds twice as many pencils: at
-// 32 x 32 x 512 every pencil of a pass is resident at once instead of in one
-// and a half rounds of workgroups.
+// Bound by memory latency and HBM; 16 values per thread keep FP64 within 128
+// registers, four waves per SIMD.  Against the two-stage form it replaces, which held
+// 32 values per thread at M3 = 1024 and 64 at 2048 and 4096 (one wave per SIMD in FP64)
+// and staged U through LDS a third time, and against the generic LDS passes, the better
+// of them for long FP64 pencils, forward + inverse in us: FP64 30 x 12 pencils of 4096
+// 131 -> 85, 32 x 32 of 4096 422 -> 227 (floor at the copy rate 64 + 92), of 1024
+// 52 -> 50; FP32 67 -> 57, 129 -> 105, 36 -> 31.
 #include <hip/hip_runtime.h>
 
 #include "block_maps.hpp"
-#include "dft_reg.hpp"
+#include "dft_codelets.hpp"
 #include "vie_internal.hpp"
 
 namespace vie {
 
 namespace {
-// exchange slot of (pencil p, frequency k1, source thread a): rotated so that
-// the A reads of one thread and the A writes of one frequency hit distinct banks
-template <int A>
-__device__ __forceinline__ int xslot(int p, int M, int k1, int a) {
-  return p * M + k1 * A + ((a + k1) & (A - 1));
-}
-// Pencils exchange real and imaginary parts separately and stage half of the
-// kz range at a time (both precisions: it halves the LDS of a workgroup, so
-// twice as many are resident; FP32 forward pass 21.4 -> 15.6 us at 32x32x512)
-template <typename T>
-constexpr bool z4_split() {
-  return true;
-}
 
-// Thread a of pencil p hands v[k1] to the owner of frequency k1; afterwards
-// w[t A + j] holds frequency a + A t of thread j (t < B / A).  S must be free on
-// entry; the caller synchronises before reusing it.
-template <typename T, int A, int B>
-__device__ __forceinline__ void z4_exchange(const cx<T>* v, cx<T>* w, cx<T>* S, int p, int a, bool on) {
-  constexpr int M = A * B;
-  if constexpr (z4_split<T>()) {
-    T* Sd = reinterpret_cast<T*>(S);
-    if (on) {
-#pragma unroll
-      for (int k1 = 0; k1 < B; ++k1) Sd[xslot<A>(p, M, k1, a)] = v[k1].x;
-    }
-    __syncthreads();
-    if (on) {
-#pragma unroll
-      for (int t = 0; t < B / A; ++t)
-#pragma unroll
-        for (int j = 0; j < A; ++j) w[t * A + j].x = Sd[xslot<A>(p, M, a + A * t, j)];
-    }
-    __syncthreads();
-    if (on) {
-#pragma unroll
-      for (int k1 = 0; k1 < B; ++k1) Sd[xslot<A>(p, M, k1, a)] = v[k1].y;
-    }
-    __syncthreads();
-    if (on) {
-#pragma unroll
-      for (int t = 0; t < B / A; ++t)
-#pragma unroll
-        for (int j = 0; j < A; ++j) w[t * A + j].y = Sd[xslot<A>(p, M, a + A * t, j)];
-    }
-  } else {
-    if (on) {
-#pragma unroll
-      for (int k1 = 0; k1 < B; ++k1) S[xslot<A>(p, M, k1, a)] = v[k1];
-    }
-    __syncthreads();
-    if (on) {
-#pragma unroll
-      for (int t = 0; t < B / A; ++t)
-#pragma unroll
-        for (int j = 0; j < A; ++j) w[t * A + j] = S[xslot<A>(p, M, a + A * t, j)];
-    }
-  }
-}
-}  // namespace
+template <typename T> struct Z3Elem { using type = cx<T>; };
+template <> struct Z3Elem<double> { using type = double; };
 
-// LDS of a workgroup of P pencils of length M
-template <typename T>
-size_t z4_lds_for(int M, int P) {
-  return (size_t)(z4_split<T>() ? M / 2 : M) * (P + 1) * sizeof(cx<T>);
-}
+// LDS element of (pencil p, ...): between A and B at row(k1) + t, between B and C at
+// u * Qp + q.  Pitches modulo 32 elements: consecutive lanes (u, k1) of B read rows k1
+// as one run of R3 k1 + u, and write q = k1 + ... in steps of 32 / R3 per u; pencils
+// follow 32 / P apart for the (p, q) lanes of C.
+template <int R1, int R2, int R3>
+struct Z3Map {
+  static constexpr int M = R1 * R2 * R3, N1 = R2 * R3, TB = R1 * R3, Q = R1 * R2;
+  static constexpr int TM = N1 > TB ? (N1 > Q ? N1 : Q) : (TB > Q ? TB : Q);   // threads of a pencil
+  static constexpr int mod_up(int v, int r) { return v + ((r - v) % 32 + 32) % 32; }   // least >= v, = r mod 32
+  static constexpr int N1p = mod_up(N1, R3), Qp = mod_up(Q, (32 + R3 / 2) / R3);
+  static constexpr int S = R1 * N1p > R3 * Qp ? R1 * N1p : R3 * Qp;
+  __host__ __device__ static constexpr int pencil(int P) { return mod_up(S, 32 / P); }
+};
 
-template <typename T, int A, int B>
-__device__ __forceinline__ void zfwd4_body(gptr<const cx<T>> __restrict__ x, gptr<cx<T>> __restrict__ U,
-                                           const Geom& g, int P, gptr<const cx<T>> __restrict__ tw, int blk,
-                                           cx<T>* S, int tid) {
-  constexpr int M = A * B;
-  const PencilBlock pb = pencil_block(blk, g.n1, g.n2, P);
-  const int i2 = pb.i2, c = pb.c, i1_0 = pb.i1_0, np = pb.np;
-  const int p = tid / A, a = tid % A;
-  const int ld = P + 1;
-  cx<T> v[B];
-  if (p < np) {
-    gptr<const cx<T>> src = x + (((long)c * g.n1 + i1_0 + p) * g.n2 + i2) * g.n3;
+// v[k] of this thread to slot wa(k), k < NW; then w[j] from slot ra(j), j < NR.  S is
+// free on entry; the caller synchronises before reusing it.
+template <int NW, int NR, typename WA, typename RA>
+__device__ __forceinline__ void z3_exchange(const double2* v, double2* w, double* S, bool won, bool ron, WA wa,
+                                            RA ra) {
+  if (won) {
 #pragma unroll
-    for (int b = 0; b < B; ++b) {
-      const int n = a + A * b;
-      v[b] = cx<T>{(T)0, (T)0};
-      if (b < B / 2 && n < g.n3) v[b] = src[n];   // n >= M/2 >= n3 is padding
-    }
-    dft_reg<T, false, B>(v);
-#pragma unroll
-    for (int k1 = 1; k1 < B; ++k1) v[k1] = cmul(v[k1], tw[a * k1]);
-  }
-  cx<T> w[B];
-  z4_exchange<T, A, B>(v, w, S, p, a, p < np);
-  if (p < np) {
-#pragma unroll
-    for (int t = 0; t < B / A; ++t) dft_reg<T, false, A>(w + t * A);
+    for (int k = 0; k < NW; ++k) S[wa(k)] = v[k].x;
   }
   __syncthreads();
-  // w[t A + k2] is X[kz] at kz = a + A t + B k2; staged H kz-ranges of M / H
-  constexpr int H = z4_split<T>() ? 2 : 1;
-  const long plane = 3L * g.n1 * g.n2;
-  gptr<cx<T>> dst = U + ((long)c * g.n2 + i2) * g.n1 + i1_0;
+  if (ron) {
 #pragma unroll
-  for (int h = 0; h < H; ++h) {
-    if (p < np) {
+    for (int j = 0; j < NR; ++j) w[j].x = S[ra(j)];
+  }
+  __syncthreads();
+  if (won) {
 #pragma unroll
-      for (int t = 0; t < B / A; ++t)
+    for (int k = 0; k < NW; ++k) S[wa(k)] = v[k].y;
+  }
+  __syncthreads();
+  if (ron) {
 #pragma unroll
-        for (int k2 = 0; k2 < A / H; ++k2) S[(a + A * t + B * k2) * ld + p] = w[t * A + h * (A / H) + k2];
-    }
-    __syncthreads();
-    gptr<cx<T>> dh = dst + (long)h * (M / H) * plane;
-    if (np == P) {
-      // full block: thread t owns pencil t % P at planes t / P + A k, k < B / H;
-      // eight values in flight per batch, no divisions
-      const int pp = tid % P, kz0 = tid / P;
+    for (int j = 0; j < NR; ++j) w[j].y = S[ra(j)];
+  }
+}
+template <int NW, int NR, typename WA, typename RA>
+__device__ __forceinline__ void z3_exchange(const float2* v, float2* w, float2* S, bool won, bool ron, WA wa, RA ra) {
+  if (won) {
 #pragma unroll
-      for (int k0 = 0; k0 < B / H; k0 += 8) {
-        cx<T> tmp[8];
+    for (int k = 0; k < NW; ++k) S[wa(k)] = v[k];
+  }
+  __syncthreads();
+  if (ron) {
 #pragma unroll
-        for (int k = 0; k < 8; ++k) tmp[k] = S[(kz0 + A * (k0 + k)) * ld + pp];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) dh[(long)(kz0 + A * (k0 + k)) * plane + pp] = tmp[k];
-      }
-    } else {
-      for (int t = tid; t < np * (M / H); t += blockDim.x) {
-        const int pp = t % np, kz = t / np;
-        dh[kz * plane + pp] = S[kz * ld + pp];
-      }
-    }
-    __syncthreads();
+    for (int j = 0; j < NR; ++j) w[j] = S[ra(j)];
   }
 }
 
-template <typename T, int A, int B>
-__global__ __launch_bounds__(256) void k_zfwd4(const cx<T>* __restrict__ x, cx<T>* __restrict__ U, Geom g,
-                                                int P, const cx<T>* __restrict__ tw) {
-  extern __shared__ unsigned char smem_raw[];
-  zfwd4_body<T, A, B>((gptr<const cx<T>>)x, (gptr<cx<T>>)U, g, P, (gptr<const cx<T>>)tw,
-                      xcd_group(blockIdx.x, gridDim.x, P, (int)sizeof(cx<T>)), reinterpret_cast<cx<T>*>(smem_raw), threadIdx.x);
+// Forward stages from A's inputs v[0, R1) (LINE: all of them, else the lower half) of
+// the tasks (p, t) to C's outputs z[k3] of the tasks (p3, q).  tw: the plan's tables,
+// W_M3 in natural order, W_M3^(t k1) at M3 + N1 k1 + t, W_(R2 R3)^(u k2) at
+// 2 M3 + R3 k2 + u.
+template <typename T, int R1, int R2, int R3, bool LINE>
+__device__ __forceinline__ void z3_forward(cx<T>* v, cx<T>* z, int np, int P, gptr<const cx<T>> tw,
+                                           typename Z3Elem<T>::type* S, int tid) {
+  using L = Z3Map<R1, R2, R3>;
+  const int PS = L::pencil(P);
+  const int pa = tid / L::N1, t = tid % L::N1;
+  if (pa < np) {
+    if constexpr (LINE) dft_codelet<T, false, R1>(v);
+    else dft_half<T, R1>(v);
+#pragma unroll
+    for (int k = 1; k < R1; ++k) v[k] = cmul(v[k], tw[L::M + k * L::N1 + t]);
+  }
+  const int pb = tid / L::TB, rb = tid % L::TB, u = rb % R3, k1 = rb / R3;
+  cx<T> w[R2];
+  z3_exchange<R1, R2>(
+      v, w, S, pa < np, pb < np, [&](int k) { return pa * PS + k * L::N1p + t; },
+      [&](int s) { return pb * PS + k1 * L::N1p + u + R3 * s; });
+  if (pb < np) {
+    dft_codelet<T, false, R2>(w);
+#pragma unroll
+    for (int k = 1; k < R2; ++k) w[k] = cmul(w[k], tw[2 * L::M + k * R3 + u]);
+  }
+  __syncthreads();
+  const int pc = tid & (P - 1), q = tid >> (31 - __clz(P));
+  const bool on = pc < np && q < L::Q;
+  z3_exchange<R2, R3>(
+      w, z, S, pb < np, on, [&](int k) { return pb * PS + u * L::Qp + k1 + R1 * k; },
+      [&](int j) { return pc * PS + j * L::Qp + q; });
+  if (on) dft_codelet<T, false, R3>(z);
 }
 
-template <typename T, int A, int B, int MODE>
-__device__ __forceinline__ void zinv4_body(gptr<const cx<T>> __restrict__ U, gptr<const cx<T>> __restrict__ x,
+template <typename T, int R1, int R2, int R3>
+__device__ __forceinline__ void zfwd3_body(gptr<const cx<T>> __restrict__ x, gptr<cx<T>> __restrict__ U,
+                                           const Geom& g, int P, gptr<const cx<T>> __restrict__ tw, int blk,
+                                           typename Z3Elem<T>::type* S, int tid) {
+  using L = Z3Map<R1, R2, R3>;
+  const PencilBlock pb = pencil_block(blk, g.n1, g.n2, P);
+  const int i2 = pb.i2, c = pb.c, i1_0 = pb.i1_0, np = pb.np;
+  cx<T> v[R1];
+  {
+    const int p = tid / L::N1, t = tid % L::N1;
+    if (p < np) {
+      gptr<const cx<T>> src = x + (((long)c * g.n1 + i1_0 + p) * g.n2 + i2) * g.n3;
+#pragma unroll
+      for (int j = 0; j < R1 / 2; ++j) {   // n >= M3 / 2 >= n3 is padding
+        const int n = t + L::N1 * j;
+        const cx<T> in = src[n < g.n3 ? n : g.n3 - 1];
+        v[j] = cx<T>{n < g.n3 ? in.x : (T)0, n < g.n3 ? in.y : (T)0};
+      }
+    }
+  }
+  cx<T> z[R3];
+  z3_forward<T, R1, R2, R3, false>(v, z, np, P, tw, S, tid);
+  const int p = tid & (P - 1), q = tid >> (31 - __clz(P));
+  if (p < np && q < L::Q) {
+    const long plane = 3L * g.n1 * g.n2;
+    gptr<cx<T>> dst = U + ((long)c * g.n2 + i2) * g.n1 + i1_0 + p;
+#pragma unroll
+    for (int k = 0; k < R3; ++k) dst[(long)(q + L::Q * k) * plane] = z[k];
+  }
+}
+
+template <typename T, int R1, int R2, int R3, int MODE>
+__device__ __forceinline__ void zinv3_body(gptr<const cx<T>> __restrict__ U, gptr<const cx<T>> __restrict__ x,
                                            gptr<cx<T>> __restrict__ y, gptr<const cx<T>> __restrict__ bvec,
                                            gptr<const cx<T>> __restrict__ chi, const Geom& g, int P,
-                                           gptr<const cx<T>> __restrict__ tw, int blk, cx<T>* S, int tid) {
-  constexpr int M = A * B;
-  const PencilBlock pb = pencil_block(blk, g.n1, g.n2, P);
-  const int i2 = pb.i2, c = pb.c, i1_0 = pb.i1_0, np = pb.np;
-  const int p = tid / A, a = tid % A;
-  const int ld = P + 1;
-  const long plane = 3L * g.n1 * g.n2;
-  gptr<const cx<T>> src = U + ((long)c * g.n2 + i2) * g.n1 + i1_0;
-  // staged H kz-ranges of M / H; range h holds v[b] for b in [h B / H, (h + 1) B / H)
-  constexpr int H = z4_split<T>() ? 2 : 1;
-  cx<T> v[B];
+                                           gptr<const cx<T>> __restrict__ tw, int blk,
+                                           typename Z3Elem<T>::type* S, int tid) {
+  using L = Z3Map<R1, R2, R3>;
+  const int PS = L::pencil(P);
+  const PencilBlock pk = pencil_block(blk, g.n1, g.n2, P);
+  const int i2 = pk.i2, c = pk.c, i1_0 = pk.i1_0, np = pk.np;
+  const int pc = tid & (P - 1), q = tid >> (31 - __clz(P));
+  const bool on = pc < np && q < L::Q;
+  cx<T> z[R3];
+  if (on) {
+    const long plane = 3L * g.n1 * g.n2;
+    gptr<const cx<T>> src = U + ((long)c * g.n2 + i2) * g.n1 + i1_0 + pc;
 #pragma unroll
-  for (int h = 0; h < H; ++h) {
-    gptr<const cx<T>> sh = src + (long)h * (M / H) * plane;
-    if (np == P) {
-      // full block: thread t owns pencil t % P at planes t / P + A k, k < B / H;
-      // eight loads in flight per batch (one at a time would expose every
-      // latency), no divisions
-      const int pp = tid % P, kz0 = tid / P;
+    for (int k = 0; k < R3; ++k) z[k] = src[(long)(q + L::Q * k) * plane];
+    dft_codelet<T, true, R3>(z);
+    const int k2 = q / R1;
 #pragma unroll
-      for (int k0 = 0; k0 < B / H; k0 += 8) {
-        cx<T> tmp[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) tmp[k] = sh[(long)(kz0 + A * (k0 + k)) * plane + pp];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) S[(kz0 + A * (k0 + k)) * ld + pp] = tmp[k];
-      }
-    } else {
-      for (int t = tid; t < np * (M / H); t += blockDim.x) {
-        const int pp = t % np, kz = t / np;
-        S[kz * ld + pp] = sh[kz * plane + pp];
-      }
-    }
-    __syncthreads();
-    if (p < np) {
-#pragma unroll
-      for (int b = 0; b < B / H; ++b) v[h * (B / H) + b] = S[(a + A * b) * ld + p];
-    }
-    __syncthreads();
+    for (int j = 1; j < R3; ++j) z[j] = cmulc(z[j], tw[2 * L::M + k2 * R3 + j]);
   }
-  if (p < np) {
-    dft_reg<T, true, B>(v);
+  const int pb = tid / L::TB, rb = tid % L::TB, u = rb % R3, k1 = rb / R3;
+  cx<T> w[R2];
+  z3_exchange<R3, R2>(
+      z, w, S, on, pb < np, [&](int j) { return pc * PS + j * L::Qp + q; },
+      [&](int k) { return pb * PS + u * L::Qp + k1 + R1 * k; });
+  if (pb < np) {
+    dft_codelet<T, true, R2>(w);
 #pragma unroll
-    for (int k1 = 1; k1 < B; ++k1) v[k1] = cmulc(v[k1], tw[a * k1]);
-  }
-  cx<T> w[B];
-  z4_exchange<T, A, B>(v, w, S, p, a, p < np);
-  if (p < np) {
-    const long vox = ((long)(i1_0 + p) * g.n2 + i2) * g.n3;
-    const long off = (long)c * g.N + vox;
-#pragma unroll
-    for (int t = 0; t < B / A; ++t) {
-      const int k1 = a + A * t;
-      cx<T>* z = w + t * A;
-      dft_reg<T, true, A>(z);
-      // Pin the kept outputs in registers here.  Otherwise the compiler sinks
-      // their arithmetic into the conditional stores below, which keeps the
-      // transform's intermediates live across all of them (280 instead of 168
-      // VGPRs in FP64 at A = 32: one wave per SIMD instead of three).
-#pragma unroll
-      for (int k2 = 0; k2 < A / 2; ++k2) asm volatile("" : "+v"(z[k2].x), "+v"(z[k2].y));
-#pragma unroll
-      for (int k2 = 0; k2 < A / 2; ++k2) {
-        const int n = k1 + B * k2;
-        if (n < g.n3) {   // n >= M/2 >= n3 is cropped
-          const cx<T> r = csub(x[off + n], cmul(chi[vox + n], z[k2]));
-          y[off + n] = MODE == 0 ? r : csub(bvec[off + n], r);
-        }
-      }
-    }
+    for (int s = 0; s < R2; ++s) w[s] = cmulc(w[s], tw[L::M + k1 * L::N1 + u + R3 * s]);
   }
   __syncthreads();
+  const int pa = tid / L::N1, t = tid % L::N1;
+  cx<T> v[R1];
+  z3_exchange<R2, R1>(
+      w, v, S, pb < np, pa < np, [&](int s) { return pb * PS + k1 * L::N1p + u + R3 * s; },
+      [&](int k) { return pa * PS + k * L::N1p + t; });
+  if (pa < np) {
+    dft_codelet<T, true, R1>(v);
+    // the kept outputs, in registers here (else their arithmetic sinks into the conditional
+    // stores with the transform's intermediates live across all of them)
+#pragma unroll
+    for (int j = 0; j < R1 / 2; ++j) asm volatile("" : "+v"(v[j].x), "+v"(v[j].y));
+    const long vox = ((long)(i1_0 + pa) * g.n2 + i2) * g.n3;
+    const long off = (long)c * g.N + vox;
+#pragma unroll
+    for (int j = 0; j < R1 / 2; ++j) {   // n >= M3 / 2 >= n3 is cropped
+      const int n = t + L::N1 * j, m = n < g.n3 ? n : g.n3 - 1;
+      cx<T> r = csub(x[off + m], cmul(chi[vox + m], v[j]));
+      if (MODE == 1) r = csub(bvec[off + m], r);
+      if (n < g.n3) y[off + n] = r;
+    }
+  }
 }
 
-template <typename T, int A, int B, int MODE>
-__global__ __launch_bounds__(256) void k_zinv4(const cx<T>* __restrict__ U, const cx<T>* __restrict__ x,
+template <typename T, int R1, int R2, int R3>
+__global__ __launch_bounds__(1024) void k_zfwd3(const cx<T>* __restrict__ x, cx<T>* __restrict__ U, Geom g, int P,
+                                                const cx<T>* __restrict__ tw) {
+  extern __shared__ unsigned char smem_raw[];
+  zfwd3_body<T, R1, R2, R3>((gptr<const cx<T>>)x, (gptr<cx<T>>)U, g, P, (gptr<const cx<T>>)tw,
+                            xcd_group(blockIdx.x, gridDim.x, P, (int)sizeof(cx<T>)),
+                            reinterpret_cast<typename Z3Elem<T>::type*>(smem_raw), threadIdx.x);
+}
+
+template <typename T, int R1, int R2, int R3, int MODE>
+__global__ __launch_bounds__(1024) void k_zinv3(const cx<T>* __restrict__ U, const cx<T>* __restrict__ x,
                                                 cx<T>* __restrict__ y, const cx<T>* __restrict__ bvec,
                                                 const cx<T>* __restrict__ chi, Geom g, int P,
                                                 const cx<T>* __restrict__ tw) {
   extern __shared__ unsigned char smem_raw[];
-  zinv4_body<T, A, B, MODE>((gptr<const cx<T>>)U, (gptr<const cx<T>>)x, (gptr<cx<T>>)y, (gptr<const cx<T>>)bvec,
-                            (gptr<const cx<T>>)chi, g, P, (gptr<const cx<T>>)tw, xcd_group(blockIdx.x, gridDim.x, P, (int)sizeof(cx<T>)),
-                            reinterpret_cast<cx<T>*>(smem_raw), threadIdx.x);
+  zinv3_body<T, R1, R2, R3, MODE>((gptr<const cx<T>>)U, (gptr<const cx<T>>)x, (gptr<cx<T>>)y, (gptr<const cx<T>>)bvec,
+                                  (gptr<const cx<T>>)chi, g, P, (gptr<const cx<T>>)tw,
+                                  xcd_group(blockIdx.x, gridDim.x, P, (int)sizeof(cx<T>)),
+                                  reinterpret_cast<typename Z3Elem<T>::type*>(smem_raw), threadIdx.x);
 }
 
-// Launch: returns hipErrorNotSupported when (M3, precision) has no four-step
-// instance, so the caller falls back to the generic LDS Stockham passes.
-template <typename T>
-struct ZShape {
-  int A, B, P;
-};
-
-// Pencil counts P tried by the plan-time tuner, default first; each keeps the
-// workgroup (A P threads) within the kernels' 256 and its LDS (z4_lds_for)
-// within 160 KiB.
-template <typename T>
-int z4_pencil_options(int M3, int* out, int cap) {
-  const bool dbl = sizeof(T) == 8;
-  int opts[6] = {0, 0, 0, 0, 0, 0}, n = 0;
-  if (M3 == 512) {                                   // A = 16
-    if (dbl) { opts[0] = 8; opts[1] = 4; opts[2] = 16; opts[3] = 2; n = 4; }
-    else { opts[0] = 16; opts[1] = 8; opts[2] = 4; opts[3] = 2; n = 4; }
-  } else if (M3 == 1024) {                           // A = 32
-    if (dbl) { opts[0] = 4; opts[1] = 2; opts[2] = 8; n = 3; }
-    else { opts[0] = 8; opts[1] = 4; opts[2] = 2; n = 3; }
-  } else if (M3 == 2048) {                           // A = 32, 64 values per thread
-    if (dbl) { opts[0] = 2; opts[1] = 4; opts[2] = 1; n = 3; }
-    else { opts[0] = 4; opts[1] = 2; n = 2; }
-  } else if (M3 == 4096) {                           // A = 64, 64 values per thread
-    if (dbl) { opts[0] = 2; opts[1] = 1; n = 2; }
-    else { opts[0] = 2; opts[1] = 4; opts[2] = 1; n = 3; }
+// In-place transforms of contiguous lines of M3 values, one workgroup each (the spectra
+// of the tables at plan time).
+template <int R1, int R2, int R3>
+__global__ __launch_bounds__(1024) void k_z3_lines(double2* __restrict__ F, const double2* __restrict__ tw) {
+  extern __shared__ unsigned char smem_raw[];
+  using L = Z3Map<R1, R2, R3>;
+  double2* line = F + (long)blockIdx.x * L::M;
+  const int tid = threadIdx.x;
+  double2 v[R1], z[R3];
+  if (tid < L::N1) {
+#pragma unroll
+    for (int j = 0; j < R1; ++j) v[j] = line[tid + L::N1 * j];
   }
-  for (int i = 0; i < n && i < cap; ++i) out[i] = opts[i];
-  return n;
-}
-
-template <typename T>
-static bool zshape(int M3, ZShape<T>* s, int P = 0) {
-  int opts[8];
-  const int n = z4_pencil_options<T>(M3, opts, 8);
-  if (n == 0) return false;
-  bool ok = P == 0;
-  for (int i = 0; i < n; ++i) ok = ok || opts[i] == P;
-  if (!ok) return false;
-  const int p = P ? P : opts[0];
-  if (M3 == 512) *s = {16, 32, p};
-  else if (M3 == 1024) *s = {32, 32, p};
-  else if (M3 == 2048) *s = {32, 64, p};
-  else *s = {64, 64, p};
-  return true;
-}
-
-template <typename T>
-size_t z4_lds_bytes(int M3, int P) {
-  ZShape<T> s;
-  if (!zshape<T>(M3, &s, P)) return 0;
-  return z4_lds_for<T>(M3, s.P);
-}
-
-template <typename T>
-hipError_t launch_z4(int which, const Geom& g, int P, const void* x, void* y, const void* b, int mode, void* U,
-                     const void* chi, const void* twz, hipStream_t st) {
-  using C = cx<T>;
-  ZShape<T> s;
-  if (!zshape<T>(g.M3, &s, P)) return hipErrorNotSupported;
-  const int nb1 = (g.n1 + s.P - 1) / s.P;
-  const dim3 grid(3 * g.n2 * nb1), block(s.A * s.P);
-  const size_t lds = z4_lds_for<T>(g.M3, s.P);
-#define VIE_Z4(AA, BB)                                                                                        \
-  if (s.A == AA && s.B == BB) {                                                                               \
-    if (which == 0)                                                                                           \
-      hipLaunchKernelGGL((k_zfwd4<T, AA, BB>), grid, block, lds, st, (const C*)x, (C*)U, g, s.P, (const C*)twz); \
-    else if (mode == 0)                                                                                       \
-      hipLaunchKernelGGL((k_zinv4<T, AA, BB, 0>), grid, block, lds, st, (const C*)U, (const C*)x, (C*)y,      \
-                         (const C*)nullptr, (const C*)chi, g, s.P, (const C*)twz);                             \
-    else                                                                                                      \
-      hipLaunchKernelGGL((k_zinv4<T, AA, BB, 1>), grid, block, lds, st, (const C*)U, (const C*)x, (C*)y,      \
-                         (const C*)b, (const C*)chi, g, s.P, (const C*)twz);                                   \
-    return hipGetLastError();                                                                                 \
+  z3_forward<double, R1, R2, R3, true>(v, z, 1, 1, (gptr<const double2>)tw, reinterpret_cast<double*>(smem_raw), tid);
+  if (tid < L::Q) {
+#pragma unroll
+    for (int k = 0; k < R3; ++k) line[tid + L::Q * k] = z[k];
   }
-  VIE_Z4(16, 32)
-  VIE_Z4(32, 32)
-  VIE_Z4(32, 64)
-  VIE_Z4(64, 64)
-#undef VIE_Z4
-  return hipErrorNotSupported;
 }
 
 __device__ __forceinline__ int find_sys(const int* prefix, int nsys, int item) {
@@ -352,120 +266,229 @@ __device__ __forceinline__ int find_sys(const int* prefix, int nsys, int item) {
 
 // Persistent batched z passes: each workgroup walks the (system, pencil block)
 // items of the batch with a grid stride.
-template <typename T, int A, int B>
-__global__ __launch_bounds__(256) void k_zfwd4_batch(const PassDesc* __restrict__ d, const int* __restrict__ prefix,
-                                                     int nsys, int total, int jx, int jy) {
+template <typename T, int R1, int R2, int R3>
+__global__ __launch_bounds__(1024) void k_zfwd3_batch(const PassDesc* __restrict__ d, const int* __restrict__ prefix,
+                                                      int nsys, int total, int jx, int jy) {
   extern __shared__ unsigned char smem_raw[];
-  cx<T>* S = reinterpret_cast<cx<T>*>(smem_raw);
+  auto* S = reinterpret_cast<typename Z3Elem<T>::type*>(smem_raw);
   for (int item = blockIdx.x; item < total; item += gridDim.x) {
     const int s = find_sys(prefix, nsys, item);
     const PassDesc& D = d[s];
     if (D.active && *D.active == 0) continue;
-    zfwd4_body<T, A, B>((gptr<const cx<T>>)(const cx<T>*)D.xb + (long)jx * D.xs, (gptr<cx<T>>)(cx<T>*)D.U, D.g, D.P,
-                        (gptr<const cx<T>>)(const cx<T>*)D.twz, item - prefix[s], S, opaque_tid());
+    zfwd3_body<T, R1, R2, R3>((gptr<const cx<T>>)(const cx<T>*)D.xb + (long)jx * D.xs, (gptr<cx<T>>)(cx<T>*)D.U, D.g,
+                              D.P, (gptr<const cx<T>>)(const cx<T>*)D.twz, item - prefix[s], S, opaque_tid());
+    __syncthreads();
   }
 }
 
-template <typename T, int A, int B, int MODE>
-__global__ __launch_bounds__(256) void k_zinv4_batch(const PassDesc* __restrict__ d, const int* __restrict__ prefix,
-                                                     int nsys, int total, int jx, int jy) {
+template <typename T, int R1, int R2, int R3, int MODE>
+__global__ __launch_bounds__(1024) void k_zinv3_batch(const PassDesc* __restrict__ d, const int* __restrict__ prefix,
+                                                      int nsys, int total, int jx, int jy) {
   extern __shared__ unsigned char smem_raw[];
-  cx<T>* S = reinterpret_cast<cx<T>*>(smem_raw);
+  auto* S = reinterpret_cast<typename Z3Elem<T>::type*>(smem_raw);
   for (int item = blockIdx.x; item < total; item += gridDim.x) {
     const int s = find_sys(prefix, nsys, item);
     const PassDesc& D = d[s];
     if (D.active && *D.active == 0) continue;
-    zinv4_body<T, A, B, MODE>((gptr<const cx<T>>)(const cx<T>*)D.U, (gptr<const cx<T>>)(const cx<T>*)D.xb + (long)jx * D.xs,
-                              (gptr<cx<T>>)(cx<T>*)D.yb + (long)jy * D.ys, (gptr<const cx<T>>)(const cx<T>*)D.b,
-                              (gptr<const cx<T>>)(const cx<T>*)D.chi, D.g, D.P, (gptr<const cx<T>>)(const cx<T>*)D.twz,
-                              item - prefix[s], S, opaque_tid());
+    zinv3_body<T, R1, R2, R3, MODE>(
+        (gptr<const cx<T>>)(const cx<T>*)D.U, (gptr<const cx<T>>)(const cx<T>*)D.xb + (long)jx * D.xs,
+        (gptr<cx<T>>)(cx<T>*)D.yb + (long)jy * D.ys, (gptr<const cx<T>>)(const cx<T>*)D.b,
+        (gptr<const cx<T>>)(const cx<T>*)D.chi, D.g, D.P, (gptr<const cx<T>>)(const cx<T>*)D.twz, item - prefix[s], S,
+        opaque_tid());
+    __syncthreads();
   }
 }
 
+// Every length with its radices: the first even (half of its inputs are padding), all near each
+// other (a pencil has as many threads as its stage of smallest radix has tasks), the length a
+// multiple of 16, which the plane order of the cross-section passes wants, and at most 1.25
+// times the one before.
+#define VIE_Z3_LENGTHS(X) \
+  X(8, 8, 8)              \
+  X(8, 8, 10)             \
+  X(8, 8, 12)             \
+  X(10, 10, 8)            \
+  X(12, 10, 8)            \
+  X(16, 8, 8)             \
+  X(12, 12, 8)            \
+  X(16, 10, 8)            \
+  X(12, 12, 10)           \
+  X(16, 10, 10)           \
+  X(16, 12, 10)           \
+  X(16, 16, 8)            \
+  X(16, 12, 12)           \
+  X(16, 16, 10)           \
+  X(16, 15, 12)           \
+  X(16, 16, 12)           \
+  X(16, 15, 15)           \
+  X(16, 16, 16)
+
+struct Z3Shape {
+  int threads;   // of a pencil
+  int pencil;    // LDS elements of a pencil of P
+};
+bool z3_shape(int M3, int P, Z3Shape* s) {
+#define VIE_Z3(A, B, C)                                                    \
+  if (M3 == A * B * C) {                                                   \
+    *s = {Z3Map<A, B, C>::TM, Z3Map<A, B, C>::pencil(P)};                  \
+    return true;                                                           \
+  }
+  VIE_Z3_LENGTHS(VIE_Z3)
+#undef VIE_Z3
+  return false;
+}
+int z3_threads(int M3, int P) {
+  Z3Shape s;
+  return z3_shape(M3, P, &s) ? (P * s.threads + 63) / 64 * 64 : 0;
+}
+
+}  // namespace
+
+bool z3_radices(int M3, int r[3]) {
+#define VIE_Z3(A, B, C)   \
+  if (M3 == A * B * C) {  \
+    r[0] = A;             \
+    r[1] = B;             \
+    r[2] = C;             \
+    return true;          \
+  }
+  VIE_Z3_LENGTHS(VIE_Z3)
+#undef VIE_Z3
+  return false;
+}
+
+int z3_length(int need) {
+  int m = 0;
+#define VIE_Z3(A, B, C) \
+  if (A * B * C >= need && (m == 0 || A * B * C < m)) m = A * B * C;
+  VIE_Z3_LENGTHS(VIE_Z3)
+#undef VIE_Z3
+  return m;
+}
+
+// Pencil counts P tried by the plan-time tuner, default first, by the power of two the
+// length belongs to; each keeps the workgroup within 1024 threads and its LDS within
+// 160 KiB.
 template <typename T>
-bool z4_shape(int M3, int* A, int* B, int* P) {
-  ZShape<T> s;
-  if (!zshape<T>(M3, &s)) return false;
-  *A = s.A;
-  *B = s.B;
-  *P = s.P;
-  return true;
+int z3_pencil_options(int M3, int* out, int cap) {
+  const bool dbl = sizeof(T) == 8;
+  int r[3];
+  if (!z3_radices(M3, r)) return 0;
+  int opts[6] = {0, 0, 0, 0, 0, 0}, n = 0;
+  if (M3 <= 512) {
+    if (dbl) { opts[0] = 8; opts[1] = 4; opts[2] = 16; opts[3] = 2; n = 4; }
+    else { opts[0] = 16; opts[1] = 8; opts[2] = 4; opts[3] = 2; n = 4; }
+  } else if (M3 <= 1024) {
+    if (dbl) { opts[0] = 4; opts[1] = 2; opts[2] = 8; n = 3; }
+    else { opts[0] = 8; opts[1] = 4; opts[2] = 2; n = 3; }
+  } else if (M3 <= 2048) {
+    if (dbl) { opts[0] = 2; opts[1] = 4; opts[2] = 1; n = 3; }
+    else { opts[0] = 4; opts[1] = 2; n = 2; }
+  } else {
+    if (dbl) { opts[0] = 2; opts[1] = 1; n = 2; }
+    else { opts[0] = 2; opts[1] = 4; opts[2] = 1; n = 3; }
+  }
+  for (int i = 0; i < n && i < cap; ++i) out[i] = opts[i];
+  return n;
+}
+
+size_t z3_lds_bytes(int M3, int P) {
+  Z3Shape s;
+  return z3_shape(M3, P, &s) ? (size_t)P * s.pencil * 8 : 0;
 }
 
 template <typename T>
-hipError_t launch_z4_batch(int which, int mode, const PassDesc* d, const int* prefix, int nsys, int total, int A,
-                           int B, int P, int jx, int jy, hipStream_t st) {
-  const size_t lds = z4_lds_for<T>(A * B, P);
-  const dim3 grid(total < 4096 ? total : 4096), block(A * P);
-#define VIE_Z4B(AA, BB)                                                                                      \
-  if (A == AA && B == BB) {                                                                                  \
-    if (which == 0)                                                                                          \
-      hipLaunchKernelGGL((k_zfwd4_batch<T, AA, BB>), grid, block, lds, st, d, prefix, nsys, total, jx, jy);  \
-    else if (mode == 0)                                                                                      \
-      hipLaunchKernelGGL((k_zinv4_batch<T, AA, BB, 0>), grid, block, lds, st, d, prefix, nsys, total, jx, jy); \
-    else                                                                                                     \
-      hipLaunchKernelGGL((k_zinv4_batch<T, AA, BB, 1>), grid, block, lds, st, d, prefix, nsys, total, jx, jy); \
-    return hipGetLastError();                                                                                \
+hipError_t launch_z3(int which, const Geom& g, int P, const void* x, void* y, const void* b, int mode, void* U,
+                     const void* chi, const void* twz, hipStream_t st) {
+  using C = cx<T>;
+  int opts[8];
+  const int n = z3_pencil_options<T>(g.M3, opts, 8);
+  if (n == 0) return hipErrorNotSupported;
+  if (P == 0) P = opts[0];
+  bool ok = P == 1;
+  for (int i = 0; i < n; ++i) ok = ok || opts[i] == P;
+  if (!ok) return hipErrorNotSupported;
+  const dim3 grid(pencil_blocks(g.n1, g.n2, P)), block(z3_threads(g.M3, P));
+  const size_t lds = z3_lds_bytes(g.M3, P);
+#define VIE_Z3(A, B, D)                                                                                        \
+  if (g.M3 == A * B * D) {                                                                                     \
+    if (which == 0)                                                                                            \
+      hipLaunchKernelGGL((k_zfwd3<T, A, B, D>), grid, block, lds, st, (const C*)x, (C*)U, g, P, (const C*)twz);  \
+    else if (mode == 0)                                                                                        \
+      hipLaunchKernelGGL((k_zinv3<T, A, B, D, 0>), grid, block, lds, st, (const C*)U, (const C*)x, (C*)y,        \
+                         (const C*)nullptr, (const C*)chi, g, P, (const C*)twz);                                \
+    else                                                                                                       \
+      hipLaunchKernelGGL((k_zinv3<T, A, B, D, 1>), grid, block, lds, st, (const C*)U, (const C*)x, (C*)y,        \
+                         (const C*)b, (const C*)chi, g, P, (const C*)twz);                                      \
+    return hipGetLastError();                                                                                  \
   }
-  VIE_Z4B(16, 32)
-  VIE_Z4B(32, 32)
-  VIE_Z4B(32, 64)
-  VIE_Z4B(64, 64)
-#undef VIE_Z4B
+  VIE_Z3_LENGTHS(VIE_Z3)
+#undef VIE_Z3
+  return hipErrorNotSupported;
+}
+
+hipError_t launch_z3_lines(int M3, long lines, double2* F, const double2* twz, hipStream_t st) {
+  const size_t lds = z3_lds_bytes(M3, 1);
+#define VIE_Z3(A, B, D)                                                                                       \
+  if (M3 == A * B * D) {                                                                                      \
+    hipLaunchKernelGGL((k_z3_lines<A, B, D>), dim3((unsigned)lines), dim3(z3_threads(M3, 1)), lds, st, F, twz); \
+    return hipGetLastError();                                                                                 \
+  }
+  VIE_Z3_LENGTHS(VIE_Z3)
+#undef VIE_Z3
   return hipErrorNotSupported;
 }
 
 template <typename T>
-hipError_t allow_lds_z4() {
-  hipError_t e;
-  const int big = 160 * 1024;
-#define VIE_ALLOW(AA, BB)                                                                                   \
-  if ((e = hipFuncSetAttribute((const void*)k_zfwd4<T, AA, BB>, hipFuncAttributeMaxDynamicSharedMemorySize, big))) \
-    return e;                                                                                                 \
-  if ((e = hipFuncSetAttribute((const void*)k_zinv4<T, AA, BB, 0>, hipFuncAttributeMaxDynamicSharedMemorySize,    \
-                               big)))                                                                         \
-    return e;                                                                                                 \
-  if ((e = hipFuncSetAttribute((const void*)k_zinv4<T, AA, BB, 1>, hipFuncAttributeMaxDynamicSharedMemorySize,    \
-                               big)))                                                                         \
-    return e;
-  VIE_ALLOW(16, 32)
-  VIE_ALLOW(32, 32)
-  VIE_ALLOW(32, 64)
-  VIE_ALLOW(64, 64)
-#undef VIE_ALLOW
-#define VIE_ALLOWB(AA, BB)                                                                                         \
-  if ((e = hipFuncSetAttribute((const void*)k_zfwd4_batch<T, AA, BB>,                                           \
-                               hipFuncAttributeMaxDynamicSharedMemorySize, big)))                                \
-    return e;                                                                                                      \
-  if ((e = hipFuncSetAttribute((const void*)k_zinv4_batch<T, AA, BB, 0>,                                        \
-                               hipFuncAttributeMaxDynamicSharedMemorySize, big)))                                \
-    return e;                                                                                                      \
-  if ((e = hipFuncSetAttribute((const void*)k_zinv4_batch<T, AA, BB, 1>,                                        \
-                               hipFuncAttributeMaxDynamicSharedMemorySize, big)))                                \
-    return e;
-  VIE_ALLOWB(16, 32)
-  VIE_ALLOWB(32, 32)
-  VIE_ALLOWB(32, 64)
-  VIE_ALLOWB(64, 64)
-#undef VIE_ALLOWB
-  return hipSuccess;
+hipError_t launch_z3_batch(int which, int mode, const PassDesc* d, const int* prefix, int nsys, int total, int M3,
+                           int P, int jx, int jy, hipStream_t st) {
+  const size_t lds = z3_lds_bytes(M3, P);
+  const dim3 grid(total < 4096 ? total : 4096), block(z3_threads(M3, P));
+#define VIE_Z3(A, B, D)                                                                                          \
+  if (M3 == A * B * D) {                                                                                         \
+    if (which == 0)                                                                                              \
+      hipLaunchKernelGGL((k_zfwd3_batch<T, A, B, D>), grid, block, lds, st, d, prefix, nsys, total, jx, jy);       \
+    else if (mode == 0)                                                                                          \
+      hipLaunchKernelGGL((k_zinv3_batch<T, A, B, D, 0>), grid, block, lds, st, d, prefix, nsys, total, jx, jy);    \
+    else                                                                                                         \
+      hipLaunchKernelGGL((k_zinv3_batch<T, A, B, D, 1>), grid, block, lds, st, d, prefix, nsys, total, jx, jy);    \
+    return hipGetLastError();                                                                                    \
+  }
+  VIE_Z3_LENGTHS(VIE_Z3)
+#undef VIE_Z3
+  return hipErrorNotSupported;
 }
 
-template hipError_t launch_z4<double>(int, const Geom&, int, const void*, void*, const void*, int, void*,
+template <typename T>
+hipError_t allow_lds_z3() {
+  const int big = 160 * 1024;
+  hipError_t e = hipSuccess;
+  auto allow = [&](const void* k) {
+    if (!e) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, big);
+  };
+#define VIE_Z3(A, B, D)                              \
+  allow((const void*)k_zfwd3<T, A, B, D>);           \
+  allow((const void*)k_zinv3<T, A, B, D, 0>);        \
+  allow((const void*)k_zinv3<T, A, B, D, 1>);        \
+  allow((const void*)k_zfwd3_batch<T, A, B, D>);     \
+  allow((const void*)k_zinv3_batch<T, A, B, D, 0>);  \
+  allow((const void*)k_zinv3_batch<T, A, B, D, 1>);
+  VIE_Z3_LENGTHS(VIE_Z3)
+#undef VIE_Z3
+  return e;
+}
+
+template hipError_t launch_z3<double>(int, const Geom&, int, const void*, void*, const void*, int, void*,
                                       const void*, const void*, hipStream_t);
-template hipError_t launch_z4<float>(int, const Geom&, int, const void*, void*, const void*, int, void*,
+template hipError_t launch_z3<float>(int, const Geom&, int, const void*, void*, const void*, int, void*,
                                      const void*, const void*, hipStream_t);
-template int z4_pencil_options<double>(int, int*, int);
-template int z4_pencil_options<float>(int, int*, int);
-template hipError_t allow_lds_z4<double>();
-template hipError_t allow_lds_z4<float>();
-template size_t z4_lds_bytes<double>(int, int);
-template bool z4_shape<double>(int, int*, int*, int*);
-template bool z4_shape<float>(int, int*, int*, int*);
-template hipError_t launch_z4_batch<double>(int, int, const PassDesc*, const int*, int, int, int, int, int, int, int,
+template int z3_pencil_options<double>(int, int*, int);
+template int z3_pencil_options<float>(int, int*, int);
+template hipError_t allow_lds_z3<double>();
+template hipError_t allow_lds_z3<float>();
+template hipError_t launch_z3_batch<double>(int, int, const PassDesc*, const int*, int, int, int, int, int, int,
                                             hipStream_t);
-template hipError_t launch_z4_batch<float>(int, int, const PassDesc*, const int*, int, int, int, int, int, int, int,
+template hipError_t launch_z3_batch<float>(int, int, const PassDesc*, const int*, int, int, int, int, int, int,
                                            hipStream_t);
-template size_t z4_lds_bytes<float>(int, int);
 
 }  // namespace vie

@@ -323,6 +323,44 @@ def test_register_cross_section_with_many_planes_sampled_outputs():
     assert _sparse_sample_check(vie, wg, nnz=16, nout=48, precision=32, seed=6) < 5e-6
 
 
+# circulant lengths of the three-stage z passes; each with the fewest and the most z voxels
+Z_LENGTHS = [512, 640, 768, 800, 960, 1024, 1152, 1280, 1440, 1600, 1920, 2048, 2304, 2560, 2880, 3072, 3600, 4096]
+
+
+@pytest.mark.parametrize("length", Z_LENGTHS)
+@pytest.mark.parametrize("edge", ["least", "most"])
+def test_z_lengths_match_the_oracle(length, edge):
+    """5 pencils of 2 rows per component: full and incomplete pencil blocks, with every
+    pencil count that the plan accepts, the residual form included."""
+    vie = _dev()
+    below = max((v for v in Z_LENGTHS if v < length), default=256)
+    n = (5, 2, length // 2 if edge == "most" else below // 2 + 1)
+    rng = np.random.default_rng(length + n[2])
+    kap = mv.kappa_of(H, K0, EPSB)
+    spec = mv.spectrum(green.green_table(n, kap))
+    eps = EPSB + 10 * rng.random(n) + 1j * rng.random(n)
+    chi = mv.contrast(eps, EPSB)
+    plan = vie.Plan(n, H, K0, EPSB, fp32=True)
+    plan.set_contrast(_t(eps))
+    x, b = _cvec(rng, (3,) + n), _cvec(rng, (3,) + n)
+    want = mv.matvec_fft(spec, chi, x)
+    for precision, bar in ((0, 1e-12), (1, 5e-6)):
+        tried = 0
+        for zp in (1, 2, 4, 8, 16, -1):
+            try:
+                plan.set_tune(precision, 1, zp)
+            except vie.VieError:
+                continue
+            tried += 1
+            got = plan.matvec(_t(x)) if precision == 0 else plan.matvec_c64(_t(x, torch.complex64))
+            err = np.linalg.norm(got.cpu().numpy() - want) / np.linalg.norm(want)
+            assert err < bar, (n, precision, zp, err)
+            if precision == 0:
+                res = plan.residual(_t(x), _t(b)).cpu().numpy()
+                assert np.linalg.norm(res - (b - want)) / np.linalg.norm(b - want) < bar
+        assert tried >= 3
+
+
 TUNED_GRIDS = {
     "30x12x1377_M3_4096": lambda: inputs.strip_paper(9.45, 2),
     "32x32x512_M3_1024": lambda: inputs.strip_long(d=2),
