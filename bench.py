@@ -181,18 +181,19 @@ def profiled_traffic(kernel: str):
     return None
 
 
-Z_LENGTHS = (512, 640, 768, 800, 960, 1024, 1152, 1280, 1440, 1600, 1920, 2048, 2304, 2560, 2880, 3072, 3600, 4096)
+Z_LENGTHS = (64, 80, 96, 128, 144, 160, 192, 240, 256,
+             512, 640, 768, 800, 960, 1024, 1152, 1280, 1440, 1600, 1920, 2048, 2304, 2560, 2880, 3072, 3600, 4096)
 
 
 def circulant(n):
-    """The library's circulant lengths: powers of two, along z from 512 on its own list."""
+    """The library's circulant lengths: powers of two, along z from 64 on its own list."""
     out = []
     for v in n:
         m = 1
         while m < 2 * v - 1:
             m *= 2
         out.append(m)
-    if out[2] >= 512:
+    if out[2] >= 64:
         out[2] = min(m for m in Z_LENGTHS if m >= 2 * n[2] - 1)
     return tuple(out)
 

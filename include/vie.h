@@ -31,8 +31,8 @@
  *
  * Size limits of this version: n1, n2 <= 32 and n3 <= 2048 (circulant lengths
  * up to 64, 64 and 4096); each circulant length is the power of two
- * >= 2 n_d - 1, along z where that is 512 or more the shortest length
- * >= 2 n3 - 1 among 512, 640, 768, 800, 960, 1024, 1152, 1280, 1440, 1600, 1920,
+ * >= 2 n_d - 1, along z where that is 64 or more the shortest length
+ * >= 2 n3 - 1 among 64, 80, 96, 128, 144, 160, 192, 240, 256, 512, 640, 768, 800, 960, 1024, 1152, 1280, 1440, 1600, 1920,
  * 2048, 2304, 2560, 2880, 3072, 3600 and 4096.
  */
 #ifndef VIE_H
@@ -276,9 +276,8 @@ int vie_circulant_apply(vie_plan_t plan, const vie_c128* r, vie_c128* z);
  * candidate shapes of the product's kernels on the plan's own buffers (two
  * untimed and five timed whole products each, HIP events, in three interleaved
  * rounds of which each candidate keeps its best) and keeps the fastest:
- * pencils per workgroup of the three-stage z passes (circulant lengths from 512
- * on), or the generic z passes (at a length that is no power of two: one pencil
- * per workgroup), crossed with, for
+ * pencils per workgroup of the z passes (circulant lengths from 512 on), crossed
+ * with, for
  * 64 x 64 circulant cross-sections, the xy pass variant (0: full plane in LDS;
  * 1: x-frequency halves, two workgroups per CU; 2: full plane with 512 threads
  * and private exchange areas, one workgroup per CU) and, for 64 x 32 ones (the
@@ -293,11 +292,10 @@ int vie_circulant_apply(vie_plan_t plan, const vie_c128* r, vie_c128* z);
  * the GPU architecture and CU count, the grid and the precision.
  * vie_get_tune: the current choice for precision 0 (FP64) or 1 (FP32):
  *   *xy_variant (-1 when the cross-section has a single xy pass),
- *   *z_pencils (0 when the z passes use the generic kernels).
+ *   *z_pencils (0 without a choice: below 512, or forced by z_pencils -1).
  * vie_set_tune: force a choice (xy_variant 0-2, ignored where the cross-section
- *   has a single xy pass); z_pencils -1 = the generic z passes, 0 = the
- *   three-stage z passes with their default pencils (generic below a length of
- *   512), any other value must be one of the tuner's candidates
+ *   has a single xy pass); z_pencils -1 = one pencil per workgroup (below a
+ *   length of 512 the default), 0 = the default pencils, any other value must be one of the tuner's candidates
  *   (VIE_EINVAL otherwise).  Synchronises the plan's stream first.
  */
 int vie_get_tune(vie_plan_t plan, int precision, int* xy_variant, int* z_pencils);

@@ -641,7 +641,7 @@ struct PassSet {
     PassDesc* d_res = nullptr;
   };
   std::vector<Group> zgroups;
-  std::vector<int> zsingle;      // systems on the generic z kernels
+  std::vector<int> zsingle;      // systems with z passes of their own
   // cross-section groups: systems of one circulant cross-section with a batched kernel
   struct XyGroup {
     int M1, M2;
@@ -781,16 +781,16 @@ hipError_t build_passes(vie_batch_s* B, PassSet& PS, const BatchLevel<T>& L, std
   }
   if ((e = alloc((void**)&PS.d_sd, sizeof(SDesc) * n))) return e;
   if ((e = hipMemcpy(PS.d_sd, PS.h_sd.data(), sizeof(SDesc) * n, hipMemcpyHostToDevice))) return e;
-  // z groups.  A plan's own operator keeps its tuned choice between the three-stage and
-  // the generic passes; on a box the batch has pencils enough for the three-stage ones.  Pencils per workgroup: those that leave the
+  // z groups.  A plan's own operator keeps its tuned choice of one
+  // pencil per workgroup.  Pencils per workgroup: those that leave the
   // fewest idle in the last block of a row, then the most.
   for (int s = 0; s < n; ++s) {
     const SysPlan& P = B->sp[s];
     const Tune& t = dbl ? P.t64 : P.t32;
-    int opts[8];
+    int opts[8], r[3];
     const int no = z3_pencil_options<T>(P.g.M3, opts, 8);
-    if ((P.box || t.z3) && no) {
-      int Pp = opts[0];
+    if (z3_radices(P.g.M3, r) && (P.box || t.z3 || !no)) {
+      int Pp = z3_pencils<T>(P.g.M3, P.g.n1);
       auto padded = [&](int q) { return (P.g.n1 + q - 1) / q * q; };
       for (int i = 0; i < no; ++i)
         if (padded(opts[i]) < padded(Pp) || (padded(opts[i]) == padded(Pp) && opts[i] > Pp)) Pp = opts[i];

@@ -5,7 +5,7 @@
 // product is a circular convolution after embedding in a circulant of size
 // M = (M1, M2, M3) >= 2n - 1 and zero padding x.  Three passes over HBM:
 //
-//   pass 1 (k_zfwd, from M3 = 512 on zpass.hip):  per z-pencil of one component:
+//   pass 1 (k_zfwd, from M3 = 64 on zpass.hip):  per z-pencil of one component:
 //                     zero-pad n3 -> M3, forward FFT, write kz-plane-major
 //                     U[kz][c][i2][i1]
 //   pass 2 (k_xyp):   per kz plane: forward FFT along i1 (pad n1 -> M1) and i2
@@ -39,7 +39,7 @@ template <typename T>
 hipError_t launch_z3(int which, const Geom& g, int P, const void* x, void* y, const void* b, int mode, void* U,
                      const void* chi, const void* twz, hipStream_t st);
 template <typename T>
-hipError_t allow_lds_z3();
+hipError_t allow_lds_z3(int M3);
 constexpr int kMaxV = 16;   // complex values per thread per FFT stage
 
 // ------------------------------------------------------------------ pass 1
@@ -182,9 +182,8 @@ template <typename T>
 hipError_t launch_pass(int which, const Geom& g, const Tune& t, const void* x, void* y, const void* b, int mode,
                        void* U, const void* goct, const void* chi, const void* const tw[3], hipStream_t s) {
   using C = cx<T>;
-  // a length that is no power of two has no generic form: one pencil per workgroup instead
-  if (which != 1 && (t.z3 || (g.M3 & (g.M3 - 1))))
-    return launch_z3<T>(which, g, t.z3 ? t.zp : 1, x, y, b, mode, U, chi, tw[2], s);
+  if (which != 1 && g.M3 >= 64)
+    return launch_z3<T>(which, g, g.M3 < 512 ? 0 : t.z3 ? t.zp : 1, x, y, b, mode, U, chi, tw[2], s);
   const int nb1 = (g.n1 + t.tp - 1) / t.tp;
   const dim3 gz(3 * g.n2 * nb1);
   const size_t zl = z_lds_bytes<T>(g, t.tp);
@@ -230,7 +229,7 @@ template hipError_t launch_matvec<float>(const Geom&, const Tune&, const void*, 
 
 // Kernel attribute set-up for large LDS allocations (called once per plan).
 template <typename T>
-hipError_t allow_lds(size_t bytes) {
+hipError_t allow_lds(size_t bytes, int M3) {
   hipError_t e;
   if ((e = hipFuncSetAttribute((const void*)k_zfwd<T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes)))
     return e;
@@ -240,11 +239,11 @@ hipError_t allow_lds(size_t bytes) {
     return e;
   if ((e = allow_lds_xy64<T>())) return e;
   if ((e = allow_lds_xy6432<T>())) return e;
-  if ((e = allow_lds_z3<T>())) return e;
+  if ((e = allow_lds_z3<T>(M3))) return e;
   return hipFuncSetAttribute((const void*)k_xyp<T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
-template hipError_t allow_lds<double>(size_t);
-template hipError_t allow_lds<float>(size_t);
+template hipError_t allow_lds<double>(size_t, int);
+template hipError_t allow_lds<float>(size_t, int);
 
 // ------------------------------------------------------------------ spectrum (plan time)
 

@@ -226,7 +226,7 @@ int pow2_at_least(int v) {
 // the library's circulant length along z
 int circulant_length(int n3) {
   const int m = pow2_at_least(2 * n3 - 1);
-  return m >= 512 ? vie::z3_length(2 * n3 - 1) : m;
+  return m >= 64 ? vie::z3_length(2 * n3 - 1) : m;
 }
 
 bool run_all(Checker& ck) {
@@ -239,16 +239,17 @@ bool run_all(Checker& ck) {
       for (int tp = 1; tp <= 16; tp <<= 1)
         if (!check_pencil_map(ck, n1, n2, tp, [](int b, int nb) { return vie::xcd_group8(b, nb); }, "generic z"))
           return false;
-      // three-stage z passes: every pencil count of each precision
-      for (int M3 = 512; M3 <= 4096; M3 = M3 == 4096 ? 4097 : vie::z3_length(M3 + 1)) {
+      // register z passes: every pencil count of each precision
+      for (int M3 = 64; M3 <= 4096; M3 = M3 == 4096 ? 4097 : vie::z3_length(M3 + 1)) {
         for (int vb : {8, 16}) {
           int opts[8];
-          const int n = vb == 16 ? vie::z3_pencil_options<double>(M3, opts, 8)
-                                 : vie::z3_pencil_options<float>(M3, opts, 8);
+          int n = vb == 16 ? vie::z3_pencil_options<double>(M3, opts, 8)
+                           : vie::z3_pencil_options<float>(M3, opts, 8);
+          if (n == 0) opts[n++] = vb == 16 ? vie::z3_pencils<double>(M3, n1) : vie::z3_pencils<float>(M3, n1);
           for (int i = 0; i < n; ++i) {
             const int P = opts[i];
             if (!check_pencil_map(ck, n1, n2, P,
-                                  [P, vb](int b, int nb) { return vie::xcd_group(b, nb, P, vb); }, "three-stage z"))
+                                  [P, vb](int b, int nb) { return vie::xcd_group(b, nb, P, vb); }, "register z"))
               return false;
           }
         }

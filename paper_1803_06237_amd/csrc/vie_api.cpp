@@ -27,7 +27,7 @@
 
 namespace vie {
 template <typename T>
-hipError_t allow_lds(size_t bytes);
+hipError_t allow_lds(size_t bytes, int M3);
 hipError_t net_apply(vie_net_s* N, const double2* r, const double2* w, const double2* chi, double2* z);
 const int* net_grid(vie_net_s* N);
 void net_set_stream(vie_net_s* N, hipStream_t s);
@@ -250,15 +250,15 @@ int ilog2(int v) {
   return l;
 }
 
-// circulant lengths: the power of two >= 2 n - 1, along z from 512 on the shortest of the
-// three-stage passes' lengths (every pass's work and the intermediate are proportional to it:
+// circulant lengths: the power of two >= 2 n - 1, along z from 64 on the shortest of the
+// register z passes' lengths (every pass's work and the intermediate are proportional to it:
 // FP64 30 x 12 x 1377 takes 206 us at 4096 and 158 us at 2880)
 Geom make_geom(const int n[3]) {
   Geom g{};
   int M[3];
   for (int d = 0; d < 3; ++d)
     for (M[d] = 1; M[d] < 2 * n[d] - 1;) M[d] <<= 1;
-  if (M[2] >= 512) M[2] = z3_length(2 * n[2] - 1);
+  if (M[2] >= 64) M[2] = z3_length(2 * n[2] - 1);
   g.n1 = n[0];
   g.n2 = n[1];
   g.n3 = n[2];
@@ -310,7 +310,7 @@ bool pick_tune(const Geom& g, size_t budget, size_t zbudget, Tune* t) {
 }
 
 // ---- plan-time tuning of launch shapes ----------------------------------------
-// Candidates: the three-stage z passes' pencils per workgroup (the forward and the
+// Candidates: the register z passes' pencils per workgroup (the forward and the
 // inverse pass share the choice) and the 64 x 64 xy pass variant.  Each candidate
 // runs two untimed and five timed whole products (all three passes) between HIP
 // events; the fastest wins.  Results are kept per (device, grid, precision) for
@@ -440,9 +440,8 @@ hipError_t autotune(const Geom& g, int device, Tune* t, void* U, const void* goc
   // round: single rounds let launch noise decide between shapes within 1 % of
   // each other, and the choice then changed from one process to the next.
   constexpr int kRounds = 3;
-  // Candidates: the three-stage pencil counts and the generic LDS z passes (one pencil
-  // per workgroup where the length is no power of two), crossed with
-  // the xy variants of 64 x 64 planes.  They are timed jointly, as whole
+  // Candidates: the z passes' pencil counts crossed with the xy variants of 64 x 64 and
+  // 64 x 32 planes.  They are timed jointly, as whole
   // back-to-back products: the z pass's write pattern decides what the xy pass
   // finds in L2 and the Infinity Cache, so a pass timed alone, or with events
   // between the passes, can rank the shapes differently (FP64 32x32x512: with
@@ -459,10 +458,6 @@ hipError_t autotune(const Geom& g, int device, Tune* t, void* U, const void* goc
         c.zp = opts[i];
         zc.push_back(c);
       }
-      Tune c = *t;
-      c.z3 = 0;
-      c.zp = 0;
-      zc.push_back(c);
     } else {
       zc.push_back(*t);
     }
@@ -553,7 +548,7 @@ void box_release(vie_plan_s* p) {
 }
 
 // Launch shapes of the box, by rule (its first solve does not wait for timing): the
-// three-stage z passes with the most pencils per workgroup that still leave one workgroup per
+// register z passes with the most pencils per workgroup that still leave one workgroup per
 // CU, else with the fewest.
 template <typename T>
 bool box_tune(const Geom& g, size_t budget, Tune* t) {
@@ -1027,7 +1022,7 @@ int vie_plan(vie_plan_t* out, const int grid[3], double h, double k0, double eps
   const size_t zbudget = budget < 65536 ? budget : 65536;
   if (!pick_tune<double>(g, budget, zbudget, &p->t64) || !pick_tune<float>(g, budget, zbudget, &p->t32))
     return bail(fail(nullptr, VIE_EINVAL, "grid does not fit the LDS budget"));
-  if ((e = allow_lds<double>(budget)) || (e = allow_lds<float>(budget)))
+  if ((e = allow_lds<double>(budget, g.M3)) || (e = allow_lds<float>(budget, g.M3)))
     return bail(hipfail(nullptr, e, "hipFuncSetAttribute"));
   // host table
   const auto table = cached_table(grid, p->kappa);

@@ -17,7 +17,7 @@ int curl_table(const int n[3], double kappa, std::complex<double>* out, int nthr
 // Geometry and launch shapes of one operator, passed to the kernel launchers.
 struct Geom {
   int n1, n2, n3;           // voxel grid
-  int M1, M2, M3;           // circulant sizes: powers of two, M3 from 512 on a length of the z3 passes
+  int M1, M2, M3;           // circulant sizes: powers of two, M3 from 64 on a length of the register z passes
   int L1, L2, L3;           // log2 of M (where it is a power of two)
   int H1, H2, H3;           // octant extents M/2 + 1
   long N;                   // voxels
@@ -28,28 +28,30 @@ struct Tune {
   int zthreads;  // threads per workgroup in the z passes
   int cc;        // column chunk in the xy pass
   int xythreads; // threads per workgroup in the xy pass
-  int z3;        // 1: z passes use the three-stage register kernels
+  int z3;        // 1: the register z passes with zp pencils, 0: with one (from M3 = 512 on)
   int xyv;       // xy pass variant; 64 x 64: 0 full plane, 1 x-frequency halves, 2 wide;
                  // 64 x 32: 0 generic padded LDS pass, 1 and 2 register transforms
                  // (1: column exchange areas of their own, 2: exchange in the hand-off)
-  int zp;        // pencils per workgroup in the three-stage z passes (0: the default for M3)
+  int zp;        // pencils per workgroup in the register z passes (0: z3_pencils)
 };
 
 // Number of xy pass variants of a cross-section: 3 for 64 x 64 and 64 x 32, else 1.
 inline int xy_variants(const Geom& g) { return g.M1 == 64 && (g.M2 == 64 || g.M2 == 32) ? 3 : 1; }
 
-// Three-stage z passes (zpass.hip).  Candidate pencil counts for M3 (empty when M3 is not
-// one of their lengths), the first is the default; their shortest length >= need (0: none);
-// the radices of a length; LDS of P pencils.
+// Register z passes (zpass.hip) of M3 >= 64.  Candidate pencil counts for M3 (none below
+// 512); the count without a choice; their shortest length >= need (0: none); the radices of
+// a length; LDS of P pencils.
 template <typename T>
 int z3_pencil_options(int M3, int* out, int cap);
+template <typename T>
+int z3_pencils(int M3, int n1);
 int z3_length(int need);
 bool z3_radices(int M3, int r[3]);
 size_t z3_lds_bytes(int M3, int P);
 // in-place FFT of contiguous lines of M3 values
 hipError_t launch_z3_lines(int M3, long lines, double2* F, const double2* twz, hipStream_t st);
-// Entries of the z twiddle table: W_M3^k, k < M3, and for the three-stage lengths
-// M3 = R1 R2 R3 also W_M3^(t k1) at M3 + R2 R3 k1 + t and W_(R2 R3)^(u k2) at 2 M3 + R3 k2 + u.
+// Entries of the z twiddle table: W_M3^k, k < M3, and for the lengths
+// M3 = R1 R2 R3 of zpass.hip also W_M3^(t k1) at M3 + R2 R3 k1 + t and W_(R2 R3)^(u k2) at 2 M3 + R3 k2 + u.
 inline size_t z_twiddles(int M3) {
   int r[3];
   return z3_radices(M3, r) ? 2 * (size_t)M3 + r[1] * r[2] : M3;

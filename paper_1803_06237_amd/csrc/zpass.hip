@@ -1,14 +1,15 @@
 // Passes 1 and 3 of the matvec (zero-padded z FFT / inverse z FFT with crop and
-// contrast) as three-stage transforms held in registers, for circulant lengths
-// M3 >= 512.
+// contrast) as transforms of two or three stages held in registers, for circulant
+// lengths M3 >= 64.
 //
-// M3 = R1 R2 R3 with radices of 8 to 16 (z3_radices).  With n = u + R3 s + R2 R3 j
+// From 512 on M3 = R1 R2 R3 with radices of 8 to 16 (z3_radices).  With n = u + R3 s + R2 R3 j
 // and k = k1 + R1 k2 + R1 R2 k3 (u, k3 < R3; s, k2 < R2; j, k1 < R1):
 //   A: per t = u + R3 s: R1 points over j, times W_M3^(t k1);
 //   B: per (u, k1): R2 points over s, times W_(R2 R3)^(u k2);
 //   C: per q = k1 + R1 k2: R3 points over u, giving X[q + R1 R2 k3].
 // The inverse runs C, B, A with conjugate twiddles.  The zero padding (x[n] = 0 for
-// n >= n3) and the crop (only n < n3 kept) are half of A's R1 values.
+// n >= n3) and the crop (only n < n3 kept) are half of A's R1 values.  Up to 256 points
+// M3 = R1 R2 (R3 = 1 below): A and then, in C's place, R2 points over t for each k1.
 //
 // A workgroup handles P pencils of consecutive i1 at fixed (component, i2), one
 // task of each stage per thread.  A's threads run along z, the contiguous axis of
@@ -24,7 +25,9 @@
 // and staged U through LDS a third time, and against the generic LDS passes, the better
 // of them for long FP64 pencils, forward + inverse in us: FP64 30 x 12 pencils of 4096
 // 131 -> 85, 32 x 32 of 4096 422 -> 227 (floor at the copy rate 64 + 92), of 1024
-// 52 -> 50; FP32 67 -> 57, 129 -> 105, 36 -> 31.
+// 52 -> 50; FP32 67 -> 57, 129 -> 105, 36 -> 31.  Two stages against the generic passes:
+// 8 x 8 pencils of 64 15.5 -> 13, 16 x 16 of 128 26 -> 15, 32 x 32 of 256 33 -> 26; FP32
+// 32 x 32 of 256 36 -> 22.
 #include <hip/hip_runtime.h>
 
 #include "block_maps.hpp"
@@ -44,12 +47,13 @@ template <> struct Z3Elem<double> { using type = double; };
 // follow 32 / P apart for the (p, q) lanes of C.
 template <int R1, int R2, int R3>
 struct Z3Map {
-  static constexpr int M = R1 * R2 * R3, N1 = R2 * R3, TB = R1 * R3, Q = R1 * R2;
+  static constexpr bool two = R3 == 1;   // C: Q tasks of RC points
+  static constexpr int M = R1 * R2 * R3, N1 = R2 * R3, TB = R1 * R3, Q = two ? R1 : R1 * R2, RC = two ? R2 : R3;
   static constexpr int TM = N1 > TB ? (N1 > Q ? N1 : Q) : (TB > Q ? TB : Q);   // threads of a pencil
   static constexpr int mod_up(int v, int r) { return v + ((r - v) % 32 + 32) % 32; }   // least >= v, = r mod 32
-  static constexpr int N1p = mod_up(N1, R3), Qp = mod_up(Q, (32 + R3 / 2) / R3);
-  static constexpr int S = R1 * N1p > R3 * Qp ? R1 * N1p : R3 * Qp;
-  __host__ __device__ static constexpr int pencil(int P) { return mod_up(S, 32 / P); }
+  static constexpr int N1p = two ? N1 | 1 : mod_up(N1, R3), Qp = mod_up(Q, (32 + R3 / 2) / R3);
+  static constexpr int S = two || R1 * N1p > R3 * Qp ? R1 * N1p : R3 * Qp;
+  __host__ __device__ static constexpr int pencil(int P) { return two ? mod_up(S, R2 % 32) : mod_up(S, 32 / P); }
 };
 
 // v[k] of this thread to slot wa(k), k < NW; then w[j] from slot ra(j), j < NR.  S is
@@ -106,23 +110,30 @@ __device__ __forceinline__ void z3_forward(cx<T>* v, cx<T>* z, int np, int P, gp
 #pragma unroll
     for (int k = 1; k < R1; ++k) v[k] = cmul(v[k], tw[L::M + k * L::N1 + t]);
   }
-  const int pb = tid / L::TB, rb = tid % L::TB, u = rb % R3, k1 = rb / R3;
-  cx<T> w[R2];
-  z3_exchange<R1, R2>(
-      v, w, S, pa < np, pb < np, [&](int k) { return pa * PS + k * L::N1p + t; },
-      [&](int s) { return pb * PS + k1 * L::N1p + u + R3 * s; });
-  if (pb < np) {
-    dft_codelet<T, false, R2>(w);
-#pragma unroll
-    for (int k = 1; k < R2; ++k) w[k] = cmul(w[k], tw[2 * L::M + k * R3 + u]);
-  }
-  __syncthreads();
   const int pc = tid & (P - 1), q = tid >> (31 - __clz(P));
   const bool on = pc < np && q < L::Q;
-  z3_exchange<R2, R3>(
-      w, z, S, pb < np, on, [&](int k) { return pb * PS + u * L::Qp + k1 + R1 * k; },
-      [&](int j) { return pc * PS + j * L::Qp + q; });
-  if (on) dft_codelet<T, false, R3>(z);
+  if constexpr (L::two) {
+    z3_exchange<R1, R2>(
+        v, z, S, pa < np, on, [&](int k) { return pa * PS + k * L::N1p + t; },
+        [&](int j) { return pc * PS + q * L::N1p + j; });
+    if (on) dft_codelet<T, false, R2>(z);
+  } else {
+    const int pb = tid / L::TB, rb = tid % L::TB, u = rb % R3, k1 = rb / R3;
+    cx<T> w[R2];
+    z3_exchange<R1, R2>(
+        v, w, S, pa < np, pb < np, [&](int k) { return pa * PS + k * L::N1p + t; },
+        [&](int s) { return pb * PS + k1 * L::N1p + u + R3 * s; });
+    if (pb < np) {
+      dft_codelet<T, false, R2>(w);
+#pragma unroll
+      for (int k = 1; k < R2; ++k) w[k] = cmul(w[k], tw[2 * L::M + k * R3 + u]);
+    }
+    __syncthreads();
+    z3_exchange<R2, R3>(
+        w, z, S, pb < np, on, [&](int k) { return pb * PS + u * L::Qp + k1 + R1 * k; },
+        [&](int j) { return pc * PS + j * L::Qp + q; });
+    if (on) dft_codelet<T, false, R3>(z);
+  }
 }
 
 template <typename T, int R1, int R2, int R3>
@@ -145,14 +156,14 @@ __device__ __forceinline__ void zfwd3_body(gptr<const cx<T>> __restrict__ x, gpt
       }
     }
   }
-  cx<T> z[R3];
+  cx<T> z[L::RC];
   z3_forward<T, R1, R2, R3, false>(v, z, np, P, tw, S, tid);
   const int p = tid & (P - 1), q = tid >> (31 - __clz(P));
   if (p < np && q < L::Q) {
     const long plane = 3L * g.n1 * g.n2;
     gptr<cx<T>> dst = U + ((long)c * g.n2 + i2) * g.n1 + i1_0 + p;
 #pragma unroll
-    for (int k = 0; k < R3; ++k) dst[(long)(q + L::Q * k) * plane] = z[k];
+    for (int k = 0; k < L::RC; ++k) dst[(long)(q + L::Q * k) * plane] = z[k];
   }
 }
 
@@ -168,33 +179,39 @@ __device__ __forceinline__ void zinv3_body(gptr<const cx<T>> __restrict__ U, gpt
   const int i2 = pk.i2, c = pk.c, i1_0 = pk.i1_0, np = pk.np;
   const int pc = tid & (P - 1), q = tid >> (31 - __clz(P));
   const bool on = pc < np && q < L::Q;
-  cx<T> z[R3];
+  cx<T> z[L::RC];
   if (on) {
     const long plane = 3L * g.n1 * g.n2;
     gptr<const cx<T>> src = U + ((long)c * g.n2 + i2) * g.n1 + i1_0 + pc;
 #pragma unroll
-    for (int k = 0; k < R3; ++k) z[k] = src[(long)(q + L::Q * k) * plane];
-    dft_codelet<T, true, R3>(z);
-    const int k2 = q / R1;
+    for (int k = 0; k < L::RC; ++k) z[k] = src[(long)(q + L::Q * k) * plane];
+    dft_codelet<T, true, L::RC>(z);
+    const int row = L::two ? L::M + q * R2 : 2 * L::M + q / R1 * R3;
 #pragma unroll
-    for (int j = 1; j < R3; ++j) z[j] = cmulc(z[j], tw[2 * L::M + k2 * R3 + j]);
+    for (int j = 1; j < L::RC; ++j) z[j] = cmulc(z[j], tw[row + j]);
   }
-  const int pb = tid / L::TB, rb = tid % L::TB, u = rb % R3, k1 = rb / R3;
-  cx<T> w[R2];
-  z3_exchange<R3, R2>(
-      z, w, S, on, pb < np, [&](int j) { return pc * PS + j * L::Qp + q; },
-      [&](int k) { return pb * PS + u * L::Qp + k1 + R1 * k; });
-  if (pb < np) {
-    dft_codelet<T, true, R2>(w);
-#pragma unroll
-    for (int s = 0; s < R2; ++s) w[s] = cmulc(w[s], tw[L::M + k1 * L::N1 + u + R3 * s]);
-  }
-  __syncthreads();
   const int pa = tid / L::N1, t = tid % L::N1;
   cx<T> v[R1];
-  z3_exchange<R2, R1>(
-      w, v, S, pb < np, pa < np, [&](int s) { return pb * PS + k1 * L::N1p + u + R3 * s; },
-      [&](int k) { return pa * PS + k * L::N1p + t; });
+  if constexpr (L::two) {
+    z3_exchange<R2, R1>(
+        z, v, S, on, pa < np, [&](int j) { return pc * PS + q * L::N1p + j; },
+        [&](int k) { return pa * PS + k * L::N1p + t; });
+  } else {
+    const int pb = tid / L::TB, rb = tid % L::TB, u = rb % R3, k1 = rb / R3;
+    cx<T> w[R2];
+    z3_exchange<R3, R2>(
+        z, w, S, on, pb < np, [&](int j) { return pc * PS + j * L::Qp + q; },
+        [&](int k) { return pb * PS + u * L::Qp + k1 + R1 * k; });
+    if (pb < np) {
+      dft_codelet<T, true, R2>(w);
+#pragma unroll
+      for (int s = 0; s < R2; ++s) w[s] = cmulc(w[s], tw[L::M + k1 * L::N1 + u + R3 * s]);
+    }
+    __syncthreads();
+    z3_exchange<R2, R1>(
+        w, v, S, pb < np, pa < np, [&](int s) { return pb * PS + k1 * L::N1p + u + R3 * s; },
+        [&](int k) { return pa * PS + k * L::N1p + t; });
+  }
   if (pa < np) {
     dft_codelet<T, true, R1>(v);
     // the kept outputs, in registers here (else their arithmetic sinks into the conditional
@@ -242,7 +259,7 @@ __global__ __launch_bounds__(1024) void k_z3_lines(double2* __restrict__ F, cons
   using L = Z3Map<R1, R2, R3>;
   double2* line = F + (long)blockIdx.x * L::M;
   const int tid = threadIdx.x;
-  double2 v[R1], z[R3];
+  double2 v[R1], z[L::RC];
   if (tid < L::N1) {
 #pragma unroll
     for (int j = 0; j < R1; ++j) v[j] = line[tid + L::N1 * j];
@@ -250,7 +267,7 @@ __global__ __launch_bounds__(1024) void k_z3_lines(double2* __restrict__ F, cons
   z3_forward<double, R1, R2, R3, true>(v, z, 1, 1, (gptr<const double2>)tw, reinterpret_cast<double*>(smem_raw), tid);
   if (tid < L::Q) {
 #pragma unroll
-    for (int k = 0; k < R3; ++k) line[tid + L::Q * k] = z[k];
+    for (int k = 0; k < L::RC; ++k) line[tid + L::Q * k] = z[k];
   }
 }
 
@@ -304,6 +321,15 @@ __global__ __launch_bounds__(1024) void k_zinv3_batch(const PassDesc* __restrict
 // multiple of 16, which the plane order of the cross-section passes wants, and at most 1.25
 // times the one before.
 #define VIE_Z3_LENGTHS(X) \
+  X(8, 8, 1)              \
+  X(10, 8, 1)             \
+  X(12, 8, 1)             \
+  X(16, 8, 1)             \
+  X(12, 12, 1)            \
+  X(16, 10, 1)            \
+  X(16, 12, 1)            \
+  X(16, 15, 1)            \
+  X(16, 16, 1)            \
   X(8, 8, 8)              \
   X(8, 8, 10)             \
   X(8, 8, 12)             \
@@ -368,12 +394,13 @@ int z3_length(int need) {
 
 // Pencil counts P tried by the plan-time tuner, default first, by the power of two the
 // length belongs to; each keeps the workgroup within 1024 threads and its LDS within
-// 160 KiB.
+// 160 KiB.  None below 512 points, where P is the power of two that holds a row of pencils,
+// up to 128 bytes of the intermediate (z3_pencils): a workgroup has few waves anyway.
 template <typename T>
 int z3_pencil_options(int M3, int* out, int cap) {
   const bool dbl = sizeof(T) == 8;
   int r[3];
-  if (!z3_radices(M3, r)) return 0;
+  if (M3 < 512 || !z3_radices(M3, r)) return 0;
   int opts[6] = {0, 0, 0, 0, 0, 0}, n = 0;
   if (M3 <= 512) {
     if (dbl) { opts[0] = 8; opts[1] = 4; opts[2] = 16; opts[3] = 2; n = 4; }
@@ -392,6 +419,15 @@ int z3_pencil_options(int M3, int* out, int cap) {
   return n;
 }
 
+template <typename T>
+int z3_pencils(int M3, int n1) {
+  int opts[8];
+  if (z3_pencil_options<T>(M3, opts, 8)) return opts[0];
+  int P = 1;
+  while (P < n1 && P < (sizeof(T) == 8 ? 8 : 16)) P *= 2;
+  return P;
+}
+
 size_t z3_lds_bytes(int M3, int P) {
   Z3Shape s;
   return z3_shape(M3, P, &s) ? (size_t)P * s.pencil * 8 : 0;
@@ -401,13 +437,8 @@ template <typename T>
 hipError_t launch_z3(int which, const Geom& g, int P, const void* x, void* y, const void* b, int mode, void* U,
                      const void* chi, const void* twz, hipStream_t st) {
   using C = cx<T>;
-  int opts[8];
-  const int n = z3_pencil_options<T>(g.M3, opts, 8);
-  if (n == 0) return hipErrorNotSupported;
-  if (P == 0) P = opts[0];
-  bool ok = P == 1;
-  for (int i = 0; i < n; ++i) ok = ok || opts[i] == P;
-  if (!ok) return hipErrorNotSupported;
+  if (P == 0) P = z3_pencils<T>(g.M3, g.n1);
+  if (P < 1 || P > 16 || (P & (P - 1)) || z3_threads(g.M3, P) > 1024) return hipErrorNotSupported;
   const dim3 grid(pencil_blocks(g.n1, g.n2, P)), block(z3_threads(g.M3, P));
   const size_t lds = z3_lds_bytes(g.M3, P);
 #define VIE_Z3(A, B, D)                                                                                        \
@@ -459,20 +490,23 @@ hipError_t launch_z3_batch(int which, int mode, const PassDesc* d, const int* pr
   return hipErrorNotSupported;
 }
 
+// large LDS for the passes of length M3
 template <typename T>
-hipError_t allow_lds_z3() {
+hipError_t allow_lds_z3(int M3) {
   const int big = 160 * 1024;
   hipError_t e = hipSuccess;
   auto allow = [&](const void* k) {
     if (!e) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, big);
   };
 #define VIE_Z3(A, B, D)                              \
-  allow((const void*)k_zfwd3<T, A, B, D>);           \
-  allow((const void*)k_zinv3<T, A, B, D, 0>);        \
-  allow((const void*)k_zinv3<T, A, B, D, 1>);        \
-  allow((const void*)k_zfwd3_batch<T, A, B, D>);     \
-  allow((const void*)k_zinv3_batch<T, A, B, D, 0>);  \
-  allow((const void*)k_zinv3_batch<T, A, B, D, 1>);
+  if (M3 == A * B * D) {                             \
+    allow((const void*)k_zfwd3<T, A, B, D>);          \
+    allow((const void*)k_zinv3<T, A, B, D, 0>);       \
+    allow((const void*)k_zinv3<T, A, B, D, 1>);       \
+    allow((const void*)k_zfwd3_batch<T, A, B, D>);    \
+    allow((const void*)k_zinv3_batch<T, A, B, D, 0>); \
+    allow((const void*)k_zinv3_batch<T, A, B, D, 1>); \
+  }
   VIE_Z3_LENGTHS(VIE_Z3)
 #undef VIE_Z3
   return e;
@@ -484,8 +518,10 @@ template hipError_t launch_z3<float>(int, const Geom&, int, const void*, void*, 
                                      const void*, const void*, hipStream_t);
 template int z3_pencil_options<double>(int, int*, int);
 template int z3_pencil_options<float>(int, int*, int);
-template hipError_t allow_lds_z3<double>();
-template hipError_t allow_lds_z3<float>();
+template int z3_pencils<double>(int, int);
+template int z3_pencils<float>(int, int);
+template hipError_t allow_lds_z3<double>(int);
+template hipError_t allow_lds_z3<float>(int);
 template hipError_t launch_z3_batch<double>(int, int, const PassDesc*, const int*, int, int, int, int, int, int,
                                             hipStream_t);
 template hipError_t launch_z3_batch<float>(int, int, const PassDesc*, const int*, int, int, int, int, int, int,

@@ -323,18 +323,18 @@ def test_register_cross_section_with_many_planes_sampled_outputs():
     assert _sparse_sample_check(vie, wg, nnz=16, nout=48, precision=32, seed=6) < 5e-6
 
 
-# circulant lengths of the three-stage z passes; each with the fewest and the most z voxels
-Z_LENGTHS = [512, 640, 768, 800, 960, 1024, 1152, 1280, 1440, 1600, 1920, 2048, 2304, 2560, 2880, 3072, 3600, 4096]
+# circulant lengths of the register z passes; each with the fewest and the most z voxels
+Z_LENGTHS = [64, 80, 96, 128, 144, 160, 192, 240, 256, 512, 640, 768, 800, 960, 1024, 1152, 1280, 1440, 1600, 1920, 2048, 2304, 2560, 2880, 3072, 3600, 4096]
 
 
 @pytest.mark.parametrize("length", Z_LENGTHS)
 @pytest.mark.parametrize("edge", ["least", "most"])
 def test_z_lengths_match_the_oracle(length, edge):
-    """5 pencils of 2 rows per component: full and incomplete pencil blocks, with every
+    """3 pencils of one row per component: full and incomplete pencil blocks, with every
     pencil count that the plan accepts, the residual form included."""
     vie = _dev()
-    below = max((v for v in Z_LENGTHS if v < length), default=256)
-    n = (5, 2, length // 2 if edge == "most" else below // 2 + 1)
+    below = max((v for v in Z_LENGTHS if v < length), default=32)
+    n = (3, 1, length // 2 if edge == "most" else below // 2 + 1)
     rng = np.random.default_rng(length + n[2])
     kap = mv.kappa_of(H, K0, EPSB)
     spec = mv.spectrum(green.green_table(n, kap))
@@ -358,7 +358,7 @@ def test_z_lengths_match_the_oracle(length, edge):
             if precision == 0:
                 res = plan.residual(_t(x), _t(b)).cpu().numpy()
                 assert np.linalg.norm(res - (b - want)) / np.linalg.norm(b - want) < bar
-        assert tried >= 3
+        assert tried >= (3 if length >= 512 else 1)
 
 
 TUNED_GRIDS = {
