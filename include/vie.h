@@ -352,7 +352,9 @@ int vie_profile_matvec(vie_plan_t plan, int precision, const void* x, void* y, i
  * vie_net_train_step: one Adam step (lr) on the mean squared error between
  *   net(r_i s) and (target_i - r_i) s over `count` samples (device pointers,
  *   3N / N / 3N), i.e. z = r + net approximates target;
- *   *loss receives the mean loss.  Synchronises.
+ *   *loss receives the mean loss.  Synchronises.  Up to four samples run
+ *   together; the first step with more samples than before enlarges the
+ *   activation buffers (where memory is short, fewer run together).
  * vie_set_preconditioner: attach a network with the plan's grid (NULL detaches);
  *   vie_solve with precision 2 uses it.  The plan does not own the network.
  * vie_nn_conv_test: diagnostic single layer on FP32 device buffers (rounded to

@@ -330,6 +330,33 @@ def test_train_step_loss_and_gradients_match_oracle():
     assert np.array_equal(w1[go == 0], w0[go == 0])
 
 
+@pytest.mark.parametrize("count", [2, 4, 5, 8])
+def test_grouped_samples_equal_single_ones(count):
+    """Samples of a step that share launches (groups of up to four; 24 voxels give three slices
+    on the deepest level, half a tile more than one) against one step per sample: the loss is
+    the mean, and for power-of-two counts, where the loss gradient scales exactly, so are the
+    weight gradients up to the order of their FP32 sums."""
+    vie = _dev()
+    n = (24, 8, 16)
+    g = torch.Generator(device="cuda").manual_seed(count)
+    c = lambda *k: torch.randn(*k, n[0] * n[1] * n[2], dtype=torch.complex128, device="cuda", generator=g)
+    samples = [(c(3), 0.3 * c(1)[0], c(3)) for _ in range(count)]
+    step = lambda net, part: net.train_step(*(list(v) for v in zip(*part)), lr=0.0)
+    losses, grads = [], []
+    for q in samples:
+        net = vie.Net(n, seed=5)
+        losses.append(step(net, [q]))
+        grads.append(net.get_grads().astype(np.float64))
+    net = vie.Net(n, seed=5)
+    w0 = net.get_params()
+    loss = step(net, samples)
+    assert abs(loss - np.mean(losses)) <= 1e-12 * np.mean(losses)
+    assert np.array_equal(net.get_params(), w0)
+    got, want = net.get_grads().astype(np.float64), np.mean(grads, axis=0)
+    # FP32 sums over 3072 voxels a sample; otherwise also the bfloat16 rounding of gscale d
+    assert np.linalg.norm(got - want) <= (1e-5 if count != 5 else 2.0 ** -8) * np.linalg.norm(want)
+
+
 def test_network_with_base_vector_is_bit_exact_on_the_integer_case():
     """vie_net_apply_base: the base vector enters input channels 8-13 and the output is
     added to it; integer base vectors keep every sum exact."""
