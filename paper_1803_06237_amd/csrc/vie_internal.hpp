@@ -40,21 +40,22 @@ inline int xy_variants(const Geom& g) { return g.M1 == 64 && (g.M2 == 64 || g.M2
 
 // Register z passes (zpass.hip) of M3 >= 64.  Candidate pencil counts for M3 (none below
 // 512); the count without a choice; their shortest length >= need (0: none); the radices of
-// a length; LDS of P pencils.
+// a length, forward and inverse; LDS of P pencils.
 template <typename T>
 int z3_pencil_options(int M3, int* out, int cap);
 template <typename T>
 int z3_pencils(int M3, int n1);
 int z3_length(int need);
-bool z3_radices(int M3, int r[3]);
+bool z3_radices(int M3, int r[3], bool inverse = false);
 size_t z3_lds_bytes(int M3, int P);
 // in-place FFT of contiguous lines of M3 values
 hipError_t launch_z3_lines(int M3, long lines, double2* F, const double2* twz, hipStream_t st);
-// Entries of the z twiddle table: W_M3^k, k < M3, and for the lengths
-// M3 = R1 R2 R3 of zpass.hip also W_M3^(t k1) at M3 + R2 R3 k1 + t and W_(R2 R3)^(u k2) at 2 M3 + R3 k2 + u.
+// Entries of the z twiddle table: W_M3^k, k < M3, and for the lengths M3 = R1 R2 R3 of
+// zpass.hip the forward pass's W_M3^(t k1) in order R2 R3 k1 + t and W_(R2 R3)^(u k2) in order
+// R3 k2 + u, then the inverse pass's.
 inline size_t z_twiddles(int M3) {
-  int r[3];
-  return z3_radices(M3, r) ? 2 * (size_t)M3 + r[1] * r[2] : M3;
+  int f[3], i[3];
+  return z3_radices(M3, f) && z3_radices(M3, i, true) ? 3 * (size_t)M3 + f[1] * f[2] + i[1] * i[2] : M3;
 }
 
 // ---- matvec passes (kernels.hip) ----------------------------------------

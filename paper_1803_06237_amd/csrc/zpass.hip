@@ -25,10 +25,12 @@
 // and staged U through LDS a third time, and against the generic LDS passes, the better
 // of them for long FP64 pencils, forward + inverse in us: FP64 30 x 12 pencils of 4096
 // 131 -> 85, 32 x 32 of 4096 422 -> 227 (floor at the copy rate 64 + 92), of 1024
-// 52 -> 50; FP32 67 -> 57, 129 -> 105, 36 -> 31.  Two stages against the generic passes:
+// 52 -> 45; FP32 67 -> 57, 129 -> 105, 36 -> 31.  Two stages against the generic passes:
 // 8 x 8 pencils of 64 15.5 -> 13, 16 x 16 of 128 26 -> 15, 32 x 32 of 256 33 -> 26; FP32
 // 32 x 32 of 256 36 -> 22.
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
 
 #include "block_maps.hpp"
 #include "dft_codelets.hpp"
@@ -37,6 +39,14 @@
 namespace vie {
 
 namespace {
+
+// The lists below give the inverse's radices; the forward pass takes them in reverse where
+// that leaves an even first one, so that both run the small radix, with every thread busy,
+// on their loads and the large one on their stores (FP64 32 x 32 pencils of 1024, us: forward
+// 20.6 as 8, 8, 16 and 25.9 as 16, 8, 8, inverse 27.3 and 25.0).
+constexpr bool z3_reverse(int R3) { return R3 != 1 && R3 % 2 == 0; }
+constexpr int z3_first(int R1, int R3) { return z3_reverse(R3) ? R3 : R1; }
+constexpr int z3_last(int R1, int R3) { return z3_reverse(R3) ? R1 : R3; }
 
 template <typename T> struct Z3Elem { using type = cx<T>; };
 template <> struct Z3Elem<double> { using type = double; };
@@ -96,8 +106,8 @@ __device__ __forceinline__ void z3_exchange(const float2* v, float2* w, float2* 
 
 // Forward stages from A's inputs v[0, R1) (LINE: all of them, else the lower half) of
 // the tasks (p, t) to C's outputs z[k3] of the tasks (p3, q).  tw: the plan's tables,
-// W_M3 in natural order, W_M3^(t k1) at M3 + N1 k1 + t, W_(R2 R3)^(u k2) at
-// 2 M3 + R3 k2 + u.
+// W_M3 in natural order, then for the forward radices W_M3^(t k1) at M3 + N1 k1 + t and
+// W_(R2 R3)^(u k2) at 2 M3 + R3 k2 + u, then the same for the inverse's.
 template <typename T, int R1, int R2, int R3, bool LINE>
 __device__ __forceinline__ void z3_forward(cx<T>* v, cx<T>* z, int np, int P, gptr<const cx<T>> tw,
                                            typename Z3Elem<T>::type* S, int tid) {
@@ -175,6 +185,7 @@ __device__ __forceinline__ void zinv3_body(gptr<const cx<T>> __restrict__ U, gpt
                                            typename Z3Elem<T>::type* S, int tid) {
   using L = Z3Map<R1, R2, R3>;
   const int PS = L::pencil(P);
+  tw += L::M + R2 * z3_last(R1, R3);   // past the forward tables
   const PencilBlock pk = pencil_block(blk, g.n1, g.n2, P);
   const int i2 = pk.i2, c = pk.c, i1_0 = pk.i1_0, np = pk.np;
   const int pc = tid & (P - 1), q = tid >> (31 - __clz(P));
@@ -316,7 +327,7 @@ __global__ __launch_bounds__(1024) void k_zinv3_batch(const PassDesc* __restrict
   }
 }
 
-// Every length with its radices: the first even (half of its inputs are padding), all near each
+// Every length with the inverse's radices: the first even (half of its inputs are padding), all near each
 // other (a pencil has as many threads as its stage of smallest radix has tasks), the length a
 // multiple of 16, which the plane order of the cross-section passes wants, and at most 1.25
 // times the one before.
@@ -356,7 +367,8 @@ struct Z3Shape {
 bool z3_shape(int M3, int P, Z3Shape* s) {
 #define VIE_Z3(A, B, C)                                                    \
   if (M3 == A * B * C) {                                                   \
-    *s = {Z3Map<A, B, C>::TM, Z3Map<A, B, C>::pencil(P)};                  \
+    using F = Z3Map<z3_first(A, C), B, z3_last(A, C)>;                      \
+    *s = {F::TM, std::max(F::pencil(P), Z3Map<A, B, C>::pencil(P))};        \
     return true;                                                           \
   }
   VIE_Z3_LENGTHS(VIE_Z3)
@@ -370,13 +382,13 @@ int z3_threads(int M3, int P) {
 
 }  // namespace
 
-bool z3_radices(int M3, int r[3]) {
-#define VIE_Z3(A, B, C)   \
-  if (M3 == A * B * C) {  \
-    r[0] = A;             \
-    r[1] = B;             \
-    r[2] = C;             \
-    return true;          \
+bool z3_radices(int M3, int r[3], bool inverse) {
+#define VIE_Z3(A, B, C)                     \
+  if (M3 == A * B * C) {                    \
+    r[0] = inverse ? A : z3_first(A, C);    \
+    r[1] = B;                               \
+    r[2] = inverse ? C : z3_last(A, C);     \
+    return true;                            \
   }
   VIE_Z3_LENGTHS(VIE_Z3)
 #undef VIE_Z3
@@ -444,7 +456,8 @@ hipError_t launch_z3(int which, const Geom& g, int P, const void* x, void* y, co
 #define VIE_Z3(A, B, D)                                                                                        \
   if (g.M3 == A * B * D) {                                                                                     \
     if (which == 0)                                                                                            \
-      hipLaunchKernelGGL((k_zfwd3<T, A, B, D>), grid, block, lds, st, (const C*)x, (C*)U, g, P, (const C*)twz);  \
+      hipLaunchKernelGGL((k_zfwd3<T, z3_first(A, D), B, z3_last(A, D)>), grid, block, lds, st, (const C*)x, (C*)U,    \
+                         g, P, (const C*)twz);                                                                   \
     else if (mode == 0)                                                                                        \
       hipLaunchKernelGGL((k_zinv3<T, A, B, D, 0>), grid, block, lds, st, (const C*)U, (const C*)x, (C*)y,        \
                          (const C*)nullptr, (const C*)chi, g, P, (const C*)twz);                                \
@@ -462,7 +475,8 @@ hipError_t launch_z3_lines(int M3, long lines, double2* F, const double2* twz, h
   const size_t lds = z3_lds_bytes(M3, 1);
 #define VIE_Z3(A, B, D)                                                                                       \
   if (M3 == A * B * D) {                                                                                      \
-    hipLaunchKernelGGL((k_z3_lines<A, B, D>), dim3((unsigned)lines), dim3(z3_threads(M3, 1)), lds, st, F, twz); \
+    hipLaunchKernelGGL((k_z3_lines<z3_first(A, D), B, z3_last(A, D)>), dim3((unsigned)lines),                  \
+                       dim3(z3_threads(M3, 1)), lds, st, F, twz);                                             \
     return hipGetLastError();                                                                                 \
   }
   VIE_Z3_LENGTHS(VIE_Z3)
@@ -478,7 +492,8 @@ hipError_t launch_z3_batch(int which, int mode, const PassDesc* d, const int* pr
 #define VIE_Z3(A, B, D)                                                                                          \
   if (M3 == A * B * D) {                                                                                         \
     if (which == 0)                                                                                              \
-      hipLaunchKernelGGL((k_zfwd3_batch<T, A, B, D>), grid, block, lds, st, d, prefix, nsys, total, jx, jy);       \
+      hipLaunchKernelGGL((k_zfwd3_batch<T, z3_first(A, D), B, z3_last(A, D)>), grid, block, lds, st, d, prefix,   \
+                         nsys, total, jx, jy);                                                                   \
     else if (mode == 0)                                                                                          \
       hipLaunchKernelGGL((k_zinv3_batch<T, A, B, D, 0>), grid, block, lds, st, d, prefix, nsys, total, jx, jy);    \
     else                                                                                                         \
@@ -500,10 +515,10 @@ hipError_t allow_lds_z3(int M3) {
   };
 #define VIE_Z3(A, B, D)                              \
   if (M3 == A * B * D) {                             \
-    allow((const void*)k_zfwd3<T, A, B, D>);          \
+    allow((const void*)k_zfwd3<T, z3_first(A, D), B, z3_last(A, D)>);       \
     allow((const void*)k_zinv3<T, A, B, D, 0>);       \
     allow((const void*)k_zinv3<T, A, B, D, 1>);       \
-    allow((const void*)k_zfwd3_batch<T, A, B, D>);    \
+    allow((const void*)k_zfwd3_batch<T, z3_first(A, D), B, z3_last(A, D)>); \
     allow((const void*)k_zinv3_batch<T, A, B, D, 0>); \
     allow((const void*)k_zinv3_batch<T, A, B, D, 1>); \
   }
