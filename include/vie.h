@@ -206,22 +206,25 @@ int vie_solve_noalloc(vie_plan_t plan, const vie_c128* b, vie_c128* x, double to
  * GMRES(restart) preconditioned by inner_restart FP32 GMRES steps (plans built
  * with VIE_WITH_FP32); 3: FP64 flexible GMRES(restart) preconditioned by each
  * plan's block circulant (vie_circulant_build on every plan first; systems of
- * one plan share it).  With opts->use_graph one restart cycle is captured as a
- * HIP graph and replayed (precisions 0 and 1; precision 3 chooses the systems to
- * precondition on the host each cycle and runs eagerly).  rhs[s], x[s]: device, 3N_s values each, x[s] out
- * (in with use_x0).  infos: host array of count entries or NULL.  Runs on a
+ * one plan share it).  With opts->use_graph the second restart cycle is captured
+ * as a HIP graph and replayed from then on (precisions 0 and 1; precision 3 chooses
+ * the systems to precondition on the host each cycle and runs eagerly).  rhs[s],
+ * x[s]: device, 3N_s values each, x[s] out (in with use_x0).  infos: host array of count entries or NULL.  Runs on a
  * stream of its own after synchronising the first plan's stream; returns
  * synchronised.  Returns VIE_OK when every system converged, else the first
  * non-OK status (each system's status is in infos[s].status).  A plan may appear
  * several times (same operator, different right-hand sides): each system gets
  * its own intermediate buffers.  As in vie_solve, each system's Krylov vectors hold
  * only its support columns (n_s = 3 |S_s| n3 values; the system solved is
- * A_SS x_S = b_S - (A b_off)_S, and x = b off the support), and every product is
- * a batched scatter into full-length buffers, the three passes and a batched
- * gather.  Device memory per system is about 16 ((restart + 1 [+ restart when
- * flexible] + 3) n_s + 2 (3 N_s) + 3 n1 n2 M3) bytes, the last term the
- * intermediate of the passes, and the mixed tier adds half as much again for
- * its FP32 level (inner_restart + 3 vectors of n_s).  A right-hand side with a
+ * A_SS x_S = b_S - (A b_off)_S, and x = b off the support), and every product
+ * runs on the bounding box of the support where that has a smaller circulant
+ * (N_s, n1, n2, M3 below are then the box's): the three passes, between a batched
+ * scatter into full-length buffers and a batched gather unless the support fills
+ * the box.  Device memory per system is about 16 ((restart + 1 [+ restart when
+ * flexible] + 3) n_s + 2 (3 N_s) [not when filled] + 3 n1 n2 M3) bytes, the last
+ * term the intermediate of the passes, and the mixed tier adds half as much again
+ * for its FP32 level (inner_restart + 3 vectors of n_s); it is taken in blocks of
+ * up to 256 MiB, the last of them in part unused.  A right-hand side with a
  * non-finite value gives VIE_EINVAL.
  */
 int vie_solve_batch(vie_plan_t const* plans, const vie_c128* const* rhs, vie_c128* const* x, int count,
