@@ -85,11 +85,29 @@ static inline size_t conv2_lds(int taps, int nt) {
   return (size_t)2 * ConvTile<TZ, MT>::hvox * 8 * 2 + (size_t)(taps == 1 ? 1 : kPairs) * nt * 64 * 16;
 }
 
+// Inference folds its neighbours into the convolutions (each was a launch of 5 to 8 us of a
+// 215 us apply at 32 x 32 x 256, APPLY_US without): the first `chunks` 16-channel chunks of
+// the input read their parents in a volume of half the size (nearest upsampling), and the
+// last layer's output goes straight into the result.
+struct ConvUp {
+  const bf16_t* X = nullptr;
+  int cs = 0, chunks = 0;
+};
+// z_c = base_c + (out[2c] + i out[2c + 1]) / s, s = sqrt(3 N / sumsq): the network predicts the
+// correction A^{-1} r - base, so an untrained (small) network leaves the base preconditioner
+// (or the identity)
+struct NetOut {
+  const double2* base = nullptr;
+  const double2* sumsq = nullptr;
+  double2* z = nullptr;
+};
+
 template <int TAPS, int NT, int TZ, int MT>
 __global__ __launch_bounds__(256) void k_conv2(const bf16_t* __restrict__ X, int xcs, int xco, int Cin,
                                                const bf16_t* __restrict__ Wt, int Cout, bf16_t* __restrict__ Y,
                                                int ycs, int yco, float* __restrict__ Yf, Vol vol, int relu,
-                                               const bf16_t* __restrict__ mask, int mcs, int mco, int n0) {
+                                               const bf16_t* __restrict__ mask, int mcs, int mco, int n0,
+                                               ConvUp up, NetOut res) {
   using Tl = ConvTile<TZ, MT>;
   constexpr int kHx = Tl::hx, kHy = Tl::hy, kHvox = Tl::hvox;
   constexpr int MI = TZ * MT;                  // M-tiles per wave
@@ -123,9 +141,16 @@ __global__ __launch_bounds__(256) void k_conv2(const bf16_t* __restrict__ X, int
     const bool in = xx >= 0 && xx < vol.W && yy >= 0 && yy < vol.H && zz >= 0 && zz < vol.D;
     return in ? (zz * vol.H + yy) * vol.W + xx : -1;
   };
+  auto halo_parent = [&](int e) {              // the same of the coarse volume
+    const int hv = e >> 1;
+    const int xx = x0 + hv % kHx - 1, yy = y0 + (hv / kHx) % kHy - 1, zz = z0 + hv / (kHx * kHy) - 1;
+    const bool in = xx >= 0 && xx < vol.W && yy >= 0 && yy < vol.H && zz >= 0 && zz < vol.D;
+    return in ? ((zz >> 1) * (vol.H / 2) + (yy >> 1)) * (vol.W / 2) + (xx >> 1) : -1;
+  };
+  // v: the halo voxel, or its parent for an upsampled chunk
   auto halo_load = [&](int e, int v, int ch) {
-    return v >= 0 ? *reinterpret_cast<const u4v*>(X + (long)v * xcs + xco + ch * 16 + (e & 1) * 8)
-                  : u4v{0u, 0u, 0u, 0u};
+    const bf16_t* p = ch < up.chunks ? up.X + (long)v * up.cs : X + (long)v * xcs + xco;
+    return v >= 0 ? *reinterpret_cast<const u4v*>(p + ch * 16 + (e & 1) * 8) : u4v{0u, 0u, 0u, 0u};
   };
   auto halo_store = [&](int e, u4v v) {
     *reinterpret_cast<u4v*>(tile + ((e & 1) * kHvox + (e >> 1)) * 8) = v;
@@ -148,10 +173,10 @@ __global__ __launch_bounds__(256) void k_conv2(const bf16_t* __restrict__ X, int
   constexpr int kHalo = 2 * kHvox, kFrag = NPAIR * NT * 64;
   constexpr int NH = kAhead ? (kHalo + 255) / 256 : 1, NW = kAhead ? (kFrag + 255) / 256 : 1;
   u4v hreg[NH], wreg[NW];
-  int hvox[NH];
+  int hvox[NH], pvox[NH];
   auto load_chunk = [&](int ch) {
 #pragma unroll
-    for (int q = 0; q < NH; ++q) hreg[q] = halo_load(threadIdx.x, hvox[q], ch);
+    for (int q = 0; q < NH; ++q) hreg[q] = halo_load(threadIdx.x, ch < up.chunks ? pvox[q] : hvox[q], ch);
 #pragma unroll
     for (int q = 0; q < NW; ++q)
       if ((int)threadIdx.x + 256 * q < kFrag) wreg[q] = frag_load(threadIdx.x + 256 * q, ch);
@@ -167,6 +192,7 @@ __global__ __launch_bounds__(256) void k_conv2(const bf16_t* __restrict__ X, int
     for (int q = 0; q < NH; ++q) {
       const int e = threadIdx.x + 256 * q;
       hvox[q] = e < kHalo ? halo_voxel(e) : -1;
+      pvox[q] = up.chunks && e < kHalo ? halo_parent(e) : -1;
     }
     load_chunk(0);
   }
@@ -180,7 +206,10 @@ __global__ __launch_bounds__(256) void k_conv2(const bf16_t* __restrict__ X, int
       for (int q = 0; q < NW; ++q)
         if ((int)threadIdx.x + 256 * q < kFrag) wfrag[threadIdx.x + 256 * q] = wreg[q];
     } else {
-      for (int e = threadIdx.x; e < kHalo; e += 256) halo_store(e, halo_load(e, halo_voxel(e), ch));
+      if (ch < up.chunks)
+        for (int e = threadIdx.x; e < kHalo; e += 256) halo_store(e, halo_load(e, halo_parent(e), ch));
+      else
+        for (int e = threadIdx.x; e < kHalo; e += 256) halo_store(e, halo_load(e, halo_voxel(e), ch));
       for (int e = threadIdx.x; e < kFrag; e += 256) wfrag[e] = frag_load(e, ch);
     }
     __syncthreads();
@@ -213,6 +242,12 @@ __global__ __launch_bounds__(256) void k_conv2(const bf16_t* __restrict__ X, int
   // D[row = 4 kq + r][col = m]: channel 4 kq + r, voxel 16 (i % MT) + m of wave row i / MT
   const int zz = z0 + wz;
   if (zz >= vol.D) return;
+  const long N = vol.V();
+  double is = 0.0;
+  if (res.z) {
+    const double s = res.sumsq->x > 0 ? sqrt(3.0 * (double)N / res.sumsq->x) : 0.0;
+    is = s > 0 ? 1.0 / s : 0.0;
+  }
 #pragma unroll
   for (int i = 0; i < MI; ++i) {
     const int yy = y0 + wy + i / MT, xx = x0 + 16 * (i % MT) + m;
@@ -238,6 +273,15 @@ __global__ __launch_bounds__(256) void k_conv2(const bf16_t* __restrict__ X, int
         *reinterpret_cast<u2v*>(Y + vo * ycs + yco + n) = o;
       }
       if (Yf) *reinterpret_cast<f4v*>(Yf + vo * Cout + n) = val;
+      if (res.z)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int c = n / 2 + h;   // component of channels n + 2 h, n + 2 h + 1
+          if (c < 3) {
+            const double2 rv = res.base[c * N + vo];
+            res.z[c * N + vo] = double2{rv.x + val[2 * h] * is, rv.y + val[2 * h + 1] * is};
+          }
+        }
     }
   }
 }
@@ -491,21 +535,6 @@ __global__ void k_pack(const double2* __restrict__ r, const double2* __restrict_
   }
 }
 
-// z[c][v] = base[c][v] + (out[v][2c] + i out[v][2c+1]) / s with base = w, or r when w
-// is null: the network predicts the correction A^{-1} r - base, so an untrained
-// (small) network leaves the base preconditioner (or the identity)
-__global__ void k_unpack(const float* __restrict__ out, const double2* __restrict__ sumsq, long N,
-                         const double2* __restrict__ base, double2* __restrict__ z) {
-  const double s = sumsq->x > 0 ? sqrt(3.0 * (double)N / sumsq->x) : 0.0;
-  const double is = s > 0 ? 1.0 / s : 0.0;
-  for (long v = blockIdx.x * (long)blockDim.x + threadIdx.x; v < N; v += (long)gridDim.x * blockDim.x)
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      const double2 rv = base[(long)c * N + v];
-      z[(long)c * N + v] = double2{rv.x + out[v * 16 + 2 * c] * is, rv.y + out[v * 16 + 2 * c + 1] * is};
-    }
-}
-
 // mean squared error of out against (target - base) * s over 6 channels; dOut = d(loss)/d(out)
 __global__ __launch_bounds__(256) void k_loss(const float* __restrict__ out, const double2* __restrict__ target,
                                               const double2* __restrict__ base, const double2* __restrict__ sumsq,
@@ -638,11 +667,11 @@ static hipError_t allow_conv_lds() {
 template <int TAPS>
 static void conv2_launch_nt(bool big, int nt, dim3 grid, int n0, hipStream_t s, const bf16_t* X, int xcs, int xco,
                             int Cin, const bf16_t* W, int Cout, bf16_t* Y, int ycs, int yco, float* Yf, Vol vol,
-                            int relu, const bf16_t* mask, int mcs, int mco) {
+                            int relu, const bf16_t* mask, int mcs, int mco, const ConvUp& up, const NetOut& res) {
 #define VIE_CONV2(NTV, TZ, MT)                                                                                   \
   if (nt == NTV && big == (TZ == 2))                                                                             \
     hipLaunchKernelGGL((k_conv2<TAPS, NTV, TZ, MT>), grid, dim3(256), (conv2_lds<TZ, MT>(TAPS, NTV)), s, X, xcs,  \
-                       xco, Cin, W, Cout, Y, ycs, yco, Yf, vol, relu, mask, mcs, mco, n0);
+                       xco, Cin, W, Cout, Y, ycs, yco, Yf, vol, relu, mask, mcs, mco, n0, up, res);
   VIE_CONV2(1, 2, 2)
   VIE_CONV2(2, 2, 2)
   VIE_CONV2(3, 2, 2)
@@ -658,7 +687,7 @@ static void conv2_launch_nt(bool big, int nt, dim3 grid, int n0, hipStream_t s, 
 // with a third of the weights to stage each.
 hipError_t conv_launch(int taps, const bf16_t* X, int xcs, int xco, int Cin, const bf16_t* W, int Cout, bf16_t* Y,
                        int ycs, int yco, float* Yf, Vol vol, int relu, const bf16_t* mask, int mcs, int mco,
-                       hipStream_t s) {
+                       hipStream_t s, const ConvUp& up = {}, const NetOut& res = {}) {
   static const hipError_t lds_ok = allow_conv_lds();
   if (lds_ok) return lds_ok;
   const long big = (long)vol.B * ((vol.D + 1) / 2) * ((vol.H + kCty - 1) / kCty) * ((vol.W + 31) / 32);
@@ -669,10 +698,10 @@ hipError_t conv_launch(int taps, const bf16_t* X, int xcs, int xco, int Cin, con
     const dim3 grid((unsigned)(use_big ? big : small), (unsigned)groups);
     if (taps == 27)
       conv2_launch_nt<27>(use_big, nt, grid, n0, s, X, xcs, xco, Cin, W, Cout, Y, ycs, yco, Yf, vol, relu, mask, mcs,
-                          mco);
+                          mco, up, res);
     else
       conv2_launch_nt<1>(use_big, nt, grid, n0, s, X, xcs, xco, Cin, W, Cout, Y, ycs, yco, Yf, vol, relu, mask, mcs,
-                         mco);
+                         mco, up, res);
   };
   if (full) go(per, full, 0);
   if (rest) go(rest, 1, full * per);
@@ -832,11 +861,18 @@ bool net_room(vie_net_s* N, int B) {
   return true;
 }
 
-// forward pass of B samples from X0 to out; all activations kept for the backward pass
-hipError_t net_forward(vie_net_s* N, int B = 1) {
+// forward pass of B samples from X0 to out; all activations kept for the backward pass.  With
+// a result (one sample, inference) the upsampled halves of the concatenations are not formed,
+// nor is out.
+hipError_t net_forward(vie_net_s* N, int B, const NetOut& res = {}) {
+  const bool infer = res.z != nullptr;
   hipStream_t s = N->stream;
   const Levels l(N, B);
   hipError_t e;
+#define CONV_UP(i, X, xcs, src, Y, ycs, yco, lev, relu)                                                            \
+  if ((e = conv_launch(N->L[i].taps, X, xcs, 0, N->L[i].cin, N->L[i].wbf, N->L[i].cout, Y, ycs, yco, nullptr,      \
+                       l[lev], relu, nullptr, 0, 0, s, infer ? src : ConvUp{})))                                    \
+    return e;
 #define CONV(i, X, xcs, xco, Y, ycs, yco, lev, relu)                                                           \
   if ((e = conv_launch(N->L[i].taps, X, xcs, xco, N->L[i].cin, N->L[i].wbf, N->L[i].cout, Y, ycs, yco, nullptr, \
                        l[lev], relu, nullptr, 0, 0, s)))                                                          \
@@ -855,20 +891,25 @@ hipError_t net_forward(vie_net_s* N, int B = 1) {
                      l[2].stack());
   CONV(6, N->P3, 48, 0, N->E4a, 64, 0, 3, 1)
   CONV(7, N->E4a, 64, 0, N->E4b, 64, 0, 3, 1)
-  hipLaunchKernelGGL(k_up, dim3(gblocks(l[2].all() * 64)), dim3(256), 0, s, N->E4b, 64, 0, N->D3cat, 112, 0, 64,
+  if (!infer)
+    hipLaunchKernelGGL(k_up, dim3(gblocks(l[2].all() * 64)), dim3(256), 0, s, N->E4b, 64, 0, N->D3cat, 112, 0, 64,
                      l[2].stack());
-  CONV(8, N->D3cat, 112, 0, N->Dd3a, 48, 0, 2, 1)
+  CONV_UP(8, N->D3cat, 112, (ConvUp{N->E4b, 64, 4}), N->Dd3a, 48, 0, 2, 1)
   CONV(9, N->Dd3a, 48, 0, N->Dd3b, 48, 0, 2, 1)
-  hipLaunchKernelGGL(k_up, dim3(gblocks(l[1].all() * 48)), dim3(256), 0, s, N->Dd3b, 48, 0, N->D2cat, 80, 0, 48,
+  if (!infer)
+    hipLaunchKernelGGL(k_up, dim3(gblocks(l[1].all() * 48)), dim3(256), 0, s, N->Dd3b, 48, 0, N->D2cat, 80, 0, 48,
                      l[1].stack());
-  CONV(10, N->D2cat, 80, 0, N->Dd2a, 32, 0, 1, 1)
+  CONV_UP(10, N->D2cat, 80, (ConvUp{N->Dd3b, 48, 3}), N->Dd2a, 32, 0, 1, 1)
   CONV(11, N->Dd2a, 32, 0, N->Dd2b, 32, 0, 1, 1)
-  hipLaunchKernelGGL(k_up, dim3(gblocks(l[0].all() * 32)), dim3(256), 0, s, N->Dd2b, 32, 0, N->D1cat, 48, 0, 32,
+  if (!infer)
+    hipLaunchKernelGGL(k_up, dim3(gblocks(l[0].all() * 32)), dim3(256), 0, s, N->Dd2b, 32, 0, N->D1cat, 48, 0, 32,
                      l[0].stack());
-  CONV(12, N->D1cat, 48, 0, N->Dd1a, 16, 0, 0, 1)
+  CONV_UP(12, N->D1cat, 48, (ConvUp{N->Dd2b, 32, 2}), N->Dd1a, 16, 0, 0, 1)
   CONV(13, N->Dd1a, 16, 0, N->Dd1b, 16, 0, 0, 1)
 #undef CONV
-  return conv_launch(1, N->Dd1b, 16, 0, 16, N->L[14].wbf, 16, nullptr, 0, 0, N->out, l[0], 0, nullptr, 0, 0, s);
+#undef CONV_UP
+  return conv_launch(1, N->Dd1b, 16, 0, 16, N->L[14].wbf, 16, nullptr, 0, 0, infer ? nullptr : N->out, l[0],
+                     0, nullptr, 0, 0, s, {}, res);
 }
 
 // backward pass of B samples from gOut; (+)= their weight gradients into L[i].g
@@ -959,9 +1000,7 @@ hipError_t net_apply(vie_net_s* N, const double2* r, const double2* w, const dou
   hipError_t e;
   if ((e = KrylovOps<double>::nrm2sq(r, 3 * V, N->red, N->sumsq, N->stream))) return e;
   hipLaunchKernelGGL(k_pack, dim3(gblocks(V)), dim3(256), 0, N->stream, r, w, chi, N->sumsq, V, N->X0);
-  if ((e = net_forward(N))) return e;
-  hipLaunchKernelGGL(k_unpack, dim3(gblocks(V)), dim3(256), 0, N->stream, N->out, N->sumsq, V, w ? w : r, z);
-  return hipGetLastError();
+  return net_forward(N, 1, NetOut{w ? w : r, N->sumsq, z});
 }
 const int* net_grid(vie_net_s* N) { return N->n; }
 void net_set_stream(vie_net_s* N, hipStream_t s) { N->stream = s; }
