@@ -86,7 +86,7 @@ static inline size_t conv2_lds(int taps, int nt) {
 }
 
 // Inference folds its neighbours into the convolutions (each was a launch of 5 to 8 us of a
-// 215 us apply at 32 x 32 x 256, APPLY_US without): the first `chunks` 16-channel chunks of
+// 215 us apply at 32 x 32 x 256, 192 so): the first `chunks` 16-channel chunks of
 // the input read their parents in a volume of half the size (nearest upsampling), and the
 // last layer's output goes straight into the result.
 struct ConvUp {
