@@ -115,7 +115,7 @@ def jm_measurement(steps: int):
 
 def strip_measurement(steps: int):
     """J-VIE products on the paper's strip with its longest absorber (30 x 12 x 1377,
-    circulant 64 x 32 x 4096: generic cross-section pass, long z pencils), FP64 and
+    circulant 64 x 32 x 2880: register cross-section pass, long z pencils), FP64 and
     FP32, timed with HIP events on the plan's stream after one device copy of a
     3N-value FP64 vector (counter calibration, bytes known)."""
     import numpy as np
@@ -156,8 +156,8 @@ KERNEL_SOURCES = {
     "k_xy64<double, 0>": ["xy64.hip", "fft_device.hpp", "block_maps.hpp"],
     "k_xy64<double, 1>": ["xy64.hip", "fft_device.hpp", "block_maps.hpp"],
     "k_xy64<double, 2>": ["xy64.hip", "fft_device.hpp", "block_maps.hpp"],
-    "k_zfwd4<double, 32, 32>": ["zpass.hip", "dft_reg.hpp", "fft_device.hpp", "block_maps.hpp"],
-    "k_zinv4<double, 32, 32, 0>": ["zpass.hip", "dft_reg.hpp", "fft_device.hpp", "block_maps.hpp"],
+    "k_zfwd3<double, 8, 8, 16>": ["zpass.hip", "dft_codelets.hpp", "fft_device.hpp", "block_maps.hpp"],
+    "k_zinv3<double, 16, 8, 8, 0>": ["zpass.hip", "dft_codelets.hpp", "fft_device.hpp", "block_maps.hpp"],
 }
 
 
@@ -481,11 +481,10 @@ def main():
     torch.cuda.synchronize()
 
     b64 = pass_bytes(n, M, 16)
-    z4 = M[2] in (512, 1024)
     tune64 = plan.tune(0)
-    names = ["k_zfwd4<double, 32, 32>" if z4 else "k_zfwd<double>",
+    names = ["k_zfwd3<double, 8, 8, 16>" if M[2] == 1024 else "k_zfwd3<double>",
              f"k_xy64<double, {tune64['xy_variant']}>" if M[0] == 64 and M[1] == 64 else "k_xyg<double>",
-             "k_zinv4<double, 32, 32, 0>" if z4 else "k_zinv<double, 0>"]
+             "k_zinv3<double, 16, 8, 8, 0>" if M[2] == 1024 else "k_zinv3<double>"]
     dom = int(np.argmax(pass_ms))
     achieved = b64[dom] / (pass_ms[dom] * 1e-3) / 1e9
     roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",

@@ -424,7 +424,7 @@ hipError_t autotune(const Geom& g, int device, Tune* t, void* U, const void* goc
     }
   }
   // the suffix names the candidate set: lines written for an older set are not read
-  const std::string arch = device_arch(device) + "/z3";
+  const std::string arch = device_arch(device) + "/z3/xy6432";
   if (tune_cache_lookup(arch, g, (int)sizeof(cx<T>), t)) {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     g_tune_cache[key] = *t;
@@ -652,7 +652,7 @@ SolveView plan_view(const vie_plan_s* p) {
 // The view the solvers use.  The box pays where it has a smaller circulant cross-section or
 // at most three quarters of the columns: all passes shrink with it (32 x 32 x 512 guide with
 // a 20 x 9 core, circulant 64 x 32 instead of 64 x 64 and a sixth of the z pencils: FP64
-// product with scatter and gather 137 us, on the box 64 us).  Built on first use unless
+// product with scatter and gather 137 us, on the box 70 us).  Built on first use unless
 // `build` is false (callers that may not allocate); where the build fails, for want of
 // memory say, the plan's own operator serves.
 SolveView solve_view(vie_plan_s* p, bool build) {
