@@ -534,7 +534,7 @@ def main():
         out["jm_matvec"] = jm_measurement(max(10, args.steps // 4))
         # the paper's strip (Section II-A, 9.45 um absorber): 64 x 32 cross-section pass
         sm = strip_measurement(max(10, args.steps // 4))
-        out["strip_matvec"] = {"workload": "J-VIE product, strip 30x12x1377, circulant 64x32x4096",
+        out["strip_matvec"] = {"workload": "J-VIE product, strip 30x12x1377, circulant 64x32x2880",
                                **{k: sm[k] for k in ("fp64", "fp32")}}
 
     if not args.no_solve:
