@@ -22,8 +22,7 @@
 // FP64 or FP32.
 //
 // Apply (z = W^{-1} r): per support row a length-n3 FFT read straight from the
-// voxel vector, one m x m matrix-vector product per frequency (from half of the
-// block where all support columns carry the same contrast), the inverse FFT
+// voxel vector, one m x m matrix-vector product per frequency, the inverse FFT
 // written straight back; voxels outside S are copied.
 #include <hip/hip_runtime.h>
 
@@ -445,143 +444,6 @@ __global__ __launch_bounds__(kThreads) void k_circ_gemv(const cx<T>* __restrict_
   }
 }
 
-// Sums over the wave of NV = 32 values per lane.  Each halving step pairs lanes and leaves
-// each with half of the values: across the 32-lane halves and the 16-lane rows by the swaps
-// that exchange a register's half with another's, within a row by lane permutations (8, 7 and
-// 3 in exclusive or: rotation, half mirror, quad reversal), where a lane sends the half that
-// it does not keep.  In the end lane l holds the sum of value fold_id(l), as does l ^ 1.
-template <int N>
-__device__ __forceinline__ float dpp_move(float v) {
-  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), N, 0xF, 0xF, true));
-}
-template <int N>
-__device__ __forceinline__ double dpp_move(double v) {
-  const long long b = __double_as_longlong(v);
-  const unsigned lo = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)b, N, 0xF, 0xF, true);
-  const unsigned hi = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)(b >> 32), N, 0xF, 0xF, true);
-  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-template <bool ROWS>
-__device__ __forceinline__ void swap_parts(unsigned& a, unsigned& b) {
-  const auto r = ROWS ? __builtin_amdgcn_permlane16_swap(a, b, false, false)
-                      : __builtin_amdgcn_permlane32_swap(a, b, false, false);
-  a = r[0];
-  b = r[1];
-}
-// a's sums in the lower lanes of each pair, b's in the upper ones
-template <bool ROWS>
-__device__ __forceinline__ float fold_swap(float a, float b) {
-  unsigned x = __float_as_uint(a), y = __float_as_uint(b);
-  swap_parts<ROWS>(x, y);
-  return __uint_as_float(x) + __uint_as_float(y);
-}
-template <bool ROWS>
-__device__ __forceinline__ double fold_swap(double a, double b) {
-  const unsigned long long p = (unsigned long long)__double_as_longlong(a), q = (unsigned long long)__double_as_longlong(b);
-  unsigned xl = (unsigned)p, yl = (unsigned)q, xh = (unsigned)(p >> 32), yh = (unsigned)(q >> 32);
-  swap_parts<ROWS>(xl, yl);
-  swap_parts<ROWS>(xh, yh);
-  return __longlong_as_double((long long)(((unsigned long long)xh << 32) | xl)) +
-         __longlong_as_double((long long)(((unsigned long long)yh << 32) | yl));
-}
-template <typename T>
-__device__ __forceinline__ T wave_fold32(T (&v)[32], int lane) {
-#pragma unroll
-  for (int i = 0; i < 16; ++i) v[i] = fold_swap<false>(v[i], v[i + 16]);
-#pragma unroll
-  for (int i = 0; i < 8; ++i) v[i] = fold_swap<true>(v[i], v[i + 8]);
-  const bool b8 = lane & 8, b4 = lane & 4, b2 = lane & 2;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const T keep = b8 ? v[i + 4] : v[i], send = b8 ? v[i] : v[i + 4];
-    v[i] = keep + dpp_move<0x128>(send);   // row_ror:8
-  }
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const T keep = b4 ? v[i + 2] : v[i], send = b4 ? v[i] : v[i + 2];
-    v[i] = keep + dpp_move<0x141>(send);   // row_half_mirror
-  }
-  const T keep = b2 ? v[1] : v[0], send = b2 ? v[0] : v[1];
-  const T r = keep + dpp_move<0x1B>(send);   // quad_perm [3, 2, 1, 0]
-  return r + dpp_move<0xB1>(r);              // quad_perm [1, 0, 3, 2]
-}
-__device__ __forceinline__ int fold_id(int lane) {
-  return (lane & 32 ? 16 : 0) | (lane & 16 ? 8 : 0) | (lane & 8 ? 4 : 0) | (lane & 4 ? 2 : 0) | (lane & 2 ? 1 : 0);
-}
-
-// The same product where every support column carries the same contrast along the window (a
-// guide of constant cross-section): W_k is then a scalar times N_k, whose blocks satisfy
-// N^T = D N D with D = diag(1, 1, -1) over the components, and so do W^ and its inverse.  Only
-// the lower triangle is read, each entry used for its row and, transposed, for its column.
-// One workgroup per frequency; its waves share the 64 x 64 tiles, 16 columns at a time (the
-// column sums go over the wave once per 16), each adding to a result vector of its own.
-// Bound by the read: 32 x 32 x 512 with 180 support columns (1.2 GB of FP32 inverses) 230 us
-// in full, 140 so.
-constexpr int kSymCols = 16;
-template <typename T> constexpr int kSymWaves = sizeof(T) == 8 ? 4 : 8;   // 160 KiB of LDS at m = 2048
-template <typename T>
-__global__ __launch_bounds__((64 * kSymWaves<T>)) void k_circ_symv(const cx<T>* __restrict__ inv,
-                                                                   const cx<T>* __restrict__ xhat,
-                                                                   cx<T>* __restrict__ yhat, int m, int n3) {
-  extern __shared__ unsigned char smem_raw[];
-  constexpr int W = kSymWaves<T>;
-  cx<T>* xs = reinterpret_cast<cx<T>*>(smem_raw);   // [m]
-  cx<T>* ys = xs + m;                               // [W][m]
-  const int f = blockIdx.x;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int j = threadIdx.x; j < m; j += 64 * W) {
-    xs[j] = xhat[(long)j * n3 + f];
-    for (int w = 0; w < W; ++w) ys[w * m + j] = cx<T>{(T)0, (T)0};
-  }
-  __syncthreads();
-  const cx<T>* A = inv + (long)f * m * m;
-  cx<T>* yw = ys + wave * m;
-  const int nb = (m + 63) / 64, tiles = nb * (nb + 1) / 2, neg = 2 * (m / 3);   // rows from neg on: z
-  const int id = fold_id(lane);
-  int I = 0, first = 0;   // tile row, its first tile
-  for (int t = wave; t < tiles; t += W) {
-    while (t > first + I) first += ++I;
-    const int J = t - first;
-    const int i = 64 * I + lane, ic = i < m ? i : m - 1;
-    const T si = i >= m ? (T)0 : i < neg ? (T)1 : (T)-1;
-    const cx<T> xi = cscale(xs[ic], si);
-    cx<T> acc{(T)0, (T)0};
-    for (int c0 = 64 * J; c0 < 64 * J + 64 && c0 < m; c0 += kSymCols) {
-      cx<T> a[kSymCols];
-#pragma unroll
-      for (int c = 0; c < kSymCols; ++c) a[c] = A[(long)(c0 + c < m ? c0 + c : m - 1) * m + ic];
-      T v[2 * kSymCols];
-#pragma unroll
-      for (int c = 0; c < kSymCols; ++c) {
-        const int j = c0 + c;
-        cx<T> xj = xs[j < m ? j : m - 1];
-        const bool on = j < m && j <= i, below = j < i;   // all true off the diagonal tiles and the edge
-        xj = cx<T>{on ? xj.x : (T)0, on ? xj.y : (T)0};
-        acc = cadd(acc, cmul(a[c], xj));
-        const cx<T> p = cmul(a[c], xi);
-        v[c] = below ? p.x : (T)0;
-        v[kSymCols + c] = below ? p.y : (T)0;
-      }
-      const T sum = wave_fold32(v, lane);
-      const int j = c0 + (id & (kSymCols - 1));
-      if (!(lane & 1) && j < m) {
-        T* y = reinterpret_cast<T*>(yw + j) + (id >> 4);
-        *y += j < neg ? sum : -sum;
-      }
-    }
-    if (i < m) yw[i] = cadd(yw[i], acc);
-  }
-  __syncthreads();
-  for (int j = threadIdx.x; j < m; j += 64 * W) {
-    cx<T> y = ys[j];
-    for (int w = 1; w < W; ++w) y = cadd(y, ys[w * m + j]);
-    yhat[(long)j * n3 + f] = y;
-  }
-}
-
-template <typename T>
-size_t symv_lds(int m) { return (size_t)(kSymWaves<T> + 1) * m * sizeof(cx<T>); }
-
 template <typename T, bool INV, class IO>
 hipError_t launch_fft(const Radices& rd, const double2* tw, const IO& io, long count, double scale, hipStream_t s) {
   if (count <= 0) return hipSuccess;
@@ -613,7 +475,6 @@ struct Circ {
   int s = 0, m = 0, n1 = 0, n2 = 0, n3 = 0;
   int z0 = 0, P = 0;           // slice window of the circulant
   bool fp64 = false;
-  bool sym = false;            // equal contrast on all support columns: D-symmetric blocks
   int* col = nullptr;          // voxel column i1 * n2 + i2 of each support column
   double2* tw = nullptr;       // exp(-2 pi i t / P)
   double2* inv64 = nullptr;    // P blocks, column-major m x m
@@ -706,11 +567,6 @@ int circ_build(Circ** out, const Geom& g, const std::complex<double>* table, con
   c->P = P;
   c->info.z0 = z0;
   c->info.P = P;
-  c->sym = true;
-  for (int p = 1; p < c->s && c->sym; ++p)
-    c->sym = std::equal(chi.data() + (long)cols[p] * n3 + z0, chi.data() + (long)cols[p] * n3 + z0 + P,
-                        chi.data() + (long)cols[0] * n3 + z0,
-                        [](const double2& u, const double2& v) { return u.x == v.x && u.y == v.y; });
   const long m2 = (long)m * m;
   const size_t blk = sizeof(double2) * (size_t)P * m2;
   size_t free_b = 0, total_b = 0;
@@ -827,8 +683,6 @@ int circ_build(Circ** out, const Geom& g, const std::complex<double>* table, con
     CTRY(hipFuncSetAttribute((const void*)k_circ_fft<float, false, IoRowsIn<float>>, attr, lds_need));
     CTRY(hipFuncSetAttribute((const void*)k_circ_fft<float, true, IoRowsOut<float>>, attr, lds_need));
   }
-  CTRY(hipFuncSetAttribute((const void*)(fp64 ? (const void*)k_circ_symv<double> : (const void*)k_circ_symv<float>), attr,
-                           (int)(fp64 ? symv_lds<double>(m) : symv_lds<float>(m))));
   c->info.bytes = (fp64 ? sizeof(double2) : sizeof(float2)) * (size_t)P * m2;
   c->info.seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
   if (info) *info = c->info;
@@ -844,12 +698,8 @@ hipError_t apply_t(Circ* c, const cx<T>* inv, const IN& in, const OUT& out, hipS
   auto* yh = reinterpret_cast<cx<T>*>(c->yhat);
   hipError_t e = launch_fft<T, false>(c->rd, c->tw, in, c->m, 1.0, s);
   if (e) return e;
-  if (c->sym)
-    hipLaunchKernelGGL(k_circ_symv<T>, dim3(c->P), dim3(64 * kSymWaves<T>), symv_lds<T>(c->m), s, inv, xh, yh, c->m,
-                       c->P);
-  else
-    hipLaunchKernelGGL(k_circ_gemv<T>, dim3((c->m + kGemvRows - 1) / kGemvRows, c->P), dim3(kThreads), 0, s, inv, xh,
-                       yh, c->m, c->P);
+  hipLaunchKernelGGL(k_circ_gemv<T>, dim3((c->m + kGemvRows - 1) / kGemvRows, c->P), dim3(kThreads), 0, s, inv, xh,
+                     yh, c->m, c->P);
   if ((e = hipGetLastError())) return e;
   return launch_fft<T, true>(c->rd, c->tw, out, c->m, 1.0 / c->P, s);
 }

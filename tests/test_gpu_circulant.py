@@ -98,28 +98,6 @@ def test_apply_matches_oracle(name, make, fp64):
     assert np.array_equal(z[:, :, :, z0 + P:], r[:, :, :, z0 + P:])
 
 
-@pytest.mark.parametrize("fp64", [True, False], ids=["fp64", "fp32"])
-@pytest.mark.parametrize("same", [True, False], ids=["same", "one_differs"])
-@pytest.mark.parametrize("core", [(1, 1), (7, 3), (11, 2), (5, 5), (8, 8)], ids=lambda c: f"m{3 * c[0] * c[1]}")
-def test_half_read_blocks_match_oracle(core, same, fp64):
-    """Blocks of 3, 63, 66, 75 and 192 unknowns around the 64 x 64 tiles and 16-column groups:
-    with the same contrast on every support column (half of each block is read) and with one
-    column that differs in one slice (all of it)."""
-    vie = _dev()
-    n = (12, 9, 20)
-    eps = _guide(n, (1, 1 + core[0]), (1, 1 + core[1]), 6).eps()
-    if not same:
-        eps[1, 1, 7] += 0.5
-    plan = vie.Plan(n, 0.05, inputs.K0, inputs.EPS_B)
-    plan.set_contrast(torch.from_numpy(eps).cuda())
-    plan.build_circulant(fp64=fp64)
-    rng = np.random.default_rng(core[0])
-    r = rng.standard_normal((3,) + n) + 1j * rng.standard_normal((3,) + n)
-    z = plan.apply_circulant(torch.from_numpy(r).cuda()).cpu().numpy()
-    zo = _oracle_apply(eps, 0.05, r)
-    assert np.max(np.abs(z - zo)) / np.max(np.abs(zo)) <= (1e-11 if fp64 else 2e-5)
-
-
 def test_no_contrast_is_the_identity():
     vie = _dev()
     n = (4, 4, 8)
