@@ -389,7 +389,7 @@ int vie_net_train_step(vie_net_t net, int count, const vie_c128* const* r, const
  * w and predicts the correction A^{-1} r - w, so z = w + net(r s, chi, w s) / s.  With
  * w = W^{-1} r from the block-circulant preconditioner (vie_circulant_apply) the
  * network corrects that preconditioner (vie_solve precision 4).  train_step_base:
- * w is an array of count device pointers or NULL.
+ * w is an array of count device pointers or NULL; a NULL entry is that sample's r.
  */
 int vie_net_apply_base(vie_net_t net, const vie_c128* r, const vie_c128* w, const vie_c128* chi, vie_c128* z);
 int vie_net_train_step_base(vie_net_t net, int count, const vie_c128* const* r, const vie_c128* const* w,

@@ -1188,7 +1188,7 @@ int vie_net_train_step_base(vie_net_t N, int count, const vie_c128* const* r, co
   for (int i0 = 0; i0 < count; i0 += group) {
     const int B = std::min(group, count - i0);
     const float gscale = 2.0f / (6.0f * (float)V * (float)count);
-    auto base = [&](int i) { return reinterpret_cast<const double2*>(w ? w[i] : r[i]); };
+    auto base = [&](int i) { return reinterpret_cast<const double2*>(w && w[i] ? w[i] : r[i]); };
     for (int q = 0; q < B; ++q) {
       const double2* ri = reinterpret_cast<const double2*>(r[i0 + q]);
       double2* sumsq = N->sumsq + 2 * q;

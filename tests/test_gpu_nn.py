@@ -357,6 +357,27 @@ def test_grouped_samples_equal_single_ones(count):
     assert np.linalg.norm(got - want) <= (1e-5 if count != 5 else 2.0 ** -8) * np.linalg.norm(want)
 
 
+def test_null_base_of_a_sample_is_its_residual():
+    """vie_net_train_step_base with a null entry among the base vectors: that sample is the
+    one vie_net_train_step takes, in a group with samples that have a base."""
+    import ctypes
+    vie = _dev()
+    n = (8, 8, 16)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    c = lambda *k: torch.randn(*k, n[0] * n[1] * n[2], dtype=torch.complex128, device="cuda", generator=g)
+    r, chi, t, w = c(3, 3), 0.3 * c(3), c(3, 3), c(3)
+    net = vie.Net(n, seed=5)
+    want = np.mean([net.train_step([r[0]], [chi[0]], [t[0]], lr=0.0),
+                    net.train_step_base([r[1]], [w], [chi[1]], [t[1]], lr=0.0),
+                    net.train_step([r[2]], [chi[2]], [t[2]], lr=0.0)])
+    arr = lambda ts: (ctypes.c_void_p * 3)(*[x.data_ptr() if x is not None else None for x in ts])
+    loss = ctypes.c_double()
+    code = vie.lib().vie_net_train_step_base(net.handle, 3, arr(r), arr([None, w, None]), arr(chi), arr(t),
+                                             0.0, ctypes.byref(loss))
+    assert code == vie.VIE_OK
+    assert abs(loss.value - want) <= 1e-12 * want
+
+
 def test_network_with_base_vector_is_bit_exact_on_the_integer_case():
     """vie_net_apply_base: the base vector enters input channels 8-13 and the output is
     added to it; integer base vectors keep every sum exact."""
