@@ -10,6 +10,17 @@
 // column, rotation, estimate to host memory).  Measured per step with the sweeps apart (dots
 // and update of the second gated by a cancellation test): ten kernels and a copy, 110 us at
 // n = 276480 and j ~ 20, 33 us at n = 1536 and j ~ 25; merged 60 and 18 us.
+//
+// The merged second sweep corrects for G != I but takes V^H w' from the rounded dots of w
+// instead of measuring it, so V^H v_{j+1} is of order eps ||h|| / ||w''|| (two measured sweeps:
+// eps).  On guides ||w''|| is 0.3 to 0.5 of ||h||.  Where it is below kCancel = 0.1 of it in
+// FP64, one more sweep measures V^H w'' and subtracts it, which bounds the loss by 10 eps at
+// any cancellation (without it a permittivity of 1e-10 in one voxel, ratios of 1e-10, made a
+// cycle of 15 steps end at 27 times the minimal residual, the basis no longer one).  k_finish reports such a step; the
+// solver repeats it with the extra sweep and queues that, gated on the device by the same
+// test (k_gate), for the steps that follow.  FP32 vectors do not need it: their dots are FP64
+// sums of exact products, so what the merging leaves out is below their own rounding until
+// w'' is nothing but the rounding of w.
 // The Hessenberg matrix is kept in upper-triangular form with complex Givens rotations by one
 // device thread; the host reads only the residual estimate |g_{j+1}| / ||b|| after each step.
 // G_ij, i < j, lies in the unused strict lower triangle of that matrix.  Reductions are
@@ -36,6 +47,7 @@ constexpr int kDotEPT = 4;                  // elements per thread and round of 
 constexpr int kDotChunk = kThreads * kDotEPT;
 constexpr int kDotBlocks = 256;             // most blocks (partials) per vector group of the multi-dot
 constexpr int kAxpyBlocks = 2048;           // most blocks (partials) of k_maxpy_nrm
+constexpr double kCancel2 = 0.01;           // kCancel^2: ||w''||^2 / ||h||^2 of a step that needs the extra sweep
 
 __device__ __forceinline__ double2 to_d(double2 v) { return v; }
 __device__ __forceinline__ double2 to_d(float2 v) { return double2{(double)v.x, (double)v.y}; }
@@ -69,11 +81,12 @@ __device__ __forceinline__ void block_sum(double (&v)[NV], double* lds) {
 }
 
 // partial[(2 i + s) nblk + blk] = the block's share of V_i^H w (s = 0) and of V_i^H V_{nv-1}
-// (s = 1), for the kGroup vectors i of blockIdx.y
+// (s = 1), for the kGroup vectors i of blockIdx.y; nothing where *gate == 0
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_mdot2(const cx<T>* __restrict__ V, long ldv, int nv,
                                                      const cx<T>* __restrict__ w, long n,
-                                                     double2* __restrict__ partial) {
+                                                     double2* __restrict__ partial, const int* __restrict__ gate) {
+  if (gate && *gate == 0) return;
   constexpr int kVals = 4 * kGroup;
   __shared__ double lds[kThreads / 64][kVals];
   const cx<T>* vj = V + (long)(nv - 1) * ldv;
@@ -184,6 +197,41 @@ __global__ __launch_bounds__(kProjThreads) void k_proj(const double2* __restrict
   }
 }
 
+// *gate = 1 where ||w''||^2, the sum of nblk partials, is too small a part of ||h||^2
+__global__ __launch_bounds__(kThreads) void k_gate(const double* __restrict__ partial, int nblk,
+                                                   const double2* __restrict__ h, int nv, int* __restrict__ gate) {
+  __shared__ double lds[(kThreads / 64) * 2];
+  double v[2] = {0.0, 0.0};
+  for (int b = threadIdx.x; b < nblk; b += kThreads) v[0] += partial[b];
+  for (int i = threadIdx.x; i < nv; i += kThreads) v[1] += h[i].x * h[i].x + h[i].y * h[i].y;
+  block_sum<2>(v, lds);
+  if (threadIdx.x == 0) *gate = v[0] < kCancel2 * v[1] ? 1 : 0;
+}
+
+// The extra sweep's coefficients from k_mdot2's partials: c = V^H w'', and h += c
+__global__ __launch_bounds__(kThreads) void k_proj_again(const double2* __restrict__ partial, int nblk, int nv,
+                                                         double2* __restrict__ c, double2* __restrict__ h,
+                                                         const int* __restrict__ gate) {
+  if (*gate == 0) return;
+  const int sub = threadIdx.x & 7, i = blockIdx.x * (kThreads / 8) + (threadIdx.x >> 3);
+  double2 s{0.0, 0.0};
+  if (i < nv)
+    for (int b = sub; b < nblk; b += 8) {
+      const double2 p = partial[2L * i * nblk + b];
+      s.x += p.x;
+      s.y += p.y;
+    }
+#pragma unroll
+  for (int o = 1; o < 8; o <<= 1) {
+    s.x += __shfl_xor(s.x, o, 64);
+    s.y += __shfl_xor(s.y, o, 64);
+  }
+  if (sub == 0 && i < nv) {
+    c[i] = s;
+    h[i] = double2{h[i].x + s.x, h[i].y + s.y};
+  }
+}
+
 // out[i] = sum_b partial[i * nblk + b], one workgroup per i, fixed order
 __global__ __launch_bounds__(kThreads) void k_reduce(const double2* __restrict__ partial, int nblk,
                                                       double2* __restrict__ out) {
@@ -266,11 +314,13 @@ __global__ __launch_bounds__(kThreads) void k_zero(cx<T>* __restrict__ dst, long
     dst[e] = cx<T>{(T)0, (T)0};
 }
 
-// w -= sum_i h_i V_i and, of the stored result, the block partial sums of |w|^2
+// w -= sum_i h_i V_i and, of the stored result, the block partial sums of |w|^2; nothing where
+// *gate == 0
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_maxpy_nrm(const cx<T>* __restrict__ V, long ldv, int nv,
                                                          const double2* __restrict__ h, cx<T>* __restrict__ w, long n,
-                                                         double* __restrict__ partial) {
+                                                         double* __restrict__ partial, const int* __restrict__ gate) {
+  if (gate && *gate == 0) return;
   extern __shared__ unsigned char smem_raw[];
   double2* c = reinterpret_cast<double2*>(smem_raw);   // nv values, zeros up to a multiple of 8
   __shared__ double lds[kThreads / 64];
@@ -303,10 +353,12 @@ __global__ __launch_bounds__(kThreads) void k_maxpy_nrm(const cx<T>* __restrict_
 // Column j of the Hessenberg matrix (hs[0..j] = the projections, hn = ||w||) through the previous
 // rotations, the new rotation and g, by one thread: it sweeps the rotations down the column with
 // the running entry in a register (the loads of hs, cs, sn do not depend on the sweep, so they
-// are issued ahead).  state: see k_finish.
+// are issued ahead).  pend[j] is the rotated right-hand side's entry before rotation j, so that
+// a step can be repeated.  state: see k_finish.
 __device__ __forceinline__ void hessenberg_column(double2* hs, double hn, double* __restrict__ cs,
-                                                  double2* __restrict__ sn, double2* __restrict__ gvec, int j,
-                                                  double bnorm, double* __restrict__ state) {
+                                                  double2* __restrict__ sn, double2* __restrict__ gvec,
+                                                  double2* __restrict__ pend, int j, double bnorm, bool cancelled,
+                                                  double* __restrict__ state) {
   // previous rotations: [c s; -conj(s) c] on (h_i, h_{i+1})
   double2 a = hs[0];
   for (int i = 0; i < j; ++i) {
@@ -340,15 +392,16 @@ __device__ __forceinline__ void hessenberg_column(double2* hs, double hn, double
   cs[j] = c;
   sn[j] = sv;
   hs[j] = r;
-  const double2 gj = gvec[j];
+  const double2 gj = pend[j];
   // g_{j+1} = -conj(s) g_j ; g_j = c g_j
   const double2 gn = double2{-(sv.x * gj.x + sv.y * gj.y), -(sv.x * gj.y - sv.y * gj.x)};
-  gvec[j + 1] = gn;
+  pend[j + 1] = gn;
   gvec[j] = double2{c * gj.x, c * gj.y};
   const double est = hypot(gn.x, gn.y) / bnorm;
   state[0] = est;
   state[1] = hn;
   state[2] = (isfinite(est) && isfinite(hn) && isfinite(r.x) && isfinite(r.y)) ? 0.0 : 1.0;
+  state[3] = cancelled ? 1.0 : 0.0;
   __threadfence_system();
 }
 
@@ -356,24 +409,32 @@ __device__ __forceinline__ void hessenberg_column(double2* hs, double hn, double
 // result) and scales its share of w; workgroup 0 also does the Hessenberg bookkeeping: column
 // j = (h, ||w||) through the previous rotations, the new rotation, g.  state (host memory):
 // [0] residual estimate |g_{j+1}| / bnorm, [1] ||w|| (breakdown when 0), [2] = 1 if any value
-// is non-finite.
+// is non-finite, [3] = 1 if the step cancelled too much for the merged sweeps alone.  After the
+// extra sweep, *gate != 0, the partials are those of its update.
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_finish(cx<T>* __restrict__ w, long n,
                                                       const double* __restrict__ partial, int nblk,
-                                                      const double2* __restrict__ h, double2* __restrict__ H, int ldh,
-                                                      double* __restrict__ cs, double2* __restrict__ sn,
-                                                      double2* __restrict__ gvec, int j, double bnorm,
+                                                      const int* __restrict__ gate, const double2* __restrict__ h,
+                                                      double2* __restrict__ H, int ldh, double* __restrict__ cs,
+                                                      double2* __restrict__ sn, double2* __restrict__ gvec,
+                                                      double2* __restrict__ pend, int j, double bnorm,
                                                       double* __restrict__ state) {
   extern __shared__ unsigned char smem_raw[];
   double2* hs = reinterpret_cast<double2*>(smem_raw);   // j + 2 entries (workgroup 0)
-  __shared__ double lds[kThreads / 64];
+  __shared__ double lds[(kThreads / 64) * 2];
   __shared__ double s_norm;
-  double v[1] = {0.0};
+  const bool again = gate && *gate != 0;
+  if (again) partial += nblk;
+  double v[2] = {0.0, 0.0};   // ||w||^2, ||h||^2 (workgroup 0)
   for (int b = threadIdx.x; b < nblk; b += kThreads) v[0] += partial[b];
-  block_sum<1>(v, lds);
-  if (threadIdx.x == 0) s_norm = sqrt(v[0]);
   if (blockIdx.x == 0)
-    for (int i = threadIdx.x; i <= j; i += kThreads) hs[i] = h[i];
+    for (int i = threadIdx.x; i <= j; i += kThreads) {
+      const double2 hi = h[i];
+      hs[i] = hi;
+      v[1] += hi.x * hi.x + hi.y * hi.y;
+    }
+  block_sum<2>(v, lds);
+  if (threadIdx.x == 0) s_norm = sqrt(v[0]);
   __syncthreads();
   const double hn = s_norm;
   const double scale = hn > 0.0 ? 1.0 / hn : 0.0;
@@ -382,7 +443,8 @@ __global__ __launch_bounds__(kThreads) void k_finish(cx<T>* __restrict__ w, long
     w[e] = from_d<cx<T>>(double2{a.x * scale, a.y * scale});
   }
   if (blockIdx.x != 0) return;
-  if (threadIdx.x == 0) hessenberg_column(hs, hn, cs, sn, gvec, j, bnorm, state);
+  if (threadIdx.x == 0)
+    hessenberg_column(hs, hn, cs, sn, gvec, pend, j, bnorm, again || v[0] < kCancel2 * v[1], state);
   __syncthreads();
   double2* col = H + (long)j * ldh;
   for (int i = threadIdx.x; i <= j; i += kThreads) col[i] = hs[i];
@@ -419,10 +481,7 @@ __global__ __launch_bounds__(kThreads) void k_trisolve(const double2* __restrict
   }
 }
 
-__global__ void k_set_g(double2* gvec, int m, const double2* sumsq) {
-  for (int i = threadIdx.x; i <= m; i += blockDim.x) gvec[i] = double2{0.0, 0.0};
-  if (threadIdx.x == 0) gvec[0] = double2{sqrt(sumsq->x), 0.0};
-}
+__global__ void k_set_g(double2* pend, const double2* sumsq) { pend[0] = double2{sqrt(sumsq->x), 0.0}; }
 
 // ---- support compression ------------------------------------------------------
 template <typename T>
@@ -506,18 +565,29 @@ static hipError_t allow_step_lds() {
 
 template <typename T>
 hipError_t KrylovOps<T>::orthogonalise(const cx<T>* V, int j, cx<T>* w, long n, const ArnoldiData& d, double bnorm,
-                                       double* state, hipStream_t s) {
+                                       bool again, double* state, hipStream_t s) {
   static const hipError_t lds_ok = allow_step_lds<T>();
   if (lds_ok != hipSuccess) return lds_ok;
   const int nv = j + 1, nd = dot_blocks(n), na = axpy_blocks(n);
-  double* norms = reinterpret_cast<double*>(d.partial);
-  hipLaunchKernelGGL((k_mdot2<T>), dim3(nd, (nv + kGroup - 1) / kGroup), dim3(kThreads), 0, s, V, n, nv, w, n,
-                     d.partial);
-  hipLaunchKernelGGL(k_proj, dim3(1), dim3(kProjThreads), 0, s, d.partial, nd, nv, d.raw, d.gd, d.H, d.ldh, d.h);
-  hipLaunchKernelGGL((k_maxpy_nrm<T>), dim3(na), dim3(kThreads), (size_t)(nv + 7) * sizeof(double2), s, V, n, nv, d.h, w, n,
-                     norms);
+  double* norms = reinterpret_cast<double*>(d.partial);   // of the update and of the extra sweep's
+  double2* dots = d.partial + na;
+  int* gate = again ? d.gate : nullptr;
+  const dim3 dgrid(nd, (nv + kGroup - 1) / kGroup);
+  const size_t coef = (size_t)(nv + 7) * sizeof(double2);
+  hipLaunchKernelGGL((k_mdot2<T>), dgrid, dim3(kThreads), 0, s, V, n, nv, w, n, dots, (const int*)nullptr);
+  hipLaunchKernelGGL(k_proj, dim3(1), dim3(kProjThreads), 0, s, dots, nd, nv, d.raw, d.gd, d.H, d.ldh, d.h);
+  hipLaunchKernelGGL((k_maxpy_nrm<T>), dim3(na), dim3(kThreads), coef, s, V, n, nv, d.h, w, n, norms,
+                     (const int*)nullptr);
+  if (again) {
+    hipLaunchKernelGGL(k_gate, dim3(1), dim3(kThreads), 0, s, norms, na, d.h, nv, gate);
+    hipLaunchKernelGGL((k_mdot2<T>), dgrid, dim3(kThreads), 0, s, V, n, nv, w, n, dots, (const int*)gate);
+    hipLaunchKernelGGL(k_proj_again, dim3((nv + kThreads / 8 - 1) / (kThreads / 8)), dim3(kThreads), 0, s, dots, nd,
+                       nv, d.raw, d.h, (const int*)gate);
+    hipLaunchKernelGGL((k_maxpy_nrm<T>), dim3(na), dim3(kThreads), coef, s, V, n, nv, d.raw, w, n, norms + na,
+                       (const int*)gate);
+  }
   hipLaunchKernelGGL((k_finish<T>), dim3(na), dim3(kThreads), (size_t)(j + 2) * sizeof(double2), s, w, n, norms,
-                     na, d.h, d.H, d.ldh, d.cs, d.sn, d.g, j, bnorm, state);
+                     na, (const int*)gate, d.h, d.H, d.ldh, d.cs, d.sn, d.g, d.pend, j, bnorm, state);
   return hipGetLastError();
 }
 
@@ -543,8 +613,8 @@ hipError_t KrylovOps<T>::trisolve(const double2* H, int ldh, const double2* g, i
 }
 
 template <typename T>
-hipError_t KrylovOps<T>::set_g(double2* g, int m, const double2* sumsq, hipStream_t s) {
-  hipLaunchKernelGGL(k_set_g, dim3(1), dim3(256), 0, s, g, m, sumsq);
+hipError_t KrylovOps<T>::set_g(double2* pend, const double2* sumsq, hipStream_t s) {
+  hipLaunchKernelGGL(k_set_g, dim3(1), dim3(1), 0, s, pend, sumsq);
   return hipGetLastError();
 }
 
@@ -566,8 +636,7 @@ template hipError_t convert<double, double>(const cx<double>*, cx<double>*, long
 
 int partial_blocks(long n) { return nblocks(n); }
 size_t arnoldi_partials(long n, int m) {
-  return std::max<size_t>(2 * (size_t)(m + 1) * dot_blocks(n),
-                          std::max<size_t>(nblocks(n), (axpy_blocks(n) + 1) / 2));
+  return std::max<size_t>(2 * (size_t)(m + 1) * dot_blocks(n) + axpy_blocks(n), nblocks(n));
 }
 
 static inline int grid_for(long n) {

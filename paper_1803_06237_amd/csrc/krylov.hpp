@@ -35,12 +35,14 @@ __device__ __forceinline__ double wave_sum_many(double (&v)[NV], int lane, int* 
 // Device data of one GMRES cycle: the reduction partials (arnoldi_partials), the raw dots and
 // the Gram diagonal (m + 1 values each), the projections h, the Hessenberg matrix
 // (column-major, leading dimension ldh; the Gram entries G_ij, i < j, at row j of column i),
-// the rotations and the right-hand side g.
+// the rotations, the right-hand side g and its entries before their last rotation, the gate of
+// the extra sweep.
 struct ArnoldiData {
   double2 *partial, *raw, *gd, *h, *H;
   int ldh;
   double* cs;
-  double2 *sn, *g;
+  double2 *sn, *g, *pend;
+  int* gate;
 };
 
 template <typename T>
@@ -52,15 +54,17 @@ struct KrylovOps {
   static hipError_t maxpy(const cx<T>* V, long ldv, int nv, const double2* coef, double sign, cx<TW>* w, long n,
                           hipStream_t s);
   // Arnoldi step j after w = A v_j: w orthogonalised against V_0 .. V_j and normalised (it is
-  // V_{j+1}), Hessenberg column, rotation and g updated; state (pinned host memory, 3 values):
-  // residual estimate, ||w||, 1 if something is not finite.
+  // V_{j+1}), Hessenberg column, rotation and g updated; state (pinned host memory, 4 values):
+  // residual estimate, ||w||, 1 if something is not finite, 1 if the step cancelled too much
+  // for the merged sweeps.  again: a further sweep where the device finds that; a step that
+  // reports it without is to be repeated from w = A v_j with it.
   static hipError_t orthogonalise(const cx<T>* V, int j, cx<T>* w, long n, const ArnoldiData& d, double bnorm,
-                                  double* state, hipStream_t s);
+                                  bool again, double* state, hipStream_t s);
   // dst = src / sqrt(sumsq->x)
   static hipError_t scale(const cx<T>* src, cx<T>* dst, long n, const double2* sumsq, hipStream_t s);
   static hipError_t zero(cx<T>* dst, long n, hipStream_t s);
   static hipError_t trisolve(const double2* H, int ldh, const double2* g, int k, double2* y, hipStream_t s);
-  static hipError_t set_g(double2* g, int m, const double2* sumsq, hipStream_t s);
+  static hipError_t set_g(double2* pend, const double2* sumsq, hipStream_t s);
 };
 
 template <typename TS, typename TD>

@@ -88,6 +88,7 @@ struct GmresWs {
   double2* H = nullptr;
   double2* sn = nullptr;
   double2* g = nullptr;
+  double2* pend = nullptr;     // entries of g before their last rotation
   double2* y = nullptr;        // raw dots during a cycle, then the coefficients of the update
   double* cs = nullptr;
   double* state_h = nullptr;
@@ -97,7 +98,7 @@ struct GmresWs {
   void release() {
     if (borrowed) return;
     for (void* p : {(void*)V, (void*)Z, (void*)partial, (void*)h, (void*)gd, (void*)sumsq, (void*)H, (void*)sn,
-                    (void*)g, (void*)y, (void*)cs})
+                    (void*)g, (void*)pend, (void*)y, (void*)cs})
       if (p) (void)hipFree(p);
     if (state_h) (void)hipHostFree(state_h);
     for (hipEvent_t e : ev)
@@ -121,6 +122,7 @@ struct GmresWs {
     if ((e = dmalloc(&H, sizeof(double2) * (size_t)(m + 1) * m))) return e;
     if ((e = dmalloc(&sn, sizeof(double2) * (m + 1)))) return e;
     if ((e = dmalloc(&g, sizeof(double2) * (m + 1)))) return e;
+    if ((e = dmalloc(&pend, sizeof(double2) * (m + 1)))) return e;
     if ((e = dmalloc(&y, sizeof(double2) * (m + 1)))) return e;
     if ((e = dmalloc(&cs, sizeof(double) * (m + 1)))) return e;
     if ((e = hipHostMalloc(&state_h, sizeof(double) * 8, hipHostMallocDefault))) return e;
@@ -807,6 +809,13 @@ int gmres_core(vie_plan_s* p, GmresWs<T>& W, OP& A, PC* M, long n, const cx<T>* 
   // stagnation: the true residual of each restart against the best so far
   double best = rel;
   int since = 0, cycles = 0;
+  // The extra Gram-Schmidt sweep: an FP64 step that cancels too much without it is repeated with
+  // it, and the next steps queue it too (four launches, skipped on the device where a step does
+  // not need it), until `patience` of them in a row did not.  The patience doubles with each
+  // repeated step, so that these stay few whatever the pattern.  A preconditioned cycle starts
+  // with it: A W^{-1} v_0 is mostly v_0.
+  bool again = false;
+  int patience = 1, idle = 0;
   while (true) {
     if (!std::isfinite(rel)) return fail(p, VIE_ENUMERIC, "non-finite residual");
     if (rel <= tol) {
@@ -824,32 +833,37 @@ int gmres_core(vie_plan_s* p, GmresWs<T>& W, OP& A, PC* M, long n, const cx<T>* 
       }
     }
     ++cycles;
-    HIPTRY(p, K::set_g(W.g, m, W.sumsq, s));
+    if (sizeof(T) == 8 && M != nullptr) {
+      again = true;
+      idle = 0;
+    }
+    HIPTRY(p, K::set_g(W.pend, W.sumsq, s));
     HIPTRY(p, K::scale(V0, V0, n, W.sumsq, s));
     // One Arnoldi step queued on the stream; its last kernel writes its state (residual
     // estimate, breakdown, non-finite flags) to pinned slot j & 1.
-    const ArnoldiData D{W.partial, W.y, W.gd, W.h, W.H, ldh, W.cs, W.sn, W.g};
-    auto step = [&](int j) -> hipError_t {
+    const ArnoldiData D{W.partial, W.y,  W.gd, W.h,    W.H, ldh, W.cs,
+                        W.sn,      W.g, W.pend, reinterpret_cast<int*>(W.sumsq + 1)};
+    auto step = [&](int j, bool repeat = false) -> hipError_t {
       cx<T>* Vj = W.V + (long)j * n;
       cx<T>* w = W.V + (long)(j + 1) * n;
       const cx<T>* z = Vj;
       hipError_t e;
       if (M) {
         cx<T>* Zj = W.Z + (long)j * n;
-        if ((e = (*M)(Vj, Zj, st))) return e;
+        if (!repeat && (e = (*M)(Vj, Zj, st))) return e;
         z = Zj;
       }
       if ((e = A.apply(z, w))) return e;
       st.matvecs++;
-      if ((e = K::orthogonalise(W.V, j, w, n, D, bnorm, W.state_h + 4 * (j & 1), s))) return e;
+      if ((e = K::orthogonalise(W.V, j, w, n, D, bnorm, again, W.state_h + 4 * (j & 1), s))) return e;
       return hipEventRecord(W.ev[j & 1], s);
     };
     // Without a preconditioner the steps are pipelined: step j + 1 is queued
     // before the host waits for step j's state, so the device does not idle
     // through the host round trip.  A step queued after convergence is
     // discarded: it writes only V_{j+2}, Hessenberg column j + 1, Gram column j + 1 (below
-    // the diagonal), the raw dots and g_{j+1}, g_{j+2}, none of which the solution with
-    // k = j + 1 columns reads.  (The
+    // the diagonal), the raw dots, g_{j+1} and the pending g_{j+2}, none of which the solution
+    // with k = j + 1 columns, or step j repeated, reads.  (The
     // flexible variant's preconditioner synchronises by itself.)
     const bool pipe = M == nullptr;
     int k = 0;
@@ -859,6 +873,17 @@ int gmres_core(vie_plan_s* p, GmresWs<T>& W, OP& A, PC* M, long n, const cx<T>* 
       else if (j + 1 < m && st.iters + 2 <= maxit) HIPTRY(p, step(j + 1));
       HIPTRY(p, hipEventSynchronize(W.ev[j & 1]));
       const double* sh = W.state_h + 4 * (j & 1);
+      if (again) {
+        idle = sh[3] != 0.0 ? 0 : idle + 1;
+        again = idle < patience;
+      } else if (sizeof(T) == 8 && sh[2] == 0.0 && sh[3] != 0.0 && sh[0] > tol) {
+        again = true;
+        idle = 0;
+        patience *= 2;
+        HIPTRY(p, step(j, true));
+        if (pipe && j + 1 < m && st.iters + 2 <= maxit) HIPTRY(p, step(j + 1));
+        HIPTRY(p, hipEventSynchronize(W.ev[j & 1]));
+      }
       st.iters++;
       k = j + 1;
       st.est = sh[0];
@@ -953,7 +978,7 @@ size_t vie::lds_budget(int device) {
 // device current) and every use goes through that pointer.
 namespace {
 constexpr size_t kScratchBytes = 64ull << 20;
-constexpr size_t kScratchSlack = 128 << 10;   // rounding of the dots' chunks (vie_solve_noalloc)
+constexpr size_t kScratchSlack = 256 << 10;   // outside the limit's count (vie_solve_noalloc)
 constexpr int kMaxDevices = 64;
 }  // namespace
 
@@ -1540,9 +1565,13 @@ int vie_solve_noalloc(vie_plan_t p, const vie_c128* b, vie_c128* x, double tol, 
   ws.g = c.take<double2>(m + 1);
   ws.y = c.take<double2>(m + 1);
   ws.cs = c.take<double>(m + 1);
-  // the limit counts half a chunk of the dots per vector as it always did; rounding their
-  // chunks up takes at most m + 1 partials more, from the array's slack
+  // The limit counts half a chunk of the dots per vector, as it always did.  From the array's
+  // slack: rounding their chunks up, at most m + 1 <= 4097 values, the norms' partials, at most
+  // 2048, and the pending right-hand side, m + 1: 160 KiB and alignment.
+  ScratchCarver tail = c;
   ws.partial = c.take<double2>((size_t)partial_blocks(n) * (m + 1));
+  tail.take<double2>(arnoldi_partials(n, m));
+  ws.pend = tail.take<double2>(m + 1);
   ws.state_h = p->npin;
   ws.ev[0] = p->nev[0];
   ws.ev[1] = p->nev[1];

@@ -186,3 +186,30 @@ def test_one_cycle_equals_the_oracle(slow_system, m):
     # both residuals in units of ||b||: FP64 rounding of a few hundred products and projections
     assert abs(true - want) <= 1e-12, (m, true, want)
     assert abs(info["rel_res_true"] - true) <= 1e-13
+
+
+# One voxel of permittivity near zero multiplies its rows of A by |1 - eps_b / eps|: every step
+# then cancels to about the reciprocal of that, and the basis stays orthogonal only if what is
+# left of w is measured against it again.
+def _near_zero_voxel(small):
+    n, h, k0, eps_b = (6, 5, 8), 0.05, inputs.K0, inputs.EPS_B
+    eps = np.full(n, 12.11 + 0.3j)
+    eps[3, 2, 4] = small * (1.0 + 0.5j)
+    chi = mv.contrast(eps, eps_b)
+    op = mv.Operator(green.green_table(n, mv.kappa_of(h, k0, eps_b)), chi)
+    # rounding of the product, 20 steps' worth, in units of ||b||
+    return (n, h, k0, eps_b), eps, op, inputs.gaussian_rhs(n, 4), 20 * 2.0 ** -52 * np.abs(chi).max()
+
+
+@pytest.mark.parametrize("small,m", [(1e-2, 30), (1e-8, 30), (1e-10, 8), (1e-10, 15), (1e-11, 15)])
+def test_one_cycle_of_cancelling_steps_equals_the_oracle(small, m):
+    vie = _dev()
+    args, eps, op, b, bound = _near_zero_voxel(small)
+    plan = vie.Plan(*args, fp32=False)
+    plan.set_contrast(torch.from_numpy(eps).cuda())
+    _, ref = solve.fgmres(op, b.ravel(), tol=1e-15, restart=m, maxit=m)
+    x, info = plan.solve(torch.from_numpy(b).cuda(), tol=1e-15, restart=m, maxit=m)
+    true = _oracle_rel_res(op, b, x.cpu().numpy())
+    assert info["iters"] == m
+    assert abs(true - ref.history[m - 1]) <= bound + 1e-12, (true, ref.history[m - 1], bound)
+    assert abs(info["rel_res_est"] - true) <= bound + 1e-12
