@@ -80,6 +80,7 @@ struct KDesc {
   long n;
   int nchunk;
   double2* partial; // 2 (m + 1) * nchunk
+  double* norms;    // 2 nchunk: ||w||^2 after the update and after the extra sweep's
   double2* h;       // projections of the step
   double2* raw;     // V^H w
   double2* gd;      // Gram diagonal
@@ -91,6 +92,7 @@ struct KDesc {
   double2* y;
   int* act;         // active in the current step
   int* go;          // act as the step's projections found it (act may clear while it ends)
+  int* again;       // the step needs the extra sweep (FP64)
   const int* act0;  // active for the cycle
   int* kdone;       // Arnoldi steps of the current cycle
   int* iters;       // accumulated steps
@@ -127,17 +129,19 @@ __device__ __forceinline__ cx<T>* vsel(const KDesc& D, int which, int j) {
 // the Gram matrix G = V^H V, h = 2 V^H w - G V^H w, one dot pass and one update pass over the
 // basis per step.  (With the sweeps apart, in workgroups that walked all vectors of a chunk:
 // 117 us of dots and updates per FP32 step of eight systems of 968k unknowns together; now 28.)
+// An FP64 step that cancels too much is measured against the basis once more, as there: k_b_gate
+// decides it per system, and dots, their sums and the update run again (AGAIN) for those systems.
 
 // partial[(2 i + s) nchunk + chunk] = V_i^H w (s = 0) and V_i^H V_j (s = 1) over the chunk, for
 // the four vectors i of blockIdx.y; w = V_{j+1}
-template <typename T>
+template <typename T, bool AGAIN>
 __global__ __launch_bounds__(kT) void k_b_mdot(const KDesc* __restrict__ d, const int* __restrict__ prefix, int nsys,
                                                int j) {
   __shared__ double lds[kT / 64][16];
   const int item = blockIdx.x;
   const int s = find_item(prefix, nsys, item);
   const KDesc& D = d[s];
-  if (*D.act == 0) return;
+  if (*(AGAIN ? D.again : D.act) == 0) return;
   const int chunk = item - prefix[s], i0 = blockIdx.y * 4;
   const long n = D.n;
   const cx<T>* V = (const cx<T>*)D.V;
@@ -243,8 +247,47 @@ __global__ __launch_bounds__(kProjT) void k_b_proj(const KDesc* __restrict__ d, 
   }
 }
 
-// w = V_{j+1} -= sum_{i <= j} h_i V_i and partial[chunk].x = ||w||^2 over the chunk
-template <typename T>
+// again = 1 where ||w||^2 is too small a part of ||h||^2, one workgroup per system
+__global__ __launch_bounds__(kT) void k_b_gate(const KDesc* __restrict__ d, int j) {
+  __shared__ double lds[(kT / 64) * 2];
+  const KDesc& D = d[blockIdx.x];
+  if (*D.go == 0) {
+    if (threadIdx.x == 0) *D.again = 0;
+    return;
+  }
+  double v[2] = {0.0, 0.0};
+  for (int c = threadIdx.x; c < D.nchunk; c += kT) v[0] += D.norms[c];
+  for (int i = threadIdx.x; i <= j; i += kT) v[1] += D.h[i].x * D.h[i].x + D.h[i].y * D.h[i].y;
+  bsum<2>(v, lds);
+  if (threadIdx.x == 0) *D.again = v[0] < kCancel2 * v[1] ? 1 : 0;
+}
+
+// The extra sweep's coefficients: raw = V^H w, and h += raw; one workgroup per system
+__global__ __launch_bounds__(kProjT) void k_b_proj_again(const KDesc* __restrict__ d, int j) {
+  const KDesc& D = d[blockIdx.x];
+  if (*D.again == 0) return;
+  const int sub = threadIdx.x & 7;
+  for (int i = threadIdx.x >> 3; i <= j; i += kProjT / 8) {
+    double2 s{0.0, 0.0};
+    for (int b = sub; b < D.nchunk; b += 8) {
+      const double2 p = D.partial[2L * i * D.nchunk + b];
+      s.x += p.x;
+      s.y += p.y;
+    }
+#pragma unroll
+    for (int o = 1; o < 8; o <<= 1) {
+      s.x += __shfl_xor(s.x, o, 64);
+      s.y += __shfl_xor(s.y, o, 64);
+    }
+    if (sub == 0) {
+      D.raw[i] = s;
+      D.h[i] = double2{D.h[i].x + s.x, D.h[i].y + s.y};
+    }
+  }
+}
+
+// w = V_{j+1} -= sum_{i <= j} h_i V_i (AGAIN: raw_i) and norms[chunk] = ||w||^2 over the chunk
+template <typename T, bool AGAIN>
 __global__ __launch_bounds__(kT) void k_b_orth(const KDesc* __restrict__ d, const int* __restrict__ prefix, int nsys,
                                                int j) {
   __shared__ double2 c[512];
@@ -252,8 +295,9 @@ __global__ __launch_bounds__(kT) void k_b_orth(const KDesc* __restrict__ d, cons
   const int item = blockIdx.x;
   const int s = find_item(prefix, nsys, item);
   const KDesc& D = d[s];
-  if (*D.go == 0) return;
-  for (int i = threadIdx.x; i <= j + 1; i += kT) c[i] = i <= j ? D.h[i] : double2{0.0, 0.0};
+  if (*(AGAIN ? D.again : D.go) == 0) return;
+  const double2* coef = AGAIN ? D.raw : D.h;
+  for (int i = threadIdx.x; i <= j + 1; i += kT) c[i] = i <= j ? coef[i] : double2{0.0, 0.0};
   __syncthreads();
   const long n = D.n;
   const int chunk = item - prefix[s];
@@ -297,7 +341,7 @@ __global__ __launch_bounds__(kT) void k_b_orth(const KDesc* __restrict__ d, cons
     }
   }
   bsum<1>(v, lds);
-  if (threadIdx.x == 0) D.partial[chunk] = double2{v[0], 0.0};
+  if (threadIdx.x == 0) D.norms[(AGAIN ? D.nchunk : 0) + chunk] = v[0];
 }
 
 // partial[chunk] = ||v||^2 over the chunk, v selected by (which, j); act_sel: 0 -> act, 1 -> act0
@@ -375,7 +419,7 @@ __global__ void k_b_init(const KDesc* __restrict__ d, int nsys, int m) {
   }
 }
 
-// End of step j: every workgroup sums its system's partials of ||w||^2 and scales its chunk of
+// End of step j: every workgroup sums its system's parts of ||w||^2 and scales its chunk of
 // V_{j+1}; the system's first one also does the Hessenberg column, the rotations, the residual
 // estimate and the step mask.
 template <typename T>
@@ -390,7 +434,8 @@ __global__ __launch_bounds__(kT) void k_b_finish(const KDesc* __restrict__ d, co
   if (*D.go == 0) return;
   const int chunk = item - prefix[s];
   double v[1] = {0.0};
-  for (int c = threadIdx.x; c < D.nchunk; c += kT) v[0] += D.partial[c].x;
+  const double* norms = D.norms + (sizeof(T) == 8 && *D.again != 0 ? D.nchunk : 0);
+  for (int c = threadIdx.x; c < D.nchunk; c += kT) v[0] += norms[c];
   bsum<1>(v, lds);
   if (threadIdx.x == 0) s_norm = sqrt(v[0]);
   if (chunk == 0)
@@ -709,9 +754,9 @@ hipError_t build_level(BatchLevel<T>& L, Arena& A, const std::vector<long>& n, i
   L.h.resize(L.nsys);
   L.cpre.assign(L.nsys + 1, 0);
   hipError_t e;
-  int* flags = nullptr;   // per system: act, kdone, iters, go
-  if ((e = A.take((void**)&flags, sizeof(int) * 4 * L.nsys))) return e;
-  if ((e = hipMemset(flags, 0, sizeof(int) * 4 * L.nsys))) return e;
+  int* flags = nullptr;   // per system: act, kdone, iters, go, again
+  if ((e = A.take((void**)&flags, sizeof(int) * 5 * L.nsys))) return e;
+  if ((e = hipMemset(flags, 0, sizeof(int) * 5 * L.nsys))) return e;
   double* est = nullptr;
   if ((e = A.take((void**)&est, sizeof(double) * L.nsys))) return e;
   for (int s = 0; s < L.nsys; ++s) {
@@ -730,6 +775,7 @@ hipError_t build_level(BatchLevel<T>& L, Arena& A, const std::vector<long>& n, i
     D.b = b[s];
     if ((e = A.take(&D.r, sizeof(cx<T>) * len))) return e;
     if ((e = A.take((void**)&D.partial, sizeof(double2) * 2 * (size_t)(m + 1) * nch))) return e;
+    if ((e = A.take((void**)&D.norms, sizeof(double) * 2 * nch))) return e;
     double2* small = nullptr;
     const size_t per = (size_t)(m + 2) * 3 + 2 + (size_t)(m + 1) * m + 3 * (size_t)(m + 1);
     if ((e = A.take((void**)&small, sizeof(double2) * per))) return e;
@@ -746,6 +792,7 @@ hipError_t build_level(BatchLevel<T>& L, Arena& A, const std::vector<long>& n, i
     D.kdone = flags + L.nsys + s;
     D.iters = flags + 2 * L.nsys + s;
     D.go = flags + 3 * L.nsys + s;
+    D.again = flags + 4 * L.nsys + s;
     D.act0 = act_cycle_src ? act_cycle_src + s : act_cycle + s;
     D.est = est + s;
     D.tol = tol;
@@ -990,11 +1037,16 @@ hipError_t enqueue_cycle(vie_batch_s* B, BatchLevel<T>& L, PassSet& PS, int) {
     }
     if ((e = batch_matvec<T>(B, PS, L, false, j))) return e;
     if (L.ctotal > 0) {
-      const dim3 chunks((unsigned)L.ctotal);
-      hipLaunchKernelGGL((k_b_mdot<T>), dim3((unsigned)L.ctotal, (unsigned)(j + 4) / 4), dim3(kT), 0, s, L.d, L.d_cpre,
-                         L.nsys, j);
-      hipLaunchKernelGGL(k_b_proj, dim3((unsigned)L.nsys), dim3(kProjT), 0, s, L.d, j, L.m);
-      hipLaunchKernelGGL((k_b_orth<T>), chunks, dim3(kT), 0, s, L.d, L.d_cpre, L.nsys, j);
+      const dim3 chunks((unsigned)L.ctotal), dots((unsigned)L.ctotal, (unsigned)(j + 4) / 4), systems((unsigned)L.nsys);
+      hipLaunchKernelGGL((k_b_mdot<T, false>), dots, dim3(kT), 0, s, L.d, L.d_cpre, L.nsys, j);
+      hipLaunchKernelGGL(k_b_proj, systems, dim3(kProjT), 0, s, L.d, j, L.m);
+      hipLaunchKernelGGL((k_b_orth<T, false>), chunks, dim3(kT), 0, s, L.d, L.d_cpre, L.nsys, j);
+      if (sizeof(T) == 8) {
+        hipLaunchKernelGGL(k_b_gate, systems, dim3(kT), 0, s, L.d, j);
+        hipLaunchKernelGGL((k_b_mdot<T, true>), dots, dim3(kT), 0, s, L.d, L.d_cpre, L.nsys, j);
+        hipLaunchKernelGGL(k_b_proj_again, systems, dim3(kProjT), 0, s, L.d, j);
+        hipLaunchKernelGGL((k_b_orth<T, true>), chunks, dim3(kT), 0, s, L.d, L.d_cpre, L.nsys, j);
+      }
       hipLaunchKernelGGL((k_b_finish<T>), chunks, dim3(kT), 0, s, L.d, L.d_cpre, L.nsys, j, L.m);
     }
   }

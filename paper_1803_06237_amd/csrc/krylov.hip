@@ -13,7 +13,7 @@
 //
 // The merged second sweep corrects for G != I but takes V^H w' from the rounded dots of w
 // instead of measuring it, so V^H v_{j+1} is of order eps ||h|| / ||w''|| (two measured sweeps:
-// eps).  On guides ||w''|| is 0.3 to 0.5 of ||h||.  Where it is below kCancel = 0.1 of it in
+// eps).  On guides ||w''|| is 0.3 to 0.5 of ||h||.  Where it is below a tenth of it (kCancel2) in
 // FP64, one more sweep measures V^H w'' and subtracts it, which bounds the loss by 10 eps at
 // any cancellation (without it a permittivity of 1e-10 in one voxel, ratios of 1e-10, made a
 // cycle of 15 steps end at 27 times the minimal residual, the basis no longer one).  k_finish reports such a step; the
@@ -47,7 +47,6 @@ constexpr int kDotEPT = 4;                  // elements per thread and round of 
 constexpr int kDotChunk = kThreads * kDotEPT;
 constexpr int kDotBlocks = 256;             // most blocks (partials) per vector group of the multi-dot
 constexpr int kAxpyBlocks = 2048;           // most blocks (partials) of k_maxpy_nrm
-constexpr double kCancel2 = 0.01;           // kCancel^2: ||w''||^2 / ||h||^2 of a step that needs the extra sweep
 
 __device__ __forceinline__ double2 to_d(double2 v) { return v; }
 __device__ __forceinline__ double2 to_d(float2 v) { return double2{(double)v.x, (double)v.y}; }

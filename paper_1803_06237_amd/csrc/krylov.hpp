@@ -6,6 +6,9 @@
 
 namespace vie {
 
+// ||w||^2 / ||h||^2 of an FP64 Arnoldi step below which it needs the extra sweep (krylov.hip)
+constexpr double kCancel2 = 0.01;
+
 // Sums of NV (a power of two up to 64) values per lane over the wave: lane l gets that of value *idx, with half
 // as many exchanges per halving step as values left (17 in all for 16 values instead of 96).
 template <int NV, int H>

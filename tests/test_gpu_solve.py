@@ -213,3 +213,21 @@ def test_one_cycle_of_cancelling_steps_equals_the_oracle(small, m):
     assert info["iters"] == m
     assert abs(true - ref.history[m - 1]) <= bound + 1e-12, (true, ref.history[m - 1], bound)
     assert abs(info["rel_res_est"] - true) <= bound + 1e-12
+
+
+@pytest.mark.parametrize("cycles", [1, 3])
+def test_cycles_of_cancelling_steps_in_a_batch(cycles):
+    """The same in a batch, next to a system without the voxel, whose steps do not cancel; the
+    second cycle is captured, the third replays it."""
+    vie = _dev()
+    m, cases, plans = 15, [_near_zero_voxel(s) for s in (1e-10, 12.11, 1e-2, 1e-11)], []
+    for args, eps, *_ in cases:
+        plans.append(vie.Plan(*args, fp32=False))
+        plans[-1].set_contrast(torch.from_numpy(eps).cuda())
+    bs = [torch.from_numpy(c[3]).cuda() for c in cases]
+    xs, infos, _ = vie.solve_batch(plans, bs, tol=1e-15, restart=m, maxit=cycles * m)
+    for (_, _, op, b, bound), x, info in zip(cases, xs, infos):
+        _, ref = solve.fgmres(op, b.ravel(), tol=1e-15, restart=m, maxit=cycles * m)
+        true = _oracle_rel_res(op, b, x.cpu().numpy())
+        assert info["iters"] == cycles * m
+        assert abs(true - ref.history[-1]) <= bound + 1e-12, (true, ref.history[-1], bound)
