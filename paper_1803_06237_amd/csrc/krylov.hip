@@ -80,12 +80,12 @@ __device__ __forceinline__ void block_sum(double (&v)[NV], double* lds) {
 }
 
 // partial[(2 i + s) nblk + blk] = the block's share of V_i^H w (s = 0) and of V_i^H V_{nv-1}
-// (s = 1), for the kGroup vectors i of blockIdx.y; nothing where *gate == 0
-template <typename T>
+// (s = 1), for the kGroup vectors i of blockIdx.y; GATED: nothing where *gate == 0
+template <typename T, bool GATED>
 __global__ __launch_bounds__(kThreads) void k_mdot2(const cx<T>* __restrict__ V, long ldv, int nv,
                                                      const cx<T>* __restrict__ w, long n,
                                                      double2* __restrict__ partial, const int* __restrict__ gate) {
-  if (gate && *gate == 0) return;
+  if (GATED && *gate == 0) return;
   constexpr int kVals = 4 * kGroup;
   __shared__ double lds[kThreads / 64][kVals];
   const cx<T>* vj = V + (long)(nv - 1) * ldv;
@@ -313,13 +313,13 @@ __global__ __launch_bounds__(kThreads) void k_zero(cx<T>* __restrict__ dst, long
     dst[e] = cx<T>{(T)0, (T)0};
 }
 
-// w -= sum_i h_i V_i and, of the stored result, the block partial sums of |w|^2; nothing where
-// *gate == 0
-template <typename T>
+// w -= sum_i h_i V_i and, of the stored result, the block partial sums of |w|^2; GATED: nothing
+// where *gate == 0
+template <typename T, bool GATED>
 __global__ __launch_bounds__(kThreads) void k_maxpy_nrm(const cx<T>* __restrict__ V, long ldv, int nv,
                                                          const double2* __restrict__ h, cx<T>* __restrict__ w, long n,
                                                          double* __restrict__ partial, const int* __restrict__ gate) {
-  if (gate && *gate == 0) return;
+  if (GATED && *gate == 0) return;
   extern __shared__ unsigned char smem_raw[];
   double2* c = reinterpret_cast<double2*>(smem_raw);   // nv values, zeros up to a multiple of 8
   __shared__ double lds[kThreads / 64];
@@ -356,7 +356,7 @@ __global__ __launch_bounds__(kThreads) void k_maxpy_nrm(const cx<T>* __restrict_
 // a step can be repeated.  state: see k_finish.
 __device__ __forceinline__ void hessenberg_column(double2* hs, double hn, double* __restrict__ cs,
                                                   double2* __restrict__ sn, double2* __restrict__ gvec,
-                                                  double2* __restrict__ pend, int j, double bnorm, bool cancelled,
+                                                  double2* __restrict__ pend, int j, double bnorm,
                                                   double* __restrict__ state) {
   // previous rotations: [c s; -conj(s) c] on (h_i, h_{i+1})
   double2 a = hs[0];
@@ -400,7 +400,6 @@ __device__ __forceinline__ void hessenberg_column(double2* hs, double hn, double
   state[0] = est;
   state[1] = hn;
   state[2] = (isfinite(est) && isfinite(hn) && isfinite(r.x) && isfinite(r.y)) ? 0.0 : 1.0;
-  state[3] = cancelled ? 1.0 : 0.0;
   __threadfence_system();
 }
 
@@ -420,20 +419,16 @@ __global__ __launch_bounds__(kThreads) void k_finish(cx<T>* __restrict__ w, long
                                                       double* __restrict__ state) {
   extern __shared__ unsigned char smem_raw[];
   double2* hs = reinterpret_cast<double2*>(smem_raw);   // j + 2 entries (workgroup 0)
-  __shared__ double lds[(kThreads / 64) * 2];
+  __shared__ double lds[kThreads / 64];
   __shared__ double s_norm;
   const bool again = gate && *gate != 0;
   if (again) partial += nblk;
-  double v[2] = {0.0, 0.0};   // ||w||^2, ||h||^2 (workgroup 0)
+  double v[1] = {0.0};
   for (int b = threadIdx.x; b < nblk; b += kThreads) v[0] += partial[b];
-  if (blockIdx.x == 0)
-    for (int i = threadIdx.x; i <= j; i += kThreads) {
-      const double2 hi = h[i];
-      hs[i] = hi;
-      v[1] += hi.x * hi.x + hi.y * hi.y;
-    }
-  block_sum<2>(v, lds);
+  block_sum<1>(v, lds);
   if (threadIdx.x == 0) s_norm = sqrt(v[0]);
+  if (blockIdx.x == 0)
+    for (int i = threadIdx.x; i <= j; i += kThreads) hs[i] = h[i];
   __syncthreads();
   const double hn = s_norm;
   const double scale = hn > 0.0 ? 1.0 / hn : 0.0;
@@ -442,8 +437,13 @@ __global__ __launch_bounds__(kThreads) void k_finish(cx<T>* __restrict__ w, long
     w[e] = from_d<cx<T>>(double2{a.x * scale, a.y * scale});
   }
   if (blockIdx.x != 0) return;
-  if (threadIdx.x == 0)
-    hessenberg_column(hs, hn, cs, sn, gvec, pend, j, bnorm, again || v[0] < kCancel2 * v[1], state);
+  if (threadIdx.x == 0) hessenberg_column(hs, hn, cs, sn, gvec, pend, j, bnorm, state);
+  if (threadIdx.x >= 64 && threadIdx.x < 128) {   // meanwhile the second wave: the cancellation
+    double hh = 0.0;
+    for (int i = threadIdx.x - 64; i <= j; i += 64) hh += h[i].x * h[i].x + h[i].y * h[i].y;
+    hh = wave_sum(hh);
+    if (threadIdx.x == 64) state[3] = again || hn * hn < kCancel2 * hh ? 1.0 : 0.0;
+  }
   __syncthreads();
   double2* col = H + (long)j * ldh;
   for (int i = threadIdx.x; i <= j; i += kThreads) col[i] = hs[i];
@@ -556,7 +556,8 @@ template <typename T>
 static hipError_t allow_step_lds() {
   const auto a = hipFuncAttributeMaxDynamicSharedMemorySize;
   const int bytes = (4096 + 8) * 16;
-  hipError_t e = hipFuncSetAttribute((const void*)k_maxpy_nrm<T>, a, bytes);
+  hipError_t e = hipFuncSetAttribute((const void*)k_maxpy_nrm<T, false>, a, bytes);
+  if (!e) e = hipFuncSetAttribute((const void*)k_maxpy_nrm<T, true>, a, bytes);
   if (!e) e = hipFuncSetAttribute((const void*)k_finish<T>, a, bytes);
   if (!e) e = hipFuncSetAttribute((const void*)k_trisolve, a, 160 * 1024);
   return e;
@@ -573,16 +574,16 @@ hipError_t KrylovOps<T>::orthogonalise(const cx<T>* V, int j, cx<T>* w, long n, 
   int* gate = again ? d.gate : nullptr;
   const dim3 dgrid(nd, (nv + kGroup - 1) / kGroup);
   const size_t coef = (size_t)(nv + 7) * sizeof(double2);
-  hipLaunchKernelGGL((k_mdot2<T>), dgrid, dim3(kThreads), 0, s, V, n, nv, w, n, dots, (const int*)nullptr);
+  hipLaunchKernelGGL((k_mdot2<T, false>), dgrid, dim3(kThreads), 0, s, V, n, nv, w, n, dots, (const int*)nullptr);
   hipLaunchKernelGGL(k_proj, dim3(1), dim3(kProjThreads), 0, s, dots, nd, nv, d.raw, d.gd, d.H, d.ldh, d.h);
-  hipLaunchKernelGGL((k_maxpy_nrm<T>), dim3(na), dim3(kThreads), coef, s, V, n, nv, d.h, w, n, norms,
+  hipLaunchKernelGGL((k_maxpy_nrm<T, false>), dim3(na), dim3(kThreads), coef, s, V, n, nv, d.h, w, n, norms,
                      (const int*)nullptr);
   if (again) {
     hipLaunchKernelGGL(k_gate, dim3(1), dim3(kThreads), 0, s, norms, na, d.h, nv, gate);
-    hipLaunchKernelGGL((k_mdot2<T>), dgrid, dim3(kThreads), 0, s, V, n, nv, w, n, dots, (const int*)gate);
+    hipLaunchKernelGGL((k_mdot2<T, true>), dgrid, dim3(kThreads), 0, s, V, n, nv, w, n, dots, (const int*)gate);
     hipLaunchKernelGGL(k_proj_again, dim3((nv + kThreads / 8 - 1) / (kThreads / 8)), dim3(kThreads), 0, s, dots, nd,
                        nv, d.raw, d.h, (const int*)gate);
-    hipLaunchKernelGGL((k_maxpy_nrm<T>), dim3(na), dim3(kThreads), coef, s, V, n, nv, d.raw, w, n, norms + na,
+    hipLaunchKernelGGL((k_maxpy_nrm<T, true>), dim3(na), dim3(kThreads), coef, s, V, n, nv, d.raw, w, n, norms + na,
                        (const int*)gate);
   }
   hipLaunchKernelGGL((k_finish<T>), dim3(na), dim3(kThreads), (size_t)(j + 2) * sizeof(double2), s, w, n, norms,
