@@ -189,16 +189,14 @@ __global__ __launch_bounds__(kT) void k_b_mdot(const KDesc* __restrict__ d, cons
 }
 
 // Sums of the dots, the new Gram column and h, one workgroup per system (as k_proj)
-constexpr int kProjT = 1024;
-__global__ __launch_bounds__(kProjT) void k_b_proj(const KDesc* __restrict__ d, int j, int m) {
-  __shared__ double2 sums[kProjT / 64][64];
+__global__ __launch_bounds__(kProjThreads) void k_b_proj(const KDesc* __restrict__ d, int j, int m) {
+  __shared__ ProjLds lds;
   const KDesc& D = d[blockIdx.x];
   const int on = *D.act;
   if (threadIdx.x == 0) *D.go = on;
   if (on == 0) return;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nv = j + 1, ldh = m + 1, sub = threadIdx.x & 7;
-  constexpr int kW = kProjT / 64;
-  for (int v = threadIdx.x >> 3; v < 2 * nv; v += kProjT / 8) {
+  const int nv = j + 1, ldh = m + 1, sub = threadIdx.x & 7;
+  for (int v = threadIdx.x >> 3; v < 2 * nv; v += kProjThreads / 8) {
     double2 s{0.0, 0.0};
 #pragma unroll 8
     for (int b = sub; b < D.nchunk; b += 8) {
@@ -219,32 +217,7 @@ __global__ __launch_bounds__(kProjT) void k_b_proj(const KDesc* __restrict__ d, 
     }
   }
   __syncthreads();
-  for (int i0 = 0; i0 < nv; i0 += 64) {
-    const int i = i0 + lane;
-    double2 s{0.0, 0.0};
-    if (i < nv)
-      for (int k = wave; k < nv; k += kW) {
-        const double2 r = D.raw[k];
-        double2 g;                                   // G_ik
-        if (k == i) g = D.gd[i];
-        else if (k > i) g = D.H[(long)i * ldh + k];
-        else g = D.H[(long)k * ldh + i], g.y = -g.y;
-        s.x += g.x * r.x - g.y * r.y;
-        s.y += g.x * r.y + g.y * r.x;
-      }
-    sums[wave][lane] = s;
-    __syncthreads();
-    if (wave == 0 && i < nv) {
-      double2 t{0.0, 0.0};
-      for (int k = 0; k < kW; ++k) {
-        t.x += sums[k][lane].x;
-        t.y += sums[k][lane].y;
-      }
-      const double2 r = D.raw[i];
-      D.h[i] = double2{2.0 * r.x - t.x, 2.0 * r.y - t.y};
-    }
-    __syncthreads();
-  }
+  for (int i0 = 0; i0 < nv; i0 += 64) project_rows(D.raw, D.gd, D.H, ldh, nv, i0, D.h, lds);
 }
 
 // again = 1 where ||w||^2 is too small a part of ||h||^2, one workgroup per system
@@ -263,11 +236,11 @@ __global__ __launch_bounds__(kT) void k_b_gate(const KDesc* __restrict__ d, int 
 }
 
 // The extra sweep's coefficients: raw = V^H w, and h += raw; one workgroup per system
-__global__ __launch_bounds__(kProjT) void k_b_proj_again(const KDesc* __restrict__ d, int j) {
+__global__ __launch_bounds__(kProjThreads) void k_b_proj_again(const KDesc* __restrict__ d, int j) {
   const KDesc& D = d[blockIdx.x];
   if (*D.again == 0) return;
   const int sub = threadIdx.x & 7;
-  for (int i = threadIdx.x >> 3; i <= j; i += kProjT / 8) {
+  for (int i = threadIdx.x >> 3; i <= j; i += kProjThreads / 8) {
     double2 s{0.0, 0.0};
     for (int b = sub; b < D.nchunk; b += 8) {
       const double2 p = D.partial[2L * i * D.nchunk + b];
@@ -1039,12 +1012,12 @@ hipError_t enqueue_cycle(vie_batch_s* B, BatchLevel<T>& L, PassSet& PS, int) {
     if (L.ctotal > 0) {
       const dim3 chunks((unsigned)L.ctotal), dots((unsigned)L.ctotal, (unsigned)(j + 4) / 4), systems((unsigned)L.nsys);
       hipLaunchKernelGGL((k_b_mdot<T, false>), dots, dim3(kT), 0, s, L.d, L.d_cpre, L.nsys, j);
-      hipLaunchKernelGGL(k_b_proj, systems, dim3(kProjT), 0, s, L.d, j, L.m);
+      hipLaunchKernelGGL(k_b_proj, systems, dim3(kProjThreads), 0, s, L.d, j, L.m);
       hipLaunchKernelGGL((k_b_orth<T, false>), chunks, dim3(kT), 0, s, L.d, L.d_cpre, L.nsys, j);
       if (sizeof(T) == 8) {
         hipLaunchKernelGGL(k_b_gate, systems, dim3(kT), 0, s, L.d, j);
         hipLaunchKernelGGL((k_b_mdot<T, true>), dots, dim3(kT), 0, s, L.d, L.d_cpre, L.nsys, j);
-        hipLaunchKernelGGL(k_b_proj_again, systems, dim3(kProjT), 0, s, L.d, j);
+        hipLaunchKernelGGL(k_b_proj_again, systems, dim3(kProjThreads), 0, s, L.d, j);
         hipLaunchKernelGGL((k_b_orth<T, true>), chunks, dim3(kT), 0, s, L.d, L.d_cpre, L.nsys, j);
       }
       hipLaunchKernelGGL((k_b_finish<T>), chunks, dim3(kT), 0, s, L.d, L.d_cpre, L.nsys, j, L.m);

@@ -6,7 +6,7 @@
 // w'' = w - V h with h = 2 h1 - G h1 needs one pass over the basis for the dots and one for
 // the update instead of two each; G's new column V^H v_j comes out of the same dot pass (v_j
 // is its last vector).  Four kernels a step: k_mdot2 (dots with w and with v_j), k_proj (their
-// sums, h), k_maxpy_nrm (w'' and block sums of |w''|^2), k_finish (norm, v_{j+1}, Hessenberg
+// sums, h; two launches in long cycles), k_maxpy_nrm (w'' and block sums of |w''|^2), k_finish (norm, v_{j+1}, Hessenberg
 // column, rotation, estimate to host memory).  Measured per step with the sweeps apart (dots
 // and update of the second gated by a cancellation test): ten kernels and a copy, 110 us at
 // n = 276480 and j ~ 20, 33 us at n = 1536 and j ~ 25; merged 60 and 18 us.
@@ -136,18 +136,13 @@ __global__ __launch_bounds__(kThreads) void k_mdot2(const cx<T>* __restrict__ V,
 }
 
 // The sums of k_mdot2's partials (raw = V^H w into `raw`, the new Gram column into gd[j] and
-// H's lower triangle) and h = 2 raw - G raw, j = nv - 1, by one workgroup; the product with G
-// is split over its 16 waves by columns.
-constexpr int kProjThreads = 1024;
-__global__ __launch_bounds__(kProjThreads) void k_proj(const double2* __restrict__ partial, int nblk, int nv,
-                                                       double2* __restrict__ raw, double2* __restrict__ gd,
-                                                       double2* __restrict__ H, int ldh, double2* __restrict__ h) {
-  __shared__ double2 sums[kProjThreads / 64][64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  constexpr int kW = kProjThreads / 64;
+// H's lower triangle), j = nv - 1
+__device__ __forceinline__ void dot_sums(const double2* __restrict__ partial, int nblk, int nv,
+                                         double2* __restrict__ raw, double2* __restrict__ gd,
+                                         double2* __restrict__ H, int ldh) {
   // 8 lanes per value: one round of loads for up to 64 vectors, kDotBlocks / 8 per lane
   const int sub = threadIdx.x & 7;
-  for (int v = threadIdx.x >> 3; v < 2 * nv; v += kProjThreads / 8) {
+  for (int v = (blockIdx.x * kProjThreads + threadIdx.x) >> 3; v < 2 * nv; v += gridDim.x * (kProjThreads / 8)) {
     double2 s{0.0, 0.0};
 #pragma unroll 8
     for (int b = sub; b < nblk; b += 8) {
@@ -167,33 +162,32 @@ __global__ __launch_bounds__(kProjThreads) void k_proj(const double2* __restrict
       else gd[i] = s;
     }
   }
+}
+
+// Sums and h = 2 raw - G raw by one workgroup.  Its share grows with nv^2: past kProjOne vectors
+// the sums and the rows are two launches over as many workgroups as they fill (an average step
+// at n = 12288, us: cycles of 150 steps 57.5 with 64, 59.8 with 192, of 200 65.6 and 69.4; of
+// 1000 152, by one workgroup throughout 380).
+constexpr int kProjOne = 64;
+__global__ __launch_bounds__(kProjThreads) void k_proj(const double2* __restrict__ partial, int nblk, int nv,
+                                                       double2* __restrict__ raw, double2* __restrict__ gd,
+                                                       double2* __restrict__ H, int ldh, double2* __restrict__ h) {
+  __shared__ ProjLds lds;
+  dot_sums(partial, nblk, nv, raw, gd, H, ldh);
   __syncthreads();
-  for (int i0 = 0; i0 < nv; i0 += 64) {
-    const int i = i0 + lane;
-    double2 s{0.0, 0.0};
-    if (i < nv)
-      for (int k = wave; k < nv; k += kW) {
-        const double2 r = raw[k];
-        double2 g;                                   // G_ik
-        if (k == i) g = gd[i];
-        else if (k > i) g = H[(long)i * ldh + k];
-        else g = H[(long)k * ldh + i], g.y = -g.y;
-        s.x += g.x * r.x - g.y * r.y;
-        s.y += g.x * r.y + g.y * r.x;
-      }
-    sums[wave][lane] = s;
-    __syncthreads();
-    if (wave == 0 && i < nv) {
-      double2 t{0.0, 0.0};
-      for (int k = 0; k < kW; ++k) {
-        t.x += sums[k][lane].x;
-        t.y += sums[k][lane].y;
-      }
-      const double2 r = raw[i];
-      h[i] = double2{2.0 * r.x - t.x, 2.0 * r.y - t.y};
-    }
-    __syncthreads();
-  }
+  for (int i0 = 0; i0 < nv; i0 += 64) project_rows(raw, gd, H, ldh, nv, i0, h, lds);
+}
+__global__ __launch_bounds__(kProjThreads) void k_dot_sums(const double2* __restrict__ partial, int nblk, int nv,
+                                                           double2* __restrict__ raw, double2* __restrict__ gd,
+                                                           double2* __restrict__ H, int ldh) {
+  dot_sums(partial, nblk, nv, raw, gd, H, ldh);
+}
+__global__ __launch_bounds__(kProjThreads) void k_proj_rows(const double2* __restrict__ raw,
+                                                            const double2* __restrict__ gd,
+                                                            const double2* __restrict__ H, int ldh, int nv,
+                                                            double2* __restrict__ h) {
+  __shared__ ProjLds lds;
+  project_rows(raw, gd, H, ldh, nv, blockIdx.x * 64, h, lds);
 }
 
 // *gate = 1 where ||w''||^2, the sum of nblk partials, is too small a part of ||h||^2
@@ -575,7 +569,13 @@ hipError_t KrylovOps<T>::orthogonalise(const cx<T>* V, int j, cx<T>* w, long n, 
   const dim3 dgrid(nd, (nv + kGroup - 1) / kGroup);
   const size_t coef = (size_t)(nv + 7) * sizeof(double2);
   hipLaunchKernelGGL((k_mdot2<T, false>), dgrid, dim3(kThreads), 0, s, V, n, nv, w, n, dots, (const int*)nullptr);
-  hipLaunchKernelGGL(k_proj, dim3(1), dim3(kProjThreads), 0, s, dots, nd, nv, d.raw, d.gd, d.H, d.ldh, d.h);
+  if (nv <= kProjOne) {
+    hipLaunchKernelGGL(k_proj, dim3(1), dim3(kProjThreads), 0, s, dots, nd, nv, d.raw, d.gd, d.H, d.ldh, d.h);
+  } else {
+    hipLaunchKernelGGL(k_dot_sums, dim3((16 * nv + kProjThreads - 1) / kProjThreads), dim3(kProjThreads), 0, s, dots,
+                       nd, nv, d.raw, d.gd, d.H, d.ldh);
+    hipLaunchKernelGGL(k_proj_rows, dim3((nv + 63) / 64), dim3(kProjThreads), 0, s, d.raw, d.gd, d.H, d.ldh, nv, d.h);
+  }
   hipLaunchKernelGGL((k_maxpy_nrm<T, false>), dim3(na), dim3(kThreads), coef, s, V, n, nv, d.h, w, n, norms,
                      (const int*)nullptr);
   if (again) {
