@@ -445,9 +445,9 @@ __global__ __launch_bounds__(kThreads) void k_finish(cx<T>* __restrict__ w, long
 
 // y = R^{-1} g for the leading k x k upper triangle of H, column by column from the last: one
 // workgroup, the right-hand side in LDS, every thread updating its rows with the new y_i.  A
-// triangle of up to 64 columns is staged in LDS first (by one thread from global memory the
-// solve took 133 us at k = 50, a load latency per entry).
-constexpr int kTriLds = 64;
+// triangle of up to kTriLds columns, within the default limit of 64 KiB, is staged in LDS first
+// (by one thread from global memory the solve took 133 us at k = 50, a load latency per entry).
+constexpr int kTriLds = 63;
 __global__ __launch_bounds__(kThreads) void k_trisolve(const double2* __restrict__ H, int ldh,
                                                         const double2* __restrict__ gvec, int k,
                                                         double2* __restrict__ y) {
@@ -545,29 +545,25 @@ static int axpy_blocks(long n) {
 }
 static int dot_blocks(long n) { return (int)std::min<long>(kDotBlocks, (n + kDotChunk - 1) / kDotChunk); }
 
-// up to 4103 staged values (restart <= 4096): a little above the default 64 KiB
-template <typename T>
-static hipError_t allow_step_lds() {
-  const auto a = hipFuncAttributeMaxDynamicSharedMemorySize;
-  const int bytes = (4096 + 8) * 16;
-  hipError_t e = hipFuncSetAttribute((const void*)k_maxpy_nrm<T, false>, a, bytes);
-  if (!e) e = hipFuncSetAttribute((const void*)k_maxpy_nrm<T, true>, a, bytes);
-  if (!e) e = hipFuncSetAttribute((const void*)k_finish<T>, a, bytes);
-  if (!e) e = hipFuncSetAttribute((const void*)k_trisolve, a, 160 * 1024);
-  return e;
+// Coefficients in LDS: past 64 KiB, the default limit (cycles of more than 4000 steps), a kernel
+// has to be told, on the device that it runs on; so for each such launch.
+static hipError_t allow_coefs(const void* kernel, size_t bytes) {
+  return bytes <= 4000 * sizeof(double2)
+             ? hipSuccess
+             : hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
 template <typename T>
 hipError_t KrylovOps<T>::orthogonalise(const cx<T>* V, int j, cx<T>* w, long n, const ArnoldiData& d, double bnorm,
                                        bool again, double* state, hipStream_t s) {
-  static const hipError_t lds_ok = allow_step_lds<T>();
-  if (lds_ok != hipSuccess) return lds_ok;
   const int nv = j + 1, nd = dot_blocks(n), na = axpy_blocks(n);
   double* norms = reinterpret_cast<double*>(d.partial);   // of the update and of the extra sweep's
   double2* dots = d.partial + na;
   int* gate = again ? d.gate : nullptr;
   const dim3 dgrid(nd, (nv + kGroup - 1) / kGroup);
   const size_t coef = (size_t)(nv + 7) * sizeof(double2);
+  for (const void* k : {(const void*)k_maxpy_nrm<T, false>, (const void*)k_maxpy_nrm<T, true>, (const void*)k_finish<T>})
+    if (hipError_t e = allow_coefs(k, coef)) return e;
   hipLaunchKernelGGL((k_mdot2<T, false>), dgrid, dim3(kThreads), 0, s, V, n, nv, w, n, dots, (const int*)nullptr);
   if (nv <= kProjOne) {
     hipLaunchKernelGGL(k_proj, dim3(1), dim3(kProjThreads), 0, s, dots, nd, nv, d.raw, d.gd, d.H, d.ldh, d.h);
@@ -605,8 +601,6 @@ hipError_t KrylovOps<T>::zero(cx<T>* dst, long n, hipStream_t s) {
 
 template <typename T>
 hipError_t KrylovOps<T>::trisolve(const double2* H, int ldh, const double2* g, int k, double2* y, hipStream_t s) {
-  static const hipError_t lds_ok = allow_step_lds<T>();
-  if (lds_ok != hipSuccess) return lds_ok;
   const size_t lds = sizeof(double2) * (size_t)(k + (k <= kTriLds ? k * k : 0));
   hipLaunchKernelGGL(k_trisolve, dim3(1), dim3(kThreads), lds, s, H, ldh, g, k, y);
   return hipGetLastError();

@@ -648,7 +648,8 @@ static inline AdamK adam_constants(int t, float lr) {
 
 static inline int gblocks(long n) { return (int)std::min<long>(4096, (n + 255) / 256); }
 
-// k_conv2 may use more than 64 KiB of dynamic LDS (83.5 KiB with four N-tiles)
+// k_conv2 may use more than 64 KiB of dynamic LDS (83.5 KiB with four N-tiles); to be allowed on
+// the current device before conv_launch
 template <int TAPS>
 static hipError_t allow_conv_lds_taps() {
   const auto a = hipFuncAttributeMaxDynamicSharedMemorySize;
@@ -688,8 +689,6 @@ static void conv2_launch_nt(bool big, int nt, dim3 grid, int n0, hipStream_t s, 
 hipError_t conv_launch(int taps, const bf16_t* X, int xcs, int xco, int Cin, const bf16_t* W, int Cout, bf16_t* Y,
                        int ycs, int yco, float* Yf, Vol vol, int relu, const bf16_t* mask, int mcs, int mco,
                        hipStream_t s, const ConvUp& up = {}, const NetOut& res = {}) {
-  static const hipError_t lds_ok = allow_conv_lds();
-  if (lds_ok) return lds_ok;
   const long big = (long)vol.B * ((vol.D + 1) / 2) * ((vol.H + kCty - 1) / kCty) * ((vol.W + 31) / 32);
   const long small = (long)vol.B * vol.D * ((vol.H + kCty - 1) / kCty) * ((vol.W + 15) / 16);
   const bool use_big = big >= 512;
@@ -1026,6 +1025,7 @@ int vie_net_create(vie_net_t* out, const int grid[3], unsigned seed, void* hip_s
     vie_net_destroy(N);
     return code;
   };
+  if (allow_conv_lds()) return bail(VIE_EDEVICE);
   size_t total = 0;
   for (int i = 0; i < kLayers; ++i) {
     Conv& C = N->L[i];
@@ -1242,6 +1242,7 @@ int vie_nn_conv_test(int mode, const int dims[3], int taps, int cin, int cout, c
   };
   // convert inputs: x has (mode 0, 2: cin; mode 1: cout) channels per voxel
   const int xc = mode == 1 ? cout : cin;
+  if (allow_conv_lds()) return fin(VIE_EDEVICE);
   bf16_t* xb = (bf16_t*)al(sizeof(bf16_t) * V * xc);
   if (!xb) return fin(VIE_ENOMEM);
   hipLaunchKernelGGL(k_f2bf, dim3(gblocks(V * xc)), dim3(256), 0, s, x, xb, V * xc);

@@ -111,3 +111,13 @@ def test_block_maps_are_bijections_with_writes_in_bounds():
     assert b"not injective" in buf.value
     assert L.vie_check_block_maps(buf, 512, 2) != 0
     assert b"bank conflict" in buf.value
+
+
+def test_no_function_attribute_is_set_once_per_process():
+    """A kernel's attributes belong to a device: the calls that set them are not kept in statics,
+    which a second device of the process would find done."""
+    csrc = os.path.join(ROOT, "paper_1803_06237_amd", "csrc")
+    for f in sorted(os.listdir(csrc)):
+        txt = re.sub(r"//[^\n]*", "", open(os.path.join(csrc, f)).read())
+        found = re.findall(r"\bstatic\s+(?:const\s+)?hipError_t\s+\w+\s*=[^;]*;", txt)
+        assert not found, (f, found)
