@@ -223,9 +223,9 @@ int vie_solve_noalloc(vie_plan_t plan, const vie_c128* b, vie_c128* x, double to
  * the box.  Device memory per system is about 16 ((restart + 1 [+ restart when
  * flexible] + 3) n_s + 2 (3 N_s) [not when filled] + 3 n1 n2 M3) bytes, the last
  * term the intermediate of the passes, and the mixed tier adds half as much again
- * for its FP32 level (inner_restart + 3 vectors of n_s); it is taken in blocks of
- * up to 256 MiB, the last of them in part unused.  A right-hand side with a
- * non-finite value gives VIE_EINVAL.
+ * for its FP32 level (inner_restart + 3 vectors of n_s); it is taken in two
+ * allocations of the sizes needed, next to one full-length vector.  A right-hand
+ * side with a non-finite value gives VIE_EINVAL.
  */
 int vie_solve_batch(vie_plan_t const* plans, const vie_c128* const* rhs, vie_c128* const* x, int count,
                     double tol, const vie_solve_opts* opts, vie_solve_info* infos);

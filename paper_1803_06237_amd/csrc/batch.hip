@@ -616,47 +616,12 @@ namespace {
 
 struct SysPlan : SolveView {};   // the operator of one system; U64, U32 are the batch's own
 
-// Device memory of one batch solve: pieces of a few growing blocks, given back together (158
-// single allocations of an eight-system batch took 3.5 ms to make and 11 ms to free).
-struct Arena {
-  std::vector<void*> blocks;
-  char* at = nullptr;
-  size_t left = 0, next = (size_t)4 << 20;
-  hipError_t take(void** p, size_t bytes) {
-    bytes = (bytes + 255) / 256 * 256;
-    if (bytes > left) {
-      size_t size = std::max(bytes, next);
-      void* q = nullptr;
-      hipError_t e = dmalloc(&q, size);
-      if (e && size > bytes) {   // short of memory: what is needed alone
-        (void)hipGetLastError();
-        e = dmalloc(&q, size = bytes);
-      }
-      if (e) return e;
-      blocks.push_back(q);
-      at = static_cast<char*>(q);
-      left = size;
-      next = std::min(2 * next, (size_t)256 << 20);
-    }
-    *p = at;
-    at += bytes;
-    left -= bytes;
-    return hipSuccess;
-  }
-  template <typename V>
-  hipError_t take(V** p, size_t bytes) {
-    return take(reinterpret_cast<void**>(p), bytes);
-  }
-  ~Arena() {
-    for (void* q : blocks) (void)hipFree(q);
-  }
-};
-
 template <typename T>
 struct BatchLevel {         // one Krylov level (outer FP64 or inner FP32) for the whole batch
   int nsys = 0, m = 0;
   bool flex = false;
   std::vector<KDesc> h;
+  int* flags = nullptr;     // per system: act, kdone, iters, go, again
   KDesc* d = nullptr;
   std::vector<int> cpre;    // chunk prefix
   int* d_cpre = nullptr;
@@ -667,6 +632,7 @@ struct BatchLevel {         // one Krylov level (outer FP64 or inner FP32) for t
 // the full-length buffers of the support descriptors or, for direct systems, on the vectors
 struct PassSet {
   std::vector<SDesc> h_sd;        // per system, filled before build_passes
+  unsigned char* tables = nullptr;   // device memory of everything below, pass_table_bytes
   SDesc* d_sd = nullptr;
   PassDesc* d_step = nullptr;
   PassDesc* d_res = nullptr;
@@ -710,49 +676,36 @@ struct vie_batch_s {
   bool circ_tier = false;         // FP64 FGMRES preconditioned by each plan's block circulant
   std::vector<Circ*> circ;        // per system (systems of one plan share it)
   std::vector<int> on;            // host copy of the cycle flags
-  Arena arena;
+  unsigned char* mem[2] = {nullptr, nullptr};   // the intermediates and vectors; the levels and tables
   hipGraphExec_t graph = nullptr;
   std::string err;
 };
 
 namespace {
 
+// The level's arrays (a system without support has length 0 and no chunks; its arrays keep one
+// element so every pointer is valid)
 template <typename T>
-hipError_t build_level(BatchLevel<T>& L, Arena& A, const std::vector<long>& n, int m, bool flex, double tol,
-                       const std::vector<const void*>& b, const std::vector<void*>& x, int* act_cycle,
-                       const int* act_cycle_src) {
+void carve_level(BatchLevel<T>& L, ScratchCarver& c, const std::vector<long>& n, int m, bool flex) {
   L.nsys = (int)n.size();
   L.m = m;
   L.flex = flex;
-  L.h.resize(L.nsys);
+  L.h.assign(L.nsys, KDesc{});
   L.cpre.assign(L.nsys + 1, 0);
-  hipError_t e;
-  int* flags = nullptr;   // per system: act, kdone, iters, go, again
-  if ((e = A.take((void**)&flags, sizeof(int) * 5 * L.nsys))) return e;
-  if ((e = hipMemset(flags, 0, sizeof(int) * 5 * L.nsys))) return e;
-  double* est = nullptr;
-  if ((e = A.take((void**)&est, sizeof(double) * L.nsys))) return e;
+  L.flags = c.take<int>(5 * (size_t)L.nsys);
+  double* est = c.take<double>(L.nsys);
   for (int s = 0; s < L.nsys; ++s) {
     KDesc& D = L.h[s];
-    std::memset(&D, 0, sizeof(D));
     D.n = n[s];
     D.nchunk = (int)((n[s] + kC - 1) / kC);
     L.cpre[s + 1] = L.cpre[s] + D.nchunk;
-    // (a system without support has length 0 and no chunks; its buffers keep one
-    // element so every pointer is valid)
-    const size_t len = n[s] > 0 ? (size_t)n[s] : 1;
-    const size_t nch = D.nchunk > 0 ? (size_t)D.nchunk : 1;
-    if ((e = A.take(&D.V, sizeof(cx<T>) * len * (m + 1)))) return e;
-    if (flex && (e = A.take(&D.Z, sizeof(cx<T>) * len * m))) return e;
-    D.x = x[s];
-    D.b = b[s];
-    if ((e = A.take(&D.r, sizeof(cx<T>) * len))) return e;
-    if ((e = A.take((void**)&D.partial, sizeof(double2) * 2 * (size_t)(m + 1) * nch))) return e;
-    if ((e = A.take((void**)&D.norms, sizeof(double) * 2 * nch))) return e;
-    double2* small = nullptr;
-    const size_t per = (size_t)(m + 2) * 3 + 2 + (size_t)(m + 1) * m + 3 * (size_t)(m + 1);
-    if ((e = A.take((void**)&small, sizeof(double2) * per))) return e;
-    D.h = small;
+    const size_t len = n[s] > 0 ? (size_t)n[s] : 1, nch = D.nchunk > 0 ? (size_t)D.nchunk : 1;
+    D.V = c.take<cx<T>>(len * (m + 1));
+    if (flex) D.Z = c.take<cx<T>>(len * m);
+    D.r = c.take<cx<T>>(len);
+    D.partial = c.take<double2>(2 * (size_t)(m + 1) * nch);
+    D.norms = c.take<double>(2 * nch);
+    D.h = c.take<double2>((size_t)(m + 2) * 3 + 2 + (size_t)(m + 1) * m + 3 * (size_t)(m + 1));
     D.raw = D.h + (m + 2);
     D.gd = D.raw + (m + 2);
     D.sumsq = D.gd + (m + 2);
@@ -760,27 +713,42 @@ hipError_t build_level(BatchLevel<T>& L, Arena& A, const std::vector<long>& n, i
     D.sn = D.H + (size_t)(m + 1) * m;
     D.g = D.sn + (m + 1);
     D.y = D.g + (m + 1);
-    if ((e = A.take((void**)&D.cs, sizeof(double) * (m + 1)))) return e;
-    D.act = flags + s;
-    D.kdone = flags + L.nsys + s;
-    D.iters = flags + 2 * L.nsys + s;
-    D.go = flags + 3 * L.nsys + s;
-    D.again = flags + 4 * L.nsys + s;
-    D.act0 = act_cycle_src ? act_cycle_src + s : act_cycle + s;
+    D.cs = c.take<double>(m + 1);
+    D.act = L.flags + s;
+    D.kdone = L.flags + L.nsys + s;
+    D.iters = L.flags + 2 * L.nsys + s;
+    D.go = L.flags + 3 * L.nsys + s;
+    D.again = L.flags + 4 * L.nsys + s;
     D.est = est + s;
-    D.tol = tol;
   }
   L.ctotal = L.cpre[L.nsys];
-  if ((e = A.take((void**)&L.d, sizeof(KDesc) * L.nsys))) return e;
-  if ((e = hipMemcpy(L.d, L.h.data(), sizeof(KDesc) * L.nsys, hipMemcpyHostToDevice))) return e;
-  if ((e = A.take((void**)&L.d_cpre, sizeof(int) * (L.nsys + 1)))) return e;
-  return hipMemcpy(L.d_cpre, L.cpre.data(), sizeof(int) * (L.nsys + 1), hipMemcpyHostToDevice);
+  L.d = c.take<KDesc>(L.nsys);
+  L.d_cpre = c.take<int>(L.nsys + 1);
+}
+
+// cleared flags and the descriptors, completed by the caller
+template <typename T>
+hipError_t upload_level(BatchLevel<T>& L) {
+  hipError_t e = hipMemset(L.flags, 0, sizeof(int) * 5 * L.nsys);
+  if (!e) e = hipMemcpy(L.d, L.h.data(), sizeof(KDesc) * L.nsys, hipMemcpyHostToDevice);
+  return e ? e : hipMemcpy(L.d_cpre, L.cpre.data(), sizeof(int) * (L.nsys + 1), hipMemcpyHostToDevice);
+}
+
+// Bytes of the tables of build_passes at most: each system in one group of either kind, each
+// group with two lists of descriptors and a prefix.
+size_t pass_table_bytes(int n) {
+  return (size_t)n * (sizeof(SDesc) + 4 * sizeof(PassDesc) + 2 * sizeof(int)) +
+         (size_t)n * 2 * (sizeof(int) + 3 * 256) + 256;
 }
 
 template <typename T>
 hipError_t build_passes(vie_batch_s* B, PassSet& PS, const BatchLevel<T>& L) {
   const bool dbl = sizeof(T) == 8;
-  auto alloc = [&](void** p, size_t bytes) { return B->arena.take(p, bytes); };
+  ScratchCarver tables{PS.tables};
+  auto alloc = [&](void** p, size_t bytes) {
+    *p = tables.take<unsigned char>(bytes);
+    return tables.used <= pass_table_bytes(B->nsys) ? hipSuccess : hipErrorOutOfMemory;
+  };
   hipError_t e;
   const int n = B->nsys;
   PS.h_step.resize(n);
@@ -1089,7 +1057,9 @@ extern "C" int vie_solve_batch(vie_plan_t const* plans, const vie_c128* const* r
     if (B.graph) (void)hipGraphExecDestroy(B.graph);
     for (void* q : extra) (void)hipFree(q);
     if (hflags) (void)hipHostFree(hflags);
-    (void)hipStreamSynchronize(B.stream);   // the arena goes after it, with B
+    (void)hipStreamSynchronize(B.stream);
+    for (unsigned char* q : B.mem)
+      if (q) (void)hipFree(q);
     (void)hipStreamDestroy(B.stream);
   };
 #define BTRY(expr)                  \
@@ -1100,59 +1070,73 @@ extern "C" int vie_solve_batch(vie_plan_t const* plans, const vie_c128* const* r
       return VIE_EDEVICE;           \
     }                               \
   } while (0)
-  BTRY(B.arena.take(&act, sizeof(int) * count));
-  // every system gets its own intermediate buffers, so one plan may serve
-  // several right-hand sides of the batch
-  for (int i = 0; i < count; ++i) {
-    SysPlan& P = B.sp[i];
-    const size_t u = (size_t)3 * P.g.n1 * P.g.n2 * P.g.M3;
-    BTRY(B.arena.take(&P.U64, sizeof(double2) * u));
-    if (B.mixed) {
-      BTRY(B.arena.take(&P.U32, sizeof(float2) * u));
-    }
-  }
-  BTRY(hipHostMalloc(&hflags, sizeof(int) * count * 4 + sizeof(double) * count * 4, hipHostMallocDefault));
   // Support compression (as in vie_solve): off the support A is the identity, so
   // x = b there; on it the system is A_SS x_S = b_S - (A b_off)_S with b_off = b
-  // off the support.  Per system: the compressed right-hand side bc and solution xc and,
+  // off the support.  Per system: intermediates of its own, so that one plan may serve several
+  // right-hand sides of the batch, the compressed right-hand side bc and solution xc and,
   // unless its support is every column of its operator's grid, the product's full-length
   // buffers fx (zero off the support) and fy.
   B.p64.h_sd.resize(count);
   B.p32.h_sd.resize(count);
   long nmax = 1;
-  for (int i = 0; i < count; ++i) {
-    const SysPlan& P = B.sp[i];
-    const size_t len = n[i] > 0 ? (size_t)n[i] : 1, nv = 3 * (size_t)P.g.N;
-    void *fx = nullptr, *fy = nullptr, *bc = nullptr, *xc = nullptr;
-    BTRY(B.arena.take(&bc, sizeof(double2) * len));
-    BTRY(B.arena.take(&xc, sizeof(double2) * len));
-    if (!P.direct) {
-      BTRY(B.arena.take(&fx, sizeof(double2) * nv));
-      BTRY(B.arena.take(&fy, sizeof(double2) * nv));
-      BTRY(hipMemsetAsync(fx, 0, sizeof(double2) * nv, s));
-    }
-    B.p64.h_sd[i] = SDesc{P.col, P.ns, P.g.n3, (long)P.g.n1 * P.g.n2, fx, fy};
-    bptr[i] = bc;
-    xptr[i] = xc;
-    if (B.mixed) {
-      void *fx32 = nullptr, *fy32 = nullptr;
+  for (int i = 0; i < count; ++i) nmax = std::max(nmax, nfull[i]);
+  double2 *boffv = nullptr, *dsq = nullptr, *part = nullptr;
+  auto carve_vectors = [&](ScratchCarver& c) {
+    act = c.take<int>(count);
+    for (int i = 0; i < count; ++i) {
+      SysPlan& P = B.sp[i];
+      const size_t len = n[i] > 0 ? (size_t)n[i] : 1, nv = 3 * (size_t)P.g.N;
+      const size_t u = (size_t)3 * P.g.n1 * P.g.n2 * P.g.M3;
+      P.U64 = c.take<double2>(u);
+      bptr[i] = c.take<double2>(len);
+      xptr[i] = c.take<double2>(len);
+      SDesc sd{P.col, P.ns, P.g.n3, (long)P.g.n1 * P.g.n2, nullptr, nullptr};
+      B.p64.h_sd[i] = B.p32.h_sd[i] = sd;
       if (!P.direct) {
-        BTRY(B.arena.take(&fx32, sizeof(float2) * nv));
-        BTRY(B.arena.take(&fy32, sizeof(float2) * nv));
-        BTRY(hipMemsetAsync(fx32, 0, sizeof(float2) * nv, s));
+        B.p64.h_sd[i].fx = c.take<double2>(nv);
+        B.p64.h_sd[i].fy = c.take<double2>(nv);
       }
-      B.p32.h_sd[i] = SDesc{P.col, P.ns, P.g.n3, (long)P.g.n1 * P.g.n2, fx32, fy32};
+      if (!B.mixed) continue;
+      P.U32 = c.take<float2>(u);
+      if (!P.direct) {
+        B.p32.h_sd[i].fx = c.take<float2>(nv);
+        B.p32.h_sd[i].fy = c.take<float2>(nv);
+      }
     }
-    nmax = std::max(nmax, nfull[i]);
+    boffv = c.take<double2>(nmax);   // b off the support, one system after the other
+    // norms: dsq[3 i] = ||b_S||^2, dsq[3 i + 1] = ||b_off||^2, dsq[3 i + 2] = ||b_c||^2
+    dsq = c.take<double2>(3 * count);
+    part = c.take<double2>(partial_blocks(nmax));
+  };
+  std::vector<float2*> ib(count, nullptr), ix(count, nullptr);   // inner right-hand sides and solutions
+  auto carve_levels = [&](ScratchCarver& c) {
+    carve_level<double>(B.outer, c, n, o.restart, B.mixed || B.circ_tier);
+    B.p64.tables = c.take<unsigned char>(pass_table_bytes(count));
+    if (!B.mixed) return;
+    for (int i = 0; i < count; ++i) {
+      ib[i] = c.take<float2>(n[i] > 0 ? n[i] : 1);
+      ix[i] = c.take<float2>(n[i] > 0 ? n[i] : 1);
+    }
+    carve_level<float>(B.inner, c, n, o.inner_restart, false);
+    B.p32.tables = c.take<unsigned char>(pass_table_bytes(count));
+  };
+  // One allocation of the size that a first walk over the arrays finds (158 single ones of an
+  // eight-system batch took 3.5 ms to make and 11 ms to free).
+  auto allocate = [&](unsigned char*& base, auto carve) -> hipError_t {
+    ScratchCarver size{nullptr};
+    carve(size);
+    if (hipError_t e = dmalloc(&base, size.used)) return e;
+    ScratchCarver c{base};
+    carve(c);
+    return hipSuccess;
+  };
+  BTRY(allocate(B.mem[0], carve_vectors));
+  BTRY(hipHostMalloc(&hflags, sizeof(int) * count * 4 + sizeof(double) * count * 4, hipHostMallocDefault));
+  for (int i = 0; i < count; ++i) {
+    const size_t nv = 3 * (size_t)B.sp[i].g.N;
+    if (B.p64.h_sd[i].fx) BTRY(hipMemsetAsync(B.p64.h_sd[i].fx, 0, sizeof(double2) * nv, s));
+    if (B.p32.h_sd[i].fx) BTRY(hipMemsetAsync(B.p32.h_sd[i].fx, 0, sizeof(float2) * nv, s));
   }
-  // b off the support, one system after the other (set-up only)
-  double2* boffv = nullptr;
-  BTRY(B.arena.take(&boffv, sizeof(double2) * nmax));
-  // norms: sq[3 i] = ||b_S||^2, sq[3 i + 1] = ||b_off||^2, sq[3 i + 2] = ||b_c||^2
-  double2* dsq = nullptr;
-  double2* part = nullptr;
-  BTRY(B.arena.take(&dsq, sizeof(double2) * 3 * count));
-  BTRY(B.arena.take(&part, sizeof(double2) * partial_blocks(nmax)));
   BTRY(hipMemsetAsync(dsq, 0, sizeof(double2) * 3 * count, s));
   using K = KrylovOps<double>;
   for (int i = 0; i < count; ++i) {
@@ -1206,25 +1190,26 @@ extern "C" int vie_solve_batch(vie_plan_t const* plans, const vie_c128* const* r
       tolc[i] = tol / ratio[i];
     }
   }
-  BTRY(build_level<double>(B.outer, B.arena, n, o.restart, B.mixed || B.circ_tier, tol, bptr, xptr, act, nullptr));
-  for (int i = 0; i < count; ++i) B.outer.h[i].tol = tolc[i];
-  BTRY(hipMemcpy(B.outer.d, B.outer.h.data(), sizeof(KDesc) * count, hipMemcpyHostToDevice));
+  BTRY(allocate(B.mem[1], carve_levels));
+  for (int i = 0; i < count; ++i) {
+    KDesc& D = B.outer.h[i];
+    D.b = bptr[i];
+    D.x = xptr[i];
+    D.act0 = act + i;
+    D.tol = tolc[i];
+  }
+  BTRY(upload_level(B.outer));
   if (B.mixed) {
-    std::vector<const void*> ib(count);
-    std::vector<void*> ix(count);
-    for (int i = 0; i < count; ++i) {
-      void *bb = nullptr, *xx = nullptr;
-      const size_t len = n[i] > 0 ? (size_t)n[i] : 1;
-      BTRY(B.arena.take(&bb, sizeof(float2) * len));
-      BTRY(B.arena.take(&xx, sizeof(float2) * len));
-      ib[i] = bb;
-      ix[i] = xx;
-    }
     // inner cycle flags alias the outer step flags (an outer system that stopped
     // needs no preconditioning); the inner level has its own step flags
-    BTRY(build_level<float>(B.inner, B.arena, n, o.inner_restart, false, o.inner_tol, ib, ix, nullptr, nullptr));
-    for (int i = 0; i < count; ++i) B.inner.h[i].act0 = B.outer.h[i].act;
-    BTRY(hipMemcpy(B.inner.d, B.inner.h.data(), sizeof(KDesc) * count, hipMemcpyHostToDevice));
+    for (int i = 0; i < count; ++i) {
+      KDesc& D = B.inner.h[i];
+      D.b = ib[i];
+      D.x = ix[i];
+      D.act0 = B.outer.h[i].act;
+      D.tol = o.inner_tol;
+    }
+    BTRY(upload_level(B.inner));
     BTRY(build_passes<float>(&B, B.p32, B.inner));
   }
   BTRY(build_passes<double>(&B, B.p64, B.outer));

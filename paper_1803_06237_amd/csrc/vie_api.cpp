@@ -132,19 +132,6 @@ struct GmresWs {
   }
 };
 
-// Bump allocation inside one array, 256-byte aligned.
-struct ScratchCarver {
-  unsigned char* base;
-  size_t used = 0;
-  template <typename P>
-  P* take(size_t count) {
-    used = (used + 255) & ~(size_t)255;
-    P* r = reinterpret_cast<P*>(base + used);
-    used += sizeof(P) * (count ? count : 1);
-    return r;
-  }
-};
-
 // The operator on the bounding box of the support; every array lies in one allocation.
 struct BoxOp {
   int lo1 = 0, lo2 = 0;        // first column of the box in the plan's grid

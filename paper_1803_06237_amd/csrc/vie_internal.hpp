@@ -178,6 +178,19 @@ inline hipError_t dmalloc(P** p, size_t bytes) {
   return dmalloc_bytes(reinterpret_cast<void**>(p), bytes);
 }
 
+// Bump allocation inside one array, 256-byte aligned.
+struct ScratchCarver {
+  unsigned char* base;
+  size_t used = 0;
+  template <typename P>
+  P* take(size_t count) {
+    used = (used + 255) & ~(size_t)255;
+    P* r = reinterpret_cast<P*>(base + used);
+    used += sizeof(P) * (count ? count : 1);
+    return r;
+  }
+};
+
 // LDS budget the kernels may use per workgroup (queried once per device)
 size_t lds_budget(int device);
 

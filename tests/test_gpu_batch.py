@@ -202,3 +202,40 @@ def test_batch_circulant_tier(systems):
     with pytest.raises(vie.VieError) as ei:
         vie.solve_batch(plans, bs, tol=1e-8, restart=30, precision=3)
     assert ei.value.code == vie.VIE_ESTATE
+
+
+def test_device_memory_of_a_batch_is_what_its_vectors_take():
+    """Free device memory, watched from another thread while two 32 x 32 x 512 guides with a
+    20 x 9 core are solved, against the documented sum of the arrays."""
+    import threading
+    import time
+    vie = _dev()
+    n, m, inner, ns = (32, 32, 512), 30, 20, 3 * 20 * 9 * 512
+    eps = np.full(n, inputs.EPS_B, complex)
+    eps[6:26, 11:20] = 12.11 + 0.3j
+    plans, bs = [], []
+    for i in range(2):
+        plans.append(vie.Plan(n, 0.025, inputs.K0, inputs.EPS_B, fp32=True))
+        plans[-1].set_contrast(torch.from_numpy(eps).cuda())
+        bs.append(torch.from_numpy(inputs.gaussian_rhs(n, i)).cuda())
+    run = lambda steps: vie.solve_batch(plans, bs, tol=1e-300, restart=steps, maxit=steps, precision=1,
+                                        inner_restart=inner)
+    run(2)                                 # boxes and kernels are there
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    least, done = [before], threading.Event()
+
+    def watch():
+        while not done.is_set():
+            least[0] = min(least[0], torch.cuda.mem_get_info()[0])
+            time.sleep(0.0005)
+
+    t = threading.Thread(target=watch)
+    t.start()
+    run(m)
+    done.set()
+    t.join()
+    U = 3 * 20 * 9 * 1024
+    want = 2 * (16 * ((2 * m + 4) * ns + U) + 8 * ((inner + 4) * ns + U)) + 16 * 3 * n[0] * n[1] * n[2]
+    used = before - least[0]
+    assert 0.5 * want <= used <= 1.1 * want + (32 << 20), (used, want)
