@@ -780,13 +780,15 @@ struct vie_net_s {
   bf16_t *wbf, *wtbf;
   LayerTable lt;
   size_t params;
-  // activation buffers, each `batch` samples of elems values
+  // activation buffers, each `batch` samples of elems values, and out, in one allocation (37
+  // single ones made the first step of a small network twice as long as the next)
   struct Act {
     bf16_t** p;
     long elems;
   };
   std::vector<Act> acts;
-  int batch = 1;
+  void* act_mem = nullptr;
+  int batch = 0;
   // activations and their gradients
   bf16_t *X0, *E1a, *D1cat, *Dd1a, *Dd1b, *P1, *E2a, *D2cat, *Dd2a, *Dd2b, *P2, *E3a, *D3cat, *Dd3a, *Dd3b, *P3, *E4a,
       *E4b;
@@ -828,35 +830,24 @@ struct Levels {
 // there is not enough memory
 bool net_room(vie_net_s* N, int B) {
   if (B <= N->batch) return true;
-  std::vector<void*> fresh;
-  auto take = [&](size_t bytes) {
-    void* q = nullptr;
-    if (dmalloc(&q, bytes)) return false;
-    fresh.push_back(q);
-    return true;
-  };
-  bool ok = true;
-  for (auto& a : N->acts) ok = ok && take(sizeof(bf16_t) * a.elems * B);
-  ok = ok && take(sizeof(float) * N->lv[0].V() * 16 * B) && hipStreamSynchronize(N->stream) == hipSuccess;
-  if (!ok) {
-    for (void* q : fresh) (void)hipFree(q);
+  void* fresh = nullptr;
+  ScratchCarver c{nullptr};
+  for (auto& a : N->acts) c.take<bf16_t>((size_t)a.elems * B);
+  const size_t acts = c.used;
+  c.take<float>((size_t)N->lv[0].V() * 16 * B);
+  if (dmalloc(&fresh, c.used) || hipStreamSynchronize(N->stream)) {
+    if (fresh) (void)hipFree(fresh);
     (void)hipGetLastError();
     return false;
   }
-  auto swap_in = [&](void* old, void* now) {
-    for (void*& q : N->allocs)
-      if (q == old) q = now;
-    (void)hipFree(old);
-  };
-  for (size_t i = 0; i < N->acts.size(); ++i) {
-    auto& a = N->acts[i];
-    swap_in(*a.p, fresh[i]);
-    *a.p = static_cast<bf16_t*>(fresh[i]);
-    hipLaunchKernelGGL(k_fill_bf, dim3(gblocks(a.elems * B)), dim3(256), 0, N->stream, *a.p, a.elems * B);
-  }
-  swap_in(N->out, fresh.back());
-  N->out = static_cast<float*>(fresh.back());
+  if (N->act_mem) (void)hipFree(N->act_mem);
+  N->act_mem = fresh;
   N->batch = B;
+  c = ScratchCarver{static_cast<unsigned char*>(fresh)};
+  for (auto& a : N->acts) *a.p = c.take<bf16_t>((size_t)a.elems * B);
+  N->out = c.take<float>((size_t)N->lv[0].V() * 16 * B);
+  const long fill = (long)(acts / sizeof(bf16_t));
+  hipLaunchKernelGGL(k_fill_bf, dim3(gblocks(fill)), dim3(256), 0, N->stream, static_cast<bf16_t*>(fresh), fill);
   return true;
 }
 
@@ -1079,12 +1070,8 @@ int vie_net_create(vie_net_t* out, const int grid[3], unsigned seed, void* hip_s
               {&N->gD2cat, V[1], 80}, {&N->gDd2a, V[1], 32}, {&N->gDd2b, V[1], 32}, {&N->gP2, V[2], 32},
               {&N->gE3a, V[2], 48},  {&N->gD3cat, V[2], 112}, {&N->gDd3a, V[2], 48}, {&N->gDd3b, V[2], 48},
               {&N->gP3, V[3], 48},   {&N->gE4a, V[3], 64},  {&N->gE4b, V[3], 64},  {&N->gOut, V[0], 16}};
-  for (auto& b : bufs) {
-    if (nalloc(N, (void**)b.p, sizeof(bf16_t) * b.v * b.c)) return bail(VIE_ENOMEM);
-    hipLaunchKernelGGL(k_fill_bf, dim3(gblocks(b.v * b.c)), dim3(256), 0, N->stream, *b.p, b.v * b.c);
-    N->acts.push_back({b.p, b.v * b.c});
-  }
-  if (nalloc(N, (void**)&N->out, sizeof(float) * V[0] * 16)) return bail(VIE_ENOMEM);
+  for (auto& b : bufs) N->acts.push_back({b.p, b.v * b.c});
+  if (!net_room(N, 1)) return bail(VIE_ENOMEM);
   N->partial_cap = 8L << 20;   // floats
   if (nalloc(N, (void**)&N->partial, sizeof(float) * N->partial_cap)) return bail(VIE_ENOMEM);
   if (nalloc(N, (void**)&N->sumsq, sizeof(double2) * 2 * kGroup)) return bail(VIE_ENOMEM);
@@ -1100,6 +1087,7 @@ int vie_net_create(vie_net_t* out, const int grid[3], unsigned seed, void* hip_s
 void vie_net_destroy(vie_net_t N) {
   if (!N) return;
   for (void* p : N->allocs) (void)hipFree(p);
+  if (N->act_mem) (void)hipFree(N->act_mem);
   if (N->lpart_h) (void)hipHostFree(N->lpart_h);
   delete N;
 }

@@ -357,6 +357,31 @@ def test_grouped_samples_equal_single_ones(count):
     assert np.linalg.norm(got - want) <= (1e-5 if count != 5 else 2.0 ** -8) * np.linalg.norm(want)
 
 
+def test_first_step_of_a_fresh_network_is_not_much_dearer():
+    """The first step with a group of samples enlarges the activation buffers: one allocation,
+    about 0.05 ms at this size (37 and as many frees took 0.5 ms, more than the step itself)."""
+    import time
+    vie = _dev()
+    n = (8, 8, 16)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    c = lambda *k: torch.randn(*k, n[0] * n[1] * n[2], dtype=torch.complex128, device="cuda", generator=g)
+    r, chi, t = c(4, 3), 0.3 * c(4), c(4, 3)
+
+    def step(net):
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        net.train_step(list(r), list(chi), list(t), lr=0.0)
+        return time.perf_counter() - t0
+
+    first, later = [], []
+    for _ in range(8):
+        net = vie.Net(n, seed=5)
+        first.append(step(net))
+        later += [step(net) for _ in range(3)]
+        net.close()
+    assert np.median(first) - np.median(later) <= 0.35e-3, (first, later)
+
+
 def test_null_base_of_a_sample_is_its_residual():
     """vie_net_train_step_base with a null entry among the base vectors: that sample is the
     one vie_net_train_step takes, in a group with samples that have a base."""
