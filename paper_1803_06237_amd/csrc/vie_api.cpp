@@ -132,18 +132,27 @@ struct GmresWs {
   }
 };
 
-// The operator on the bounding box of the support; every array lies in one allocation.
+// Spectrum and twiddles of one circulant cross-section M1 x M2, for every box of up to M / 2
+// columns a side; one allocation, none where they are the plan's own.
+struct BoxSpectrum {
+  int M1 = 0, M2 = 0;
+  void* arena = nullptr;
+  double2* goct64 = nullptr;
+  float2* goct32 = nullptr;
+  double2* tw64[2] = {nullptr, nullptr};
+  float2* tw32[2] = {nullptr, nullptr};
+};
+
+// The operator on the bounding box of the support, with the plan's intermediates.
 struct BoxOp {
-  int lo1 = 0, lo2 = 0;        // first column of the box in the plan's grid
   Geom g{};
   Tune t64{}, t32{};
-  void* arena = nullptr;
-  double2 *goct64 = nullptr, *chi64 = nullptr, *U64 = nullptr;
-  float2 *goct32 = nullptr, *chi32 = nullptr, *U32 = nullptr;
-  double2* tw64[3] = {nullptr, nullptr, nullptr};
-  float2* tw32[3] = {nullptr, nullptr, nullptr};
+  BoxSpectrum spectrum;        // of this box, one of the plan's
+  void* arena = nullptr;       // chi64, chi32 and col, for a box of any size
+  double2* chi64 = nullptr;
+  float2* chi32 = nullptr;
   int* col = nullptr;
-  bool fresh = false;          // chi and col match the plan's contrast
+  bool fresh = false;          // all of it matches the plan's contrast
 };
 
 }  // namespace
@@ -172,8 +181,10 @@ struct vie_plan_s {
   int* scol = nullptr;         // device, ns column indices i1 n2 + i2, increasing
   int ns = 0;
   int box[4] = {0, 0, 0, 0};   // bounding box of the support columns: [i1 lo, hi), [i2 lo, hi)
-  BoxOp* sub = nullptr;        // the operator on that box (solve_view)
-  bool sub_none = false;       // the box is not worth an operator of its own
+  std::vector<int> scol_h;     // scol on the host
+  BoxOp sub;                   // the operator on that box (solve_view)
+  std::vector<BoxSpectrum> spectra;   // the last used at the end, at most kBoxSpectra
+  bool sub_none = true;        // the box is not worth an operator of its own, or there is no memory
   std::mutex sub_mu;           // solves of several threads may share the plan's read-only parts
   double2* table_dev = nullptr;   // Toeplitz table on the device
   double2* fx = nullptr;       // full FP64 operator input, zero off the support
@@ -533,12 +544,20 @@ struct Op32 {
 };
 
 // ---- the operator on the support's bounding box --------------------------------
+constexpr size_t kBoxSpectra = 4;
+
 void box_release(vie_plan_s* p) {
-  if (!p->sub) return;
   (void)hipStreamSynchronize(p->stream);
-  if (p->sub->arena) (void)hipFree(p->sub->arena);
-  delete p->sub;
-  p->sub = nullptr;
+  for (BoxSpectrum& b : p->spectra)
+    if (b.arena) (void)hipFree(b.arena);
+  p->spectra.clear();
+  if (p->sub.arena) (void)hipFree(p->sub.arena);
+  p->sub = BoxOp();
+}
+
+Geom box_geom(const vie_plan_s* p) {
+  const int n[3] = {p->box[1] - p->box[0], p->box[3] - p->box[2], p->g.n3};
+  return make_geom(n);
 }
 
 // Launch shapes of the box, by rule (its first solve does not wait for timing): the
@@ -557,38 +576,48 @@ bool box_tune(const Geom& g, size_t budget, Tune* t) {
   return true;
 }
 
-hipError_t box_build(vie_plan_s* p) {
-  auto* b = new BoxOp();
-  p->sub = b;
-  const int n[3] = {p->box[1] - p->box[0], p->box[3] - p->box[2], p->g.n3};
-  b->g = make_geom(n);
-  const Geom& g = b->g;
-  const size_t budget = lds_budget(p->device);
-  if (!box_tune<double>(g, budget, &b->t64) || !box_tune<float>(g, budget, &b->t32)) return hipErrorInvalidValue;
+// The spectrum of the circulant cross-section M1 x M2, made on first use: embedded for the most
+// columns that it takes, so that it serves every box of these lengths (a box as large as the
+// plan's circulant takes the plan's own).  A few are kept, as boxes of rough guides go back and
+// forth between neighbouring lengths.
+hipError_t box_spectrum(vie_plan_s* p, int M1, int M2, BoxSpectrum* out) {
+  for (size_t i = 0; i < p->spectra.size(); ++i)
+    if (p->spectra[i].M1 == M1 && p->spectra[i].M2 == M2) {
+      std::rotate(p->spectra.begin() + i, p->spectra.begin() + i + 1, p->spectra.end());
+      *out = p->spectra.back();
+      return hipSuccess;
+    }
+  BoxSpectrum b;
+  b.M1 = M1;
+  b.M2 = M2;
+  if (M1 == p->g.M1 && M2 == p->g.M2) {
+    b.goct64 = p->goct64;
+    b.goct32 = p->goct32;
+    for (int d = 0; d < 2; ++d) {
+      b.tw64[d] = p->tw64[d];
+      b.tw32[d] = p->tw32[d];
+    }
+    *out = b;
+    return hipSuccess;
+  }
+  const int n[3] = {std::min(p->g.n1, std::max(1, M1 / 2)), std::min(p->g.n2, std::max(1, M2 / 2)), p->g.n3};
+  const Geom g = make_geom(n);
   const bool f32 = p->goct32 != nullptr;
-  const size_t H = (size_t)g.H1 * g.H2 * g.H3, N = (size_t)g.N, u = (size_t)3 * g.n1 * g.n2 * g.M3;
-  const int M[2] = {g.M1, g.M2};
+  const size_t H = (size_t)g.H1 * g.H2 * g.H3;
+  const int M[2] = {M1, M2};
   // sizes first, then the same walk with the allocation's address
   for (int walk = 0; walk < 2; ++walk) {
-    ScratchCarver c{static_cast<unsigned char*>(b->arena)};
-    b->goct64 = c.take<double2>(6 * H);
-    b->chi64 = c.take<double2>(N);
-    b->U64 = c.take<double2>(u);
-    if (f32) {
-      b->goct32 = c.take<float2>(6 * H);
-      b->chi32 = c.take<float2>(N);
-      b->U32 = c.take<float2>(u);
-    }
+    ScratchCarver c{static_cast<unsigned char*>(b.arena)};
+    b.goct64 = c.take<double2>(6 * H);
+    if (f32) b.goct32 = c.take<float2>(6 * H);
     for (int d = 0; d < 2; ++d) {
-      b->tw64[d] = c.take<double2>(M[d]);
-      b->tw32[d] = c.take<float2>(M[d]);
+      b.tw64[d] = c.take<double2>(M[d]);
+      b.tw32[d] = c.take<float2>(M[d]);
     }
-    b->col = c.take<int>((size_t)g.n1 * g.n2);
     if (walk == 0)
-      if (hipError_t e = dmalloc(&b->arena, c.used)) return e;
+      if (hipError_t e = dmalloc(&b.arena, c.used)) return e;
   }
-  b->tw64[2] = p->tw64[2];   // the box keeps the plan's length along z
-  b->tw32[2] = p->tw32[2];
+  hipError_t e = hipSuccess;
   for (int d = 0; d < 2; ++d) {
     std::vector<double2> h64(M[d]);
     std::vector<float2> h32(M[d]);
@@ -597,38 +626,60 @@ hipError_t box_build(vie_plan_s* p) {
       h64[k] = double2{(double)std::cos(a), (double)std::sin(a)};
       h32[k] = float2{(float)std::cos(a), (float)std::sin(a)};
     }
-    hipError_t e = hipMemcpy(b->tw64[d], h64.data(), sizeof(double2) * M[d], hipMemcpyHostToDevice);
-    if (!e) e = hipMemcpy(b->tw32[d], h32.data(), sizeof(float2) * M[d], hipMemcpyHostToDevice);
-    if (e) return e;
+    if (!e) e = hipMemcpy(b.tw64[d], h64.data(), sizeof(double2) * M[d], hipMemcpyHostToDevice);
+    if (!e) e = hipMemcpy(b.tw32[d], h32.data(), sizeof(float2) * M[d], hipMemcpyHostToDevice);
   }
   double2* full = nullptr;
-  hipError_t e = dmalloc(&full, sizeof(double2) * (size_t)g.M1 * g.M2 * g.M3);
+  if (!e) e = dmalloc(&full, sizeof(double2) * (size_t)g.M1 * g.M2 * g.M3);
   const int t[3] = {p->g.n1, p->g.n2, p->g.n3};
-  const double2* tw[3] = {b->tw64[0], b->tw64[1], b->tw64[2]};
-  if (!e) e = launch_spectrum(g, p->table_dev, t, full, b->goct64, b->goct32, tw, p->stream);
+  const double2* tw[3] = {b.tw64[0], b.tw64[1], p->tw64[2]};   // the box keeps the plan's length along z
+  if (!e) e = launch_spectrum(g, p->table_dev, t, full, b.goct64, b.goct32, tw, p->stream);
   if (!e) e = hipStreamSynchronize(p->stream);
   if (full) (void)hipFree(full);
-  return e;
+  if (e) {
+    (void)hipFree(b.arena);
+    return e;
+  }
+  if (p->spectra.size() == kBoxSpectra) {
+    (void)hipFree(p->spectra.front().arena);
+    p->spectra.erase(p->spectra.begin());
+  }
+  p->spectra.push_back(b);
+  *out = b;
+  return hipSuccess;
 }
 
-// The plan's contrast and support columns in the box's numbering.
+// The operator for the plan's contrast, whose columns and values it takes over in the box's
+// numbering.
 hipError_t box_refresh(vie_plan_s* p) {
-  BoxOp* b = p->sub;
-  b->lo1 = p->box[0];
-  b->lo2 = p->box[2];
-  const Geom &f = p->g, &g = b->g;
-  const size_t at = ((size_t)b->lo1 * f.n2 + b->lo2) * f.n3, run = (size_t)g.n2 * g.n3, pitch = (size_t)f.n2 * f.n3;
-  hipError_t e = hipMemcpy2DAsync(b->chi64, run * sizeof(double2), p->chi64 + at, pitch * sizeof(double2),
-                                  run * sizeof(double2), g.n1, hipMemcpyDeviceToDevice, p->stream);
-  if (!e && b->goct32)
-    e = hipMemcpy2DAsync(b->chi32, run * sizeof(float2), p->chi32 + at, pitch * sizeof(float2), run * sizeof(float2),
+  BoxOp& b = p->sub;
+  const Geom& f = p->g;
+  const Geom g = box_geom(p);
+  const size_t budget = lds_budget(p->device);
+  if (!box_tune<double>(g, budget, &b.t64) || !box_tune<float>(g, budget, &b.t32)) return hipErrorInvalidValue;
+  hipError_t e = box_spectrum(p, g.M1, g.M2, &b.spectrum);
+  if (e) return e;
+  b.g = g;
+  for (int walk = 0; walk < 2 && !b.chi64; ++walk) {
+    ScratchCarver c{static_cast<unsigned char*>(b.arena)};
+    double2* chi64 = c.take<double2>(f.N);
+    b.chi32 = c.take<float2>(p->goct32 ? f.N : 0);
+    b.col = c.take<int>((size_t)f.n1 * f.n2);
+    if (walk == 1) b.chi64 = chi64;
+    else if ((e = dmalloc(&b.arena, c.used))) return e;
+  }
+  const size_t at = ((size_t)p->box[0] * f.n2 + p->box[2]) * f.n3, run = (size_t)g.n2 * g.n3,
+               pitch = (size_t)f.n2 * f.n3;
+  e = hipMemcpy2DAsync(b.chi64, run * sizeof(double2), p->chi64 + at, pitch * sizeof(double2), run * sizeof(double2),
+                       g.n1, hipMemcpyDeviceToDevice, p->stream);
+  if (!e && p->goct32)
+    e = hipMemcpy2DAsync(b.chi32, run * sizeof(float2), p->chi32 + at, pitch * sizeof(float2), run * sizeof(float2),
                          g.n1, hipMemcpyDeviceToDevice, p->stream);
-  std::vector<int> col(p->ns);
-  if (!e) e = hipMemcpyAsync(col.data(), p->scol, sizeof(int) * p->ns, hipMemcpyDeviceToHost, p->stream);
+  std::vector<int> col(p->scol_h);
+  for (int& c : col) c = (c / f.n2 - p->box[0]) * g.n2 + c % f.n2 - p->box[2];
+  if (!e) e = hipMemcpyAsync(b.col, col.data(), sizeof(int) * col.size(), hipMemcpyHostToDevice, p->stream);
   if (!e) e = hipStreamSynchronize(p->stream);
-  for (int& c : col) c = (c / f.n2 - b->lo1) * g.n2 + c % f.n2 - b->lo2;
-  if (!e) e = hipMemcpy(b->col, col.data(), sizeof(int) * p->ns, hipMemcpyHostToDevice);
-  b->fresh = e == hipSuccess;
+  b.fresh = e == hipSuccess;
   return e;
 }
 
@@ -639,33 +690,24 @@ SolveView plan_view(const vie_plan_s* p) {
 }
 
 // The view the solvers use.  The box pays where it has a smaller circulant cross-section or
-// at most three quarters of the columns: all passes shrink with it (32 x 32 x 512 guide with
-// a 20 x 9 core, circulant 64 x 32 instead of 64 x 64 and a sixth of the z pencils: FP64
-// product with scatter and gather 137 us, on the box 70 us).  Built on first use unless
-// `build` is false (callers that may not allocate); where the build fails, for want of
+// at most three quarters of the columns (vie_set_contrast): all passes shrink with it (32 x 32
+// x 512 guide with a 20 x 9 core, circulant 64 x 32 instead of 64 x 64 and a sixth of the z
+// pencils: FP64 product with scatter and gather 137 us, on the box 70 us).  Made on first use
+// unless `build` is false (callers that may not allocate); where that fails, for want of
 // memory say, the plan's own operator serves.
 SolveView solve_view(vie_plan_s* p, bool build) {
   std::lock_guard<std::mutex> lk(p->sub_mu);
-  if (p->ns > 0 && !p->sub && !p->sub_none && build) {
-    const int n[3] = {p->box[1] - p->box[0], p->box[3] - p->box[2], p->g.n3};
-    const Geom g = make_geom(n);
-    p->sub_none = !(g.M1 * g.M2 < p->g.M1 * p->g.M2 || 4L * n[0] * n[1] <= 3L * p->g.n1 * p->g.n2);
-    if (!p->sub_none && box_build(p) != hipSuccess) {
-      (void)hipGetLastError();
-      box_release(p);
-      p->sub_none = true;
-    }
-  }
-  if (p->sub && !p->sub->fresh && build && box_refresh(p) != hipSuccess) {
+  if (!p->sub_none && !p->sub.fresh && build && box_refresh(p) != hipSuccess) {
     (void)hipGetLastError();
     box_release(p);
     p->sub_none = true;
   }
-  if (!p->sub || !p->sub->fresh) return plan_view(p);
-  const BoxOp* b = p->sub;
-  return SolveView{b->g, b->t64, b->t32, b->goct64, b->goct32, b->chi64, b->chi32, b->U64, b->U32,
-                   {b->tw64[0], b->tw64[1], b->tw64[2]}, {b->tw32[0], b->tw32[1], b->tw32[2]}, b->col, p->ns,
-                   (long)p->ns == (long)b->g.n1 * b->g.n2, true};
+  const BoxOp& b = p->sub;
+  if (p->sub_none || !b.fresh) return plan_view(p);
+  const BoxSpectrum& sp = b.spectrum;
+  return SolveView{b.g, b.t64, b.t32, sp.goct64, sp.goct32, b.chi64, b.chi32, p->U64, p->U32,
+                   {sp.tw64[0], sp.tw64[1], p->tw64[2]}, {sp.tw32[0], sp.tw32[1], p->tw32[2]}, b.col, p->ns,
+                   (long)p->ns == (long)b.g.n1 * b.g.n2, true};
 }
 
 // The operator on support-compressed vectors.  Where the support is every column of the
@@ -1135,15 +1177,16 @@ int vie_set_contrast(vie_plan_t p, const vie_c128* eps) {
   p->ns = (int)cols.size();
   {
     std::lock_guard<std::mutex> lk(p->sub_mu);
-    if (p->sub) {
-      // another box of the same size keeps the spectrum, which depends on its size only
-      if (box[1] - box[0] == p->sub->g.n1 && box[3] - box[2] == p->sub->g.n2) p->sub->fresh = false;
-      else box_release(p);
-    }
-    p->sub_none = false;
     std::copy(box, box + 4, p->box);
+    p->sub.fresh = false;
+    p->sub_none = true;
+    if (p->ns > 0) {
+      const Geom g = box_geom(p), &f = p->g;
+      p->sub_none = !(g.M1 * g.M2 < f.M1 * f.M2 || 4L * g.n1 * g.n2 <= 3L * f.n1 * f.n2);
+    }
   }
   if (p->ns) HIPTRY(p, hipMemcpy(p->scol, cols.data(), sizeof(int) * cols.size(), hipMemcpyHostToDevice));
+  p->scol_h = std::move(cols);
   p->has_contrast = true;
   return VIE_OK;
 }
