@@ -83,7 +83,8 @@ int vie_green_table(const int grid[3], double kappa, vie_c128* out, int nthreads
  * vie_plan -- build the operator for a grid (Section III-A): the Toeplitz table
  * on the host (FP64, threaded), its circulant embedding and 3-D spectrum on the
  * device.  h and k0 in one consistent length unit; eps_b > 0 the background
- * relative permittivity.  hip_stream: a hipStream_t (NULL = default stream).
+ * relative permittivity.  hip_stream: a hipStream_t (NULL = default stream).  The table
+ * (96 N bytes) stays on the device with the plan, for the spectra of vie_solve's boxes.
  * Returns VIE_EINVAL for sizes outside the limits above or non-positive h, k0, eps_b.
  */
 int vie_plan(vie_plan_t* out, const int grid[3], double h, double k0, double eps_b,
@@ -171,7 +172,15 @@ typedef struct {
  * the true FP64 relative residual ||b - A x||/||b|| are <= tol.
  * b, x: device, 3N values (x in/out).  opts, info: host, may be NULL (defaults /
  * no report).  Returns VIE_OK, or VIE_ENOCONV with the best iterate in x.
- * The Krylov basis (restart + 1 vectors of 3N FP64 complex) is allocated per call.
+ * The Krylov basis holds the contrast's support columns only (restart + 1 vectors of
+ * n_s = 3 |S| n3 FP64 complex values) and is kept for the next call.
+ *   Precisions 0, 1, 3 and 5 run on the bounding box of the support where that has a smaller
+ * circulant cross-section or at most three quarters of the grid's columns.  The first
+ * such solve after vie_set_contrast takes over the box's contrast (about 0.1 ms) and, the
+ * first time for a pair of circulant lengths M1 x M2, makes their spectrum (96 bytes an
+ * entry of (M1/2 + 1) (M2/2 + 1) (M3/2 + 1), half as much again with FP32; 1 ms at 64 x 32 x
+ * 1024).  The plan keeps the last four; without memory for one it solves on its whole grid
+ * until the next contrast, any other error is returned.
  */
 int vie_solve(vie_plan_t plan, const vie_c128* b, vie_c128* x, double tol,
               const vie_solve_opts* opts, vie_solve_info* info);
@@ -192,7 +201,8 @@ int vie_solve(vie_plan_t plan, const vie_c128* b, vie_c128* x, double tol,
  * one GPU share its array and each call starts by clearing what must start at
  * zero; calls that overlap on one GPU (other threads, other plans' streams) race
  * and must be serialised by the caller.  Results equal vie_solve's for the same
- * arguments.
+ * arguments, to rounding where only one of the two runs on the support's box: this call
+ * does once a vie_solve has made it for the contrast.
  */
 int vie_solve_noalloc(vie_plan_t plan, const vie_c128* b, vie_c128* x, double tol,
                       const vie_solve_opts* opts, vie_solve_info* info);
@@ -301,6 +311,10 @@ int vie_circulant_apply(vie_plan_t plan, const vie_c128* r, vie_c128* z);
  *   length of 512 the default), 0 = the default pencils, any other value must be one of the tuner's candidates
  *   (VIE_EINVAL otherwise).  Synchronises the plan's stream first.
  */
+/* vie_solve_box (diagnostic): the columns [box[0], box[1]) x [box[2], box[3]) that a
+ * vie_solve_noalloc would run on now: the support's box once a solve has made it, else the
+ * whole grid. */
+int vie_solve_box(vie_plan_t plan, int box[4]);
 int vie_get_tune(vie_plan_t plan, int precision, int* xy_variant, int* z_pencils);
 int vie_set_tune(vie_plan_t plan, int precision, int xy_variant, int z_pencils);
 

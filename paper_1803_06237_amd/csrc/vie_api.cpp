@@ -693,21 +693,27 @@ SolveView plan_view(const vie_plan_s* p) {
 // at most three quarters of the columns (vie_set_contrast): all passes shrink with it (32 x 32
 // x 512 guide with a 20 x 9 core, circulant 64 x 32 instead of 64 x 64 and a sixth of the z
 // pencils: FP64 product with scatter and gather 137 us, on the box 70 us).  Made on first use
-// unless `build` is false (callers that may not allocate); where that fails, for want of
-// memory say, the plan's own operator serves.
-SolveView solve_view(vie_plan_s* p, bool build) {
+// unless `build` is false (callers that may not allocate); where there is no memory for it the
+// plan's own operator serves until the next contrast.
+hipError_t solve_view(vie_plan_s* p, bool build, SolveView* v) {
   std::lock_guard<std::mutex> lk(p->sub_mu);
-  if (!p->sub_none && !p->sub.fresh && build && box_refresh(p) != hipSuccess) {
-    (void)hipGetLastError();
-    box_release(p);
-    p->sub_none = true;
+  if (!p->sub_none && !p->sub.fresh && build) {
+    const hipError_t e = box_refresh(p);
+    if (e) box_release(p);
+    if (e != hipSuccess && e != hipErrorOutOfMemory) return e;
+    if (e) {
+      (void)hipGetLastError();
+      p->sub_none = true;
+    }
   }
   const BoxOp& b = p->sub;
-  if (p->sub_none || !b.fresh) return plan_view(p);
+  *v = plan_view(p);
+  if (p->sub_none || !b.fresh) return hipSuccess;
   const BoxSpectrum& sp = b.spectrum;
-  return SolveView{b.g, b.t64, b.t32, sp.goct64, sp.goct32, b.chi64, b.chi32, p->U64, p->U32,
-                   {sp.tw64[0], sp.tw64[1], p->tw64[2]}, {sp.tw32[0], sp.tw32[1], p->tw32[2]}, b.col, p->ns,
-                   (long)p->ns == (long)b.g.n1 * b.g.n2, true};
+  *v = SolveView{b.g, b.t64, b.t32, sp.goct64, sp.goct32, b.chi64, b.chi32, p->U64, p->U32,
+                 {sp.tw64[0], sp.tw64[1], p->tw64[2]}, {sp.tw32[0], sp.tw32[1], p->tw32[2]}, b.col, p->ns,
+                 (long)p->ns == (long)b.g.n1 * b.g.n2, true};
+  return hipSuccess;
 }
 
 // The operator on support-compressed vectors.  Where the support is every column of the
@@ -969,7 +975,7 @@ vie::Circ* vie::plan_circ(vie_plan_t p) { return p ? p->circ : nullptr; }
 
 int vie::plan_solve_view(vie_plan_t p, SolveView* v) {
   if (!p || !p->has_contrast) return VIE_ESTATE;
-  *v = solve_view(p, true);
+  HIPTRY(p, solve_view(p, true, v));
   return VIE_OK;
 }
 
@@ -985,6 +991,11 @@ hipError_t vie::dmalloc_bytes(void** p, size_t bytes) {
     const char* v = std::getenv("VIE_DEBUG_NANFILL");
     return v && v[0] == '1';
   }();
+  // VIE_DEBUG_MALLOC_ERROR="bytes error": larger allocations fail with that HIP error
+  size_t least = 0;
+  int code = 0;
+  if (const char* v = std::getenv("VIE_DEBUG_MALLOC_ERROR"))
+    if (std::sscanf(v, "%zu %d", &least, &code) == 2 && bytes > least) return static_cast<hipError_t>(code);
   hipError_t e = hipMalloc(p, bytes);
   if (e || !nanfill || bytes == 0) return e;
   if ((e = hipMemset(*p, 0xFF, bytes))) return e;
@@ -1318,7 +1329,8 @@ int solve_impl(vie_plan_s* p, const vie_c128* b, vie_c128* x, double tol, const 
   using K = KrylovOps<double>;
   // the learned tiers' network works on the plan's grid and shares fx with the operator
   const bool learned = o.precision == 2 || o.precision == 4;
-  const SolveView view = learned ? plan_view(p) : solve_view(p, may_allocate);
+  SolveView view = plan_view(p);
+  if (!learned) HIPTRY(p, solve_view(p, may_allocate, &view));
   if (learned || !view.direct) {
     HIPTRY(p, K::zero(B.fx, nfull, s));
     if (p->fx32) HIPTRY(p, KrylovOps<float>::zero(p->fx32, nfull, s));
@@ -1662,6 +1674,15 @@ int vie_set_preconditioner(vie_plan_t p, vie_net_t net) {
       return fail(p, VIE_EINVAL, "network grid differs from the plan's grid");
   }
   p->net = net;
+  return VIE_OK;
+}
+
+int vie_solve_box(vie_plan_t p, int box[4]) {
+  if (!p || !box) return fail(p, VIE_EINVAL, "null argument");
+  std::lock_guard<std::mutex> lk(p->sub_mu);
+  const int grid[4] = {0, p->g.n1, 0, p->g.n2};
+  const int* b = !p->sub_none && p->sub.fresh ? p->box : grid;
+  std::copy(b, b + 4, box);
   return VIE_OK;
 }
 

@@ -171,7 +171,8 @@ const CircInfo& circ_info(const Circ* c);
 // Device allocation used throughout the library.  With VIE_DEBUG_NANFILL=1 in the
 // environment every fresh allocation is filled with all-ones bytes (a NaN in FP32
 // and FP64), so a kernel that reads memory nothing has written shows NaN in its
-// results instead of stale zeros.
+// results instead of stale zeros.  With VIE_DEBUG_MALLOC_ERROR="bytes error" every
+// allocation of more bytes fails with that hipError_t, for tests of what follows.
 hipError_t dmalloc_bytes(void** p, size_t bytes);
 template <typename P>
 inline hipError_t dmalloc(P** p, size_t bytes) {

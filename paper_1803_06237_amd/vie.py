@@ -100,6 +100,7 @@ def lib() -> ctypes.CDLL:
         L.vie_circulant_build.argtypes = [vp, ctypes.c_uint, ctypes.POINTER(CirculantInfo)]
         L.vie_get_tune.argtypes = [vp, ctypes.c_int, ip, ip]
         L.vie_set_tune.argtypes = [vp, ctypes.c_int, ctypes.c_int, ctypes.c_int]
+        L.vie_solve_box.argtypes = [vp, ip]
         L.vie_circulant_apply.argtypes = [vp, vp, vp]
         L.vie_nn_conv_test.argtypes = [ctypes.c_int, ip, ctypes.c_int, ctypes.c_int, ctypes.c_int, vp, vp, vp,
                                        ctypes.c_int, vp]
@@ -256,6 +257,12 @@ class Plan:
     def set_preconditioner(self, net):
         _check(lib().vie_set_preconditioner(self._h, net.handle if net is not None else None), self._h)
         self._net = net
+
+    def solve_box(self) -> tuple:
+        """Columns (i1, i1 end, i2, i2 end) that solves run on now (vie_solve_box)."""
+        box = (ctypes.c_int * 4)()
+        _check(lib().vie_solve_box(self._h, box), self._h)
+        return tuple(box)
 
     def tune(self, precision: int = 0) -> dict:
         """Launch shapes in use (vie_get_tune)."""

@@ -159,3 +159,50 @@ def test_boxes_of_many_circulant_lengths_on_one_plan():
             x, info = plan.solve(_t(b), tol=1e-9, restart=60, precision=precision)
             assert info["status"] == 0, (w1, w2, info)
             assert _residual(tab, eps, b, x.cpu().numpy()) <= 1.01e-9, (w1, w2)
+
+
+@pytest.mark.parametrize("precision", [0, 1, 3])
+def test_box_is_in_use_unless_there_is_no_memory(table, precision, monkeypatch):
+    """Solves run on the box where the rule says so.  Without memory for it they run on the plan's
+    own grid until the next contrast; another error of making it is the solve's."""
+    vie = _dev()
+    boxes = {"box": (3, 8, 2, 5), "moved": (7, 12, 7, 10), "holes": (1, 7, 1, 8), "column": (11, 12, 0, 1)}
+    plan = vie.Plan(N, H, K0, EPSB, fp32=True)
+    rng = np.random.default_rng(7)
+    b = rng.standard_normal((3,) + N) + 1j * rng.standard_normal((3,) + N)
+
+    def contrast(kind, eps=None):
+        plan.set_contrast(_t(_eps(kind) if eps is None else eps))
+        if precision == 3:
+            plan.build_circulant()
+
+    def solve(kind):
+        x, info = plan.solve(_t(b), tol=1e-9, restart=60, precision=precision)
+        assert info["status"] == 0
+        assert _residual(table, _eps(kind), b, x.cpu().numpy()) <= 1.01e-9, kind
+
+    for kind in KINDS:
+        contrast(kind)
+        assert plan.solve_box() == (0, N[0], 0, N[1])
+        solve(kind)
+        assert plan.solve_box() == boxes.get(kind, (0, N[0], 0, N[1])), kind
+    plan = vie.Plan(N, H, K0, EPSB, fp32=True)
+    spread = np.full(N, EPSB, complex)                   # as many columns, all over the grid
+    spread.reshape(-1, N[2])[np.linspace(0, N[0] * N[1] - 1, 15).astype(int)] = 9.0 + 0.5j
+    contrast("spread", spread)
+    plan.solve(_t(b), tol=1e-9, restart=60, precision=precision)
+    assert plan.solve_box() == (0, N[0], 0, N[1])        # the workspaces are there, no box is
+    contrast("box")
+    monkeypatch.setenv("VIE_DEBUG_MALLOC_ERROR", "0 2")  # hipErrorOutOfMemory
+    solve("box")
+    monkeypatch.delenv("VIE_DEBUG_MALLOC_ERROR")
+    solve("box")
+    assert plan.solve_box() == (0, N[0], 0, N[1])
+    contrast("box")
+    monkeypatch.setenv("VIE_DEBUG_MALLOC_ERROR", "0 1")  # hipErrorInvalidValue
+    with pytest.raises(vie.VieError) as err:
+        plan.solve(_t(b), tol=1e-9, restart=60, precision=precision)
+    assert err.value.code == vie.VIE_EDEVICE
+    monkeypatch.delenv("VIE_DEBUG_MALLOC_ERROR")
+    solve("box")
+    assert plan.solve_box() == boxes["box"]
