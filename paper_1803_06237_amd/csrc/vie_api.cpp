@@ -112,6 +112,12 @@ struct GmresWs {
     n = n_;
     m = m_;
     flex = flex_;
+    const hipError_t e = make();
+    if (e) release();   // nothing half made is found by the next call
+    return e;
+  }
+
+  hipError_t make() {
     hipError_t e;
     if ((e = dmalloc(&V, sizeof(cx<T>) * (size_t)n * (m + 1)))) return e;
     if (flex && (e = dmalloc(&Z, sizeof(cx<T>) * (size_t)n * m))) return e;

@@ -256,3 +256,21 @@ def test_long_cycles_stay_cheap():
         return best
 
     assert step(700) <= 2.5 * step(50)
+
+
+def test_workspace_that_did_not_fit_is_made_again(monkeypatch):
+    """A cycle whose Hessenberg matrix is larger than its basis: the first allocations of the
+    workspace succeed, that one fails, and the next call makes all of it."""
+    vie = _dev()
+    args, eps, op, b, _ = _near_zero_voxel(12.11)
+    plan = vie.Plan(*args, fp32=False)
+    plan.set_contrast(torch.from_numpy(eps).cuda())
+    run = lambda m: plan.solve(torch.from_numpy(b).cuda(), tol=1e-9, restart=m, maxit=m)
+    run(50)
+    monkeypatch.setenv("VIE_DEBUG_MALLOC_ERROR", f"{14 << 20} 2")   # the basis 11.5 MB, the matrix 16
+    with pytest.raises(vie.VieError) as err:
+        run(1000)
+    assert err.value.code in (vie.VIE_ENOMEM, vie.VIE_EDEVICE)
+    monkeypatch.delenv("VIE_DEBUG_MALLOC_ERROR")
+    x, info = run(1000)
+    assert info["status"] == 0 and _oracle_rel_res(op, b, x.cpu().numpy()) <= 1.01e-9
