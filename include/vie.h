@@ -498,6 +498,11 @@ int vie_jm_solve(vie_plan_t plan, const vie_c128* b, vie_c128* x, double tol, co
  */
 int vie_check_block_maps(char* msg, size_t cap, int planted);
 
+/* vie_check_tune_choice -- host-only diagnostic: the index that the plan-time tuner keeps of
+ * pencils x variants times ms[pencil * variants + variant], the default pencils first (-1 for
+ * arguments out of range). */
+int vie_check_tune_choice(const float* ms, int pencils, int variants);
+
 /* Message for the last failing call on this plan (plan = NULL: on this thread). */
 const char* vie_last_error(vie_plan_t plan);
 

@@ -417,6 +417,21 @@ void tune_cache_store(const std::string& arch, const Geom& g, int vb, const Tune
   ::close(fd);
 }
 
+// The candidate kept of nz pencil counts, the default first, times nv xy variants, timed as
+// ms[z nv + v].  The variant is the fastest of each count.  Within 2 % the default pencils stay:
+// repeated products on buffers that fit the Infinity Cache rank fewer pencils, whose writes
+// fill less of a line, as equal (FP64 32 x 32 x 512: 96.4 us with two, 96.9 with four), but with
+// other work in between they are slower (115 and 109).  No such bias is known between the
+// variants (FP32 21 x 13 x 389: 37.9 and 37.5 us in every process).
+int tune_choice(const float* ms, int nz, int nv) {
+  int best = 0;
+  for (int z = 0; z < nz; ++z) {
+    const int v = (int)(std::min_element(ms + z * nv, ms + (z + 1) * nv) - ms);
+    if (z == 0 || ms[v] < 0.98f * ms[best]) best = v;
+  }
+  return best;
+}
+
 template <typename T>
 hipError_t autotune(const Geom& g, int device, Tune* t, void* U, const void* goct, const void* chi,
                     const void* const tw[3], hipStream_t s) {
@@ -453,9 +468,9 @@ hipError_t autotune(const Geom& g, int device, Tune* t, void* U, const void* goc
   // between the passes, can rank the shapes differently (FP64 32x32x512: with
   // events between the passes 8 pencils per workgroup look 7 us faster than 4;
   // back to back, 4 stay ahead).
-  std::vector<Tune> cand;
+  std::vector<Tune> cand, zc;
+  const int nv = xy_variants(g);
   {
-    std::vector<Tune> zc;
     if (t->z3) {
       int opts[8];
       const int n = z3_pencil_options<T>(g.M3, opts, 8);
@@ -467,7 +482,6 @@ hipError_t autotune(const Geom& g, int device, Tune* t, void* U, const void* goc
     } else {
       zc.push_back(*t);
     }
-    const int nv = xy_variants(g);
     for (const Tune& z : zc)
       for (int v = 0; v < nv; ++v) {
         Tune c = z;
@@ -484,13 +498,7 @@ hipError_t autotune(const Geom& g, int device, Tune* t, void* U, const void* goc
         if (!e && ms < best[i]) best[i] = ms;
       }
     }
-    // Within 2 % the earlier candidate stays, the default pencils first: repeated products on
-    // buffers that fit the Infinity Cache rank fewer pencils, whose writes fill less of a line,
-    // as equal (FP64 32 x 32 x 512: 96.4 us with two, 96.9 with four), but with other work in
-    // between they are slower (115 and 109).
-    size_t bi = 0;
-    for (size_t i = 1; i < cand.size(); ++i)
-      if (best[i] < 0.98f * best[bi]) bi = i;
+    const size_t bi = (size_t)tune_choice(best.data(), (int)zc.size(), nv);
     if (!e) *t = cand[bi];
   }
   if (x) (void)hipFree(x);
@@ -1681,6 +1689,10 @@ int vie_set_preconditioner(vie_plan_t p, vie_net_t net) {
   }
   p->net = net;
   return VIE_OK;
+}
+
+int vie_check_tune_choice(const float* ms, int pencils, int variants) {
+  return ms && pencils > 0 && variants > 0 ? tune_choice(ms, pencils, variants) : -1;
 }
 
 int vie_solve_box(vie_plan_t p, int box[4]) {

@@ -113,6 +113,22 @@ def test_block_maps_are_bijections_with_writes_in_bounds():
     assert b"bank conflict" in buf.value
 
 
+@pytest.mark.parametrize("times,want", [
+    ([[10.0]], 0),
+    ([[10.1, 10.0, 10.05]], 1),                         # the variant by time, however close
+    ([[10.0, 11.0], [9.9, 11.0]], 0),                   # the default pencils within 2 %
+    ([[10.1, 10.0], [9.9, 9.85]], 1),
+    ([[10.0, 11.0], [9.7, 9.75], [9.6, 9.65]], 2),      # a third count within 2 % of the second
+    ([[12.0, 11.0], [11.0, 10.0], [10.0, 9.0]], 5),
+    ([[10.0, float("inf")], [float("inf"), 9.0]], 3),   # not measured
+])
+def test_tuner_keeps_default_pencils_within_two_percent_and_the_fastest_variant(times, want):
+    L = vie.lib()
+    L.vie_check_tune_choice.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_int]
+    ms = np.array(times, np.float32)
+    assert L.vie_check_tune_choice(ms.ctypes.data, *ms.shape) == want
+
+
 def test_no_function_attribute_is_set_once_per_process():
     """A kernel's attributes belong to a device: the calls that set them are not kept in statics,
     which a second device of the process would find done."""
