@@ -239,3 +239,32 @@ def test_device_memory_of_a_batch_is_what_its_vectors_take():
     want = 2 * (16 * ((2 * m + 4) * ns + U) + 8 * ((inner + 4) * ns + U)) + 16 * 3 * n[0] * n[1] * n[2]
     used = before - least[0]
     assert 0.5 * want <= used <= 1.1 * want + (32 << 20), (used, want)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_supports_of_64_x_64_circulants_in_one_batch(precision):
+    """The batched 64 x 64 cross-section pass (32 x 32 and 64 x 32 sections have another): supports
+    over 16 columns both ways that fill their box, leave holes in it, are nearly or all of the
+    grid, on guides of two circulant lengths and one too short for the batched z passes."""
+    vie = _dev()
+    rng = np.random.default_rng(precision)
+    plans, ops, bs = [], [], []
+    for n, box, hole in (((26, 26, 40), np.s_[3:21, 5:23], None),      # 18 x 18 box, filled
+                         ((26, 26, 34), np.s_[3:21, 5:23], np.s_[8:11, 9:20]),
+                         ((18, 17, 40), np.s_[:, :], None),            # every column
+                         ((20, 18, 40), np.s_[1:, :], None),           # nearly: the plan's grid
+                         ((17, 18, 5), np.s_[:, :], None)):
+        eps = np.full(n, inputs.EPS_B, complex)
+        eps[box] = 9.0 + 1j * np.linspace(0.2, 2.0, n[2])
+        if hole:
+            eps[hole] = inputs.EPS_B
+        chi = mv.contrast(eps, inputs.EPS_B)
+        ops.append(mv.Operator(vie.green_table(n, mv.kappa_of(0.05, inputs.K0, inputs.EPS_B)), chi))
+        plans.append(vie.Plan(n, 0.05, inputs.K0, inputs.EPS_B, fp32=True))
+        plans[-1].set_contrast(torch.from_numpy(eps).cuda())
+        bs.append(rng.standard_normal((3,) + n) + 1j * rng.standard_normal((3,) + n))
+    xs, infos, code = vie.solve_batch(plans, [torch.from_numpy(b).cuda() for b in bs], tol=1e-8, restart=40,
+                                      precision=precision)
+    assert code == vie.VIE_OK, infos
+    for op, b, x in zip(ops, bs, xs):
+        assert _rel(op, b, x.cpu().numpy()) <= 1.01e-8

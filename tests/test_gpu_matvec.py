@@ -412,3 +412,59 @@ def test_every_launch_shape_matches_the_oracle(grid):
     with pytest.raises(vie.VieError) as ei:
         plan.set_tune(0, 1, 3)
     assert ei.value.code == vie.VIE_EINVAL
+
+
+def _sparse_product(vie, n, rng, nnz=12):
+    """Random contrast, a vector with nnz non-zeros and its product at every voxel, summed from
+    the library's host table (which a test of its own pins to the oracle's)."""
+    table = vie.green_table(n, mv.kappa_of(H, K0, EPSB))
+    eps = EPSB + 10 * rng.random(n) + 1j * rng.random(n)
+    x, u = np.zeros((3,) + n, complex), np.zeros((3,) + n, complex)
+    for _ in range(nnz):
+        src, c, v = [int(rng.integers(m)) for m in n], int(rng.integers(3)), _cvec(rng, 1)[0]
+        x[(c, *src)] += v
+        off = [np.arange(m) - s for m, s in zip(n, src)]
+        at = np.ix_(*(np.abs(o) for o in off))
+        for q, (a, b) in enumerate(green.COMPONENTS):
+            if c not in (a, b):
+                continue
+            N = table[q][at]
+            if a != b:   # odd in both of its axes
+                for d in (a, b):
+                    N = N * np.sign(off[d]).reshape([-1 if k == d else 1 for k in range(3)])
+            u[a if c == b else b] += v * N
+    return eps, x, x - mv.contrast(eps, EPSB) * u
+
+
+@pytest.mark.parametrize("length", Z_LENGTHS)
+def test_z_lengths_with_full_pencil_blocks(length):
+    """17 pencils a row: every pencil count up to 16 has full blocks and one with a single pencil."""
+    vie = _dev()
+    n = (17, 1, length // 2 - 1)
+    rng = np.random.default_rng(length)
+    eps, x, want = _sparse_product(vie, n, rng)
+    plan = vie.Plan(n, H, K0, EPSB, fp32=True)
+    plan.set_contrast(_t(eps))
+    for precision, bar in ((0, 1e-12), (1, 5e-6)):
+        for zp in (1, 2, 4, 8, 16, 0):
+            try:
+                plan.set_tune(precision, 1, zp)
+            except vie.VieError:
+                continue
+            got = plan.matvec(_t(x)) if precision == 0 else plan.matvec_c64(_t(x, torch.complex64))
+            err = np.linalg.norm(got.cpu().numpy() - want) / np.linalg.norm(want)
+            assert err < bar, (n, precision, zp, err)
+
+
+# more than 256 workgroups, so that the spectra are not preloaded: circulant sections of 64 x 8,
+# 64 x 16, 16 x 64, 32 x 64, 32 x 16, 16 x 32, 8 x 64, 32 x 8, 16 x 16 and 8 x 32
+@pytest.mark.parametrize("n", [(32, 4, 600), (29, 8, 260), (7, 32, 260), (16, 31, 260), (15, 8, 600), (8, 13, 600),
+                               (4, 29, 600), (16, 3, 1100), (7, 8, 1100), (4, 16, 1100)], ids=lambda g: "x".join(map(str, g)))
+def test_register_cross_sections_of_many_workgroups_match_the_oracle(n):
+    vie = _dev()
+    eps, x, want = _sparse_product(vie, n, np.random.default_rng(sum(n)))
+    plan = vie.Plan(n, H, K0, EPSB, fp32=True)
+    plan.set_contrast(_t(eps))
+    for got, bar in ((plan.matvec(_t(x)), 1e-12), (plan.matvec_c64(_t(x, torch.complex64)), 5e-6)):
+        err = np.linalg.norm(got.cpu().numpy() - want) / np.linalg.norm(want)
+        assert err < bar, (got.dtype, err)
