@@ -482,9 +482,10 @@ def main():
 
     b64 = pass_bytes(n, M, 16)
     tune64 = plan.tune(0)
-    names = ["k_zfwd3<double, 8, 8, 16>" if M[2] == 1024 else "k_zfwd3<double>",
-             f"k_xy64<double, {tune64['xy_variant']}>" if M[0] == 64 and M[1] == 64 else "k_xyg<double>",
-             "k_zinv3<double, 16, 8, 8, 0>" if M[2] == 1024 else "k_zinv3<double>"]
+    z = "3" if M[2] >= 64 else ""
+    names = ["k_zfwd3<double, 8, 8, 16>" if M[2] == 1024 else f"k_zfwd{z}<double>",
+             f"k_xy64<double, {tune64['xy_variant']}>" if M[0] == 64 and M[1] == 64 else "cross-section pass",
+             "k_zinv3<double, 16, 8, 8, 0>" if M[2] == 1024 else f"k_zinv{z}<double>"]
     dom = int(np.argmax(pass_ms))
     achieved = b64[dom] / (pass_ms[dom] * 1e-3) / 1e9
     roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",

@@ -309,7 +309,8 @@ int vie_circulant_apply(vie_plan_t plan, const vie_c128* r, vie_c128* z);
  * vie_set_tune: force a choice (xy_variant 0-2, ignored where the cross-section
  *   has a single xy pass); z_pencils -1 = one pencil per workgroup (below a
  *   length of 512 the default), 0 = the default pencils, any other value must be one of the tuner's candidates
- *   (VIE_EINVAL otherwise).  Synchronises the plan's stream first.
+ *   (VIE_EINVAL otherwise).  Synchronises the plan's stream first.  Solves that run on the
+ *   support's box (vie_solve) choose their shapes there by rule instead.
  */
 /* vie_solve_box (diagnostic): the columns [box[0], box[1]) x [box[2], box[3]) that a
  * vie_solve_noalloc would run on now: the support's box once a solve has made it, else the

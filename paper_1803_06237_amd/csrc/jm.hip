@@ -9,7 +9,7 @@
 // z passes of the J-VIE once per half.  Between them one fused kernel over the
 // kz planes, rows along x, columns along y, the 6 x 6 product with N^ and K^,
 // inverse columns and rows, crop, U_e and U_m in place: the register pass of
-// jmr.hip, or on cross-sections with a circulant side of 1, 2 or 4 points
+// jmr.hip, or on cross-sections with a circulant side of 1 or 4 points
 //   k_jm_xy:      the same on padded LDS stages, one plane per workgroup.
 // The other route, kept for comparison, three kernels over full cross-section
 // spectra in HBM:

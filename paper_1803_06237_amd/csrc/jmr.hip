@@ -12,7 +12,7 @@
 // exp(-2 pi i / M1), and the inverse with the crop adds the two half-length inverses, the second
 // untwisted; the workgroup does both in turn, U holding the first half's outputs meanwhile.
 // Against the fused pass over LDS transforms (k_jm_xy, kept for sections with a side under 8
-// or over 64 points): see jmr_fits.
+// points): see jmr_fits.
 #include <hip/hip_runtime.h>
 
 #include "block_maps.hpp"

@@ -97,8 +97,9 @@ __global__ __launch_bounds__(1024) void k_zinv(const cx<T>* __restrict__ U, cons
 }
 
 // ------------------------------------------------------------------ pass 2
-// Cross-sections the register kernels do not take (a side of 1, 2 or 4 points), and the 64 x 32
-// pass the tuner compares with them: one workgroup per kz plane.  x transforms
+// Cross-sections the register kernels do not take (a side of 1 or 4 points, sections of up to
+// 16 x 32 with at most 256 planes by the rule at xyr_fits), and the 64 x 32 pass the tuner
+// compares with them: one workgroup per kz plane.  x transforms
 // of the 3 n2 valid rows, then for each chunk of cc x-frequencies the y
 // transforms, the 3 x 3 Green product and the inverse y transforms, finally the
 // inverse x transforms and the crop; U is read and overwritten in place.  The

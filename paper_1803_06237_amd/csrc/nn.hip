@@ -8,13 +8,13 @@
 // Activations are channels-last bfloat16 [V][C] (V = D H W voxels, W fastest,
 // C a multiple of 16, channel stride / offset per view so concatenations are
 // written in place).  Convolutions are implicit GEMMs on the matrix cores:
-// v_mfma_f32_16x16x16bf16_1k, FP32 accumulation.  Forward: M = voxels, N = Cout,
-// K = 27 Cin, operands loaded straight from global memory into MFMA fragments
-// (a 16-voxel x 4-channel slab per lane group is one 8-byte load).  Input
+// v_mfma_f32_16x16x32_bf16, FP32 accumulation.  Forward: output channels x voxels,
+// K = 27 Cin; a tile's input with its halo and the weights of 16 input channels are
+// staged in LDS and read as fragments (k_conv2).  Input
 // gradient: the same kernel with taps flipped and channels swapped, the ReLU
 // mask of the forward input fused into the epilogue.  Weight gradient: a GEMM over
 // voxels with every tap in registers, split over voxel tiles with a fixed-order
-// reduction.  Master weights, gradients and
+// reduction (k_wgrad).  Master weights, gradients and
 // Adam moments are FP32.
 #include <hip/hip_runtime.h>
 

@@ -329,8 +329,9 @@ __global__ __launch_bounds__(1024) void k_zinv3_batch(const PassDesc* __restrict
 
 // Every length with the inverse's radices: the first even (half of its inputs are padding), all near each
 // other (a pencil has as many threads as its stage of smallest radix has tasks), the length a
-// multiple of 16, which the plane order of the cross-section passes wants, and at most 1.25
-// times the one before.
+// multiple of 16, which the plane order of the cross-section passes wants.  Each is at most 1.25
+// times the one before but for 128 after 96 (16 x 7 would need a radix of 7) and 512 after 256
+// (two radices of up to 16 end there, three of 8 and more begin at 512).
 #define VIE_Z3_LENGTHS(X) \
   X(8, 8, 1)              \
   X(10, 8, 1)             \

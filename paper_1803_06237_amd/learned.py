@@ -248,6 +248,7 @@ class CirculantCorrectionStudy:
         agg = {}
         for name in ("fp64", "mixed", "circulant", "learned_circulant"):
             agg[name] = {"seconds_mean": float(np.mean([r[name]["seconds"] for r in rows])),
+                         "seconds_max": float(max(r[name]["seconds"] for r in rows)),
                          "iters_mean": float(np.mean([r[name]["iters"] for r in rows])),
                          "max_rel_res_fp64": float(max(r[name]["rel_res_fp64"] for r in rows)),
                          "fallbacks": int(sum(r[name]["fallback"] for r in rows))}
