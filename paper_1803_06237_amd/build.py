@@ -23,10 +23,7 @@ ARCH = "gfx950"
 
 COMMON = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-          "-Wno-unused-result", f"-I{INCLUDE}", f"-I{CSRC}",
-          # host functions on cache lines: with the linker's placement the weight generator of
-          # vie_net_create took 27 or 48 ms for the same instructions
-          "-Xarch_host", "-falign-functions=64"]
+          "-Wno-unused-result", f"-I{INCLUDE}", f"-I{CSRC}"]
 
 
 def hipcc() -> str:
