@@ -215,6 +215,24 @@ def test_one_cycle_of_cancelling_steps_equals_the_oracle(small, m):
     assert abs(info["rel_res_est"] - true) <= bound + 1e-12
 
 
+@pytest.mark.parametrize("precision", [1, 3])
+@pytest.mark.parametrize("small,m", [(1e-2, 10), (1e-10, 5), (1e-10, 15)])
+def test_estimate_of_a_preconditioned_cycle_of_cancelling_steps(precision, small, m):
+    """Flexible cycles queue the extra sweep with their first steps and repeat a later one that
+    turns out to need it (the 1e-10 cases, on its stored preconditioned vector): the Hessenberg
+    estimate stays the true residual."""
+    vie = _dev()
+    args, eps, op, b, bound = _near_zero_voxel(small)
+    plan = vie.Plan(*args, fp32=True)
+    plan.set_contrast(torch.from_numpy(eps).cuda())
+    plan.build_circulant()
+    x, info = plan.solve(torch.from_numpy(b).cuda(), tol=1e-15, restart=m, maxit=m, precision=precision,
+                         inner_restart=3, inner_tol=1e-1)
+    true = _oracle_rel_res(op, b, x.cpu().numpy())
+    assert info["iters"] == m
+    assert abs(info["rel_res_est"] - true) <= bound + 1e-12, (info, true, bound)
+
+
 @pytest.mark.parametrize("cycles", [1, 3])
 def test_cycles_of_cancelling_steps_in_a_batch(cycles):
     """The same in a batch, next to a system without the voxel, whose steps do not cancel; the
